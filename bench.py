@@ -98,14 +98,14 @@ def kernel_symbol(d, kind, level, mode):
     if kind == "level_write":
         return "k_level_write_%dd<double, %d>" % (d, mode)
     if kind == "residual" and mode & 1:  # with the restriction to level 1
-        return "k_residual_restrict_%dd<double>" % d
+        return "k_residual_restrict_%dd<double, false>" % d
     if kind == "residual":
-        return "k_residual_%dd<double%s>" % (d, var2)
+        return "k_residual_%dd<double%s, false>" % (d, var2)
     if kind == "tail":
         return "k_coarse_tail<double, %d>" % d
     if kind == "transfer":
         return "k_level_transfer_%dd<double, %s>" % (d, "true" if mode & 1 else "false")
-    return {"restrict": "k_restrict_%dd<double>" % d, "norm": "k_norm2_%dd" % d,
+    return {"restrict": "k_restrict_%dd<double>" % d,
             "finalize": "k_finalize", "gather": "k_gather<double>"}[kind]
 
 
@@ -120,8 +120,6 @@ def kernel_bytes(d, n, entry):
         nf = (n - 1) // (1 << level) + 1
         Nf = float(nf) ** d
         return (8 * Nf + 8 * Nf / 2 ** d) * entry["launches"]
-    if kind == "norm":
-        return 8 * N * entry["launches"]
     lat = N / float(1 << level) ** d
     if kind == "gather":
         return 16 * lat * entry["launches"]

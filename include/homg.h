@@ -248,7 +248,7 @@ homg_status homg_step_cycle(homg_handle h, const double *r0, double *acc, void *
  * times are accumulated per kernel class (kind, level, mode) at the end of
  * every solve and by homg_get_profile.  Enabling or disabling clears the
  * accumulated times.
- *   kind: 0 norm of f, 1 residual, 2 norm finalisation, 3 restriction from
+ *   kind: 0 unused (the first residual also sums f^2), 1 residual, 2 norm finalisation, 3 restriction from
  *   `level` to level+1, 4 whole-grid iteration at `level`, 5 sampling of the
  *   grid on the level lattice, 6 iterations on the compact lattice, 7
  *   whole-grid pass of a blocked level, 8 learned relaxation of the level

@@ -40,7 +40,7 @@ void homg::set_last_error(const char* msg) { g_err = msg; }
 namespace {
 
 enum Kind {
-  K_NORM = 0, K_RESIDUAL = 1, K_FINALIZE = 2, K_RESTRICT = 3, K_SWEEP = 4,
+  K_RESIDUAL = 1, K_FINALIZE = 2, K_RESTRICT = 3, K_SWEEP = 4,
   K_GATHER = 5, K_LATTICE = 6, K_LEVEL_WRITE = 7, K_LEARNED = 8, K_TRANSFER = 9, K_TAIL = 10
 };
 
@@ -76,7 +76,7 @@ struct homg_ctx {
   std::vector<void*> xp3;  // Laplacian: third compact array per level (x_{it-1} of a multi-iteration pass)
   size_t lds_limit = 65536;
   bool has_coef = false;
-  double* partials = nullptr;
+  double* partials = nullptr;  // per-block sums of r^2, then npart further of f^2
   int npart = 0;
   DevState* st = nullptr;
   double* hist = nullptr;
@@ -708,30 +708,31 @@ homg_status prepare_rhs(homg_ctx* h, int m, const int* done, hipStream_t s) {
 }
 
 // r_0 = f - A u in the handle's precision with its norm partials (and, see
-// residual_restricts, r_1 = R r_0).
+// residual_restricts, r_1 = R r_0); fpart: and the sums of f^2.
 homg_status enqueue_residual(homg_ctx* h, const double* f, const double* u, int* count,
-                             const int* done, hipStream_t s) {
+                             const int* done, hipStream_t s, double* fpart = nullptr) {
   h->rhs_ready = residual_restricts(h) ? 1 : 0;
   h->rhs_top64 = false;
   if (residual_restricts(h)) {
     LAUNCH_K(h, s, K_RESIDUAL, 0, 1,
              launch_residual_restrict_2d(h->prec, h->n, u, h->dl, f, h->dl, h->r[0], h->rl[0], h->r[1],
-                                         h->rl[1], h->partials, count, done, s));
+                                         h->rl[1], h->partials, count, done, s, fpart));
     return HOMG_OK;
   }
   const Lay none;
   const double* a0 = h->has_coef ? h->a[0] : nullptr;
   LAUNCH_K(h, s, K_RESIDUAL, 0, 0,
            launch_residual(h->prec, h->d, h->n, u, h->dl, f, h->dl, a0, a0 ? h->al[0] : none, h->r[0],
-                           h->rl[0], h->partials, count, done, s));
+                           h->rl[0], h->partials, count, done, s, fpart));
   return HOMG_OK;
 }
 
 // Enqueue one MFMG cycle (Sec. 2): restriction pyramid of r_0, the
 // schedule's whole-grid iterations with the last one adding e into acc,
-// then (if f != null) the new residual and its norm as history[cycle].
+// then (if f != null) the new residual and its norm as history[cycle];
+// publish: the state and the history also go to their pinned mirrors.
 homg_status enqueue_cycle(homg_ctx* h, const double* f, double* acc, int cycle, const int* done,
-                          hipStream_t s) {
+                          hipStream_t s, bool publish = false) {
   int ms = 0;
   const int ntail = tail_levels(h, &ms);
   // in a solve (f given) the residual that precedes every cycle already
@@ -804,7 +805,9 @@ homg_status enqueue_cycle(homg_ctx* h, const double* f, double* acc, int cycle, 
   if (f) {
     int count = 0;
     if (homg_status e = enqueue_residual(h, f, acc, &count, done, s)) return e;
-    LAUNCH_K(h, s, K_FINALIZE, 0, 1, launch_finalize(h->partials, count, h->st, h->hist, cycle, 1, s));
+    LAUNCH_K(h, s, K_FINALIZE, 0, 1,
+             launch_finalize(h->partials, count, h->st, h->hist, cycle, s, publish ? h->h_st : nullptr,
+                             publish ? h->h_hist : nullptr));
   }
   return HOMG_OK;
 }
@@ -832,12 +835,14 @@ homg_status solve_impl(homg_ctx* h, const double* f, double* u, double tol, int 
   h->active_smoother = h->smoother;
   int fell_back = 0;
 
-  LAUNCH(h, launch_init_state(h->st, stop_on_tol ? tol : 0.0, stop_on_tol ? 1 : 0, s));
+  // the first residual also sums f^2; its reduction starts the state
   int count = 0;
-  LAUNCH_K(h, s, K_NORM, 0, 0, launch_norm2(h->d, h->n, f, h->dl, h->partials, &count, s));
-  LAUNCH_K(h, s, K_FINALIZE, 0, 0, launch_finalize(h->partials, count, h->st, h->hist, 0, 0, s));
-  if (homg_status e = enqueue_residual(h, f, u, &count, done, s)) return e;
-  LAUNCH_K(h, s, K_FINALIZE, 0, 1, launch_finalize(h->partials, count, h->st, h->hist, 0, 1, s));
+  if (homg_status e = enqueue_residual(h, f, u, &count, h->zero_flag, s, h->partials + h->npart)) return e;
+  const bool none_to_run = !stop_on_tol && fixed_cycles == 0;
+  LAUNCH_K(h, s, K_FINALIZE, 0, 1,
+           launch_finalize_first(h->partials, h->partials + h->npart, count, stop_on_tol ? tol : 0.0,
+                                 stop_on_tol ? 1 : 0, h->st, h->hist, s, none_to_run ? h->h_st : nullptr,
+                                 none_to_run ? h->h_hist : nullptr));
 
   const int limit = stop_on_tol ? h->max_cycles : fixed_cycles;
   int enqueued = 0, syncs = 0;
@@ -845,11 +850,10 @@ homg_status solve_impl(homg_ctx* h, const double* f, double* u, double tol, int 
   for (;;) {
     const int upto = std::min(limit, enqueued + std::max(batch, 0));
     for (int c = enqueued + 1; c <= upto; ++c)
-      if (homg_status e = enqueue_cycle(h, f, u, c, done, s)) return e;
+      if (homg_status e = enqueue_cycle(h, f, u, c, done, s, c == upto)) return e;
     enqueued = upto;
-    HIPCHK(h, hipMemcpyAsync(h->h_st, h->st, sizeof(DevState), hipMemcpyDeviceToHost, s));
-    HIPCHK(h, hipMemcpyAsync(h->h_hist, h->hist, sizeof(double) * (enqueued + 1),
-                             hipMemcpyDeviceToHost, s));
+    // (the batch's last reduction stored the state and the history in their
+    // pinned mirrors: two copies after it took longer than the kernel)
     HIPCHK(h, hipStreamSynchronize(s));
     ++syncs;
     if (h->h_st->done || enqueued >= limit) break;
@@ -1106,7 +1110,7 @@ homg_status homg_create(homg_handle* out, int ndim, const int64_t* dims, int lev
       if (!h->xc[2 * mt + b]) stt = dev_alloc(h, &h->xc[2 * mt + b], size_t(h->rl[mt].alloc) * eb);
   }
   h->npart = partials_bound(ndim, h->n);
-  if (!stt) stt = dev_alloc(h, reinterpret_cast<void**>(&h->partials), sizeof(double) * h->npart);
+  if (!stt) stt = dev_alloc(h, reinterpret_cast<void**>(&h->partials), 2 * sizeof(double) * h->npart);
   if (!stt) stt = dev_alloc(h, reinterpret_cast<void**>(&h->st), sizeof(DevState));
   if (!stt) stt = dev_alloc(h, reinterpret_cast<void**>(&h->hist), sizeof(double) * (max_cycles + 1));
   if (!stt) stt = dev_alloc(h, reinterpret_cast<void**>(&h->zero_flag), sizeof(int) * 64);
@@ -1203,19 +1207,16 @@ homg_status homg_residual(homg_handle h, const double* f, const double* u, doubl
   DeviceGuard guard(h->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   int count = 0;
-  LAUNCH(h, launch_init_state(h->st, 0.0, 0, s));
-  LAUNCH(h, launch_norm2(h->d, h->n, f, h->dl, h->partials, &count, s));
-  LAUNCH(h, launch_finalize(h->partials, count, h->st, h->hist, 0, 0, s));
   const double* a0 = h->has_coef ? h->a[0] : nullptr;
   const Lay none;
+  double* fpart = h->partials + h->npart;
   if (r)
     LAUNCH(h, launch_residual(PREC_F64, h->d, h->n, u, h->dl, f, h->dl, a0, a0 ? h->al[0] : none,
-                              r, h->dl, h->partials, &count, h->zero_flag, s));
+                              r, h->dl, h->partials, &count, h->zero_flag, s, fpart));
   else
     LAUNCH(h, launch_residual(h->prec, h->d, h->n, u, h->dl, f, h->dl, a0, a0 ? h->al[0] : none,
-                              h->r[0], h->rl[0], h->partials, &count, h->zero_flag, s));
-  LAUNCH(h, launch_finalize(h->partials, count, h->st, h->hist, 0, 1, s));
-  HIPCHK(h, hipMemcpyAsync(h->h_hist, h->hist, sizeof(double), hipMemcpyDeviceToHost, s));
+                              h->r[0], h->rl[0], h->partials, &count, h->zero_flag, s, fpart));
+  LAUNCH(h, launch_finalize_first(h->partials, fpart, count, 0.0, 0, h->st, h->hist, s, h->h_st, h->h_hist));
   HIPCHK(h, hipStreamSynchronize(s));
   if (relres_out) *relres_out = h->h_hist[0];
   return HOMG_OK;

@@ -39,33 +39,37 @@ struct DevState {
 
 enum SweepMode { SW_ZERO_OLD = 1, SW_ACCUM = 2, SW_TBLOCK = 8 };
 
-// Upper bound on the number of per-block partial sums written by the norm /
-// residual launches for a grid of side n.
+// Upper bound on the number of per-block partial sums written by the
+// residual launches for a grid of side n, and launch_residual's number.
 int partials_bound(int d, int n);
+int residual_partials(int d, int n);
 
-// ||f||^2 over interior nodes -> partials; *count receives the number.
-hipError_t launch_norm2(int d, int n, const double* f, const Lay& fl, double* partials,
-                        int* count, hipStream_t s);
-// r0 = f - A u (FP64) stored in the precision `prec`; per-block sums of r^2.
+// r0 = f - A u (FP64) stored in the precision `prec`; per-block sums of r^2
+// -> partials (their number in *count) and, given fpart, of f^2 -> fpart.
 // `a` (nullable) is the nodal coefficient for the diffusion operator, in the
 // layout al.
 hipError_t launch_residual(int prec, int d, int n, const double* u, const Lay& ul,
                            const double* f, const Lay& fl, const double* a, const Lay& al,
                            void* r0, const Lay& rl, double* partials, int* count,
-                           const int* done, hipStream_t s);
+                           const int* done, hipStream_t s, double* fpart = nullptr);
 // 2D Laplacian (n >= 5): the residual of launch_residual and, in the same
 // pass, its full-weighting restriction to level 1 (rc, layout cl of side
 // (n-1)/2+1), equal bit for bit to launch_restrict applied to the stored r0.
-// Per-wave sums of r^2 (their number in *count).
+// Per-wave sums of r^2 (their number in *count) and, given fpart, of f^2.
 hipError_t launch_residual_restrict_2d(int prec, int n, const double* u, const Lay& ul,
                                        const double* f, const Lay& fl, void* r0, const Lay& rl,
                                        void* rc, const Lay& cl, double* partials, int* count,
-                                       const int* done, hipStream_t s);
-// Sums `count` partials in a fixed order.  mode 0: fnorm = sqrt(sum) and
-// resets the state; mode 1: history[cycle] = sqrt(sum)/fnorm and updates done.
+                                       const int* done, hipStream_t s, double* fpart = nullptr);
+// Sums `count` partials in a fixed order: history[cycle] = sqrt(sum)/fnorm,
+// and `done` is updated (nothing if it is set).  Given hst / hhist (pinned
+// host memory), the state and history[0 .. the last recorded cycle] are
+// stored there as well.  _first: a solve's first residual, with its sums of
+// f^2 -- the state starts here (fnorm, tol, stop_on_tol), as cycle 0.
 hipError_t launch_finalize(const double* partials, int count, DevState* st, double* history,
-                           int cycle, int mode, hipStream_t s);
-hipError_t launch_init_state(DevState* st, double tol, int stop_on_tol, hipStream_t s);
+                           int cycle, hipStream_t s, DevState* hst = nullptr, double* hhist = nullptr);
+hipError_t launch_finalize_first(const double* partials, const double* fpart, int count, double tol,
+                                 int stop_on_tol, DevState* st, double* history, hipStream_t s,
+                                 DevState* hst = nullptr, double* hhist = nullptr);
 // Normalised L1 error (Sec. 4, discrete): *out (device) = sum |uref - v| /
 // sum |uref| over all n^d nodes, v = u + e (e: internal iterate of type
 // prec, layout el) or v = u when e is null; uref and u dense FP64.  part:

@@ -241,6 +241,28 @@ static int rr_band(int n) {
   return len;
 }
 
+// The 3D residual's grid: tiles of 64 x 16 columns on walks of RES3_LEN
+// planes, halved while that leaves fewer than 512 workgroups (two per CU).
+// A short walk loads its two halo planes again, but these come from the
+// caches, while a grid of few workgroups is one serial chain of memory
+// round trips: at 65^3 16-plane walks are 16 workgroups and took 18.4 us.
+constexpr int RES3_LEN = 16;
+static int64_t res3_blocks(int n, int len) {
+  const int64_t inner = n - 2;
+  return ((inner + BX3 - 1) / BX3) * ((inner + 4 * BY3 - 1) / (4 * BY3)) * ((inner + len - 1) / len);
+}
+static int res3_len(int n) {
+  int len = RES3_LEN;
+  while (len > 1 && res3_blocks(n, len) < 512) len /= 2;
+  return len;
+}
+
+int residual_partials(int d, int n) {
+  if (d == 3) return int(res3_blocks(n, res3_len(n)));
+  const dim3 g = grid_of(2, n, walk_len(2, n));
+  return int(g.x * g.y);
+}
+
 int partials_bound(int d, int n) {
   if (n < 3) return 1;
   dim3 g = grid_of(d, n, walk_len(d, n));
@@ -249,9 +271,8 @@ int partials_bound(int d, int n) {
     const int64_t w = rr_waves(n, rr_band(n));
     if (w > count) count = w;
   }
-  if (d == 3) {  // the 3D residual's grid: 4 rows per lane, walks of 8 planes
-    const int64_t inner = n - 2, len3 = inner < 8 ? inner : 8;
-    const int64_t c3 = ((inner + BX3 - 1) / BX3) * ((inner + 4 * BY3 - 1) / (4 * BY3)) * ((inner + len3 - 1) / len3);
+  if (d == 3) {
+    const int64_t c3 = res3_blocks(n, res3_len(n));
     if (c3 > count) count = c3;
   }
   return int(count);
@@ -305,43 +326,22 @@ __device__ __forceinline__ void tile_norm2_2d(const double* __restrict__ f, int6
   if (threadIdx.x == 0) partials[pidx] = s;
 }
 
-__global__ __launch_bounds__(256) void k_norm2_2d(const double* __restrict__ f, int64_t fp, int n,
-                                                  int len, double* __restrict__ partials) {
-  tile_norm2_2d(f, fp, n, len, partials, blockIdx.x, blockIdx.y, blockIdx.y * gridDim.x + blockIdx.x);
-}
-
-__global__ __launch_bounds__(256) void k_norm2_3d(const double* __restrict__ f, int64_t fp,
-                                                  int64_t fpl, int n, int len,
-                                                  double* __restrict__ partials) {
-  const int x = 1 + blockIdx.x * BX3 + threadIdx.x;
-  const int y = 1 + blockIdx.y * BY3 + threadIdx.y;
-  const int z0 = 1 + blockIdx.z * len;
-  const int z1 = min(n - 1, z0 + len);
-  double s = 0.0;
-  if (x <= n - 2 && y <= n - 2)
-    for (int z = z0; z < z1; ++z) {
-      double v = f[int64_t(z) * fpl + int64_t(y) * fp + x];
-      s = fmac(v, v, s);
-    }
-  s = block_sum<256>(s);
-  if (threadIdx.x == 0 && threadIdx.y == 0)
-    partials[(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = s;
-}
-
 // ------------------------------------------------------------ residual
 // r = f - A u on interior nodes (Sec. 2, residual equation), FP64
 // arithmetic; r stored in the cycle precision T; per-block sum of r^2 of the
-// FP64 values.
+// FP64 values.  NORM (a solve's first residual): the pass also sums f^2, in
+// the same order, into fpart -- f is read here anyway, and a pass of its own
+// for ||f|| with its reduction took two launches and 29 us at 257^3.
 
-template <typename T, bool VAR>
+template <typename T, bool VAR, bool NORM = false>
 __device__ __forceinline__ void tile_residual_2d(
     const double* __restrict__ u, int64_t up, const double* __restrict__ f, int64_t fp,
     const double* __restrict__ a, int64_t ap, T* __restrict__ r, int64_t rp, int n, int len,
-    double inv_h2, double* __restrict__ partials, int bx, int by, int pidx) {
+    double inv_h2, double* __restrict__ partials, int bx, int by, int pidx, double* __restrict__ fpart = nullptr) {
   const int x = t2_x(bx);
   const int y0 = t2_y0(by, len);
   const int y1 = min(n - 1, y0 + len);
-  double s = 0.0;
+  double s = 0.0, sf = 0.0;
   if (x <= n - 2 && y0 <= n - 2) {
     double ym = u[int64_t(y0 - 1) * up + x];
     double c = u[int64_t(y0) * up + x];
@@ -367,38 +367,44 @@ __device__ __forceinline__ void tile_residual_2d(
       } else {
         au = fmac(4.0, c, -((xm + xp) + (ym + yp)));
       }
-      const double rv = fmac(-inv_h2, au, f[int64_t(y) * fp + x]);
+      const double fv = f[int64_t(y) * fp + x];
+      const double rv = fmac(-inv_h2, au, fv);
       st(r + int64_t(y) * rp + x, typename Tr<T>::C(rv));
       s = fmac(rv, rv, s);
+      if (NORM) sf = fmac(fv, fv, sf);
       ym = c;
       c = yp;
     }
   }
   s = block_sum<256>(s);
   if (threadIdx.x == 0) partials[pidx] = s;
+  if (NORM) {
+    __syncthreads();
+    sf = block_sum<256>(sf);
+    if (threadIdx.x == 0) fpart[pidx] = sf;
+  }
 }
 
-template <typename T, bool VAR>
+template <typename T, bool VAR, bool NORM>
 __global__ __launch_bounds__(256) void k_residual_2d(
     const double* __restrict__ u, int64_t up, const double* __restrict__ f, int64_t fp,
     const double* __restrict__ a, int64_t ap, T* __restrict__ r, int64_t rp, int n, int len,
-    double inv_h2, double* __restrict__ partials, const int* __restrict__ done) {
+    double inv_h2, double* __restrict__ partials, const int* __restrict__ done, double* __restrict__ fpart) {
   if (*done) return;
-  tile_residual_2d<T, VAR>(u, up, f, fp, a, ap, r, rp, n, len, inv_h2, partials, blockIdx.x, blockIdx.y, blockIdx.y * gridDim.x + blockIdx.x);
+  tile_residual_2d<T, VAR, NORM>(u, up, f, fp, a, ap, r, rp, n, len, inv_h2, partials, blockIdx.x, blockIdx.y, blockIdx.y * gridDim.x + blockIdx.x, fpart);
 }
 
 // 3D residual: a lane owns R3Y consecutive y rows (as the level-0 sweep),
-// walks of RES3_LEN planes.  The x neighbours come from the neighbour lanes
+// walks of res3_len planes.  The x neighbours come from the neighbour lanes
 // (DPP wave shifts; lanes past the grid hold the boundary column); only
 // lanes 0 and 63 load the column just outside the tile.  The grid is 1D and
 // XCD-ordered (x tiles fastest, then y, then z), so the tiles that share
 // halo rows and cache lines run on the same XCD and its L2.
-constexpr int RES3_LEN = 16;
-template <typename T>
+template <typename T, bool NORM>
 __global__ __launch_bounds__(256) void k_residual_3d(
     const double* __restrict__ u, int64_t up, int64_t upl, const double* __restrict__ f,
     int64_t fp, int64_t fpl, T* __restrict__ r, int64_t rp, int64_t rpl, int n, int len,
-    double inv_h2, double* __restrict__ partials, const int* __restrict__ done) {
+    double inv_h2, double* __restrict__ partials, const int* __restrict__ done, double* __restrict__ fpart) {
   if (*done) return;
   constexpr int R = 4;  // = R3Y (declared with the sweeps below)
   const int gx = (n - 2 + BX3 - 1) / BX3, gy = (n - 2 + BY3 * R - 1) / (BY3 * R);
@@ -413,7 +419,7 @@ __global__ __launch_bounds__(256) void k_residual_3d(
   const int xc = min(x, n - 1);
   const bool edge = lane == 0 || lane == BX3 - 1;
   const int xe = lane == 0 ? x - 1 : min(x + 1, n - 1);  // the edge lanes' outside column
-  double s = 0.0;
+  double s = 0.0, sf = 0.0;
   if (yb <= n - 2) {
     double c[R], zm[R];
 #pragma unroll
@@ -450,6 +456,7 @@ __global__ __launch_bounds__(256) void k_residual_3d(
         if (xin && yb + k <= n - 2) {
           st(r + int64_t(z) * rpl + int64_t(yb + k) * rp + x, typename Tr<T>::C(rv));
           s = fmac(rv, rv, s);
+          if (NORM) sf = fmac(fv[k], fv[k], sf);
         }
       }
 #pragma unroll
@@ -461,6 +468,11 @@ __global__ __launch_bounds__(256) void k_residual_3d(
   }
   s = block_sum<256>(s);
   if (threadIdx.x == 0 && threadIdx.y == 0) partials[lg] = s;
+  if (NORM) {
+    __syncthreads();
+    sf = block_sum<256>(sf);
+    if (threadIdx.x == 0 && threadIdx.y == 0) fpart[lg] = sf;
+  }
 }
 
 // 2D residual with the restriction to level 1 fused in.  Each wave walks a
@@ -473,11 +485,11 @@ __global__ __launch_bounds__(256) void k_residual_3d(
 // residual is rounded to T before it is restricted, as the separate
 // restriction would read it back, and the weights and their order are
 // those of tile_restrict_2d.
-template <typename T>
+template <typename T, bool NORM>
 __global__ __launch_bounds__(256) void k_residual_restrict_2d(
     const double* __restrict__ u, int64_t up, const double* __restrict__ f, int64_t fp,
     T* __restrict__ r, int64_t rp, T* __restrict__ rc, int64_t cp, int n, int len, double inv_h2,
-    double* __restrict__ partials, const int* __restrict__ done) {
+    double* __restrict__ partials, const int* __restrict__ done, double* __restrict__ fpart) {
   using C = typename Tr<T>::C;
   if (*done) return;
   const int wv = __builtin_amdgcn_readfirstlane(int(xcd_order(blockIdx.x, gridDim.x)) * 4 +
@@ -496,7 +508,7 @@ __global__ __launch_bounds__(256) void k_residual_restrict_2d(
   const int xc = min(x, n - 1);
   double ym = u[int64_t(Y0 - 1) * up + xc], c = u[int64_t(Y0) * up + xc];
   C rs2 = C(0), rs1 = C(0);  // row sums of rows y - 2, y - 1
-  double s = 0.0;
+  double s = 0.0, sf = 0.0;
   const int ylast = min(Y1, n - 2);  // the next band's first row, if interior
   for (int y = Y0; y <= ylast; ++y) {
     const double* row = u + int64_t(y) * up;
@@ -507,11 +519,13 @@ __global__ __launch_bounds__(256) void k_residual_restrict_2d(
     double xp = __shfl_down(c, 1);
     if (lane == 63) xp = row[min(xc + 1, n - 1)];
     const double au = fmac(4.0, c, -((xm + xp) + (ym + yp)));
-    const double rv = fmac(-inv_h2, au, f[int64_t(y) * fp + xc]);
+    const double fv = f[int64_t(y) * fp + xc];
+    const double rv = fmac(-inv_h2, au, fv);
     const C rt = xin ? rnd<T>(C(rv)) : C(0);
     if (own && y < Y1) {
       st(r + int64_t(y) * rp + x, C(rv));
       s = fmac(rv, rv, s);
+      if (NORM) sf = fmac(fv, fv, sf);
     }
     const C rs = fmac(C(2), rt, __shfl_up(rt, 1) + __shfl_down(rt, 1));
     if ((y & 1) && y >= Y0 + 2 && emit)  // y = 2J + 1: level-1 node (x / 2, J) complete
@@ -523,41 +537,70 @@ __global__ __launch_bounds__(256) void k_residual_restrict_2d(
   }
   s = wave_sum(s);
   if (lane == 0) partials[pidx] = s;
+  if (NORM) {
+    sf = wave_sum(sf);
+    if (lane == 0) fpart[pidx] = sf;
+  }
 }
 
 // ------------------------------------------------------------ finalize
 
-__global__ __launch_bounds__(256) void k_init_state(DevState* st, double tol, int stop_on_tol) {
-  if (threadIdx.x == 0) {
-    st->done = 0;
-    st->cycles = -1;
-    st->stop_on_tol = stop_on_tol;
-    st->fnorm = 1.0;
-    st->tol = tol;
-  }
-}
-
-// One workgroup of 1024 lanes (a per-wave partial count of ~8k, as the
-// fused 2D residual gives at 4097^2, is then 8 loads per lane).
+// Adds the per-block sums of r^2 in a fixed order, records the relative
+// residual of `cycle` and sets `done`.  fpart (a solve's first residual): also
+// adds the sums of f^2 and starts the state.  hst / hhist (pinned host
+// memory, or null): the state and the history so far are stored there too,
+// by this kernel, so that a host that only waits for the stream needs no
+// copies after it.  One workgroup of 1024 lanes (a per-wave partial count of
+// ~8k, as the fused 2D residual gives at 4097^2, is then 8 loads per lane).
 constexpr int FIN_NT = 1024;
-__global__ __launch_bounds__(FIN_NT) void k_finalize(const double* __restrict__ partials, int count,
-                                                     DevState* st, double* __restrict__ history,
-                                                     int cycle, int mode) {
-  if (mode == 1 && st->done) return;
+__device__ __forceinline__ double fin_sum(const double* __restrict__ partials, int count) {
   double s = 0.0;
   for (int i = threadIdx.x; i < count; i += FIN_NT) s += partials[i];
-  s = block_sum<FIN_NT>(s);
-  if (threadIdx.x == 0) {
-    if (mode == 0) {
-      const double fn = sqrt(s);
-      st->fnorm = fn > 0.0 ? fn : 1.0;
-    } else {
-      const double rel = sqrt(s) / st->fnorm;
+  return block_sum<FIN_NT>(s);
+}
+
+// The state after the norm of cycle `cycle`'s residual (one thread): v holds
+// the state before it.
+__device__ __forceinline__ double fin_update(DevState& v, double s, int cycle) {
+  const double rel = sqrt(s) / v.fnorm;
+  v.cycles = cycle;
+  if (!(rel <= 1.7976931348623157e308)) v.done = 2;  // NaN or Inf
+  else if (v.stop_on_tol && rel <= v.tol) v.done = 1;
+  return rel;
+}
+
+__global__ __launch_bounds__(FIN_NT) void k_finalize(const double* __restrict__ partials, int count,
+                                                     const double* __restrict__ fpart, double tol,
+                                                     int stop_on_tol, DevState* st,
+                                                     double* __restrict__ history, int cycle, DevState* hst,
+                                                     double* __restrict__ hhist) {
+  DevState v;
+  if (fpart) {
+    const double fn = sqrt(fin_sum(fpart, count));
+    v.done = 0;
+    v.cycles = -1;
+    v.stop_on_tol = stop_on_tol;
+    v.pad = 0;
+    v.fnorm = fn > 0.0 ? fn : 1.0;  // (used by thread 0, which holds the sum)
+    v.tol = tol;
+    __syncthreads();
+  } else {
+    v = *st;
+  }
+  const bool was_done = v.done != 0;  // the same in every thread
+  if (!was_done) {
+    const double s = fin_sum(partials, count);
+    if (threadIdx.x == 0) {
+      const double rel = fin_update(v, s, cycle);
       history[cycle] = rel;
-      st->cycles = cycle;
-      if (!(rel <= 1.7976931348623157e308)) st->done = 2;  // NaN or Inf
-      else if (st->stop_on_tol && rel <= st->tol) st->done = 1;
+      *st = v;
+      if (hhist) hhist[cycle] = rel;
     }
+  }
+  if (hst) {
+    if (threadIdx.x == 0) *hst = v;
+    const int end = was_done ? v.cycles + 1 : cycle;  // (entry `cycle` was stored above)
+    for (int i = threadIdx.x; i < end; i += FIN_NT) hhist[i] = history[i];
   }
 }
 
@@ -2537,20 +2580,11 @@ static hipError_t allow_lds(K kernel, size_t bytes) {
                              hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
 }
 
-hipError_t launch_norm2(int d, int n, const double* f, const Lay& fl, double* partials,
-                        int* count, hipStream_t s) {
-  const int len = walk_len(d, n);
-  const dim3 g = grid_of(d, n, len);
-  *count = int(g.x * g.y * g.z);
-  if (d == 2) HOMG_LAUNCH(k_norm2_2d, g, dim3(BX2), s, f + fl.off, fl.pitch, n, len, partials);
-  HOMG_LAUNCH(k_norm2_3d, g, dim3(BX3, BY3), s, f + fl.off, fl.pitch, fl.plane, n, len, partials);
-}
-
-template <typename T>
+template <typename T, bool NORM>
 static hipError_t residual_t(int d, int n, const double* u, const Lay& ul, const double* f,
                              const Lay& fl, const double* a, const Lay& al, void* r0,
                              const Lay& rl, double* partials, int* count, const int* done,
-                             hipStream_t s) {
+                             hipStream_t s, double* fpart) {
   const int len = walk_len(d, n);
   const dim3 g = grid_of(d, n, len);
   *count = int(g.x * g.y * g.z);
@@ -2559,56 +2593,63 @@ static hipError_t residual_t(int d, int n, const double* u, const Lay& ul, const
   T* r = static_cast<T*>(r0) + rl.off;
   if (d == 2) {
     if (a)
-      HOMG_LAUNCH((k_residual_2d<T, true>), g, dim3(BX2), s, u + ul.off, ul.pitch, f + fl.off,
-                  fl.pitch, a + al.off, al.pitch, r, rl.pitch, n, len, inv_h2, partials, done);
-    HOMG_LAUNCH((k_residual_2d<T, false>), g, dim3(BX2), s, u + ul.off, ul.pitch, f + fl.off,
+      HOMG_LAUNCH((k_residual_2d<T, true, NORM>), g, dim3(BX2), s, u + ul.off, ul.pitch, f + fl.off,
+                  fl.pitch, a + al.off, al.pitch, r, rl.pitch, n, len, inv_h2, partials, done, fpart);
+    HOMG_LAUNCH((k_residual_2d<T, false, NORM>), g, dim3(BX2), s, u + ul.off, ul.pitch, f + fl.off,
                 fl.pitch, (const double*)nullptr, int64_t(0), r, rl.pitch, n, len, inv_h2,
-                partials, done);
+                partials, done, fpart);
   }
-  const int inner = n - 2, len3 = inner < RES3_LEN ? inner : RES3_LEN;
-  const dim3 g3(((inner + BX3 - 1) / BX3) * ((inner + 4 * BY3 - 1) / (4 * BY3)) * ((inner + len3 - 1) / len3));
-  *count = int(g3.x);
-  HOMG_LAUNCH((k_residual_3d<T>), g3, dim3(BX3, BY3), s, u + ul.off, ul.pitch, ul.plane,
+  const int len3 = res3_len(n);
+  *count = int(res3_blocks(n, len3));
+  HOMG_LAUNCH((k_residual_3d<T, NORM>), dim3(*count), dim3(BX3, BY3), s, u + ul.off, ul.pitch, ul.plane,
               f + fl.off, fl.pitch, fl.plane, r, rl.pitch, rl.plane, n, len3, inv_h2, partials,
-              done);
+              done, fpart);
 }
 
 hipError_t launch_residual(int prec, int d, int n, const double* u, const Lay& ul,
                            const double* f, const Lay& fl, const double* a, const Lay& al,
                            void* r0, const Lay& rl, double* partials, int* count,
-                           const int* done, hipStream_t s) {
+                           const int* done, hipStream_t s, double* fpart) {
+#define RES_CASE(T)                                                                                          \
+  return fpart ? residual_t<T, true>(d, n, u, ul, f, fl, a, al, r0, rl, partials, count, done, s, fpart)    \
+               : residual_t<T, false>(d, n, u, ul, f, fl, a, al, r0, rl, partials, count, done, s, nullptr)
   switch (prec) {
-    case PREC_F64: return residual_t<double>(d, n, u, ul, f, fl, a, al, r0, rl, partials, count, done, s);
-    case PREC_F32: return residual_t<float>(d, n, u, ul, f, fl, a, al, r0, rl, partials, count, done, s);
-    default: return residual_t<bf16>(d, n, u, ul, f, fl, a, al, r0, rl, partials, count, done, s);
+    case PREC_F64: RES_CASE(double);
+    case PREC_F32: RES_CASE(float);
+    default: RES_CASE(bf16);
   }
+#undef RES_CASE
 }
 
-template <typename T>
+template <typename T, bool NORM>
 static hipError_t residual_restrict_t(int n, const double* u, const Lay& ul, const double* f,
                                       const Lay& fl, void* r0, const Lay& rl, void* rc0,
                                       const Lay& cl, double* partials, int* count, const int* done,
-                                      hipStream_t s) {
+                                      hipStream_t s, double* fpart) {
   const int len = rr_band(n);
   const int waves = rr_waves(n, len);
   *count = waves;
   const double h = 1.0 / double(n - 1);
   const double inv_h2 = 1.0 / (h * h);
-  HOMG_LAUNCH((k_residual_restrict_2d<T>), dim3((waves + 3) / 4), dim3(256), s, u + ul.off, ul.pitch,
+  HOMG_LAUNCH((k_residual_restrict_2d<T, NORM>), dim3((waves + 3) / 4), dim3(256), s, u + ul.off, ul.pitch,
               f + fl.off, fl.pitch, static_cast<T*>(r0) + rl.off, rl.pitch, static_cast<T*>(rc0) + cl.off,
-              cl.pitch, n, len, inv_h2, partials, done);
+              cl.pitch, n, len, inv_h2, partials, done, fpart);
 }
 
 hipError_t launch_residual_restrict_2d(int prec, int n, const double* u, const Lay& ul,
                                        const double* f, const Lay& fl, void* r0, const Lay& rl,
                                        void* rc, const Lay& cl, double* partials, int* count,
-                                       const int* done, hipStream_t s) {
+                                       const int* done, hipStream_t s, double* fpart) {
   if (n < 5 || (n - 1) % 2 || cl.side != (n - 1) / 2 + 1) return hipErrorInvalidValue;
+#define RR_CASE(T)                                                                                             \
+  return fpart ? residual_restrict_t<T, true>(n, u, ul, f, fl, r0, rl, rc, cl, partials, count, done, s, fpart) \
+               : residual_restrict_t<T, false>(n, u, ul, f, fl, r0, rl, rc, cl, partials, count, done, s, nullptr)
   switch (prec) {
-    case PREC_F64: return residual_restrict_t<double>(n, u, ul, f, fl, r0, rl, rc, cl, partials, count, done, s);
-    case PREC_F32: return residual_restrict_t<float>(n, u, ul, f, fl, r0, rl, rc, cl, partials, count, done, s);
-    default: return residual_restrict_t<bf16>(n, u, ul, f, fl, r0, rl, rc, cl, partials, count, done, s);
+    case PREC_F64: RR_CASE(double);
+    case PREC_F32: RR_CASE(float);
+    default: RR_CASE(bf16);
   }
+#undef RR_CASE
 }
 
 template <typename T>
@@ -2639,12 +2680,16 @@ hipError_t launch_l1(int prec, int d, int n, const double* uref, const double* u
 }
 
 hipError_t launch_finalize(const double* partials, int count, DevState* st, double* history,
-                           int cycle, int mode, hipStream_t s) {
-  HOMG_LAUNCH(k_finalize, dim3(1), dim3(FIN_NT), s, partials, count, st, history, cycle, mode);
+                           int cycle, hipStream_t s, DevState* hst, double* hhist) {
+  HOMG_LAUNCH(k_finalize, dim3(1), dim3(FIN_NT), s, partials, count, (const double*)nullptr, 0.0, 0, st, history,
+              cycle, hst, hhist);
 }
 
-hipError_t launch_init_state(DevState* st, double tol, int stop_on_tol, hipStream_t s) {
-  HOMG_LAUNCH(k_init_state, dim3(1), dim3(256), s, st, tol, stop_on_tol);
+hipError_t launch_finalize_first(const double* partials, const double* fpart, int count, double tol,
+                                 int stop_on_tol, DevState* st, double* history, hipStream_t s, DevState* hst,
+                                 double* hhist) {
+  HOMG_LAUNCH(k_finalize, dim3(1), dim3(FIN_NT), s, partials, count, fpart, tol, stop_on_tol, st, history, 0, hst,
+              hhist);
 }
 
 template <typename T>

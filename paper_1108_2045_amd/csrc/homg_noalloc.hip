@@ -21,7 +21,8 @@ using namespace homg;
 
 namespace {
 
-// Layout: DevState (32 B) | history[1] (8 B, padded to 64 B) | partials.
+// Layout: DevState (32 B) | history[1] (8 B) | zero flag (never written,
+// padded to 64 B) | sums of r^2 | sums of f^2 (half of the rest each).
 constexpr size_t NOALLOC_HEADER = 64;
 constexpr size_t NOALLOC_PARTIALS = HOMG_NOALLOC_MAX_PARTIALS;
 constexpr size_t NOALLOC_BYTES = NOALLOC_HEADER + sizeof(double) * NOALLOC_PARTIALS;
@@ -74,7 +75,8 @@ extern "C" homg_status homg_residual_noalloc(int ndim, int64_t n, const double* 
     return nfail(HOMG_ERR_UNSUPPORTED, "grid too large");
   if (!f || !u || !r) return nfail(HOMG_ERR_INVALID_ARG, "null f, u or r");
   const int side = int(n);
-  if (size_t(partials_bound(ndim, side)) > NOALLOC_PARTIALS)
+  if (size_t(partials_bound(ndim, side)) > NOALLOC_PARTIALS ||
+      size_t(residual_partials(ndim, side)) > NOALLOC_PARTIALS / 2)
     return nfail(HOMG_ERR_WORKSPACE, "grid needs more partial sums than the static workspace holds (" +
                                          std::to_string(NOALLOC_PARTIALS) + ")");
   int dev = -1;
@@ -86,19 +88,17 @@ extern "C" homg_status homg_residual_noalloc(int ndim, int64_t n, const double* 
   char* b = static_cast<char*>(base);
   DevState* st = reinterpret_cast<DevState*>(b);
   double* hist = reinterpret_cast<double*>(b + 32);
+  const int* zero = reinterpret_cast<const int*>(b + 48);
   double* partials = reinterpret_cast<double*>(b + NOALLOC_HEADER);
+  double* fpart = partials + NOALLOC_PARTIALS / 2;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const Lay dl = dense_layout(ndim, side);
   const Lay none;
   int count = 0;
-  // the same launches as homg_residual with a caller array r; the state
-  // reset clears the `done` flag that the residual kernel reads first
-  hipError_t e = launch_init_state(st, 0.0, 0, s);
-  if (e == hipSuccess) e = launch_norm2(ndim, side, f, dl, partials, &count, s);
-  if (e == hipSuccess) e = launch_finalize(partials, count, st, hist, 0, 0, s);
-  if (e == hipSuccess)
-    e = launch_residual(PREC_F64, ndim, side, u, dl, f, dl, nullptr, none, r, dl, partials, &count, &st->done, s);
-  if (e == hipSuccess) e = launch_finalize(partials, count, st, hist, 0, 1, s);
+  // the same launches as homg_residual with a caller array r
+  hipError_t e = launch_residual(PREC_F64, ndim, side, u, dl, f, dl, nullptr, none, r, dl, partials, &count, zero, s,
+                                 fpart);
+  if (e == hipSuccess) e = launch_finalize_first(partials, fpart, count, 0.0, 0, st, hist, s);
   if (e == hipSuccess && relres_out) e = hipMemcpyAsync(relres_out, hist, sizeof(double), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess && relres_out) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return nfail(HOMG_ERR_HIP, std::string("residual launch: ") + hipGetErrorString(e));

@@ -59,7 +59,7 @@ class KernelTime(ctypes.Structure):
                 ("reserved", ctypes.c_int), ("launches", ctypes.c_longlong), ("ms", ctypes.c_double)]
 
 
-KIND_NAMES = {0: "norm", 1: "residual", 2: "finalize", 3: "restrict", 4: "sweep",
+KIND_NAMES = {1: "residual", 2: "finalize", 3: "restrict", 4: "sweep",
               5: "gather", 6: "lattice", 7: "level_write", 8: "learned", 9: "transfer", 10: "tail"}
 
 
