@@ -102,7 +102,7 @@ def kernel_symbol(d, kind, level, mode):
     if kind == "residual":
         return "k_residual_%dd<double%s, false>" % (d, var2)
     if kind == "tail":
-        return "k_coarse_tail<double, %d>" % d
+        return "k_coarse_tail<double, %d, false, false, %s>" % (d, "true" if level == 0 else "false")
     if kind == "transfer":
         return "k_level_transfer_%dd<double, %s>" % (d, "true" if mode & 1 else "false")
     return {"restrict": "k_restrict_%dd<double>" % d,

@@ -263,8 +263,8 @@ homg_status homg_step_cycle(homg_handle h, const double *r0, double *acc, void *
  *   6) = the pass also stores the iterate before its last, bit 7 (kinds 4,
  *   6) = the pass takes its first iterate from the next coarser level's
  *   compact state (chained execution: no hand-over or whole-grid write in
- *   between); mode (kind 10): 1 = the tail leaves its finest level's state
- *   for the next level's first pass instead of handing over.
+ *   between); mode (kind 10): 1 = the coarse levels down to `level`, 2 = the
+ *   cycles of a whole solve of a small grid (level 0).
  * homg_get_profile synchronises outstanding events, then writes up to cap
  * entries and their count in *len.
  */

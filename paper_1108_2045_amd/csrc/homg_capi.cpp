@@ -81,6 +81,10 @@ struct homg_ctx {
   DevState* st = nullptr;
   double* hist = nullptr;
   int* zero_flag = nullptr;
+  DevState* zero_st = nullptr;  // the same zeros, as a state that is never done
+  // a residual whose norm the next cycle's tail reduces: its cycle (-1:
+  // none) and the number of partial sums
+  int fin_pending = -1, fin_count = 0;
   DevState* h_st = nullptr;  // pinned mirrors
   double* h_hist = nullptr;
   int device = 0;
@@ -582,23 +586,20 @@ homg_status run_level_learned(homg_ctx* h, int m, int it, bool first, bool last,
 
 // Number of leading schedule entries the coarse tail runs (0: none) and
 // the finest of their levels.  They must start at the coarsest level,
-// descend one level at a time, fit one workgroup's LDS, not be visited
-// again, and hand over to level ms - 1 >= 1 (chained execution, Laplacian,
-// damped Jacobi).
+// descend one level at a time, fit one workgroup, not be visited again, and
+// be followed by level ms - 1 (chained execution, Laplacian, damped Jacobi).
 int tail_levels(const homg_ctx* h, int* ms) {
   const int np = int(h->sched.size() / 2);
   if (h->temporal != 2 || h->active_smoother != 0 || h->has_coef || np < 3 || h->pow2) return 0;
   if (h->sched[0] != h->top_level) return 0;
   int cnt = 0;
-  for (int p = 0; p + 1 < np; ++p) {
+  for (int p = 0; p + 1 < np && p < BATCH_MAX_LEVELS; ++p) {
     const int m = h->sched[2 * p];
-    if (m != h->top_level - p || m < 2) break;
+    if (m != h->top_level - p || m < 1) break;
     const int nm = (h->n - 1) / (1 << m) + 1;
-    if (coarse_tail_lds(h->prec, h->d, nm, p + 1, top64(h)) > h->lds_limit) break;
-    if (h->sched[2 * (p + 1)] != m - 1) {  // the next entry must receive the hand-over
-      cnt = p + 1;
+    if (nm > tail_max_side(h->d) ||
+        coarse_tail_lds(h->prec, h->d, nm, p + 1, top64(h), h->has_coef, false) > h->lds_limit)
       break;
-    }
     cnt = p + 1;
   }
   // the last fused level must be followed by level ms - 1
@@ -606,11 +607,11 @@ int tail_levels(const homg_ctx* h, int* ms) {
   if (cnt < 2) return 0;
   *ms = h->sched[2 * (cnt - 1)];
   for (int p = cnt; p < np; ++p)
-    if (h->sched[2 * p] > *ms) return 0;  // a fused level is visited again
+    if (h->sched[2 * p] >= *ms) return 0;  // a fused level is visited again
   // a last coarse level in reduced precision runs whole-grid iterations
   // (its iterate goes into u unrounded) and reads the whole grid, which the
-  // tail does not write
-  if (cnt + 1 == np && h->prec != PREC_F64) return 0;
+  // tail does not write; level 0 takes the tail's state
+  if (cnt + 1 == np && h->prec != PREC_F64 && !(*ms == 1 && lat_target(h, 0))) return 0;
   return cnt;
 }
 
@@ -729,8 +730,9 @@ homg_status enqueue_residual(homg_ctx* h, const double* f, const double* u, int*
 
 // Enqueue one MFMG cycle (Sec. 2): restriction pyramid of r_0, the
 // schedule's whole-grid iterations with the last one adding e into acc,
-// then (if f != null) the new residual and its norm as history[cycle];
-// publish: the state and the history also go to their pinned mirrors.
+// then (if f != null) the new residual and its norm as history[cycle] (with a
+// coarse tail, reduced at the start of the next cycle); publish: the state
+// and the history also go to their pinned mirrors.
 homg_status enqueue_cycle(homg_ctx* h, const double* f, double* acc, int cycle, const int* done,
                           hipStream_t s, bool publish = false) {
   int ms = 0;
@@ -757,32 +759,26 @@ homg_status enqueue_cycle(homg_ctx* h, const double* f, double* acc, int cycle, 
     for (int k = 0; k < ntail; ++k) its[k] = h->sched[2 * (ntail - 1 - k) + 1];
     const int nms = (h->n - 1) / (1 << ms) + 1;
     const bool next_last = size_t(ntail) + 1 == np;
-    const bool lat = lat_target(h, ms - 1) && !(next_last && h->prec != PREC_F64);
-    if (lat || h->d == 3) {
-      // the tail leaves level ms's state; level ms - 1's first pass
-      // interpolates it, or else (3D) the multi-workgroup hand-over kernel
-      // does: the tail's own one-workgroup hand-over to 33^3 took 16 of its
-      // 37 us
-      LAUNCH_K(h, s, K_TAIL, ms, 1,
-               launch_coarse_tail(h->prec, h->d, nms, ntail, its, h->omega, h->r[ms], h->rl[ms], nullptr,
-                                  Lay(), done, s, h->xc[2 * ms], h->xc[2 * ms + 1], h->rl[ms], top64(h)));
-      if (lat) {
-        h->lat.prev = h->xc[2 * ms];
-        h->lat.cur = h->xc[2 * ms + 1];
-        h->lat.cl = h->rl[ms];
-        h->lat.zero_old = false;
-        h->lat_level = ms - 1;
-      } else {
-        LAUNCH_K(h, s, K_TRANSFER, ms - 1, 0,
-                 launch_level_transfer(h->prec, h->d, ms, h->xc[2 * ms], h->xc[2 * ms + 1], h->rl[ms], ms - 1,
-                                       h->xc[2 * (ms - 1)], h->rl[ms - 1], false, done, s));
-        h->chain_ready = ms - 1;
-      }
+    const bool lat = lat_target(h, ms - 1) && !(next_last && h->prec != PREC_F64 && ms > 1);
+    // the tail leaves level ms's state; level ms - 1's first pass
+    // interpolates it, or else the multi-workgroup hand-over kernel does
+    const Lay none;
+    LAUNCH_K(h, s, K_TAIL, ms, 1,
+             launch_coarse_tail(h->prec, h->d, nms, ntail, its, h->omega, nullptr, none, h->r[ms], h->rl[ms],
+                                h->xc[2 * ms], h->xc[2 * ms + 1], h->rl[ms], top64(h), f ? h->st : h->zero_st,
+                                h->hist, f && h->fin_pending >= 0 ? h->partials : nullptr, h->fin_count,
+                                h->fin_pending, s));
+    h->fin_pending = -1;
+    if (lat) {
+      h->lat.prev = h->xc[2 * ms];
+      h->lat.cur = h->xc[2 * ms + 1];
+      h->lat.cl = h->rl[ms];
+      h->lat.zero_old = false;
+      h->lat_level = ms - 1;
     } else {
-      LAUNCH_K(h, s, K_TAIL, ms, 0,
-               launch_coarse_tail(h->prec, h->d, nms, ntail, its, h->omega, h->r[ms], h->rl[ms],
-                                  h->xc[2 * (ms - 1)], h->rl[ms - 1], done, s, nullptr, nullptr, Lay(),
-                                  top64(h)));
+      LAUNCH_K(h, s, K_TRANSFER, ms - 1, 0,
+               launch_level_transfer(h->prec, h->d, ms, h->xc[2 * ms], h->xc[2 * ms + 1], h->rl[ms], ms - 1,
+                                     h->xc[2 * (ms - 1)], h->rl[ms - 1], false, done, s));
       h->chain_ready = ms - 1;
     }
     p0 = size_t(ntail);
@@ -805,6 +801,11 @@ homg_status enqueue_cycle(homg_ctx* h, const double* f, double* acc, int cycle, 
   if (f) {
     int count = 0;
     if (homg_status e = enqueue_residual(h, f, acc, &count, done, s)) return e;
+    if (ntail && !publish) {  // the next cycle's tail reduces the norm
+      h->fin_pending = cycle;
+      h->fin_count = count;
+      return HOMG_OK;
+    }
     LAUNCH_K(h, s, K_FINALIZE, 0, 1,
              launch_finalize(h->partials, count, h->st, h->hist, cycle, s, publish ? h->h_st : nullptr,
                              publish ? h->h_hist : nullptr));
@@ -816,6 +817,71 @@ homg_status check_ready(homg_ctx* h) {
   if (h->stencil == HOMG_DIFFUSION_5PT_2D && !h->has_coef)
     return fail(h, HOMG_ERR_INVALID_ARG, "diffusion stencil needs homg_set_coefficient first");
   return HOMG_OK;
+}
+
+// The outcome of a solve, from the pinned mirrors of the state and history.
+homg_status solve_result(homg_ctx* h, bool stop_on_tol, long long launches0, int syncs, int fell_back,
+                         homg_info* info) {
+  const int cycles = std::max(h->h_st->cycles, 0);
+  const double final_rel = h->h_hist[cycles];
+  if (info) {
+    info->cycles = cycles;
+    info->relres0 = h->h_hist[0];
+    info->final_relres = final_rel;
+    info->converged = (h->h_st->done == 1) ? 1 : 0;
+    if (info->history && info->history_cap > 0) {
+      const int nh = std::min(info->history_cap, cycles + 1);
+      std::memcpy(info->history, h->h_hist, sizeof(double) * nh);
+    }
+    info->sweeps = (long long)cycles * h->total_sweeps;
+    info->launches = h->launches - launches0;
+    info->host_syncs = syncs;
+    info->smoother_fell_back = fell_back;
+  }
+  h->active_smoother = h->smoother;
+  if (h->h_st->done == 2) return fail(h, HOMG_ERR_NUMERICAL, "non-finite residual norm");
+  if (stop_on_tol && h->h_st->done != 1)
+    return fail(h, HOMG_ERR_NOT_CONVERGED, "max_cycles reached above tol");
+  return HOMG_OK;
+}
+
+// Whether one workgroup runs whole solves (launch_small_solve): the chained
+// form with damped Jacobi on a grid of side up to tail_max_side whose
+// schedule descends from its coarsest level to level 0, each level once.
+// One launch replaces five per cycle; at these sizes a cycle is latency
+// alone.  With profiling on it is one entry (kind 10, level 0, mode 2).
+bool small_solve(const homg_ctx* h) {
+  const int np = int(h->sched.size() / 2);
+  if (h->temporal != 2 || h->active_smoother != 0 || h->pow2 || h->n > tail_max_side(h->d)) return false;
+  if (np != h->top_level + 1 || np > BATCH_MAX_LEVELS) return false;
+  for (int p = 0; p < np; ++p)
+    if (h->sched[2 * p] != h->top_level - p) return false;
+  return coarse_tail_lds(h->prec, h->d, h->n, np, top64(h), h->has_coef, true) <= h->lds_limit;
+}
+
+constexpr int SMALL_SOLVE_CYCLES = 64;  // cycles per launch at most
+
+homg_status run_small_solve(homg_ctx* h, const double* f, double* u, double tol, bool stop_on_tol, int fixed_cycles,
+                            long long launches0, hipStream_t s, homg_info* info) {
+  const int np = int(h->sched.size() / 2);
+  int its[BATCH_MAX_LEVELS];
+  for (int k = 0; k < np; ++k) its[k] = h->sched[2 * (np - 1 - k) + 1];
+  const int limit = stop_on_tol ? h->max_cycles : fixed_cycles;
+  const Lay none;
+  int syncs = 0;
+  for (int c0 = 0;; c0 += SMALL_SOLVE_CYCLES) {
+    const int c1 = std::min(limit, c0 + SMALL_SOLVE_CYCLES);
+    LAUNCH_K(h, s, K_TAIL, 0, 2,
+             launch_small_solve(h->prec, h->d, h->n, np, its, h->omega, h->has_coef ? h->a[0] : nullptr,
+                                h->has_coef ? h->al[0] : none, f, u, top64(h), residual_restricts(h), c0, c1,
+                                stop_on_tol ? tol : 0.0, stop_on_tol ? 1 : 0, h->st, h->hist, h->h_st, h->h_hist, s));
+    HIPCHK(h, hipStreamSynchronize(s));
+    ++syncs;
+    if (h->h_st->done || c1 >= limit) break;
+  }
+  if (h->prof.on)
+    if (homg_status pe = prof_harvest(h)) return pe;
+  return solve_result(h, stop_on_tol, launches0, syncs, 0, info);
 }
 
 homg_status solve_impl(homg_ctx* h, const double* f, double* u, double tol, int fixed_cycles,
@@ -835,10 +901,12 @@ homg_status solve_impl(homg_ctx* h, const double* f, double* u, double tol, int 
   h->active_smoother = h->smoother;
   int fell_back = 0;
 
+  if (small_solve(h)) return run_small_solve(h, f, u, tol, stop_on_tol, fixed_cycles, launches0, s, info);
   // the first residual also sums f^2; its reduction starts the state
   int count = 0;
   if (homg_status e = enqueue_residual(h, f, u, &count, h->zero_flag, s, h->partials + h->npart)) return e;
   const bool none_to_run = !stop_on_tol && fixed_cycles == 0;
+  h->fin_pending = -1;
   LAUNCH_K(h, s, K_FINALIZE, 0, 1,
            launch_finalize_first(h->partials, h->partials + h->npart, count, stop_on_tol ? tol : 0.0,
                                  stop_on_tol ? 1 : 0, h->st, h->hist, s, none_to_run ? h->h_st : nullptr,
@@ -888,27 +956,7 @@ homg_status solve_impl(homg_ctx* h, const double* f, double* u, double tol, int 
   // between the batches of cycles
   if (h->prof.on)
     if (homg_status pe = prof_harvest(h)) return pe;
-  const int cycles = std::max(h->h_st->cycles, 0);
-  const double final_rel = h->h_hist[cycles];
-  if (info) {
-    info->cycles = cycles;
-    info->relres0 = h->h_hist[0];
-    info->final_relres = final_rel;
-    info->converged = (h->h_st->done == 1) ? 1 : 0;
-    if (info->history && info->history_cap > 0) {
-      const int nh = std::min(info->history_cap, cycles + 1);
-      std::memcpy(info->history, h->h_hist, sizeof(double) * nh);
-    }
-    info->sweeps = (long long)cycles * h->total_sweeps;
-    info->launches = h->launches - launches0;
-    info->host_syncs = syncs;
-    info->smoother_fell_back = fell_back;
-  }
-  h->active_smoother = h->smoother;
-  if (h->h_st->done == 2) return fail(h, HOMG_ERR_NUMERICAL, "non-finite residual norm");
-  if (stop_on_tol && h->h_st->done != 1)
-    return fail(h, HOMG_ERR_NOT_CONVERGED, "max_cycles reached above tol");
-  return HOMG_OK;
+  return solve_result(h, stop_on_tol, launches0, syncs, fell_back, info);
 }
 
 }  // namespace
@@ -1154,6 +1202,7 @@ homg_status homg_create(homg_handle* out, int ndim, const int64_t* dims, int lev
     free_ctx(h);
     return fail(nullptr, HOMG_ERR_HIP, "workspace initialisation failed");
   }
+  h->zero_st = reinterpret_cast<DevState*>(h->zero_flag);
   *out = h;
   return HOMG_OK;
 }

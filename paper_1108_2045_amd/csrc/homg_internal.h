@@ -202,23 +202,36 @@ hipError_t launch_lattice_small(int prec, int d, int nm, int l, int it, double o
                                 const void* e, const Lay& el, const void* rm, const Lay& rl,
                                 const double* am, const Lay& al, void* xprev, void* xcur,
                                 const Lay& cl, const int* done, hipStream_t s);
-// Coarse tail (chained execution, Laplacian, damped Jacobi): levels ms ..
-// ms + nlev - 1 of a schedule that starts at the coarsest of them and
-// descends one level at a time, run by one workgroup in LDS: restriction
-// of r_ms (side nms, layout rl) to the coarser levels, its[k] iterations of
-// level ms + k, and the hand-over of level ms's final state to the compact
-// x_0 of level ms - 1 (dst, layout tl) -- or, given scur, level ms's final
-// x_it and x_{it-1} at every node into scur and sprev (layout sl, side nms)
-// for a next pass that interpolates them itself.  coarse_tail_lds: its LDS
-// bytes.
-// top64 (FP32/BF16 cycles): the coarsest level of the tail in FP64 (its
-// restriction, iterates and arithmetic), rounded to the storage type only
-// for the hand-over.
-size_t coarse_tail_lds(int prec, int d, int nms, int nlev, bool top64 = false);
-hipError_t launch_coarse_tail(int prec, int d, int nms, int nlev, const int* its, double omega,
-                              const void* rms, const Lay& rl, void* dst, const Lay& tl,
-                              const int* done, hipStream_t s, void* sprev = nullptr,
-                              void* scur = nullptr, const Lay& sl = Lay(), bool top64 = false);
+// One-workgroup kernels (chained execution, damped Jacobi): levels ms .. ms +
+// nlev - 1 of a schedule that starts at the coarsest of them and descends
+// one level at a time, its[k] iterations of level ms + k, on a finest side
+// of at most tail_max_side(d) (its nodes in registers, four per lane).
+// coarse_tail_lds: the LDS bytes.  top64 (FP32/BF16 cycles): the coarsest
+// level in FP64 (its restriction, iterates and arithmetic), rounded to the
+// storage type only for the hand-over.  a (2D, or null): level ms's nodal
+// coefficient, layout al.
+//
+// launch_coarse_tail: restricts r_ms (side nms, layout rl) and leaves level
+// ms's final x_it and x_{it-1} in scur and sprev (layout sl, interior nodes)
+// for a next pass that interpolates them itself or the hand-over kernel.
+// Does nothing if st->done; given partials, it first records the relative
+// residual of `cycle` from them, as launch_finalize, and stops there if that
+// ends the solve.
+// launch_small_solve: cycles c0 .. c1 of a solve of A u = f on a grid of side
+// n (f, u dense) from the residual to the update of u, with the residual
+// norms in hist and hhist and the final state in st and hst; c0 = 0 starts
+// the state.  rr: the norms summed as launch_residual_restrict_2d's, else as
+// launch_residual's.
+constexpr int tail_max_side(int d) { return d == 2 ? 65 : 17; }
+size_t coarse_tail_lds(int prec, int d, int nms, int nlev, bool top64, bool var, bool solve);
+hipError_t launch_coarse_tail(int prec, int d, int nms, int nlev, const int* its, double omega, const double* a,
+                              const Lay& al, const void* rms, const Lay& rl, void* sprev, void* scur, const Lay& sl,
+                              bool top64, DevState* st, double* hist, const double* partials, int count, int cycle,
+                              hipStream_t s);
+hipError_t launch_small_solve(int prec, int d, int n, int nlev, const int* its, double omega, const double* a,
+                              const Lay& al, const double* f, double* u, bool top64, bool rr, int c0, int c1,
+                              double tol, int stop, DevState* st, double* hist, DevState* hst, double* hhist,
+                              hipStream_t s);
 // FP64 coarsest level of a reduced-precision cycle: the restriction to it
 // (input in the storage type of prec, widened exactly, FP64 sums and
 // output); the exact widening of the level-l lattice of an array in the

@@ -20,162 +20,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "homg_device.h"
 #include "homg_internal.h"
 
 namespace homg {
-
-// ------------------------------------------------------------ storage types
-
-struct bf16 {
-  uint16_t bits;
-};
-
-template <typename T> struct Tr;
-template <> struct Tr<double> { using C = double; };
-template <> struct Tr<float> { using C = float; };
-template <> struct Tr<bf16> { using C = float; };
-
-__device__ __forceinline__ double ld(const double* p) { return *p; }
-__device__ __forceinline__ float ld(const float* p) { return *p; }
-__device__ __forceinline__ float ld(const bf16* p) {
-  return __uint_as_float(uint32_t(p->bits) << 16);
-}
-// Stores are streaming (non-temporal): every kernel here writes each output
-// element once and the next kernel reads it from memory, so the written
-// lines need not stay in the caches (on MI355X this lifts a read+write
-// stream from about 5.2 to 7.5 TB/s).
-__device__ __forceinline__ void st(double* p, double v) { __builtin_nontemporal_store(v, p); }
-__device__ __forceinline__ void st(float* p, float v) { __builtin_nontemporal_store(v, p); }
-// FP32 -> BF16, round to nearest even; NaN stays NaN (quieted: the upper
-// half of its bits with bit 6 set).  One v_cvt_pk_bf16_f32: on MI355X it
-// gives exactly that result for every one of the 2^32 FP32 bit patterns,
-// where the same rounding done with integer operations took five or six
-// instructions per value.
-__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, __bf16(f)); }
-__device__ __forceinline__ void st(bf16* p, float v) { __builtin_nontemporal_store(f2bf(v), &p->bits); }
-// Write-only passes (a level's whole-grid write, the coarse-level sweeps)
-// keep ordinary stores: on MI355X a pure write stream runs faster with them
-// (5.6 against 4.5 TB/s), while streams that also read gain from streaming
-// stores.
-__device__ __forceinline__ void st_w(double* p, double v) { *p = v; }
-__device__ __forceinline__ void st_w(float* p, float v) { *p = v; }
-__device__ __forceinline__ void st_w(bf16* p, float v) { p->bits = f2bf(v); }
-// u += v on the caller's FP64 array (the last iteration of a cycle).
-__device__ __forceinline__ void add_to(double* p, double v) { __builtin_nontemporal_store(*p + v, p); }
-
-// Value as it reads back after a store in storage type T.
-template <typename T> __device__ __forceinline__ typename Tr<T>::C rnd(typename Tr<T>::C v) { return v; }
-template <> __device__ __forceinline__ float rnd<bf16>(float v) {
-  return __uint_as_float(uint32_t(f2bf(v)) << 16);
-}
-
-__device__ __forceinline__ double fmac(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ __forceinline__ float fmac(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-
-// ------------------------------------------------------------ node formulas
-// Shared by every kernel that evaluates a node, so results agree bit for bit.
-
-// Damped Jacobi at a lattice node, constant coefficient (Sec. 2, level-m
-// relaxation with the sign that converges): c + w (h_l^2 r - (2d c - sum nb)),
-// w = omega / 2d.  q is the neighbour sum, added pairwise per axis.
-template <typename C>
-__device__ __forceinline__ C relax_const(C c, C q, C r, C w, C hl2, C two_d) {
-  C lap = fmac(two_d, c, -q);           // 2d c - sum nb
-  C res = fmac(hl2, r, -lap);           // h_l^2 r - (2d c - sum nb)
-  return fmac(w, res, c);
-}
-
-// Harmonic mean of two nodal coefficients (the face coefficient).
-__device__ __forceinline__ double harm(double a, double b) { return 2.0 * a * b / (a + b); }
-
-// Damped Jacobi for -div(a grad) at a lattice node: c + w (h_l^2 r - flux) / sum_a
-// with face coefficients the harmonic means of the nodal coefficient
-// (w = omega here).  Neighbours in the order -x, +x, -y, +y.
-template <typename C>
-__device__ __forceinline__ C relax_var(C c, C xm, C xp, C ym, C yp, double ac, double axm,
-                                       double axp, double aym, double ayp, C r, C w, C hl2) {
-  const C cxm = C(harm(ac, axm)), cxp = C(harm(ac, axp));
-  const C cym = C(harm(ac, aym)), cyp = C(harm(ac, ayp));
-  const C sa = (cxm + cxp) + (cym + cyp);
-  const C flux = fmac(cxm, c - xm, cxp * (c - xp)) + fmac(cym, c - ym, cyp * (c - yp));
-  return fmac(w / sa, fmac(hl2, r, -flux), c);
-}
-
-// Linear interpolation a + t (b - a), t in [0, 1).
-template <typename C>
-__device__ __forceinline__ C lerp(C a, C b, C t) { return fmac(t, b - a, a); }
-
-// ------------------------------------------------------------ lane exchange
-// The value of the previous / next lane of the wave (lane i gets lane i - 1
-// / i + 1) by a DPP wave shift (a VALU move; no LDS round trip as with
-// __shfl_up / __shfl_down).  The lane at the wave's end reads 0; every
-// caller discards what those lanes compute.
-__device__ __forceinline__ int dpp_prev(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, true);  // wave_shr:1
-}
-__device__ __forceinline__ int dpp_next(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, true);  // wave_shl:1
-}
-__device__ __forceinline__ float lane_prev(float v) { return __int_as_float(dpp_prev(__float_as_int(v))); }
-__device__ __forceinline__ float lane_next(float v) { return __int_as_float(dpp_next(__float_as_int(v))); }
-__device__ __forceinline__ double lane_prev(double v) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = unsigned(dpp_prev(int(b))), hi = unsigned(dpp_prev(int(b >> 32)));
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__device__ __forceinline__ double lane_next(double v) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = unsigned(dpp_next(int(b))), hi = unsigned(dpp_next(int(b >> 32)));
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-// The same shifts where the end lane takes `edge` instead: the DPP move
-// leaves a lane without a source lane at its old value (bound_ctrl off), so
-// no lane-dependent select follows the shift (the compiler may turn such a
-// select into a branch that runs the shift with the end lane switched off,
-// and an inactive source lane reads 0).
-__device__ __forceinline__ double lane_prev_or(double edge, double v) {
-  const long long b = __double_as_longlong(v), e = __double_as_longlong(edge);
-  const unsigned lo = unsigned(__builtin_amdgcn_update_dpp(int(e), int(b), 0x138, 0xf, 0xf, false));
-  const unsigned hi = unsigned(__builtin_amdgcn_update_dpp(int(e >> 32), int(b >> 32), 0x138, 0xf, 0xf, false));
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__device__ __forceinline__ double lane_next_or(double edge, double v) {
-  const long long b = __double_as_longlong(v), e = __double_as_longlong(edge);
-  const unsigned lo = unsigned(__builtin_amdgcn_update_dpp(int(e), int(b), 0x130, 0xf, 0xf, false));
-  const unsigned hi = unsigned(__builtin_amdgcn_update_dpp(int(e >> 32), int(b >> 32), 0x130, 0xf, 0xf, false));
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__device__ __forceinline__ float lane_prev_or(float edge, float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), 0x138, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float lane_next_or(float edge, float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), 0x130, 0xf, 0xf, false));
-}
-
-// ------------------------------------------------------------ reductions
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// Deterministic block sum (fixed order for a fixed block size); result valid
-// in thread 0.  Every thread of the block must call it.
-template <int NT>
-__device__ __forceinline__ double block_sum(double v) {
-  __shared__ double red[NT / 64];
-  v = wave_sum(v);
-  const int tid = threadIdx.x + threadIdx.y * blockDim.x;
-  if ((tid & 63) == 0) red[tid >> 6] = v;
-  __syncthreads();
-  double s = 0.0;
-  if (tid == 0) {
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) s += red[w];
-  }
-  return s;
-}
 
 // ------------------------------------------------------------ launch shapes
 
@@ -298,15 +146,6 @@ Lay padded_layout(int d, int side, int elem_bytes) {
   const int64_t rows = d == 3 ? int64_t(side) * side : side;
   L.alloc = L.off + rows * L.pitch + a;  // tail slack: whole final line
   return L;
-}
-
-// Workgroups of a launch are dealt to the 8 XCDs round-robin (workgroup h
-// runs on XCD h % 8).  xcd_order maps h to a logical index so that each XCD
-// receives one contiguous range of logical workgroups (a bijection on
-// [0, count)).
-__device__ __forceinline__ unsigned xcd_order(unsigned h, unsigned count) {
-  const unsigned q = count / 8, rem = count % 8, x = h % 8;
-  return x * q + min(x, rem) + h / 8;
 }
 
 // ------------------------------------------------------------ norm of f
@@ -552,23 +391,6 @@ __global__ __launch_bounds__(256) void k_residual_restrict_2d(
 // by this kernel, so that a host that only waits for the stream needs no
 // copies after it.  One workgroup of 1024 lanes (a per-wave partial count of
 // ~8k, as the fused 2D residual gives at 4097^2, is then 8 loads per lane).
-constexpr int FIN_NT = 1024;
-__device__ __forceinline__ double fin_sum(const double* __restrict__ partials, int count) {
-  double s = 0.0;
-  for (int i = threadIdx.x; i < count; i += FIN_NT) s += partials[i];
-  return block_sum<FIN_NT>(s);
-}
-
-// The state after the norm of cycle `cycle`'s residual (one thread): v holds
-// the state before it.
-__device__ __forceinline__ double fin_update(DevState& v, double s, int cycle) {
-  const double rel = sqrt(s) / v.fnorm;
-  v.cycles = cycle;
-  if (!(rel <= 1.7976931348623157e308)) v.done = 2;  // NaN or Inf
-  else if (v.stop_on_tol && rel <= v.tol) v.done = 1;
-  return rel;
-}
-
 __global__ __launch_bounds__(FIN_NT) void k_finalize(const double* __restrict__ partials, int count,
                                                      const double* __restrict__ fpart, double tol,
                                                      int stop_on_tol, DevState* st,
@@ -1914,272 +1736,6 @@ __global__ __launch_bounds__(256) void k_level_transfer_3d(
   st(dst + int64_t(K) * dpl + int64_t(J) * dp + I, v);
 }
 
-// ------------------------------------------------------------ coarse tail
-// The schedule's leading coarse levels ms .. M (descending one level at a
-// time, each visited once) in one workgroup, everything in LDS: the
-// restriction of r_ms to the coarser levels, each level's iterations from
-// the state the previous level hands over (0 on the coarsest), and the
-// hand-over itself -- the values the level's whole-grid pass would leave at
-// the lattice nodes of the next finer level.  The last hand-over goes to
-// the compact x_0 of level ms - 1 in memory.  The node formulas and the
-// rounding points are those of the restriction, small-lattice and transfer
-// kernels, so the result is theirs bit for bit.  Level ms + k has side
-// nk = ((nms - 1) >> k) + 1; LDS holds, per level, r and two iterates.
-// Per-level constants of the tail, worked out on the host (the reciprocals
-// and h^2 are the correctly rounded values the device division would give),
-// so that no level of the kernel starts with a division or a walk over the
-// coarser levels' sizes.
-struct TailLevel {
-  int it;        // iterations of level ms + k
-  int off;       // element offset of the level's R, P, Q arrays in LDS
-  float inv_ni;  // 1 / (nk - 2): splits the level's interior nodes
-  float inv_nt;  // 1 / (2 nk - 3): splits the next finer level's interior nodes
-  double hl2;    // h^2 = (1 / (nk - 1))^2
-};
-struct TailPlan {
-  TailLevel lv[BATCH_MAX_LEVELS];
-  float inv_side;  // 1 / nms: splits every node of level ms
-};
-
-template <int D>
-__device__ __forceinline__ int tail_count(int nk) { return D == 2 ? nk * nk : nk * nk * nk; }
-
-// i -> (I, J, K) in a box of side s (x fastest); a single-precision
-// reciprocal is exact here: i < 2^24 and (i + 1/2) / s stays at least
-// 1/(2 s) away from an integer.
-template <int D>
-__device__ __forceinline__ void tail_split(int i, int s, float inv_s, int& I, int& J, int& K) {
-  const int q = int((float(i) + 0.5f) * inv_s);
-  I = i - q * s;
-  if (D == 2) {
-    J = q;
-    K = 0;
-  } else {
-    K = int((float(q) + 0.5f) * inv_s);
-    J = q - K * s;
-  }
-}
-
-// TOP64 (reduced-precision cycles): the coarsest level of the tail runs in
-// FP64 -- its right-hand side restricted in FP64 from the stored values of
-// the level below, its iterates FP64 -- and only its final pair is rounded
-// to the storage type before the hand-over, as the separate launches do
-// (FP64 restriction, FP64 small-lattice iterations, rounding, transfer).
-template <typename T, int D, bool TOP64>
-__global__ __launch_bounds__(SMALL_NT) void k_coarse_tail(
-    const T* __restrict__ rms, int64_t rp, int64_t rpl, T* __restrict__ dst, int64_t dp, int64_t dpl,
-    int nms, int nlev, TailPlan tp, typename Tr<T>::C w, double w64, const int* __restrict__ done,
-    T* __restrict__ sprev, T* __restrict__ scur, int64_t sp, int64_t spl) {
-  using C = typename Tr<T>::C;
-  if (*done) return;
-  extern __shared__ __align__(16) unsigned char smem[];
-  C* base = reinterpret_cast<C*>(smem);
-  auto side = [&](int k) { return ((nms - 1) >> k) + 1; };
-  // per level: R (r), P (x_0 and odd-numbered iterates' sources), Q
-  auto lvl = [&](int k, int which) { return base + tp.lv[k].off + which * tail_count<D>(side(k)); };
-  // FP64 arrays of the coarsest level (TOP64): R, P, Q after all C arrays
-  const int ktop = nlev - 1, ctop = tail_count<D>(side(ktop));
-  double* top64 = nullptr;
-  if (TOP64) {
-    const size_t used = size_t(lvl(ktop, 3) - base) * sizeof(C);
-    top64 = reinterpret_cast<double*>(smem + ((used + 15) & ~size_t(15)));
-    for (int i = threadIdx.x; i < 3 * ctop; i += SMALL_NT) top64[i] = 0.0;
-  }
-  // Level ms: r is loaded (0 on the boundary) and the iterates' boundary
-  // nodes cleared; their interiors are written before they are read (the
-  // hand-over from level ms + 1, the first iteration).  The coarser levels'
-  // arrays start at 0 (x_0 = 0 on the coarsest level, and every boundary
-  // node).  Each thread issues its loads of r (clamped in-range addresses,
-  // the boundary's values dropped) before any LDS write, so the global
-  // latency is paid once per chunk of TAIL_LB nodes, not once per node.
-  constexpr int TAIL_LB = 8;
-  const int cnt0 = tail_count<D>(nms);
-  for (int i0 = 0; i0 < cnt0; i0 += TAIL_LB * SMALL_NT) {
-    C rv[TAIL_LB];
-    bool inner[TAIL_LB];
-#pragma unroll
-    for (int j = 0; j < TAIL_LB; ++j) {
-      const int i = min(i0 + j * SMALL_NT + int(threadIdx.x), cnt0 - 1);
-      int I, J, K;
-      tail_split<D>(i, nms, tp.inv_side, I, J, K);
-      inner[j] = I > 0 && I < nms - 1 && J > 0 && J < nms - 1 && (D == 2 || (K > 0 && K < nms - 1));
-      rv[j] = ld(rms + int64_t(K) * rpl + int64_t(J) * rp + I);
-    }
-    if (i0 == 0) {
-      const int z0 = tp.lv[nlev > 1 ? 1 : 0].off, z1 = tp.lv[ktop].off + 3 * ctop;
-      for (int i = z0 + threadIdx.x; nlev > 1 && i < z1; i += SMALL_NT) base[i] = C(0);
-    }
-    C* R = lvl(0, 0);
-    C* P = lvl(0, 1);
-    C* Q = lvl(0, 2);
-#pragma unroll
-    for (int j = 0; j < TAIL_LB; ++j) {
-      const int i = i0 + j * SMALL_NT + int(threadIdx.x);
-      if (i < cnt0) {
-        R[i] = inner[j] ? rv[j] : C(0);
-        if (!inner[j]) P[i] = Q[i] = C(0);
-      }
-    }
-  }
-  __syncthreads();
-  // restriction pyramid (full weighting, as k_restrict_*)
-  for (int k = 1; k < nlev; ++k) {
-    const int nf = side(k - 1), nc = side(k), ni = nc - 2, cnt = tail_count<D>(ni);
-    const float inv = tp.lv[k].inv_ni;
-    const C* F = lvl(k - 1, 0);
-    C* R = lvl(k, 0);  // boundary nodes stay 0
-    const int fp = nf, fpl = nf * nf;
-    for (int i = threadIdx.x; i < cnt; i += SMALL_NT) {
-      int I, J, K;
-      tail_split<D>(i, ni, inv, I, J, K);
-      ++I, ++J, K += D == 3;
-      const int o = (D == 3 ? K * nc * nc : 0) + J * nc + I;
-      if (TOP64 && k == ktop) {
-        // as k_restrict_*<T, double>: the stored values widened, FP64 sums
-        auto rs = [&](int q) { return fmac(2.0, double(F[q]), double(F[q - 1]) + double(F[q + 1])); };
-        double v;
-        if (D == 2) {
-          const int q = 2 * J * fp + 2 * I;
-          const double top = rs(q - fp), mid = rs(q), bot = rs(q + fp);
-          v = fmac(2.0, mid, top + bot) * 0.0625;
-        } else {
-          auto ps = [&](int q) { return fmac(2.0, rs(q), rs(q - fp) + rs(q + fp)); };
-          const int q = 2 * K * fpl + 2 * J * fp + 2 * I;
-          const double top = ps(q - fpl), mid = ps(q), bot = ps(q + fpl);
-          v = fmac(2.0, mid, top + bot) * 0.015625;
-        }
-        top64[o] = v;
-        continue;
-      }
-      auto rs = [&](int q) { return fmac(C(2), F[q], F[q - 1] + F[q + 1]); };
-      C v;
-      if (D == 2) {
-        const int q = 2 * J * fp + 2 * I;
-        const C top = rs(q - fp), mid = rs(q), bot = rs(q + fp);
-        v = fmac(C(2), mid, top + bot) * C(0.0625);
-      } else {
-        auto ps = [&](int q) { return fmac(C(2), rs(q), rs(q - fp) + rs(q + fp)); };
-        const int q = 2 * K * fpl + 2 * J * fp + 2 * I;
-        const C top = ps(q - fpl), mid = ps(q), bot = ps(q + fpl);
-        v = fmac(C(2), mid, top + bot) * C(0.015625);
-      }
-      R[o] = rnd<T>(v);
-    }
-    __syncthreads();
-  }
-  // levels from the coarsest down
-  for (int k = nlev - 1; k >= 0; --k) {
-    const int nk = side(k), pl = nk * nk;
-    const C hl2 = C(tp.lv[k].hl2);
-    const C* R = lvl(k, 0);
-    C* xa = lvl(k, 1);
-    C* xb = lvl(k, 2);
-    const int it = tp.lv[k].it;
-    const int ni = nk - 2, icnt = tail_count<D>(ni);
-    const float inv = tp.lv[k].inv_ni;
-    if (TOP64 && k == ktop) {
-      // FP64 iterations (as the FP64 small-lattice kernel), then the final
-      // pair rounded to the storage type into xa (x_{it-1}) and xb (x_it)
-      const double* R64 = top64;
-      double* ya = top64 + ctop;
-      double* yb = top64 + 2 * ctop;
-      const double hl2d = tp.lv[k].hl2;
-      for (int t = 1; t <= it; ++t) {
-        const double* src = (t & 1) ? ya : yb;
-        double* dstl = (t & 1) ? yb : ya;
-        for (int j = threadIdx.x; j < icnt; j += SMALL_NT) {
-          int I, J, K;
-          tail_split<D>(j, ni, inv, I, J, K);
-          const int i = (D == 3 ? (K + 1) * pl : 0) + (J + 1) * nk + (I + 1);
-          const double c = src[i];
-          double v;
-          if (D == 2)
-            v = relax_const<double>(c, (src[i - 1] + src[i + 1]) + (src[i - nk] + src[i + nk]), R64[i], w64,
-                                    hl2d, 4.0);
-          else
-            v = relax_const<double>(
-                c, ((src[i - 1] + src[i + 1]) + (src[i - nk] + src[i + nk])) + (src[i - pl] + src[i + pl]),
-                R64[i], w64, hl2d, 6.0);
-          dstl[i] = v;
-        }
-        __syncthreads();
-      }
-      const double* cur64 = (it & 1) ? yb : ya;
-      const double* prv64 = (it & 1) ? ya : yb;
-      for (int j = threadIdx.x; j < tail_count<D>(nk); j += SMALL_NT) {
-        xa[j] = rnd<T>(C(prv64[j]));
-        xb[j] = rnd<T>(C(cur64[j]));
-      }
-      __syncthreads();
-    }
-    for (int t = 1; t <= it && !(TOP64 && k == ktop); ++t) {
-      const C* src = (t & 1) ? xa : xb;
-      C* dstl = (t & 1) ? xb : xa;
-      for (int j = threadIdx.x; j < icnt; j += SMALL_NT) {
-        int I, J, K;
-        tail_split<D>(j, ni, inv, I, J, K);
-        const int i = (D == 3 ? (K + 1) * pl : 0) + (J + 1) * nk + (I + 1);
-        const C c = src[i];
-        C v;
-        if (D == 2)
-          v = relax_const<C>(c, (src[i - 1] + src[i + 1]) + (src[i - nk] + src[i + nk]), R[i], w, hl2, C(4));
-        else
-          v = relax_const<C>(c, ((src[i - 1] + src[i + 1]) + (src[i - nk] + src[i + nk])) + (src[i - pl] + src[i + pl]),
-                             R[i], w, hl2, C(6));
-        dstl[i] = rnd<T>(v);
-      }
-      __syncthreads();
-    }
-    const C* cur = (TOP64 && k == ktop) ? xb : ((it & 1) ? xb : xa);
-    const C* prv = (TOP64 && k == ktop) ? xa : ((it & 1) ? xa : xb);
-    if (k == 0 && scur) {
-      // level ms's final state (every node) for the next level's first
-      // pass, which interpolates it itself
-      for (int j = threadIdx.x; j < tail_count<D>(nk); j += SMALL_NT) {
-        int I, J, K;
-        tail_split<D>(j, nk, tp.inv_side, I, J, K);
-        const int64_t o = (D == 3 ? int64_t(K) * spl : 0) + int64_t(J) * sp + I;
-        st(sprev + o, prv[j]);
-        st(scur + o, cur[j]);
-      }
-      break;
-    }
-    // hand-over to level ms + k - 1 (side nt = 2 nk - 1): lattice nodes of
-    // this level take x_it, the others the interpolant of x_{it-1}
-    const int nt = 2 * nk - 1, ptl = nt * nt, nti = nt - 2;
-    C* tgt = k > 0 ? lvl(k - 1, 1) : nullptr;
-    const int tcnt = tail_count<D>(nti);
-    const float tinv = tp.lv[k].inv_nt;
-    for (int j = threadIdx.x; j < tcnt; j += SMALL_NT) {
-      int I, J, K;
-      tail_split<D>(j, nti, tinv, I, J, K);
-      ++I, ++J, K += D == 3;
-      const int i = (D == 3 ? K * ptl : 0) + J * nt + I;
-      const int xi = I >> 1, yj = J >> 1, zk = K >> 1;
-      const C tx = C(I & 1) * C(0.5), ty = C(J & 1) * C(0.5), tz = C(K & 1) * C(0.5);
-      const int c0 = (D == 3 ? zk * pl : 0) + yj * nk + xi;
-      C v;
-      if (!(I & 1) && !(J & 1) && !(K & 1)) {
-        v = cur[c0];
-      } else if (D == 2) {
-        const C top = lerp(prv[c0], prv[c0 + 1], tx), bot = lerp(prv[c0 + nk], prv[c0 + nk + 1], tx);
-        v = lerp(top, bot, ty);
-      } else {
-        const C* p = prv + c0;
-        const C* q = p + pl;
-        const C top = lerp(lerp(p[0], p[1], tx), lerp(p[nk], p[nk + 1], tx), ty);
-        const C bot = lerp(lerp(q[0], q[1], tx), lerp(q[nk], q[nk + 1], tx), ty);
-        v = lerp(top, bot, tz);
-      }
-      if (k > 0)
-        tgt[i] = rnd<T>(v);
-      else
-        st(dst + int64_t(K) * dpl + int64_t(J) * dp + I, v);
-    }
-    __syncthreads();
-  }
-}
-
 // ------------------------------------------------------------ tiled 3D lattice iterations
 // IT (<= 4) iterations of a small 3D compact lattice in one launch: each
 // workgroup holds a block of LT_B^3 owned nodes with a halo of IT nodes in
@@ -2560,24 +2116,6 @@ void set_launch_events(hipEvent_t start, hipEvent_t stop) {
 void current_launch_events(hipEvent_t* start, hipEvent_t* stop) {
   *start = g_ev_start;
   *stop = g_ev_stop;
-}
-
-#define HOMG_LAUNCH_SMEM(kernel, grid, block, smem, stream, ...)                              \
-  do {                                                                                        \
-    hipExtLaunchKernelGGL(kernel, grid, block, smem, stream, g_ev_start, g_ev_stop, 0,        \
-                          __VA_ARGS__);                                                       \
-    return hipGetLastError();                                                                 \
-  } while (0)
-
-#define HOMG_LAUNCH(kernel, grid, block, stream, ...) \
-  HOMG_LAUNCH_SMEM(kernel, grid, block, 0, stream, __VA_ARGS__)
-
-// Opt a kernel in to more than 64 KB of dynamic LDS.
-template <typename K>
-static hipError_t allow_lds(K kernel, size_t bytes) {
-  if (bytes <= 65536) return hipSuccess;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
 }
 
 template <typename T, bool NORM>
@@ -3336,70 +2874,6 @@ static hipError_t small_tz(int d, int nm, int l, int it, double omega, const voi
   HOMG_LAUNCH_SMEM((k_lattice_small_3d<T, ZERO>), dim3(1), dim3(SMALL_NT), lds, s, ee, el.pitch,
                    el.plane, l, r, rl.pitch, rl.plane, xp, xc, cl.pitch, cl.plane, nm, it,
                    C(omega / 6.0), hl2, done);
-}
-
-size_t coarse_tail_lds(int prec, int d, int nms, int nlev, bool top64) {
-  const size_t cs = prec == PREC_F64 ? 8 : 4;
-  size_t cnt = 0, ctop = 0;
-  for (int k = 0; k < nlev; ++k) {
-    const size_t nk = size_t((nms - 1) >> k) + 1;
-    ctop = d == 2 ? nk * nk : nk * nk * nk;
-    cnt += 3 * ctop;
-  }
-  size_t b = cnt * cs;
-  if (top64 && prec != PREC_F64) b = ((b + 15) & ~size_t(15)) + 3 * ctop * 8;
-  return b;
-}
-
-template <typename T, bool TOP64>
-static hipError_t tail_t(int d, int nms, int nlev, const int* its, double omega, const void* rms,
-                         const Lay& rl, void* dst, const Lay& tl, const int* done, hipStream_t s,
-                         void* sprev, void* scur, const Lay& sl) {
-  using C = typename Tr<T>::C;
-  TailPlan ti{};
-  int off = 0;
-  for (int k = 0; k < nlev; ++k) {
-    const int nk = ((nms - 1) >> k) + 1;
-    const double h = 1.0 / double(nk - 1);
-    ti.lv[k] = TailLevel{its[k], off, 1.0f / float(nk - 2), 1.0f / float(2 * nk - 3), h * h};
-    off += 3 * (d == 2 ? nk * nk : nk * nk * nk);
-  }
-  ti.inv_side = 1.0f / float(nms);
-  const size_t lds = coarse_tail_lds(sizeof(T) == 8 ? PREC_F64 : PREC_F32, d, nms, nlev, TOP64);
-  const T* r = static_cast<const T*>(rms) + rl.off;
-  T* o = dst ? static_cast<T*>(dst) + tl.off : nullptr;
-  T* sp = scur ? static_cast<T*>(sprev) + sl.off : nullptr;
-  T* sc = scur ? static_cast<T*>(scur) + sl.off : nullptr;
-  if (d == 2) {
-    hipError_t a = allow_lds(k_coarse_tail<T, 2, TOP64>, lds);
-    if (a != hipSuccess) return a;
-    HOMG_LAUNCH_SMEM((k_coarse_tail<T, 2, TOP64>), dim3(1), dim3(SMALL_NT), lds, s, r, rl.pitch, rl.plane, o,
-                     tl.pitch, tl.plane, nms, nlev, ti, C(omega / 4.0), omega / 4.0, done, sp, sc, sl.pitch,
-                     sl.plane);
-  }
-  hipError_t a = allow_lds(k_coarse_tail<T, 3, TOP64>, lds);
-  if (a != hipSuccess) return a;
-  HOMG_LAUNCH_SMEM((k_coarse_tail<T, 3, TOP64>), dim3(1), dim3(SMALL_NT), lds, s, r, rl.pitch, rl.plane, o,
-                   tl.pitch, tl.plane, nms, nlev, ti, C(omega / 6.0), omega / 6.0, done, sp, sc, sl.pitch,
-                   sl.plane);
-}
-
-hipError_t launch_coarse_tail(int prec, int d, int nms, int nlev, const int* its, double omega,
-                              const void* rms, const Lay& rl, void* dst, const Lay& tl,
-                              const int* done, hipStream_t s, void* sprev, void* scur, const Lay& sl,
-                              bool top64) {
-  if (nms < 5 || nlev < 2 || nlev > BATCH_MAX_LEVELS || ((nms - 1) >> (nlev - 1)) + 1 < 3 ||
-      (!scur && !dst) || (scur && (!sprev || sl.side != nms)))
-    return hipErrorInvalidValue;
-  switch (prec) {
-    case PREC_F64: return tail_t<double, false>(d, nms, nlev, its, omega, rms, rl, dst, tl, done, s, sprev, scur, sl);
-    case PREC_F32:
-      return top64 ? tail_t<float, true>(d, nms, nlev, its, omega, rms, rl, dst, tl, done, s, sprev, scur, sl)
-                   : tail_t<float, false>(d, nms, nlev, its, omega, rms, rl, dst, tl, done, s, sprev, scur, sl);
-    default:
-      return top64 ? tail_t<bf16, true>(d, nms, nlev, its, omega, rms, rl, dst, tl, done, s, sprev, scur, sl)
-                   : tail_t<bf16, false>(d, nms, nlev, its, omega, rms, rl, dst, tl, done, s, sprev, scur, sl);
-  }
 }
 
 hipError_t launch_lattice_small(int prec, int d, int nm, int l, int it, double omega, bool zero,
