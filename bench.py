@@ -80,6 +80,9 @@ def kernel_symbol(d, kind, level, mode):
     """The kernel's name as the profiler prints it (without the namespace and
     argument list), so the bench line and the rocprofv3 summary can be matched."""
     var2 = ", false" if d == 2 else ""
+    if kind in ("sweep", "lattice") and mode & 256 and mode & 8:  # several iterations in one launch, LDS tiles
+        return "k_lattice_%dd_tiled<double, %s, %s, %d%s>" % (
+            d, "true" if mode & 1 else "false", "true" if mode & 128 else "false", ((mode >> 4) & 3) + 1, var2)
     if kind == "sweep" and mode & 8:  # several level-0 iterations in one pass
         return "k_sweep_%dd_l0_tb<double, %s, %s, %d, %s>" % (
             d, "true" if mode & 1 else "false", "true" if mode & 2 else "false", ((mode >> 4) & 3) + 1,
@@ -98,7 +101,7 @@ def kernel_symbol(d, kind, level, mode):
     if kind == "level_write":
         return "k_level_write_%dd<double, %d>" % (d, mode)
     if kind == "residual" and mode & 1:  # with the restriction to level 1
-        return "k_residual_restrict_%dd<double, false>" % d
+        return "k_residual_restrict_%dd<double, false, false>" % d
     if kind == "residual":
         return "k_residual_%dd<double%s, false>" % (d, var2)
     if kind == "tail":

@@ -80,17 +80,19 @@ typedef struct homg_options {
     int temporal_block;    /* 2 (default): chained -- the iterations of a coarse level run on its
                               compact lattice, a coarse level followed by another coarse level
                               hands over only that level's lattice values, and the whole grid is
-                              written only before level 0 or the last level; for a Laplacian
-                              with damped Jacobi, a level followed by the next finer one hands
-                              over nothing: the finer level's first pass interpolates the
-                              coarser level's lattice values itself (always before level 0; in
-                              2D between any two lattices large enough for several workgroups;
-                              in 3D after the one-workgroup coarse tail);
+                              written only before level 0 or the last level; with damped
+                              Jacobi, a level followed by the next finer one hands over nothing:
+                              the finer level's first pass interpolates the coarser level's
+                              lattice values itself (always before level 0, and between any two
+                              lattices large enough for several workgroups), and the leading
+                              coarse levels run in one workgroup -- on small grids the whole
+                              solve does;
                               1: level-blocked -- as 2, but the whole grid is written after every
                               level;
                               0: one whole-grid launch per iteration.
-                              With 1 or 2, several iterations of a Laplacian (2D: four, 3D: two)
-                              run in one pass at level 0 and on large lattices.  All three give
+                              With 1 or 2, several iterations of damped Jacobi (2D: four, 3D: two
+                              or four) run in one pass at level 0 and on large lattices.  All
+                              three give
                               the same results bit for bit. */
     int grid_layout;       /* HOMG_GRID_NESTED (0): n = 2^k + 1 nodes per side, nested level
                               lattices (Sec. 2).  HOMG_GRID_POW2 (1): the power-of-two strategy of
@@ -263,7 +265,7 @@ homg_status homg_step_cycle(homg_handle h, const double *r0, double *acc, void *
  *   6) = the pass also stores the iterate before its last, bit 7 (kinds 4,
  *   6) = the pass takes its first iterate from the next coarser level's
  *   compact state (chained execution: no hand-over or whole-grid write in
- *   between); mode (kind 10): 1 = the coarse levels down to `level`, 2 = the
+ *   between), bit 8 = on LDS tiles (kind 4 with bit 3, kind 6); mode (kind 10): 1 = the coarse levels down to `level`, 2 = the
  *   cycles of a whole solve of a small grid (level 0).
  * homg_get_profile synchronises outstanding events, then writes up to cap
  * entries and their count in *len.

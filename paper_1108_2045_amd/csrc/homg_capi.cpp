@@ -73,7 +73,7 @@ struct homg_ctx {
   std::vector<void*> r;
   std::vector<double*> a;
   std::vector<void*> xc;   // level-blocked path: compact x_{t-1}, x_t pairs per level (2m, 2m+1)
-  std::vector<void*> xp3;  // Laplacian: third compact array per level (x_{it-1} of a multi-iteration pass)
+  std::vector<void*> xp3;  // third compact array per level (x_{it-1} of a multi-iteration pass)
   size_t lds_limit = 65536;
   bool has_coef = false;
   double* partials = nullptr;  // per-block sums of r^2, then npart further of f^2
@@ -279,21 +279,17 @@ bool top64(const homg_ctx* h) {
   return h->prec != PREC_F64 && h->active_smoother == 0 && h->top_level >= 1 && h->r64;
 }
 
-// Whether level mt's iterations (chained execution, Laplacian, damped
-// Jacobi) run as multi-iteration passes whose first pass takes its input
-// iterate from level mt + 1's compact state: level 0, or in 2D a compact
-// lattice too large for one workgroup.  In 3D the hand-over kernel plus a
-// plain pass measured as fast or faster on the compact lattices (MI355X,
-// 257^3: 31 against 31 us at 129^3, 13 against 16 us at 65^3, 12 against
-// 16 us at 33^3: at these sizes the pass is latency-bound and the extra
-// loads sit on its critical path).
+// Whether level mt's iterations (chained execution, damped Jacobi) run as
+// multi-iteration passes whose first pass takes its input iterate from level
+// mt + 1's compact state: level 0, or a compact lattice too large for one
+// workgroup.
 bool lat_target(const homg_ctx* h, int mt) {
-  if (h->temporal != 2 || h->active_smoother != 0 || h->has_coef || mt < 0 || h->pow2) return false;
+  if (h->temporal != 2 || h->active_smoother != 0 || mt < 0 || h->pow2) return false;
   if (top64(h) && mt == h->top_level) return false;  // starts from an FP64 x_0
   const int nm = (h->n - 1) / (1 << mt) + 1;
   if (nm < 5 || mt + 1 >= h->levels) return false;
   if (mt == 0) return true;
-  return lattice_small_lds(h->prec, h->d, nm, false) > h->lds_limit && mt < int(h->xp3.size()) &&
+  return lattice_small_lds(h->prec, h->d, nm, h->has_coef) > h->lds_limit && mt < int(h->xp3.size()) &&
          h->xp3[mt];
 }
 
@@ -346,6 +342,16 @@ homg_status run_top64(homg_ctx* h, int m, int it, bool first, bool last, int nex
   return finish_level(h, m, last, next_m, wmode, tp, tc, cur, acc, done, s);
 }
 
+// Whether level 0's multi-iteration passes run on LDS tiles: with a
+// variable coefficient always (its faces are formed once per pass), for the
+// Laplacian on grids so small that the walking passes are one serial chain
+// of row or plane steps.
+bool l0_tiled(const homg_ctx* h) {
+  if (h->pow2) return false;
+  if (h->d == 3) return h->n <= LT_MAX_SIDE && lattice_3d_tiled_lds(h->prec, LT_MAX_IT) <= h->lds_limit;
+  return h->has_coef || h->n <= LT2_MAX_L0;
+}
+
 homg_status run_level(homg_ctx* h, int m, int it, bool first, bool last, int next_m, int* cur,
                       double* acc, const int* done, hipStream_t s) {
   if (h->active_smoother == 1) return run_level_learned(h, m, it, first, last, next_m, cur, acc, done, s);
@@ -374,6 +380,26 @@ homg_status run_level(homg_ctx* h, int m, int it, bool first, bool last, int nex
   // chained path: the first pass reads the next coarser level's compact state
   const L1State* l1 = h->lat_level == m ? &h->lat : nullptr;
   h->lat_level = -1;
+  if (m == 0 && h->temporal && l0_tiled(h)) {
+    // level 0 on LDS tiles: up to LT_MAX_IT iterations per launch
+    for (int t0 = 0; t0 < it; t0 += LT_MAX_IT) {
+      const int g = std::min(LT_MAX_IT, it - t0);
+      const bool zero = first && t0 == 0, accum = last && t0 + g == it;
+      const L1State* src = t0 == 0 ? l1 : nullptr;
+      const int mode = SW_TBLOCK | (zero ? SW_ZERO_OLD : 0) | (accum ? SW_ACCUM : 0) | ((g - 1) << 4) |
+                       (src ? 128 : 0) | 256;
+      const void* xo = zero || src ? nullptr : h->e[*cur];
+      void* xn = accum ? nullptr : h->e[1 - *cur];
+      LAUNCH_K(h, s, K_SWEEP, 0, mode,
+               h->d == 3 ? launch_lattice_3d_tiled(h->prec, h->n, g, h->omega, xo, xn, nullptr, h->el, h->r[0],
+                                                   h->rl[0], zero, src, done, s, accum ? acc : nullptr, h->dl)
+                         : launch_lattice_2d_tiled(h->prec, h->n, g, h->omega, xo, xn, nullptr, h->el, h->r[0],
+                                                   h->rl[0], zero, src, done, s, accum ? acc : nullptr, h->dl, am,
+                                                   alm));
+      *cur = 1 - *cur;
+    }
+    return HOMG_OK;
+  }
   if (m == 0 && h->d == 3 && h->temporal) {
     // level 0 in 3D: up to TB3_MAX_IT iterations per pass, same iterates
     for (int t0 = 0; t0 < it; t0 += TB3_MAX_IT) {
@@ -389,9 +415,9 @@ homg_status run_level(homg_ctx* h, int m, int it, bool first, bool last, int nex
     }
     return HOMG_OK;
   }
-  if (m == 0 && h->d == 2 && !am && h->temporal) {
-    // level 0 of a 2D constant-coefficient grid: up to TB_MAX_IT iterations
-    // per pass (temporally blocked), the same iterates bit for bit
+  if (m == 0 && h->d == 2 && h->temporal) {
+    // level 0 of a larger 2D constant-coefficient grid: up to TB_MAX_IT
+    // iterations per pass (temporally blocked), the same iterates bit for bit
     for (int t0 = 0; t0 < it; t0 += TB_MAX_IT) {
       const int g = std::min(TB_MAX_IT, it - t0);
       const bool zero = first && t0 == 0, accum = last && t0 + g == it;
@@ -439,8 +465,8 @@ homg_status run_level(homg_ctx* h, int m, int it, bool first, bool last, int nex
                                   h->r[m], h->rl[m], am, alm, X0, X1, cl, done, s));
     xprev = X0;
     xcur = X1;
-  } else if (!am && m < int(h->xp3.size()) && h->xp3[m]) {
-    // Laplacian: several iterations per pass over the lattice
+  } else if (m < int(h->xp3.size()) && h->xp3[m]) {
+    // several iterations per pass over the lattice
     if (!first && !chained_in && !l1)
       LAUNCH_K(h, s, K_GATHER, m, 0, launch_gather(h->prec, h->d, h->e[*cur], h->el, l, X0, cl, done, s));
     void* X[2] = {X0, X1};
@@ -449,7 +475,7 @@ homg_status run_level(homg_ctx* h, int m, int it, bool first, bool last, int nex
     const int gmax = h->d == 2 ? TB_MAX_IT : TB3_MAX_IT;
     const bool tiled = (h->d == 3 && nm <= LT_MAX_SIDE &&
                         lattice_3d_tiled_lds(h->prec, std::min(it, LT_MAX_IT)) <= h->lds_limit) ||
-                       (h->d == 2 && nm <= LT2_MAX_SIDE);
+                       (h->d == 2 && (am || nm <= LT2_MAX_SIDE));
     for (int t0 = 0; tiled && t0 < it; t0 += LT_MAX_IT) {
       // small lattice: up to four iterations per launch on LDS tiles (x_{it-1}
       // of every launch into the third array; the last one's is kept)
@@ -461,7 +487,8 @@ homg_status run_level(homg_ctx* h, int m, int it, bool first, bool last, int nex
                h->d == 3 ? launch_lattice_3d_tiled(h->prec, nm, g, h->omega, (zero || ls) ? nullptr : X[src],
                                                    X[1 - src], h->xp3[m], cl, h->r[m], h->rl[m], zero, ls, done, s)
                          : launch_lattice_2d_tiled(h->prec, nm, g, h->omega, (zero || ls) ? nullptr : X[src],
-                                                   X[1 - src], h->xp3[m], cl, h->r[m], h->rl[m], zero, ls, done, s));
+                                                   X[1 - src], h->xp3[m], cl, h->r[m], h->rl[m], zero, ls, done, s,
+                                                   nullptr, none, am, alm));
       xprev = h->xp3[m];
       src = 1 - src;
     }
@@ -587,10 +614,10 @@ homg_status run_level_learned(homg_ctx* h, int m, int it, bool first, bool last,
 // Number of leading schedule entries the coarse tail runs (0: none) and
 // the finest of their levels.  They must start at the coarsest level,
 // descend one level at a time, fit one workgroup, not be visited again, and
-// be followed by level ms - 1 (chained execution, Laplacian, damped Jacobi).
+// be followed by level ms - 1 (chained execution, damped Jacobi).
 int tail_levels(const homg_ctx* h, int* ms) {
   const int np = int(h->sched.size() / 2);
-  if (h->temporal != 2 || h->active_smoother != 0 || h->has_coef || np < 3 || h->pow2) return 0;
+  if (h->temporal != 2 || h->active_smoother != 0 || np < 3 || h->pow2) return 0;
   if (h->sched[0] != h->top_level) return 0;
   int cnt = 0;
   for (int p = 0; p + 1 < np && p < BATCH_MAX_LEVELS; ++p) {
@@ -616,11 +643,10 @@ int tail_levels(const homg_ctx* h, int* ms) {
 }
 
 // Whether a solve's residual also restricts to level 1 in the same pass
-// (2D Laplacian whose schedule visits a coarse level).
+// (2D nested grids whose schedule visits a coarse level).
 bool residual_restricts(const homg_ctx* h) {
   // (an FP64 coarsest level 1 takes its restriction from the separate kernel)
-  return h->d == 2 && !h->has_coef && h->top_level >= 1 && h->n >= 5 && !(top64(h) && h->top_level == 1) &&
-         !h->pow2;
+  return h->d == 2 && h->top_level >= 1 && h->n >= 5 && !(top64(h) && h->top_level == 1) && !h->pow2;
 }
 
 // One restriction of the cycle's pyramid, m -> m + 1 (in FP64 onto an FP64
@@ -714,14 +740,14 @@ homg_status enqueue_residual(homg_ctx* h, const double* f, const double* u, int*
                              const int* done, hipStream_t s, double* fpart = nullptr) {
   h->rhs_ready = residual_restricts(h) ? 1 : 0;
   h->rhs_top64 = false;
-  if (residual_restricts(h)) {
-    LAUNCH_K(h, s, K_RESIDUAL, 0, 1,
-             launch_residual_restrict_2d(h->prec, h->n, u, h->dl, f, h->dl, h->r[0], h->rl[0], h->r[1],
-                                         h->rl[1], h->partials, count, done, s, fpart));
-    return HOMG_OK;
-  }
   const Lay none;
   const double* a0 = h->has_coef ? h->a[0] : nullptr;
+  if (residual_restricts(h)) {
+    LAUNCH_K(h, s, K_RESIDUAL, 0, 1,
+             launch_residual_restrict_2d(h->prec, h->n, u, h->dl, f, h->dl, a0, a0 ? h->al[0] : none, h->r[0],
+                                         h->rl[0], h->r[1], h->rl[1], h->partials, count, done, s, fpart));
+    return HOMG_OK;
+  }
   LAUNCH_K(h, s, K_RESIDUAL, 0, 0,
            launch_residual(h->prec, h->d, h->n, u, h->dl, f, h->dl, a0, a0 ? h->al[0] : none, h->r[0],
                            h->rl[0], h->partials, count, done, s, fpart));
@@ -764,7 +790,8 @@ homg_status enqueue_cycle(homg_ctx* h, const double* f, double* acc, int cycle, 
     // interpolates it, or else the multi-workgroup hand-over kernel does
     const Lay none;
     LAUNCH_K(h, s, K_TAIL, ms, 1,
-             launch_coarse_tail(h->prec, h->d, nms, ntail, its, h->omega, nullptr, none, h->r[ms], h->rl[ms],
+             launch_coarse_tail(h->prec, h->d, nms, ntail, its, h->omega, h->has_coef ? h->a[ms] : nullptr,
+                                h->has_coef ? h->al[ms] : none, h->r[ms], h->rl[ms],
                                 h->xc[2 * ms], h->xc[2 * ms + 1], h->rl[ms], top64(h), f ? h->st : h->zero_st,
                                 h->hist, f && h->fin_pending >= 0 ? h->partials : nullptr, h->fin_count,
                                 h->fin_pending, s));
@@ -1136,13 +1163,11 @@ homg_status homg_create(homg_handle* out, int ndim, const int64_t* dims, int lev
     for (int m = 1; m < levels && !stt; ++m)
       for (int b = 0; b < 2 && !stt; ++b)
         stt = dev_alloc(h, &h->xc[2 * m + b], size_t(h->rl[m].alloc) * eb);
-    if (h->stencil != HOMG_DIFFUSION_5PT_2D) {
-      h->xp3.assign(levels, nullptr);
-      for (int m = 1; m < levels && !stt; ++m) {
-        const int nm = (h->n - 1) / (1 << m) + 1;
-        if (nm >= (ndim == 2 ? 65 : 33))  // lattices that may be too large for one workgroup's LDS
-          stt = dev_alloc(h, &h->xp3[m], size_t(h->rl[m].alloc) * eb);
-      }
+    h->xp3.assign(levels, nullptr);
+    for (int m = 1; m < levels && !stt; ++m) {
+      const int nm = (h->n - 1) / (1 << m) + 1;
+      if (nm >= (ndim == 2 ? 65 : 33))  // lattices that may be too large for one workgroup's LDS
+        stt = dev_alloc(h, &h->xp3[m], size_t(h->rl[m].alloc) * eb);
     }
   }
   if (h->prec != PREC_F64 && h->top_level >= 1 && !stt) {

@@ -52,13 +52,13 @@ hipError_t launch_residual(int prec, int d, int n, const double* u, const Lay& u
                            const double* f, const Lay& fl, const double* a, const Lay& al,
                            void* r0, const Lay& rl, double* partials, int* count,
                            const int* done, hipStream_t s, double* fpart = nullptr);
-// 2D Laplacian (n >= 5): the residual of launch_residual and, in the same
+// 2D (n >= 5): the residual of launch_residual and, in the same
 // pass, its full-weighting restriction to level 1 (rc, layout cl of side
 // (n-1)/2+1), equal bit for bit to launch_restrict applied to the stored r0.
 // Per-wave sums of r^2 (their number in *count) and, given fpart, of f^2.
 hipError_t launch_residual_restrict_2d(int prec, int n, const double* u, const Lay& ul,
-                                       const double* f, const Lay& fl, void* r0, const Lay& rl,
-                                       void* rc, const Lay& cl, double* partials, int* count,
+                                       const double* f, const Lay& fl, const double* a, const Lay& al, void* r0,
+                                       const Lay& rl, void* rc, const Lay& cl, double* partials, int* count,
                                        const int* done, hipStream_t s, double* fpart = nullptr);
 // Sums `count` partials in a fixed order: history[cycle] = sqrt(sum)/fnorm,
 // and `done` is updated (nothing if it is set).  Given hst / hhist (pinned
@@ -138,22 +138,27 @@ hipError_t launch_sweep_2d_l0_tb(int prec, int n, int it, double omega, const vo
                                  const Lay& el, const void* rm, const Lay& rl, double* u,
                                  const Lay& ul, bool zero, bool accum, const int* done, hipStream_t s,
                                  int len = 0, const L1State* l1 = nullptr);
-// 3D compact lattice of side n (Laplacian, damped Jacobi): it (<= LT_MAX_IT)
+// 3D lattice of side n (Laplacian, damped Jacobi): it (<= LT_MAX_IT)
 // iterations in one launch, blocks of 8^3 owned nodes iterating with a halo
-// of `it` nodes in LDS.  x_0: 0 (zero), the compact array xo, or the next
-// coarser level's state (l1); x_it into xn and x_{it-1} into xprev (layout
-// cl; neither may alias xo).  lattice_3d_tiled_lds: its LDS bytes.
+// of `it` nodes in LDS.  x_0: 0 (zero), the array xo, or the next coarser
+// level's state (l1); x_it into xn and, if given, x_{it-1} into xprev (layout
+// cl; none may alias another), or -- u given, xn and xprev null, the last
+// pass of level 0 -- x_it, unrounded, added into u (layout ul).
+// lattice_3d_tiled_lds: its LDS bytes.
 constexpr int LT_MAX_IT = 4;
 constexpr int LT_MAX_SIDE = 65;  // the solver uses it on lattices up to this side
 size_t lattice_3d_tiled_lds(int prec, int it);
 hipError_t launch_lattice_3d_tiled(int prec, int n, int it, double omega, const void* xo, void* xn, void* xprev,
                                    const Lay& cl, const void* rm, const Lay& rl, bool zero, const L1State* l1,
-                                   const int* done, hipStream_t s);
-// The same on a 2D compact lattice (blocks of 24^2 owned nodes).
-constexpr int LT2_MAX_SIDE = 513;  // the solver uses it on lattices up to this side
+                                   const int* done, hipStream_t s, double* u = nullptr, const Lay& ul = Lay());
+// The same on a 2D lattice (blocks of 24^2 owned nodes); a: the lattice's
+// nodal coefficient (layout al), or null for the Laplacian.
+constexpr int LT2_MAX_SIDE = 513;  // the solver uses it on Laplacian lattices up to this side,
+constexpr int LT2_MAX_L0 = 257;    // on level 0 up to this one, and with a coefficient on all
 hipError_t launch_lattice_2d_tiled(int prec, int n, int it, double omega, const void* xo, void* xn, void* xprev,
                                    const Lay& cl, const void* rm, const Lay& rl, bool zero, const L1State* l1,
-                                   const int* done, hipStream_t s);
+                                   const int* done, hipStream_t s, double* u = nullptr, const Lay& ul = Lay(),
+                                   const double* a = nullptr, const Lay& al = Lay());
 // The same on the compact lattice of a coarse level (side nm): x_it into en
 // and, when eprev is not null, x_{it-1} into eprev (layout cl); l1: x_0
 // from the next coarser level's state.

@@ -324,9 +324,12 @@ __global__ __launch_bounds__(256) void k_residual_3d(
 // residual is rounded to T before it is restricted, as the separate
 // restriction would read it back, and the weights and their order are
 // those of tile_restrict_2d.
-template <typename T, bool NORM>
+// VAR: the faces of -div(a grad u) as tile_residual_2d's; a lane forms its
+// west and north face and takes the others from the next lane and the row
+// before.
+template <typename T, bool NORM, bool VAR>
 __global__ __launch_bounds__(256) void k_residual_restrict_2d(
-    const double* __restrict__ u, int64_t up, const double* __restrict__ f, int64_t fp,
+    const double* __restrict__ a, int64_t ap, const double* __restrict__ u, int64_t up, const double* __restrict__ f, int64_t fp,
     T* __restrict__ r, int64_t rp, T* __restrict__ rc, int64_t cp, int n, int len, double inv_h2,
     double* __restrict__ partials, const int* __restrict__ done, double* __restrict__ fpart) {
   using C = typename Tr<T>::C;
@@ -347,6 +350,12 @@ __global__ __launch_bounds__(256) void k_residual_restrict_2d(
   const int xc = min(x, n - 1);
   double ym = u[int64_t(Y0 - 1) * up + xc], c = u[int64_t(Y0) * up + xc];
   C rs2 = C(0), rs1 = C(0);  // row sums of rows y - 2, y - 1
+  double ac = 0.0, cym = 0.0;  // VAR: the coefficient of row y, its south face
+  const double* acol = VAR ? a + xc : nullptr;
+  if (VAR) {
+    ac = acol[int64_t(Y0) * ap];
+    cym = harm(ac, acol[int64_t(Y0 - 1) * ap]);
+  }
   double s = 0.0, sf = 0.0;
   const int ylast = min(Y1, n - 2);  // the next band's first row, if interior
   for (int y = Y0; y <= ylast; ++y) {
@@ -357,7 +366,19 @@ __global__ __launch_bounds__(256) void k_residual_restrict_2d(
     const double xm = __shfl_up(c, 1);
     double xp = __shfl_down(c, 1);
     if (lane == 63) xp = row[min(xc + 1, n - 1)];
-    const double au = fmac(4.0, c, -((xm + xp) + (ym + yp)));
+    double au;
+    if (VAR) {
+      const double ayp = acol[int64_t(y + 1) * ap];
+      // lane 0's west face belongs to no residual that is used
+      const double cxm = harm(ac, __shfl_up(ac, 1)), cyp = harm(ayp, ac);
+      double cxp = __shfl_down(cxm, 1);
+      if (lane == 63) cxp = harm(ac, a[int64_t(y) * ap + min(xc + 1, n - 1)]);
+      au = fmac(cxm, c - xm, cxp * (c - xp)) + fmac(cym, c - ym, cyp * (c - yp));
+      ac = ayp;
+      cym = cyp;
+    } else {
+      au = fmac(4.0, c, -((xm + xp) + (ym + yp)));
+    }
     const double fv = f[int64_t(y) * fp + xc];
     const double rv = fmac(-inv_h2, au, fv);
     const C rt = xin ? rnd<T>(C(rv)) : C(0);
@@ -1744,7 +1765,8 @@ __global__ __launch_bounds__(256) void k_level_transfer_3d(
 // instead of exchanged between launches.  x_0 is 0 (ZERO), the compact array
 // xo, or (LAT) the next coarser level's final state seen on this lattice
 // (its x_it at shared lattice nodes, else the trilinear interpolant of its
-// x_{it-1}); writes x_IT to xn and x_{IT-1} to xp at the owned nodes.  The
+// x_{it-1}); writes x_IT to xn and x_{IT-1} to xp (if given) at the owned
+// nodes, or adds x_IT, unrounded, into uacc (level 0's last pass).  The
 // node formula, summation order, interpolation and rounding are those of
 // k_lattice_3d_tb and k_level_transfer_3d, so the bits are theirs.  Each
 // lane keeps its tile nodes (up to four) for every phase, with r there in
@@ -1765,7 +1787,8 @@ template <typename T, bool ZERO, bool LAT, int IT>
 __global__ __launch_bounds__(LT_NT) void k_lattice_3d_tiled(
     const T* __restrict__ xo, T* __restrict__ xn, T* __restrict__ xp, int64_t cp, int64_t cpl,
     const T* __restrict__ r, int64_t rp, int64_t rpl, int n, int nb, typename Tr<T>::C w,
-    typename Tr<T>::C hl2, const int* __restrict__ done, L1Src<T> l1) {
+    typename Tr<T>::C hl2, const int* __restrict__ done, L1Src<T> l1, double* __restrict__ uacc, int64_t up,
+    int64_t upl) {
   using C = typename Tr<T>::C;
   if (*done) return;
   constexpr int S = lt_side<IT>(), S2 = S * S, S3 = S2 * S, SC = lt_cside(S), SC2 = SC * SC, SC3 = SC2 * SC;
@@ -1786,6 +1809,7 @@ __global__ __launch_bounds__(LT_NT) void k_lattice_3d_tiled(
   int qi[U], qj[U], qk[U];
   bool live[U], in[U];
   C rv[U], xv[U];
+  double uo[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int q = int(threadIdx.x) + u * LT_NT;
@@ -1800,6 +1824,7 @@ __global__ __launch_bounds__(LT_NT) void k_lattice_3d_tiled(
     rv[u] = ld(r + cz * rpl + cy * rp + cx);
     xv[u] = C(0);
     if (!ZERO && !LAT) xv[u] = ld(xo + cz * cpl + cy * cp + cx);
+    uo[u] = uacc ? uacc[cz * upl + cy * up + cx] : 0.0;
   }
   const int cx0 = max(gx0, 0) >> 1, cy0 = max(gy0, 0) >> 1, cz0 = max(gz0, 0) >> 1;
   if (LAT) {
@@ -1871,30 +1896,41 @@ __global__ __launch_bounds__(LT_NT) void k_lattice_3d_tiled(
       // the last iteration's region is the owned block: x_{IT-1} (src) and x_IT
       if (t == IT && in[u]) {
         const int64_t o = int64_t(gz0 + qk[u]) * cpl + int64_t(gy0 + qj[u]) * cp + (gx0 + qi[u]);
-        st(xn + o, v);
-        st(xp + o, src[c]);
+        if (uacc) {
+          uacc[int64_t(gz0 + qk[u]) * upl + int64_t(gy0 + qj[u]) * up + (gx0 + qi[u])] = uo[u] + double(v);
+        } else {
+          st(xn + o, v);
+          if (xp) st(xp + o, src[c]);
+        }
       }
     }
     if (t < IT) __syncthreads();
   }
 }
 
-// The same for a 2D compact lattice: blocks of LT2_B^2 owned nodes with a
-// halo of IT nodes, one lane per tile node (1024 lanes for four
-// iterations).  Interpolation, node formula and rounding are those of
-// k_lattice_2d_tb and k_level_transfer_2d.
+// The same for a 2D lattice: blocks of LT2_B^2 owned nodes with a halo of IT
+// nodes, one lane per tile node (1024 lanes for four iterations).
+// Interpolation, node formula and rounding are those of k_lattice_2d_tb and
+// k_level_transfer_2d; VAR: of k_sweep_2d_l0 with a coefficient.  There a
+// node costs four harmonic means and a division, nine tenths of a single
+// iteration's time (11.3 us at 1025^2): here each lane forms its west and
+// south face once per pass, takes the other two from its neighbours' (the
+// mean is symmetric to the bit), and keeps them and w / sum for all IT
+// iterations.
 constexpr int LT2_B = 24;
 constexpr int LT2_NT = 1024;
 
-template <typename T, bool ZERO, bool LAT, int IT>
+template <typename T, bool ZERO, bool LAT, int IT, bool VAR>
 __global__ __launch_bounds__(LT2_NT) void k_lattice_2d_tiled(
     const T* __restrict__ xo, T* __restrict__ xn, T* __restrict__ xp, int64_t cp, const T* __restrict__ r,
     int64_t rp, int n, int nb, typename Tr<T>::C w, typename Tr<T>::C hl2, const int* __restrict__ done,
-    L1Src<T> l1) {
+    L1Src<T> l1, double* __restrict__ uacc, int64_t up, const double* __restrict__ a, int64_t ap) {
   using C = typename Tr<T>::C;
   if (*done) return;
   constexpr int S = LT2_B + 2 * IT, S2 = S * S, SC = S / 2 + 2, SC2 = SC * SC;
-  __shared__ C X0[S2], X1[S2], R[S2], Pc[LAT ? SC2 : 1], Cc[LAT ? SC2 : 1];
+  __shared__ C X0[S2], X1[S2], Pc[LAT ? SC2 : 1], Cc[LAT ? SC2 : 1];
+  __shared__ double A[VAR ? S2 : 1];
+  __shared__ C FW[VAR ? S2 : 1], FS[VAR ? S2 : 1];
   const int lb = int(xcd_order(blockIdx.x, gridDim.x));
   const int bx = lb % nb, by = lb / nb;
   // tile node (i, j) is lattice node (gx0 + i, gy0 + j)
@@ -1905,12 +1941,17 @@ __global__ __launch_bounds__(LT2_NT) void k_lattice_2d_tiled(
   const int qi = q % S, qj = q / S;
   const bool live = q < S2;
   const int gx = gx0 + qi, gy = gy0 + qj;
-  if (live) {  // r and (neither ZERO nor LAT) x_0: clamped loads
+  const bool in = live && interior(gx, gy);
+  C rv = C(0);
+  double uo = 0.0;
+  if (live) {  // r, the coefficient, u and (neither ZERO nor LAT) x_0: clamped loads
     const int64_t cx = min(max(gx, 0), hi), cy = min(max(gy, 0), hi);
-    R[q] = ld(r + cy * rp + cx);
+    rv = ld(r + cy * rp + cx);
+    if (VAR) A[q] = a[cy * ap + cx];
+    if (uacc) uo = uacc[cy * up + cx];
     if (!ZERO && !LAT) {
       const C v = ld(xo + cy * cp + cx);
-      X0[q] = interior(gx, gy) ? v : C(0);
+      X0[q] = in ? v : C(0);
     }
     if (ZERO) X0[q] = C(0);
   }
@@ -1924,23 +1965,34 @@ __global__ __launch_bounds__(LT2_NT) void k_lattice_2d_tiled(
     Cc[q] = ld(l1.cur + o);
   }
   __syncthreads();
-  if (LAT) {
-    if (live) {
-      C v = C(0);
-      if (interior(gx, gy)) {
-        const int c0 = ((gy >> 1) - cy0) * SC + ((gx >> 1) - cx0);
-        if (!(gx & 1) && !(gy & 1)) {
-          v = Cc[c0];
-        } else {
-          const C tx = C(gx & 1) * C(0.5), ty = C(gy & 1) * C(0.5);
-          const C top = lerp(Pc[c0], Pc[c0 + 1], tx), bot = lerp(Pc[c0 + SC], Pc[c0 + SC + 1], tx);
-          v = lerp(top, bot, ty);
-        }
-        v = rnd<T>(v);
+  C cw = C(0), cs = C(0), ce = C(0), cn = C(0), ws = C(0);
+  if (VAR && live) {
+    const double c = A[q];
+    cw = C(harm(c, A[qi > 0 ? q - 1 : q]));
+    cs = C(harm(c, A[qj > 0 ? q - S : q]));
+    FW[q] = cw;
+    FS[q] = cs;
+  }
+  if (LAT && live) {
+    C v = C(0);
+    if (in) {
+      const int c0 = ((gy >> 1) - cy0) * SC + ((gx >> 1) - cx0);
+      if (!(gx & 1) && !(gy & 1)) {
+        v = Cc[c0];
+      } else {
+        const C tx = C(gx & 1) * C(0.5), ty = C(gy & 1) * C(0.5);
+        const C top = lerp(Pc[c0], Pc[c0 + 1], tx), bot = lerp(Pc[c0 + SC], Pc[c0 + SC + 1], tx);
+        v = lerp(top, bot, ty);
       }
-      X0[q] = v;
+      v = rnd<T>(v);
     }
-    __syncthreads();
+    X0[q] = v;
+  }
+  if (LAT || VAR) __syncthreads();
+  if (VAR && live && qi < S - 1 && qj < S - 1) {
+    ce = FW[q + 1];
+    cn = FS[q + S];
+    ws = w / ((cw + ce) + (cs + cn));
   }
 #pragma unroll
   for (int t = 1; t <= IT; ++t) {
@@ -1949,9 +2001,14 @@ __global__ __launch_bounds__(LT2_NT) void k_lattice_2d_tiled(
     // valid region after this iteration: tile nodes t .. S - 1 - t per axis
     if (live && qi >= t && qi < S - t && qj >= t && qj < S - t) {
       C v = C(0);
-      const bool in = interior(gx, gy);
       if (in) {
-        v = relax_const<C>(src[q], (src[q - 1] + src[q + 1]) + (src[q - S] + src[q + S]), R[q], w, hl2, C(4));
+        if (VAR) {
+          const C c = src[q];
+          const C flux = fmac(cw, c - src[q - 1], ce * (c - src[q + 1])) + fmac(cs, c - src[q - S], cn * (c - src[q + S]));
+          v = fmac(ws, fmac(hl2, rv, -flux), c);
+        } else {
+          v = relax_const<C>(src[q], (src[q - 1] + src[q + 1]) + (src[q - S] + src[q + S]), rv, w, hl2, C(4));
+        }
         dst[q] = rnd<T>(v);
       } else {
         dst[q] = C(0);
@@ -1959,8 +2016,12 @@ __global__ __launch_bounds__(LT2_NT) void k_lattice_2d_tiled(
       // the last iteration's region is the owned block: x_{IT-1} and x_IT
       if (t == IT && in) {
         const int64_t o = int64_t(gy) * cp + gx;
-        st(xn + o, v);
-        st(xp + o, src[q]);
+        if (uacc) {
+          uacc[int64_t(gy) * up + gx] = uo + double(v);
+        } else {
+          st(xn + o, v);
+          if (xp) st(xp + o, src[q]);
+        }
       }
     }
     if (t < IT) __syncthreads();
@@ -2161,27 +2222,35 @@ hipError_t launch_residual(int prec, int d, int n, const double* u, const Lay& u
 
 template <typename T, bool NORM>
 static hipError_t residual_restrict_t(int n, const double* u, const Lay& ul, const double* f,
-                                      const Lay& fl, void* r0, const Lay& rl, void* rc0,
-                                      const Lay& cl, double* partials, int* count, const int* done,
+                                      const Lay& fl, const double* a, const Lay& al, void* r0, const Lay& rl,
+                                      void* rc0, const Lay& cl, double* partials, int* count, const int* done,
                                       hipStream_t s, double* fpart) {
   const int len = rr_band(n);
   const int waves = rr_waves(n, len);
   *count = waves;
   const double h = 1.0 / double(n - 1);
   const double inv_h2 = 1.0 / (h * h);
-  HOMG_LAUNCH((k_residual_restrict_2d<T, NORM>), dim3((waves + 3) / 4), dim3(256), s, u + ul.off, ul.pitch,
-              f + fl.off, fl.pitch, static_cast<T*>(r0) + rl.off, rl.pitch, static_cast<T*>(rc0) + cl.off,
-              cl.pitch, n, len, inv_h2, partials, done, fpart);
+  T* r = static_cast<T*>(r0) + rl.off;
+  T* rc = static_cast<T*>(rc0) + cl.off;
+  if (a)
+    HOMG_LAUNCH((k_residual_restrict_2d<T, NORM, true>), dim3((waves + 3) / 4), dim3(256), s, a + al.off, al.pitch,
+                u + ul.off, ul.pitch, f + fl.off, fl.pitch, r, rl.pitch, rc, cl.pitch, n, len, inv_h2, partials, done,
+                fpart);
+  HOMG_LAUNCH((k_residual_restrict_2d<T, NORM, false>), dim3((waves + 3) / 4), dim3(256), s, (const double*)nullptr,
+              int64_t(0), u + ul.off, ul.pitch, f + fl.off, fl.pitch, r, rl.pitch, rc, cl.pitch, n, len, inv_h2,
+              partials, done, fpart);
 }
 
 hipError_t launch_residual_restrict_2d(int prec, int n, const double* u, const Lay& ul,
-                                       const double* f, const Lay& fl, void* r0, const Lay& rl,
-                                       void* rc, const Lay& cl, double* partials, int* count,
+                                       const double* f, const Lay& fl, const double* a, const Lay& al, void* r0,
+                                       const Lay& rl, void* rc, const Lay& cl, double* partials, int* count,
                                        const int* done, hipStream_t s, double* fpart) {
   if (n < 5 || (n - 1) % 2 || cl.side != (n - 1) / 2 + 1) return hipErrorInvalidValue;
-#define RR_CASE(T)                                                                                             \
-  return fpart ? residual_restrict_t<T, true>(n, u, ul, f, fl, r0, rl, rc, cl, partials, count, done, s, fpart) \
-               : residual_restrict_t<T, false>(n, u, ul, f, fl, r0, rl, rc, cl, partials, count, done, s, nullptr)
+#define RR_CASE(T)                                                                                            \
+  return fpart ? residual_restrict_t<T, true>(n, u, ul, f, fl, a, al, r0, rl, rc, cl, partials, count, done,  \
+                                              s, fpart)                                                       \
+               : residual_restrict_t<T, false>(n, u, ul, f, fl, a, al, r0, rl, rc, cl, partials, count, done, \
+                                               s, nullptr)
   switch (prec) {
     case PREC_F64: RR_CASE(double);
     case PREC_F32: RR_CASE(float);
@@ -2562,52 +2631,77 @@ static hipError_t tb3_tz(int n, int it, int len, double omega, const void* eo, v
 #undef TB3_ARGS
 }
 
-template <typename T, bool ZERO, bool LAT, int IT>
-static hipError_t lt2_t(int n, double omega, const void* xo_, void* xn_, void* xp_, const Lay& cl,
-                        const void* rm_, const Lay& rl, const L1Src<T>& l1, const int* done, hipStream_t s) {
+// A tiled launch's arguments beside the iterates (see launch_lattice_2d_tiled).
+struct TiledArgs {
+  int n;
+  double omega;
+  const void* xo;
+  void* xn;
+  void* xp;
+  Lay cl;
+  const void* rm;
+  Lay rl;
+  const L1State* l1;
+  double* u;
+  Lay ul;
+  const double* a;
+  Lay al;
+  const int* done;
+  hipStream_t s;
+};
+
+template <typename T, bool ZERO, bool LAT, int IT, bool VAR>
+static hipError_t lt2_t(const TiledArgs& g) {
   using C = typename Tr<T>::C;
-  const T* xo = xo_ ? static_cast<const T*>(xo_) + cl.off : nullptr;
-  T* xn = static_cast<T*>(xn_) + cl.off;
-  T* xp = static_cast<T*>(xp_) + cl.off;
-  const T* rm = static_cast<const T*>(rm_) + rl.off;
-  const double h = 1.0 / double(n - 1);
-  const C w = C(omega / 4.0), hl2 = C(h * h);
-  const int nb = (n - 2 + LT2_B - 1) / LT2_B;
-  HOMG_LAUNCH((k_lattice_2d_tiled<T, ZERO, LAT, IT>), dim3(unsigned(nb) * nb), dim3(LT2_NT), s, xo, xn, xp,
-              cl.pitch, rm, rl.pitch, n, nb, w, hl2, done, l1);
+  const T* xo = g.xo ? static_cast<const T*>(g.xo) + g.cl.off : nullptr;
+  T* xn = g.xn ? static_cast<T*>(g.xn) + g.cl.off : nullptr;
+  T* xp = g.xp ? static_cast<T*>(g.xp) + g.cl.off : nullptr;
+  const T* rm = static_cast<const T*>(g.rm) + g.rl.off;
+  const double h = 1.0 / double(g.n - 1);
+  const C w = C(VAR ? g.omega : g.omega / 4.0), hl2 = C(h * h);
+  const int nb = (g.n - 2 + LT2_B - 1) / LT2_B;
+  HOMG_LAUNCH((k_lattice_2d_tiled<T, ZERO, LAT, IT, VAR>), dim3(unsigned(nb) * nb), dim3(LT2_NT), g.s, xo, xn, xp,
+              g.cl.pitch, rm, g.rl.pitch, g.n, nb, w, hl2, g.done, l1_src<T>(g.l1), g.u ? g.u + g.ul.off : nullptr,
+              g.ul.pitch, g.a ? g.a + g.al.off : nullptr, g.al.pitch);
 }
 
 template <typename T, int IT>
-static hipError_t lt2_it(int n, double omega, const void* xo, void* xn, void* xp, const Lay& cl, const void* rm,
-                         const Lay& rl, bool zero, const L1State* l1, const int* done, hipStream_t s) {
-  const L1Src<T> v = l1_src<T>(l1);
-  if (l1) return lt2_t<T, false, true, IT>(n, omega, xo, xn, xp, cl, rm, rl, v, done, s);
-  if (zero) return lt2_t<T, true, false, IT>(n, omega, xo, xn, xp, cl, rm, rl, v, done, s);
-  return lt2_t<T, false, false, IT>(n, omega, xo, xn, xp, cl, rm, rl, v, done, s);
+static hipError_t lt2_it(const TiledArgs& g, bool zero) {
+  if (g.a) {
+    if (g.l1) return lt2_t<T, false, true, IT, true>(g);
+    return zero ? lt2_t<T, true, false, IT, true>(g) : lt2_t<T, false, false, IT, true>(g);
+  }
+  if (g.l1) return lt2_t<T, false, true, IT, false>(g);
+  return zero ? lt2_t<T, true, false, IT, false>(g) : lt2_t<T, false, false, IT, false>(g);
 }
 
 template <typename T>
-static hipError_t lt2_tz(int n, int it, double omega, const void* xo, void* xn, void* xp, const Lay& cl,
-                         const void* rm, const Lay& rl, bool zero, const L1State* l1, const int* done,
-                         hipStream_t s) {
+static hipError_t lt2_tz(const TiledArgs& g, int it, bool zero) {
   switch (it) {
-    case 1: return lt2_it<T, 1>(n, omega, xo, xn, xp, cl, rm, rl, zero, l1, done, s);
-    case 2: return lt2_it<T, 2>(n, omega, xo, xn, xp, cl, rm, rl, zero, l1, done, s);
-    case 3: return lt2_it<T, 3>(n, omega, xo, xn, xp, cl, rm, rl, zero, l1, done, s);
-    default: return lt2_it<T, 4>(n, omega, xo, xn, xp, cl, rm, rl, zero, l1, done, s);
+    case 1: return lt2_it<T, 1>(g, zero);
+    case 2: return lt2_it<T, 2>(g, zero);
+    case 3: return lt2_it<T, 3>(g, zero);
+    default: return lt2_it<T, 4>(g, zero);
   }
+}
+
+// Either x_it goes to xn (and x_{it-1} to xp), neither aliasing xo, or into u.
+static bool tiled_ok(int d, int n, int it, const void* xo, const void* xn, const void* xp, bool zero, const L1State* l1,
+                     const double* u) {
+  if (n < 3 || it < 1 || it > LT_MAX_IT || (l1 && zero) || (!l1 && !zero && !xo) || !l1_ok(l1, d, n)) return false;
+  return u ? !xn && !xp : xn && xn != xo && xn != xp && (!xp || xp != xo);
 }
 
 hipError_t launch_lattice_2d_tiled(int prec, int n, int it, double omega, const void* xo, void* xn, void* xprev,
                                    const Lay& cl, const void* rm, const Lay& rl, bool zero, const L1State* l1,
-                                   const int* done, hipStream_t s) {
-  if (n < 3 || it < 1 || it > LT_MAX_IT || !xn || !xprev || (l1 && zero) || (!l1 && !zero && !xo) ||
-      !l1_ok(l1, 2, n) || xn == xo || xprev == xo || xn == xprev)
-    return hipErrorInvalidValue;
+                                   const int* done, hipStream_t s, double* u, const Lay& ul, const double* a,
+                                   const Lay& al) {
+  if (!tiled_ok(2, n, it, xo, xn, xprev, zero, l1, u) || (a && al.side != n)) return hipErrorInvalidValue;
+  const TiledArgs g{n, omega, xo, xn, xprev, cl, rm, rl, l1, u, ul, a, al, done, s};
   switch (prec) {
-    case PREC_F64: return lt2_tz<double>(n, it, omega, xo, xn, xprev, cl, rm, rl, zero, l1, done, s);
-    case PREC_F32: return lt2_tz<float>(n, it, omega, xo, xn, xprev, cl, rm, rl, zero, l1, done, s);
-    default: return lt2_tz<bf16>(n, it, omega, xo, xn, xprev, cl, rm, rl, zero, l1, done, s);
+    case PREC_F64: return lt2_tz<double>(g, it, zero);
+    case PREC_F32: return lt2_tz<float>(g, it, zero);
+    default: return lt2_tz<bf16>(g, it, zero);
   }
 }
 
@@ -2617,54 +2711,48 @@ size_t lattice_3d_tiled_lds(int prec, int it) {
 }
 
 template <typename T, bool ZERO, bool LAT, int IT>
-static hipError_t lt3_t(int n, double omega, const void* xo_, void* xn_, void* xp_, const Lay& cl,
-                        const void* rm_, const Lay& rl, const L1Src<T>& l1, const int* done, hipStream_t s) {
+static hipError_t lt3_t(const TiledArgs& g) {
   using C = typename Tr<T>::C;
-  const T* xo = xo_ ? static_cast<const T*>(xo_) + cl.off : nullptr;
-  T* xn = static_cast<T*>(xn_) + cl.off;
-  T* xp = static_cast<T*>(xp_) + cl.off;
-  const T* rm = static_cast<const T*>(rm_) + rl.off;
-  const double h = 1.0 / double(n - 1);
-  const C w = C(omega / 6.0), hl2 = C(h * h);
-  const int nb = (n - 2 + LT_B - 1) / LT_B;
+  const T* xo = g.xo ? static_cast<const T*>(g.xo) + g.cl.off : nullptr;
+  T* xn = g.xn ? static_cast<T*>(g.xn) + g.cl.off : nullptr;
+  T* xp = g.xp ? static_cast<T*>(g.xp) + g.cl.off : nullptr;
+  const T* rm = static_cast<const T*>(g.rm) + g.rl.off;
+  const double h = 1.0 / double(g.n - 1);
+  const C w = C(g.omega / 6.0), hl2 = C(h * h);
+  const int nb = (g.n - 2 + LT_B - 1) / LT_B;
   const size_t lds = lattice_3d_tiled_lds(sizeof(T) == 8 ? PREC_F64 : PREC_F32, IT);
-  hipError_t a = allow_lds(k_lattice_3d_tiled<T, ZERO, LAT, IT>, lds);
-  if (a != hipSuccess) return a;
-  HOMG_LAUNCH_SMEM((k_lattice_3d_tiled<T, ZERO, LAT, IT>), dim3(unsigned(nb) * nb * nb), dim3(LT_NT), lds, s, xo,
-                   xn, xp, cl.pitch, cl.plane, rm, rl.pitch, rl.plane, n, nb, w, hl2, done, l1);
+  hipError_t e = allow_lds(k_lattice_3d_tiled<T, ZERO, LAT, IT>, lds);
+  if (e != hipSuccess) return e;
+  HOMG_LAUNCH_SMEM((k_lattice_3d_tiled<T, ZERO, LAT, IT>), dim3(unsigned(nb) * nb * nb), dim3(LT_NT), lds, g.s, xo,
+                   xn, xp, g.cl.pitch, g.cl.plane, rm, g.rl.pitch, g.rl.plane, g.n, nb, w, hl2, g.done,
+                   l1_src<T>(g.l1), g.u ? g.u + g.ul.off : nullptr, g.ul.pitch, g.ul.plane);
 }
 
 template <typename T, int IT>
-static hipError_t lt3_it(int n, double omega, const void* xo, void* xn, void* xp, const Lay& cl, const void* rm,
-                         const Lay& rl, bool zero, const L1State* l1, const int* done, hipStream_t s) {
-  const L1Src<T> v = l1_src<T>(l1);
-  if (l1) return lt3_t<T, false, true, IT>(n, omega, xo, xn, xp, cl, rm, rl, v, done, s);
-  if (zero) return lt3_t<T, true, false, IT>(n, omega, xo, xn, xp, cl, rm, rl, v, done, s);
-  return lt3_t<T, false, false, IT>(n, omega, xo, xn, xp, cl, rm, rl, v, done, s);
+static hipError_t lt3_it(const TiledArgs& g, bool zero) {
+  if (g.l1) return lt3_t<T, false, true, IT>(g);
+  return zero ? lt3_t<T, true, false, IT>(g) : lt3_t<T, false, false, IT>(g);
 }
 
 template <typename T>
-static hipError_t lt3_tz(int n, int it, double omega, const void* xo, void* xn, void* xp, const Lay& cl,
-                         const void* rm, const Lay& rl, bool zero, const L1State* l1, const int* done,
-                         hipStream_t s) {
+static hipError_t lt3_tz(const TiledArgs& g, int it, bool zero) {
   switch (it) {
-    case 1: return lt3_it<T, 1>(n, omega, xo, xn, xp, cl, rm, rl, zero, l1, done, s);
-    case 2: return lt3_it<T, 2>(n, omega, xo, xn, xp, cl, rm, rl, zero, l1, done, s);
-    case 3: return lt3_it<T, 3>(n, omega, xo, xn, xp, cl, rm, rl, zero, l1, done, s);
-    default: return lt3_it<T, 4>(n, omega, xo, xn, xp, cl, rm, rl, zero, l1, done, s);
+    case 1: return lt3_it<T, 1>(g, zero);
+    case 2: return lt3_it<T, 2>(g, zero);
+    case 3: return lt3_it<T, 3>(g, zero);
+    default: return lt3_it<T, 4>(g, zero);
   }
 }
 
 hipError_t launch_lattice_3d_tiled(int prec, int n, int it, double omega, const void* xo, void* xn, void* xprev,
                                    const Lay& cl, const void* rm, const Lay& rl, bool zero, const L1State* l1,
-                                   const int* done, hipStream_t s) {
-  if (n < 3 || it < 1 || it > LT_MAX_IT || !xn || !xprev || (l1 && zero) || (!l1 && !zero && !xo) ||
-      !l1_ok(l1, 3, n) || xn == xo || xprev == xo || xn == xprev)
-    return hipErrorInvalidValue;
+                                   const int* done, hipStream_t s, double* u, const Lay& ul) {
+  if (!tiled_ok(3, n, it, xo, xn, xprev, zero, l1, u)) return hipErrorInvalidValue;
+  const TiledArgs g{n, omega, xo, xn, xprev, cl, rm, rl, l1, u, ul, nullptr, Lay(), done, s};
   switch (prec) {
-    case PREC_F64: return lt3_tz<double>(n, it, omega, xo, xn, xprev, cl, rm, rl, zero, l1, done, s);
-    case PREC_F32: return lt3_tz<float>(n, it, omega, xo, xn, xprev, cl, rm, rl, zero, l1, done, s);
-    default: return lt3_tz<bf16>(n, it, omega, xo, xn, xprev, cl, rm, rl, zero, l1, done, s);
+    case PREC_F64: return lt3_tz<double>(g, it, zero);
+    case PREC_F32: return lt3_tz<float>(g, it, zero);
+    default: return lt3_tz<bf16>(g, it, zero);
   }
 }
 
