@@ -124,6 +124,16 @@ struct homg_ctx {
   bool pow2 = false;
   std::vector<double*> fam;
   std::vector<Lay> faml;
+  // its marks in the compact form (temporal != 0): level m's two states at
+  // p2x[2 m], layout p2l[m]; p2_level: the level whose final pair p2_prev,
+  // p2_cur is the current state (-1: the whole grid e is)
+  double* p2_base = nullptr;  // one allocation of p2_count values
+  size_t p2_count = 0;
+  std::vector<double*> p2x;
+  std::vector<Lay> p2l;
+  int p2_level = -1;
+  double* p2_prev = nullptr;
+  double* p2_cur = nullptr;
   // L1 error (Sec. 4): partial sums and per-iteration results (allocated on first use)
   double* l1part = nullptr;
   double* l1out = nullptr;
@@ -234,6 +244,7 @@ void free_ctx(homg_ctx* h) {
   for (void* p : h->xc) (void)hipFree(p);
   for (void* p : h->xp3) (void)hipFree(p);
   for (double* p : h->fam) (void)hipFree(p);
+  (void)hipFree(h->p2_base);
   (void)hipFree(h->partials);
   (void)hipFree(h->st);
   (void)hipFree(h->hist);
@@ -347,7 +358,6 @@ homg_status run_top64(homg_ctx* h, int m, int it, bool first, bool last, int nex
 // Laplacian on grids so small that the walking passes are one serial chain
 // of row or plane steps.
 bool l0_tiled(const homg_ctx* h) {
-  if (h->pow2) return false;
   if (h->d == 3) return h->n <= LT_MAX_SIDE && lattice_3d_tiled_lds(h->prec, LT_MAX_IT) <= h->lds_limit;
   return h->has_coef || h->n <= LT2_MAX_L0;
 }
@@ -356,9 +366,44 @@ homg_status run_level(homg_ctx* h, int m, int it, bool first, bool last, int nex
                       double* acc, const int* done, hipStream_t s) {
   if (h->active_smoother == 1) return run_level_learned(h, m, it, first, last, next_m, cur, acc, done, s);
   if (top64(h) && m == h->top_level) return run_top64(h, m, it, first, last, next_m, cur, acc, done, s);
+  const Lay none;
   if (h->pow2 && m >= 1) {
-    // power-of-two layout: one whole-grid launch per iteration
     const double* fm[4] = {h->fam[4 * m], h->fam[4 * m + 1], h->fam[4 * m + 2], h->fam[4 * m + 3]};
+    if (h->temporal) {
+      // compact form: the level's marks alone; the whole grid is written
+      // before level 0 and by the last level
+      double* X[2] = {h->p2x[2 * m], h->p2x[2 * m + 1]};
+      int src = 0;
+      if (h->p2_level == m) {
+        // a level that follows itself goes on from its last state, whose
+        // ghosts the last iteration left too
+        src = h->p2_cur == X[0] ? 0 : 1;
+      } else if (first) {
+        LAUNCH(h, launch_p2_zero(h->n, m, X[0], h->p2l[m], done, s));
+      } else {
+        const int from = std::max(h->p2_level, 0);  // 0: the whole grid
+        LAUNCH_K(h, s, K_TRANSFER, m, 2,
+                 launch_p2_enter(h->n, from, h->p2_prev, h->p2_cur, from ? h->p2l[from] : none,
+                                 static_cast<const double*>(h->e[*cur]), h->el, m, X[0], h->p2l[m], done, s));
+      }
+      for (int t = 0; t < it; ++t) {
+        LAUNCH_K(h, s, K_LATTICE, m, 512,
+                 launch_p2_iter(h->n, m, h->omega, X[src], X[1 - src], h->p2l[m], fm, h->faml[m], done, s));
+        src = 1 - src;
+      }
+      h->p2_level = m;
+      h->p2_cur = X[src];
+      h->p2_prev = X[1 - src];
+      if (last || next_m == 0) {
+        LAUNCH_K(h, s, K_LEVEL_WRITE, m, (last ? SW_ACCUM : 0) | 256,
+                 launch_p2_write(h->n, m, h->p2_prev, h->p2_cur, h->p2l[m], static_cast<double*>(h->e[1 - *cur]),
+                                 h->el, last ? acc : nullptr, h->dl, done, s));
+        *cur = 1 - *cur;
+        h->p2_level = -1;
+      }
+      return HOMG_OK;
+    }
+    // one whole-grid launch per iteration
     for (int t = 0; t < it; ++t) {
       int mode = 0;
       if (first && t == 0) mode |= SW_ZERO_OLD;
@@ -371,7 +416,6 @@ homg_status run_level(homg_ctx* h, int m, int it, bool first, bool last, int nex
     }
     return HOMG_OK;
   }
-  const Lay none;
   const double* am = h->has_coef ? h->a[m] : nullptr;
   const Lay& alm = am ? h->al[m] : none;
   // One launch per iteration: level 0 always (every node is a lattice
@@ -642,6 +686,23 @@ int tail_levels(const homg_ctx* h, int* ms) {
   return cnt;
 }
 
+// The same on a power-of-two grid: the leading entries launch_p2_tail runs.
+int p2_tail_levels(const homg_ctx* h, int* ms) {
+  const int np = int(h->sched.size() / 2);
+  if (h->temporal != 2 || !h->pow2 || h->sched[0] != h->top_level) return 0;
+  int cnt = 0;
+  for (int p = 0; p + 1 < np && p < BATCH_MAX_LEVELS; ++p) {
+    const int m = h->sched[2 * p];
+    if (m != h->top_level - p || m < 1 || !p2_tail_fits(h->n, m)) break;
+    cnt = p + 1;
+  }
+  if (!cnt) return 0;
+  *ms = h->sched[2 * (cnt - 1)];
+  for (int p = cnt; p < np; ++p)
+    if (h->sched[2 * p] >= *ms) return 0;  // a fused level is visited again
+  return cnt;
+}
+
 // Whether a solve's residual also restricts to level 1 in the same pass
 // (2D nested grids whose schedule visits a coarse level).
 bool residual_restricts(const homg_ctx* h) {
@@ -652,12 +713,11 @@ bool residual_restricts(const homg_ctx* h) {
 // One restriction of the cycle's pyramid, m -> m + 1 (in FP64 onto an FP64
 // coarsest level).
 homg_status enqueue_restrict(homg_ctx* h, int m, const int* done, hipStream_t s) {
-  if (h->pow2) {  // one restriction per quadrant family
-    for (int q = 0; q < 4; ++q)
-      LAUNCH_K(h, s, K_RESTRICT, m, 2,
-               launch_p2_restrict(m == 0 ? static_cast<const double*>(h->r[0]) : h->fam[4 * m + q],
-                                  m == 0 ? h->rl[0] : h->faml[m], m == 0, h->n, q & 1, q >> 1,
-                                  h->fam[4 * (m + 1) + q], h->faml[m + 1], done, s));
+  if (h->pow2) {  // the four quadrant families
+    LAUNCH_K(h, s, K_RESTRICT, m, 2,
+             launch_p2_restrict(m == 0 ? static_cast<const double*>(h->r[0]) : nullptr, h->rl[0],
+                                m == 0 ? nullptr : &h->fam[4 * m], h->faml[m], h->n, &h->fam[4 * (m + 1)],
+                                h->faml[m + 1], done, s));
     return HOMG_OK;
   }
   if (top64(h) && m + 1 == h->top_level) {
@@ -762,7 +822,7 @@ homg_status enqueue_residual(homg_ctx* h, const double* f, const double* u, int*
 homg_status enqueue_cycle(homg_ctx* h, const double* f, double* acc, int cycle, const int* done,
                           hipStream_t s, bool publish = false) {
   int ms = 0;
-  const int ntail = tail_levels(h, &ms);
+  const int ntail = h->pow2 ? p2_tail_levels(h, &ms) : tail_levels(h, &ms);
   // in a solve (f given) the residual that precedes every cycle already
   // restricted r_0 to level 1
   if (!h->incycle)
@@ -779,8 +839,28 @@ homg_status enqueue_cycle(homg_ctx* h, const double* f, double* acc, int cycle, 
   const size_t np = h->sched.size() / 2;
   h->chain_ready = -1;
   h->lat_level = -1;
+  h->p2_level = -1;
   size_t p0 = 0;
-  if (ntail) {
+  if (ntail && h->pow2) {
+    int its[BATCH_MAX_LEVELS];
+    for (int k = 0; k < ntail; ++k) its[k] = h->sched[2 * (ntail - 1 - k) + 1];
+    h->p2_prev = h->p2x[2 * ms];
+    h->p2_cur = h->p2x[2 * ms + 1];
+    LAUNCH_K(h, s, K_TAIL, ms, 4,
+             launch_p2_tail(h->n, ms, ntail, its, h->omega, &h->fam[4 * ms], h->faml[ms], h->p2_prev, h->p2_cur,
+                            h->p2l[ms], f ? h->st : h->zero_st, h->hist,
+                            f && h->fin_pending >= 0 ? h->partials : nullptr, h->fin_count, h->fin_pending, s));
+    h->fin_pending = -1;
+    h->p2_level = ms;
+    p0 = size_t(ntail);
+    if (h->sched[2 * ntail] == 0) {  // level 0 next: the whole grid now
+      LAUNCH_K(h, s, K_LEVEL_WRITE, ms, 256,
+               launch_p2_write(h->n, ms, h->p2_prev, h->p2_cur, h->p2l[ms], static_cast<double*>(h->e[1]), h->el,
+                               nullptr, h->dl, done, s));
+      cur = 1;
+      h->p2_level = -1;
+    }
+  } else if (ntail) {
     int its[BATCH_MAX_LEVELS];
     for (int k = 0; k < ntail; ++k) its[k] = h->sched[2 * (ntail - 1 - k) + 1];
     const int nms = (h->n - 1) / (1 << ms) + 1;
@@ -1158,6 +1238,19 @@ homg_status homg_create(homg_handle* out, int ndim, const int64_t* dims, int lev
       for (int q = 0; q < 4 && !stt; ++q)
         stt = dev_alloc(h, reinterpret_cast<void**>(&h->fam[4 * m + q]), sizeof(double) * size_t(h->faml[m].alloc));
   }
+  if (h->temporal && pow2) {
+    h->p2x.assign(2 * levels, nullptr);
+    h->p2l.assign(levels, Lay());
+    for (int m = 1; m < levels; ++m) {
+      h->p2l[m] = p2_mark_layout(h->n, m);
+      h->p2_count += 2 * size_t(h->p2l[m].alloc);
+    }
+    if (!stt && h->p2_count)
+      stt = dev_alloc(h, reinterpret_cast<void**>(&h->p2_base), sizeof(double) * h->p2_count);
+    size_t at = 0;
+    for (int m = 1; m < levels && !stt; ++m)
+      for (int b = 0; b < 2; ++b, at += size_t(h->p2l[m].alloc)) h->p2x[2 * m + b] = h->p2_base + at;
+  }
   if (h->temporal && !pow2) {
     h->xc.assign(2 * levels, nullptr);
     for (int m = 1; m < levels && !stt; ++m)
@@ -1205,6 +1298,7 @@ homg_status homg_create(homg_handle* out, int ndim, const int64_t* dims, int lev
   for (int m = 1; m < int(h->fam.size()) / 4 && ok; ++m)
     for (int q = 0; q < 4 && ok; ++q)
       ok = hipMemset(h->fam[4 * m + q], 0, sizeof(double) * size_t(h->faml[m].alloc)) == hipSuccess;
+  if (h->p2_base) ok = ok && hipMemset(h->p2_base, 0, sizeof(double) * h->p2_count) == hipSuccess;
   // compact lattices: boundary nodes are read as 0 and never written
   for (size_t m = 1; 2 * m + 1 < h->xc.size() && ok; ++m)
     for (int b = 0; b < 2 && ok; ++b)

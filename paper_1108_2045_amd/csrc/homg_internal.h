@@ -262,11 +262,36 @@ hipError_t launch_level_transfer(int prec, int d, int m, const void* xprev, cons
                                  const Lay& cl, int mt, void* dst, const Lay& tl, bool zero_old,
                                  const int* done, hipStream_t s);
 // ---- power-of-two grids (Sec. 3; 2D Laplacian, FP64), N = 2^k nodes per side
-// Family restriction of quadrant (sx, sy): level 1 from the whole-grid r_0
-// (from_r0; F in layout fl of side N, read from that quadrant's corner) or
-// level j from level j - 1 (compact, side 2 * cl.side).
-hipError_t launch_p2_restrict(const double* F, const Lay& fl, bool from_r0, int N, int sx, int sy, double* C,
-                              const Lay& cl, const int* done, hipStream_t s);
+// One level of the four restriction families (q = 2 sy + sx): level 1 from the
+// whole-grid r_0, or (r0 null) level j from level j - 1 (compact, side
+// 2 * cl.side).
+hipError_t launch_p2_restrict(const double* r0, const Lay& rl, const double* const* F, const Lay& fl, int N,
+                              double* const* Cc, const Lay& cl, const int* done, hipStream_t s);
+// Compact form (the same bits as the whole-grid iterations): the marks of
+// level m, four quadrants of (h + 2)^2 values, h = N / 2^(m+1) = layout side,
+// quadrant to quadrant `plane` apart.
+//   launch_p2_enter: the starting state of level mt from the final pair of
+//     level m >= 1 (layout ml), or (m = 0) from the whole grid e;
+//   launch_p2_zero: the starting state 0;
+//   launch_p2_iter: one iteration; the final pair of a level is the state
+//     before and after its last one;
+//   launch_p2_write: the whole grid after a level, into en or (u given)
+//     added into u;
+//   launch_p2_tail: levels ms + nlev - 1 .. ms from 0 in one workgroup
+//     (p2_tail_fits), with the norm of the residual of `cycle` reduced first
+//     as launch_coarse_tail does.
+Lay p2_mark_layout(int N, int m);
+hipError_t launch_p2_enter(int N, int m, const double* prev, const double* cur, const Lay& ml, const double* e,
+                           const Lay& el, int mt, double* out, const Lay& ol, const int* done, hipStream_t s);
+hipError_t launch_p2_zero(int N, int m, double* out, const Lay& ml, const int* done, hipStream_t s);
+hipError_t launch_p2_iter(int N, int m, double omega, const double* in, double* out, const Lay& ml,
+                          const double* const* fam, const Lay& fl, const int* done, hipStream_t s);
+hipError_t launch_p2_write(int N, int m, const double* prev, const double* cur, const Lay& ml, double* en,
+                           const Lay& el, double* u, const Lay& ul, const int* done, hipStream_t s);
+bool p2_tail_fits(int N, int ms);
+hipError_t launch_p2_tail(int N, int ms, int nlev, const int* its, double omega, const double* const* fam,
+                          const Lay& fl, double* prev, double* cur, const Lay& ml, DevState* st, double* hist,
+                          const double* partials, int count, int cycle, hipStream_t s);
 // One whole-grid iteration at level m >= 1; fam[q] (q = 2 sy + sx) is the
 // level-m family array of quadrant q (layout fl, side N >> m); mode: SW_ZERO_OLD
 // / SW_ACCUM (add into u, layout ul, instead of storing en).
