@@ -102,9 +102,10 @@ typedef struct homg_options {
                               points just outside it (index n/2 or n/2 - 1), every mark relaxing
                               with its quadrant's own restricted residual (one nested restriction
                               sequence per quadrant, anchored at its corner), every other node
-                              interpolating bilinearly from its own quadrant's marks only.  Every
-                              level-m >= 1 iteration is one whole-grid launch; level 0 runs as on
-                              nested grids.  The batched, learned, step-restrict/step-sweeps and
+                              interpolating bilinearly from its own quadrant's marks only.  With
+                              temporal_block 0 every level-m >= 1 iteration is one whole-grid
+                              launch, with 1 or 2 it touches the level's marks alone (the same
+                              bits); level 0 runs as on nested grids.  The batched, learned, step-restrict/step-sweeps and
                               variable-coefficient paths are nested-only (HOMG_ERR_UNSUPPORTED). */
     int restriction;       /* HOMG_RESTRICT_PYRAMID (0): every cycle first restricts r_0 to all its
                               levels, one compact array per level (Sec. 2, restrictions as a
@@ -284,16 +285,13 @@ homg_status homg_get_profile(homg_handle h, homg_kernel_time *out, int cap, int 
 
 /*
  * Batched solver: many independent 2D Poisson problems (5-point, zero
- * Dirichlet) of uneven sides, solved together.  All problems advance in
- * lockstep steps of their own MFMG sequence (Sec. 2), one kernel launch per
- * step for all of them (the launches captured once in a HIP graph of 64
- * steps, replayed until every problem has retired); each retires when its
- * relative residual reaches tol.  Precision, omega, MaxI and max_cycles
- * come from opt (schedule and temporal_block are ignored: the MFMG schedule
- * runs chained -- each coarse level iterates on its compact lattice and
- * hands over only the next finer level's lattice values, the whole grid is
- * written once, before level 0 -- and level 0 runs in multi-iteration
- * passes).
+ * Dirichlet) of uneven sides, solved together.  All problems advance cycle
+ * by cycle of their own MFMG sequence (Sec. 2), one kernel launch per stage
+ * of the cycle for all of them; each is done when its relative residual
+ * reaches tol.  Precision, omega, MaxI and max_cycles come from opt (schedule
+ * and temporal_block are ignored: the MFMG schedule runs chained, as a single
+ * solve's, its coarse levels in one workgroup per problem, and a problem of
+ * side up to 65 in one workgroup whole).
  *
  * homg_batch_create: count >= 1 problems with sides[i] = 2^k + 1, 3 <= side
  *   <= 32769 and at most 16 levels; allocates one device arena for all of

@@ -1,16 +1,19 @@
-// homg_batch.cpp -- batched HOMG solver: C ABI, arena, graph.
+// homg_batch.cpp -- batched HOMG solver: C ABI, workspace, stage lists.
 //
-// Many independent 2D problems of uneven size advance together: every
-// problem walks its own MFMG sequence (Sec. 2 of arXiv:1108.2045: residual,
-// restriction pyramid, fused relax+interpolate iterations, restart) one
-// stage per step, and one launch runs a step for all problems at once (the
-// tiles of every active problem's stage, one workgroup each).  A HIP graph
-// of 64 step launches and the advance of the step counter is built once
-// and replayed on the caller's stream until no problem is active; the
-// per-call inputs (array pointers, tolerance) live in device descriptors
-// uploaded before each solve, so the graph never changes.  (A persistent
-// kernel with a grid barrier per step was measured slower on MI355X: one
-// barrier costs 40-170 us against a few us per graph node.)
+// Many independent 2D problems of uneven size advance together, cycle by
+// cycle of their own MFMG sequence (Sec. 2 of arXiv:1108.2045): one launch
+// per stage of the cycle for all problems that have it -- residual with the
+// first restriction, the rest of the restriction chain, the coarse tails
+// (one workgroup per problem), the iterations of each lattice level, level 0
+// -- each workgroup taking its {problem, block} from a list made once per
+// handle (again when a tile shape or pass depth changes).  The stages are
+// the single-problem solver's, block for block.  Problems of side up to
+// tail_max_side are solved whole by one workgroup each, in one launch.
+// Convergence is decided on the device; a problem that is done returns at
+// the start of every later launch.  The host reads the states after a few
+// cycles and sizes the next batch of cycles from the slowest problem.
+// Aligned at their ends the sequences of problems of different depth share
+// their launches: side 65 .. 1025 takes 8 launches a cycle.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -19,6 +22,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "../../include/homg.h"
@@ -26,30 +30,57 @@
 
 using namespace homg;
 
+namespace {
+
+// One launch of the iteration stages.
+struct PassGroup {
+  int it, kind;
+  bool lat;
+  int first, count;  // its workgroups in the tile list
+};
+struct TileRange {
+  int first = 0, count = 0;
+};
+
+// One problem's workspace (solved in stages: side > tail_max_side).
+struct Problem {
+  int n = 0, levels = 0, ms = 0;  // ms: finest level of the coarse tail
+  Lay el, rl[BATCH_MAX_LEVELS];
+  char* r[BATCH_MAX_LEVELS] = {};  // right-hand sides of levels 0 .. ms (arrays as allocated)
+  char* x[BATCH_MAX_LEVELS][3] = {};  // levels 1 .. ms: iterate pair; below ms also x_{it-1}
+  char* e[2] = {nullptr, nullptr};    // level 0's iterates, if it takes several passes
+  double* partials = nullptr;
+};
+
+}  // namespace
+
 struct homg_batch_ctx {
   int count = 0, prec = 0, max_i = 4, max_cycles = 200;
   double omega = 0.8;
-  std::vector<int> sides, levels;
-  std::vector<int> sweep_levels;  // concatenated per-problem iteration levels
+  std::vector<int> sides;
   std::map<int, int> tile_rows;   // side -> rows per tile (absent: default)
   std::map<int, int> pass_iters;  // side -> iterations per level-0 pass (absent: TB_MAX_IT)
-  size_t sched_cap = 0;           // capacity of d_sweep_levels (ints)
-  BatchProblem* h_probs = nullptr;
-  BatchProblem* d_probs = nullptr;
-  BatchRun* h_run = nullptr;
-  BatchRun* d_run = nullptr;
-  BatchState* h_state = nullptr;
-  BatchState* d_state = nullptr;
-  int* h_done = nullptr;
-  int* d_done = nullptr;
-  int* d_sweep_levels = nullptr;
-  BatchSync* h_sync = nullptr;
-  BatchSync* d_sync = nullptr;
+  std::vector<Problem> probs;
+  std::vector<int> big, small[2];  // problems solved in stages; by one workgroup (small[1]: FP64 coarsest level)
+  // stage lists; dirty: to be made (again) before the next solve
+  bool dirty = true;
+  std::vector<PassGroup> passes;   // in launch order
+  std::vector<TileRange> restricts;  // restriction a -> a + 1 at [a]
+  TileRange residual, multi;
+  size_t multi_lds = 0, tail_lds = 0, small_lds[2] = {0, 0};
+  size_t o_res = 0, o_rs = 0, o_multi = 0, o_pass = 0, o_tail = 0, o_small[2] = {0, 0}, o_tiles = 0;  // in plan
+  char* plan = nullptr;
+  size_t plan_bytes = 0;
+  // per-call inputs and results
+  void** h_ptrs = nullptr;  // f, then u (pinned), and their device copy
+  void** d_ptrs = nullptr;
+  BatchState* h_state = nullptr;  // pinned
+  DevState* d_st = nullptr;
+  double** d_hist = nullptr;      // per problem
+  std::vector<double*> hist;
   void* arena = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  int grid = 0, device = 0;
-  int max_steps = 0;
+  void* e_arena = nullptr;
+  int device = 0;
   std::string err;
 };
 
@@ -77,60 +108,40 @@ int side_k(int64_t n) {
 
 void free_batch(homg_batch_ctx* b) {
   if (!b) return;
-  if (b->exec) (void)hipGraphExecDestroy(b->exec);
-  if (b->graph) (void)hipGraphDestroy(b->graph);
   (void)hipFree(b->arena);
-  (void)hipFree(b->d_probs);
-  (void)hipFree(b->d_run);
-  (void)hipFree(b->d_state);
-  (void)hipFree(b->d_done);
-  (void)hipFree(b->d_sweep_levels);
-  (void)hipFree(b->d_sync);
-  if (b->h_probs) (void)hipHostFree(b->h_probs);
-  if (b->h_run) (void)hipHostFree(b->h_run);
+  (void)hipFree(b->e_arena);
+  (void)hipFree(b->plan);
+  (void)hipFree(b->d_ptrs);
+  (void)hipFree(b->d_st);
+  (void)hipFree(b->d_hist);
+  if (b->h_ptrs) (void)hipHostFree(b->h_ptrs);
   if (b->h_state) (void)hipHostFree(b->h_state);
-  if (b->h_done) (void)hipHostFree(b->h_done);
-  if (b->h_sync) (void)hipHostFree(b->h_sync);
   delete b;
 }
 
-// Tile rows (the walked length of a tile) of the fine-grid stages.
-// The iteration stages of one cycle (levels M .. 0, n_m = min(2^(M-m+1),
-// MaxI) iterations each, chained as in the single-problem solver): each
-// coarse level's iterations on its compact lattice -- one multi-iteration
-// pass (BST_LTB) below the top when the lattice side is at least
-// BATCH_LTB_MIN_SIDE and n_m <= TB_MAX_IT, else one stage per iteration --
-// and its hand-over to the next finer level's lattice (to the whole grid
-// before level 0), then level 0 in passes of up to `depth` (<= TB_MAX_IT)
-// iterations, the last adding into u.
-std::vector<int> stage_codes(int n, int L, int max_i, int depth) {
-  std::vector<int> codes;
-  const int M = L - 1;
-  auto iters = [&](int m) { return std::min(1 << std::min(M - m + 1, 30), max_i); };
-  for (int m = M; m >= 1; --m) {
-    const int it = iters(m);
-    if (m < M && it <= TB_MAX_IT && (n - 1) / (1 << m) + 1 >= BATCH_LTB_MIN_SIDE) {
-      // the level's iterations in one pass, then the hand-over from its outputs
-      codes.push_back(bst_code(BST_LTB, m, it, 0, false, false));
-      codes.push_back(bst_code(BST_XFER, m, it, 1, false, false));
-      continue;
-    }
-    for (int t = 1; t <= it; ++t) codes.push_back(bst_code(BST_SWEEP, m, 1, t, m == M && t == 1, false));
-    codes.push_back(bst_code(BST_XFER, m, it, 0, m == M && it == 1, false));
+int level_iters(const homg_batch_ctx* b, int levels, int m) {
+  return std::min(1 << std::min(levels - m, 30), b->max_i);
+}
+
+// Default rows per tile: 16, halved while the batch's residual pass has
+// fewer than 8192 waves (the card's wave slots) and tiles more than 4 rows.
+// Longer tiles load fewer halo rows, shorter ones keep a small batch from
+// being a few serial chains; 512 problems of side 65 .. 1025 took 24.7 ms with
+// 8 or 16 rows, 25.3 with 32, 26.7 with 64.
+int default_rows(const homg_batch_ctx* b) {
+  int rows = 16;
+  for (; rows > 4; rows /= 2) {
+    int64_t waves = 0;
+    for (int i : b->big) waves += batch_residual_waves(b->sides[i], rows);
+    if (waves >= 8192) break;
   }
-  const int it0 = iters(0);
-  int q = 0;
-  for (int t0 = 0; t0 < it0; t0 += depth, ++q) {
-    const int g = std::min(depth, it0 - t0);
-    codes.push_back(bst_code(BST_L0, 0, g, q, M == 0 && t0 == 0, t0 + g == it0));
-  }
-  return codes;
+  return rows;
 }
 
 int rows_for(const homg_batch_ctx* b, int side) {
   auto it = b->tile_rows.find(side);
   if (it != b->tile_rows.end() && it->second > 0) return std::min(it->second, side - 2);
-  return default_walk_len(2, side);
+  return std::min(default_rows(b), side - 2);
 }
 
 int depth_for(const homg_batch_ctx* b, int side) {
@@ -138,71 +149,313 @@ int depth_for(const homg_batch_ctx* b, int side) {
   return (it != b->pass_iters.end() && it->second > 0) ? std::min(it->second, TB_MAX_IT) : TB_MAX_IT;
 }
 
-// Stage table of every problem for the current pass depths (host copy; the
-// upload happens in run_once), and the step bound that follows from it.
-void build_schedule(homg_batch_ctx* b) {
-  b->sweep_levels.clear();
-  int max_cycle_len = 0;
-  for (int i = 0; i < b->count; ++i) {
-    BatchProblem& q = b->h_probs[i];
-    const std::vector<int> codes = stage_codes(b->sides[i], b->levels[i], b->max_i, depth_for(b, b->sides[i]));
-    q.sched_off = int(b->sweep_levels.size());
-    q.sweeps = int(codes.size());
-    b->sweep_levels.insert(b->sweep_levels.end(), codes.begin(), codes.end());
-    max_cycle_len = std::max(max_cycle_len, q.top + q.sweeps + 2);
+// Up to this many nodes in all, a batch is bound by latency: its passes run
+// on tiles (1.8 times the work, but every load in one round trip; above, the
+// walking waves) and the end of the restriction chain in one launch (above,
+// one launch per step).  512 problems of side 65 .. 1025, 143e6 nodes: the
+// lattice passes took 570 us a cycle on tiles, the chain 476 us in one launch.
+constexpr int64_t BATCH_TILED_NODES = 1 << 21;
+
+constexpr int LATTICE_ROWS = 16;  // rows per band of a walking lattice pass
+
+// The stage lists of the current tile shapes and pass depths.
+homg_status build_plan(homg_batch_ctx* b) {
+  const int eb = prec_bytes(b->prec);
+  const bool red = b->prec != PREC_F64;
+  auto node = [&](char* p, const Lay& l) -> char* { return p ? p + size_t(l.off) * eb : nullptr; };
+  // level 0 in several passes keeps its iterates
+  size_t need_e = 0;
+  int64_t nodes = 0;
+  for (int i : b->big) {
+    Problem& p = b->probs[i];
+    nodes += int64_t(p.n) * p.n;
+    if (level_iters(b, p.levels, 0) > depth_for(b, p.n)) need_e += 2 * ((size_t(p.el.alloc) * eb + 255) & ~size_t(255));
   }
-  // each problem's tiles per stage of a cycle, filled on the device
-  // (launch_batch_tile_table) so that a step looks its tile count up
-  for (int i = 0; i < b->count; ++i) {
-    BatchProblem& q = b->h_probs[i];
-    q.tile_off = int(b->sweep_levels.size());
-    b->sweep_levels.insert(b->sweep_levels.end(), size_t(q.top + q.sweeps + 2), 0);
+  if (need_e) {
+    (void)hipFree(b->e_arena);
+    b->e_arena = nullptr;
+    if (hipMalloc(&b->e_arena, need_e) != hipSuccess) {
+      (void)hipGetLastError();
+      return bfail(b, HOMG_ERR_OOM, "batch allocation of " + std::to_string(need_e) + " bytes failed");
+    }
+    BHIP(b, hipMemset(b->e_arena, 0, need_e));  // boundaries stay 0
+    char* at = static_cast<char*>(b->e_arena);
+    for (int i : b->big) {
+      Problem& p = b->probs[i];
+      if (level_iters(b, p.levels, 0) <= depth_for(b, p.n)) continue;
+      for (int c = 0; c < 2; ++c, at += (size_t(p.el.alloc) * eb + 255) & ~size_t(255)) p.e[c] = at;
+    }
   }
-  b->max_steps = 4 + (b->max_cycles + 1) * max_cycle_len;
+  const bool small_batch = nodes <= BATCH_TILED_NODES;
+
+  std::vector<int2> tiles;
+  auto add_tiles = [&](int desc, int n) {
+    for (int t = 0; t < n; ++t) tiles.push_back(make_int2(desc, t));
+  };
+  auto close = [&](int first) { return TileRange{first, int(tiles.size()) - first}; };
+  // residual + restriction to level 1
+  std::vector<BatchResidual> res;
+  for (int i : b->big) {
+    Problem& p = b->probs[i];
+    const int len = std::max(2, (rows_for(b, p.n) + 1) / 2 * 2);  // whole level-1 rows
+    const int waves = batch_residual_waves(p.n, len);
+    const double h = 1.0 / double(p.n - 1);
+    res.push_back(BatchResidual{node(p.r[0], p.rl[0]), node(p.r[1], p.rl[1]), p.rl[0].pitch, p.rl[1].pitch, p.partials,
+                                p.partials + batch_residual_waves(p.n, 2), 1.0 / (h * h), i, p.n, len, waves});
+    add_tiles(int(res.size()) - 1, (waves + 3) / 4);
+  }
+  b->residual = close(0);
+  // the chain 1 -> ms: single steps, then the last P as one launch
+  std::vector<BatchRestrict> rs;
+  std::vector<char> multi;
+  constexpr int MULTI_B = 4, MULTI_P = 4;
+  b->multi_lds = 0;
+  int deepest = 0;
+  for (int i : b->big) deepest = std::max(deepest, b->probs[i].ms);
+  b->restricts.assign(deepest + 1, TileRange{});
+  auto multi_steps = [&](const Problem& p) {
+    return small_batch && p.ms - 1 >= 2 ? std::min(p.ms - 1, MULTI_P) : 0;
+  };
+  for (int a = 1; a <= deepest; ++a) {
+    const int first = int(tiles.size());
+    for (int i : b->big) {
+      const Problem& p = b->probs[i];
+      if (a >= p.ms - multi_steps(p)) continue;
+      const int nc = (p.n - 1) / (2 << a) + 1, len = default_walk_len(2, nc);
+      rs.push_back(BatchRestrict{node(p.r[a], p.rl[a]), node(p.r[a + 1], p.rl[a + 1]), p.rl[a].pitch,
+                                 p.rl[a + 1].pitch, i, nc, len, 0});
+      add_tiles(int(rs.size()) - 1, batch_restrict_tiles(nc, len));
+    }
+    b->restricts[a] = close(first);
+  }
+  {
+    const int first = int(tiles.size());
+    int k = 0;
+    for (int i : b->big) {
+      Problem& p = b->probs[i];
+      const int P = multi_steps(p);
+      if (!P) continue;
+      void* r[MR_MAX + 1];
+      Lay l[MR_MAX + 1];
+      for (int j = 0; j <= P; ++j) {
+        r[j] = p.r[p.ms - P + j];
+        l[j] = p.rl[p.ms - P + j];
+      }
+      multi.resize(multi.size() + batch_multi_bytes());
+      const int blocks = batch_multi_fill(b->prec, multi.data() + multi.size() - batch_multi_bytes(), i, P, MULTI_B, r, l);
+      b->multi_lds = std::max(b->multi_lds, restrict_multi_lds(b->prec, 2, P, MULTI_B));
+      add_tiles(k++, blocks);
+    }
+    b->multi = close(first);
+  }
+  // coarse tails
+  const size_t ta = batch_tail_bytes(b->prec);
+  std::vector<char> tails(ta * b->big.size());
+  b->tail_lds = 0;
+  for (size_t k = 0; k < b->big.size(); ++k) {
+    Problem& p = b->probs[b->big[k]];
+    const int nlev = p.levels - p.ms, nms = (p.n - 1) / (1 << p.ms) + 1;
+    int its[BATCH_MAX_LEVELS];
+    for (int j = 0; j < nlev; ++j) its[j] = level_iters(b, p.levels, p.ms + j);
+    batch_tail_fill(b->prec, tails.data() + ta * k, nms, nlev, its, b->omega, node(p.r[p.ms], p.rl[p.ms]),
+                    p.rl[p.ms].pitch, node(p.x[p.ms][0], p.rl[p.ms]), node(p.x[p.ms][1], p.rl[p.ms]),
+                    p.rl[p.ms].pitch, red, b->d_st + b->big[k], b->hist[b->big[k]], p.partials, res[k].count);
+    b->tail_lds = std::max(b->tail_lds, coarse_tail_lds(b->prec, 2, nms, nlev, red, false, false));
+  }
+  // one-workgroup problems
+  std::vector<char> smalls[2];
+  for (int t = 0; t < 2; ++t) {
+    smalls[t].resize(ta * b->small[t].size());
+    b->small_lds[t] = 0;
+    for (size_t k = 0; k < b->small[t].size(); ++k) {
+      const int i = b->small[t][k], n = b->sides[i], L = side_k(n);
+      int its[BATCH_MAX_LEVELS];
+      for (int j = 0; j < L; ++j) its[j] = level_iters(b, L, j);
+      const bool rr = n >= 5 && L >= 2 && !(t == 1 && L == 2);  // as a single solve's residual
+      batch_small_fill(b->prec, smalls[t].data() + ta * k, n, L, its, b->omega, t == 1, rr, i, b->d_st + i, b->hist[i]);
+      b->small_lds[t] = std::max(b->small_lds[t], coarse_tail_lds(b->prec, 2, n, L, t == 1, false, true));
+    }
+  }
+  // iteration passes: every problem's sequence, aligned at its end
+  std::vector<std::vector<std::pair<PassGroup, BatchPass>>> seq;  // [position from the end]
+  for (int i : b->big) {
+    Problem& p = b->probs[i];
+    std::vector<std::pair<PassGroup, BatchPass>> mine;
+    const char* prev = p.x[p.ms][0];  // the state level m starts from
+    const char* cur = p.x[p.ms][1];
+    for (int m = p.ms - 1; m >= 0; --m) {
+      const int nm = (p.n - 1) / (1 << m) + 1, it = level_iters(b, p.levels, m);
+      const int step = m ? LT_MAX_IT : depth_for(b, p.n);
+      const Lay& cl = m ? p.rl[m] : p.el;
+      const double h = 1.0 / double(nm - 1);
+      const bool walk = !(small_batch && nm <= LT2_MAX_SIDE);
+      int src = 1;
+      for (int t0 = 0; t0 < it; t0 += step) {
+        const int g = std::min(step, it - t0);
+        const bool lat = t0 == 0, accum = m == 0 && t0 + g == it;
+        const int kind = !walk ? BATCH_TILED : m ? BATCH_WALK_PREV : accum ? BATCH_WALK_ACCUM : BATCH_WALK;
+        char* from = m ? p.x[m][src] : p.e[src];
+        char* to = m ? p.x[m][1 - src] : p.e[1 - src];
+        BatchPass q{};
+        q.xo = lat ? nullptr : node(from, cl);
+        q.xn = accum ? nullptr : node(to, cl);
+        q.xp = m ? node(p.x[m][2], cl) : nullptr;
+        q.r = node(p.r[m], p.rl[m]);
+        if (lat) {
+          q.l1_prev = node(const_cast<char*>(prev), p.rl[m + 1]);
+          q.l1_cur = node(const_cast<char*>(cur), p.rl[m + 1]);
+          q.l1_pitch = p.rl[m + 1].pitch;
+        }
+        q.cp = cl.pitch;
+        q.rp = p.rl[m].pitch;
+        q.hl2 = h * h;
+        q.prob = i;
+        q.n = nm;
+        q.len = walk ? (m ? LATTICE_ROWS : std::max(16, rows_for(b, p.n))) : batch_tiled_side(nm);
+        q.accum = accum ? 1 : 0;
+        mine.push_back({PassGroup{g, kind, lat, 0, 0}, q});
+        src = 1 - src;
+      }
+      if (m) {
+        cur = p.x[m][src];
+        prev = p.x[m][2];
+      }
+    }
+    for (size_t k = 0; k < mine.size(); ++k) {
+      const size_t pos = mine.size() - 1 - k;
+      if (seq.size() <= pos) seq.resize(pos + 1);
+      seq[pos].push_back(mine[k]);
+    }
+  }
+  std::vector<BatchPass> passes;
+  b->passes.clear();
+  for (size_t pos = seq.size(); pos-- > 0;) {
+    std::map<std::tuple<int, int, bool>, std::vector<BatchPass>> by;  // the largest problems stay first
+    for (auto& e : seq[pos]) by[std::make_tuple(e.first.it, e.first.kind, e.first.lat)].push_back(e.second);
+    for (auto& kv : by) {
+      PassGroup g{std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first), int(tiles.size()), 0};
+      for (const BatchPass& q : kv.second) {
+        passes.push_back(q);
+        add_tiles(int(passes.size()) - 1, g.kind == BATCH_TILED ? q.len * q.len : tb_blocks(q.n, g.it, q.len));
+      }
+      g.count = int(tiles.size()) - g.first;
+      b->passes.push_back(g);
+    }
+  }
+  // one allocation for all lists
+  std::vector<char> host;
+  auto put = [&](const void* p, size_t bytes) {
+    const size_t at = (host.size() + 255) & ~size_t(255);
+    host.resize(at + bytes);
+    if (bytes) std::memcpy(host.data() + at, p, bytes);
+    return at;
+  };
+  b->o_res = put(res.data(), sizeof(BatchResidual) * res.size());
+  b->o_rs = put(rs.data(), sizeof(BatchRestrict) * rs.size());
+  b->o_multi = put(multi.data(), multi.size());
+  b->o_tail = put(tails.data(), tails.size());
+  for (int t = 0; t < 2; ++t) b->o_small[t] = put(smalls[t].data(), smalls[t].size());
+  b->o_pass = put(passes.data(), sizeof(BatchPass) * passes.size());
+  b->o_tiles = put(tiles.data(), sizeof(int2) * tiles.size());
+  if (host.size() > b->plan_bytes) {
+    (void)hipFree(b->plan);
+    b->plan = nullptr;
+    b->plan_bytes = 0;
+    if (hipMalloc(reinterpret_cast<void**>(&b->plan), host.size()) != hipSuccess) {
+      (void)hipGetLastError();
+      return bfail(b, HOMG_ERR_OOM, "stage list allocation of " + std::to_string(host.size()) + " bytes failed");
+    }
+    b->plan_bytes = host.size();
+  }
+  BHIP(b, hipMemcpy(b->plan, host.data(), host.size(), hipMemcpyHostToDevice));
+  b->dirty = false;
+  return HOMG_OK;
 }
 
-void apply_tiles(homg_batch_ctx* b) {
-  for (int i = 0; i < b->count; ++i) b->h_probs[i].len[0] = rows_for(b, b->sides[i]);
-  build_schedule(b);
+// One cycle of every problem solved in stages; pending: the cycle whose
+// residual norm the tails reduce first (-1: none).
+homg_status enqueue_cycle(homg_batch_ctx* b, int pending, hipStream_t s) {
+  const bool red = b->prec != PREC_F64;
+  const int2* tiles = reinterpret_cast<const int2*>(b->plan + b->o_tiles);
+  const BatchRestrict* rs = reinterpret_cast<const BatchRestrict*>(b->plan + b->o_rs);
+  const BatchPass* ps = reinterpret_cast<const BatchPass*>(b->plan + b->o_pass);
+  const double* const* f = reinterpret_cast<const double* const*>(b->d_ptrs);
+  double* const* u = reinterpret_cast<double* const*>(b->d_ptrs + b->count);
+  for (const TileRange& t : b->restricts)
+    if (t.count) BHIP(b, launch_batch_restrict(b->prec, rs, tiles + t.first, t.count, b->d_st, s));
+  if (b->multi.count)
+    BHIP(b, launch_batch_restrict_multi(b->prec, b->plan + b->o_multi, tiles + b->multi.first, b->multi.count,
+                                        b->multi_lds, b->d_st, s));
+  BHIP(b, launch_batch_tails(b->prec, red, b->plan + b->o_tail, int(b->big.size()), b->tail_lds, pending, s));
+  for (const PassGroup& g : b->passes)
+    BHIP(b, launch_batch_pass(b->prec, ps, tiles + g.first, g.count, g.it, g.lat, g.kind, b->omega, b->d_st, u, s));
+  BHIP(b, launch_batch_residual(b->prec, reinterpret_cast<const BatchResidual*>(b->plan + b->o_res),
+                                tiles + b->residual.first, b->residual.count, false, f, u, b->d_st, s));
+  return HOMG_OK;
 }
+
+constexpr int SMALL_CYCLES = 64;  // cycles per launch of the one-workgroup problems
 
 homg_status run_once(homg_batch_ctx* b, const double* const* f, double* const* u, double tol,
                      hipStream_t s) {
   for (int i = 0; i < b->count; ++i) {
     if (!f[i] || !u[i]) return bfail(b, HOMG_ERR_INVALID_ARG, "null f or u pointer");
-    b->h_probs[i].f = f[i];
-    b->h_probs[i].u = u[i];
+    b->h_ptrs[i] = const_cast<double*>(f[i]);
+    b->h_ptrs[b->count + i] = u[i];
   }
-  *b->h_run = BatchRun{tol, b->omega, b->count, b->max_cycles, b->max_steps, 0};
-  if (b->sweep_levels.size() > b->sched_cap)
-    return bfail(b, HOMG_ERR_INVALID_ARG, "stage table exceeds its allocation");
-  BHIP(b, hipMemcpyAsync(b->d_sweep_levels, b->sweep_levels.data(), sizeof(int) * b->sweep_levels.size(),
-                         hipMemcpyHostToDevice, s));
-  BHIP(b, hipMemcpyAsync(b->d_probs, b->h_probs, sizeof(BatchProblem) * b->count,
-                         hipMemcpyHostToDevice, s));
-  BHIP(b, hipMemcpyAsync(b->d_run, b->h_run, sizeof(BatchRun), hipMemcpyHostToDevice, s));
-  if (!b->exec) {
-    hipGraph_t g = nullptr;
-    hipError_t ge = build_batch_graph(b->prec, b->count, b->grid, b->d_probs, b->d_state, b->d_done,
-                                      b->d_sweep_levels, b->d_run, b->d_sync, &g);
-    if (ge != hipSuccess)
-      return bfail(b, HOMG_ERR_HIP, std::string("graph construction failed: ") + hipGetErrorString(ge));
-    b->graph = g;
-    BHIP(b, hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0));
+  if (b->dirty)
+    if (homg_status e = build_plan(b)) return e;
+  BHIP(b, hipMemcpyAsync(b->d_ptrs, b->h_ptrs, 2 * sizeof(void*) * b->count, hipMemcpyHostToDevice, s));
+  const double* const* df = reinterpret_cast<const double* const*>(b->d_ptrs);
+  double* const* du = reinterpret_cast<double* const*>(b->d_ptrs + b->count);
+  const BatchResidual* res = reinterpret_cast<const BatchResidual*>(b->plan + b->o_res);
+  const int2* tiles = reinterpret_cast<const int2*>(b->plan + b->o_tiles);
+  const int nbig = int(b->big.size());
+  int small_c0 = 0;  // the one-workgroup problems' next cycles
+  auto launch_small = [&]() -> homg_status {
+    const int c1 = std::min(b->max_cycles, small_c0 + SMALL_CYCLES);
+    for (int t = 0; t < 2; ++t)
+      if (!b->small[t].empty())
+        BHIP(b, launch_batch_small(b->prec, t == 1, b->plan + b->o_small[t], int(b->small[t].size()), b->small_lds[t],
+                                   df, du, tol, small_c0, c1, s));
+    small_c0 = c1;
+    return HOMG_OK;
+  };
+  if (homg_status e = launch_small()) return e;
+  if (nbig) {
+    BHIP(b, launch_batch_residual(b->prec, res, tiles + b->residual.first, b->residual.count, true, df, du, b->d_st, s));
+    BHIP(b, launch_batch_finalize(res, nbig, b->d_st, b->d_hist, 0, true, tol, s));
   }
-  BHIP(b, launch_batch_tile_table(b->count, b->d_probs, b->d_sweep_levels, s));
-  BHIP(b, launch_batch_init(b->count, b->d_state, b->d_done, b->d_sync, s));
-  // replays of 64 steps until a step finds no active problem (or the step
-  // bound of max_cycles is reached)
-  for (int done_steps = 0; done_steps < b->max_steps; done_steps += BATCH_STEPS_PER_REPLAY) {
-    BHIP(b, hipGraphLaunch(b->exec, s));
-    BHIP(b, hipMemcpyAsync(b->h_sync, b->d_sync, sizeof(BatchSync), hipMemcpyDeviceToHost, s));
+  int enqueued = 0, batch = 2;
+  for (;;) {
+    const int upto = nbig ? std::min(b->max_cycles, enqueued + batch) : enqueued;
+    for (int c = enqueued + 1; c <= upto; ++c)
+      if (homg_status e = enqueue_cycle(b, c > enqueued + 1 ? c - 1 : -1, s)) return e;
+    if (upto > enqueued) BHIP(b, launch_batch_finalize(res, nbig, b->d_st, b->d_hist, upto, false, tol, s));
+    enqueued = upto;
+    BHIP(b, launch_batch_publish(b->count, b->d_st, b->d_hist, b->h_state, s));
     BHIP(b, hipStreamSynchronize(s));
-    if (b->h_sync->idle) break;
+    // the next batch of cycles from the slowest problem still running
+    bool run_big = false, run_small = false;
+    double need = 1.0;
+    for (int i : b->big) {
+      const BatchState& v = b->h_state[i];
+      if (v.done) continue;
+      run_big = true;
+      double q = 0.5;
+      if (v.cycles >= 2 && v.prev > 0) q = v.rel / v.prev;
+      q = std::min(std::max(q, 1e-3), 0.95);
+      need = std::max(need, std::log(tol / v.rel) / std::log(q));
+    }
+    for (int t = 0; t < 2; ++t)
+      for (int i : b->small[t]) run_small = run_small || !b->h_state[i].done;
+    run_big = run_big && enqueued < b->max_cycles;
+    run_small = run_small && small_c0 < b->max_cycles;
+    if (!run_big && !run_small) break;
+    batch = run_big ? int(std::ceil(std::min(need, 16.0))) : 0;
+    if (run_small)
+      if (homg_status e = launch_small()) return e;
   }
-  BHIP(b, hipMemcpyAsync(b->h_state, b->d_state, sizeof(BatchState) * b->count, hipMemcpyDeviceToHost, s));
-  BHIP(b, hipMemcpyAsync(b->h_done, b->d_done, sizeof(int) * b->count, hipMemcpyDeviceToHost, s));
-  BHIP(b, hipStreamSynchronize(s));
   return HOMG_OK;
 }
 
@@ -245,66 +498,54 @@ homg_status homg_batch_create(homg_batch* out, int count, const int64_t* sides, 
     return bfail(nullptr, HOMG_ERR_HIP, "hipGetDevice failed");
   }
   const int eb = prec_bytes(b->prec);
-  // arena layout: per problem e0, e1, r_0..r_M (storage type), partials, history
-  std::vector<size_t> off;
-  size_t total = 0;
+  // one arena: what must start at 0 (boundaries) first, then sums and histories
+  size_t total = 0, zeroed = 0;
   auto take = [&](size_t bytes) {
     const size_t o2 = total;
     total += (bytes + 255) & ~size_t(255);
     return o2;
   };
-  struct Plan {
-    size_t e[2], r[BATCH_MAX_LEVELS], x[BATCH_MAX_LEVELS][2], x3[BATCH_MAX_LEVELS] = {}, part, hist, r64 = 0,
-        x64[2] = {0, 0};
-    Lay el, rl[BATCH_MAX_LEVELS], l64;
-  };
-  std::vector<Plan> plans(count);
+  b->probs.resize(count);
+  std::vector<std::vector<size_t>> at(count);
   for (int i = 0; i < count; ++i) {
-    const int n = int(sides[i]);
-    const int L = side_k(n);
+    const int n = int(sides[i]), L = side_k(n);
     b->sides.push_back(n);
-    b->levels.push_back(L);
-    Plan& p = plans[i];
+    Problem& p = b->probs[i];
+    p.n = n;
+    p.levels = L;
+    if (n <= tail_max_side(2)) {
+      b->small[b->prec != PREC_F64 && L >= 2 ? 1 : 0].push_back(i);
+      continue;
+    }
+    b->big.push_back(i);
     p.el = padded_layout(2, n, eb);
-    p.e[0] = take(size_t(p.el.alloc) * eb);
-    p.e[1] = take(size_t(p.el.alloc) * eb);
-    for (int m = 0; m < L; ++m) {
+    while (((n - 1) >> p.ms) + 1 > tail_max_side(2)) ++p.ms;
+    for (int m = 0; m <= p.ms; ++m) {
       p.rl[m] = padded_layout(2, (n - 1) / (1 << m) + 1, eb);
-      p.r[m] = take(size_t(p.rl[m].alloc) * eb);
-      for (int c = 0; c < 2 && m >= 1; ++c) p.x[m][c] = take(size_t(p.rl[m].alloc) * eb);
-      if (m >= 1 && (n - 1) / (1 << m) + 1 >= BATCH_LTB_MIN_SIDE) p.x3[m] = take(size_t(p.rl[m].alloc) * eb);
+      const size_t bytes = size_t(p.rl[m].alloc) * eb;
+      at[i].push_back(take(bytes));
+      for (int c = 0; m && c < (m < p.ms ? 3 : 2); ++c) at[i].push_back(take(bytes));
     }
-    if (b->prec != PREC_F64 && L >= 2) {
-      // the FP64 coarsest level of reduced-precision cycles
-      p.l64 = padded_layout(2, (n - 1) / (1 << (L - 1)) + 1, 8);
-      p.r64 = take(sizeof(double) * size_t(p.l64.alloc));
-      p.x64[0] = take(sizeof(double) * size_t(p.l64.alloc));
-      p.x64[1] = take(sizeof(double) * size_t(p.l64.alloc));
-    }
-    p.part = take(sizeof(double) * size_t(batch_tiles(n, 1)));
-    p.hist = take(sizeof(double) * size_t(b->max_cycles + 1));
-    // the stage table is sized for one iteration per level-0 pass, the
-    // longest sequence any pass depth gives: the codes and the row of
-    // tiles per stage (restrictions, codes, residual, finalize)
-    b->sched_cap += 2 * stage_codes(n, L, b->max_i, 1).size() + size_t(L - 1) + 2;
   }
-  homg_status st = HOMG_OK;
+  zeroed = total;
+  // the largest problems first in every list: a launch does not end on them
+  std::stable_sort(b->big.begin(), b->big.end(), [&](int x, int y) { return b->sides[x] > b->sides[y]; });
+  std::vector<size_t> part(count), hist(count);
+  for (int i = 0; i < count; ++i) {
+    if (b->sides[i] > tail_max_side(2)) part[i] = take(2 * sizeof(double) * size_t(batch_residual_waves(b->sides[i], 2)));
+    hist[i] = take(sizeof(double) * size_t(b->max_cycles + 1));
+  }
   if (hipMalloc(&b->arena, total) != hipSuccess) {
     (void)hipGetLastError();
     free_batch(b);
     return bfail(nullptr, HOMG_ERR_OOM, "batch arena allocation of " + std::to_string(total) + " bytes failed");
   }
-  bool ok = hipMemset(b->arena, 0, total) == hipSuccess;  // e boundaries stay 0 forever
-  ok = ok && hipMalloc(reinterpret_cast<void**>(&b->d_probs), sizeof(BatchProblem) * count) == hipSuccess;
-  ok = ok && hipMalloc(reinterpret_cast<void**>(&b->d_run), sizeof(BatchRun)) == hipSuccess;
-  ok = ok && hipMalloc(reinterpret_cast<void**>(&b->d_state), sizeof(BatchState) * count) == hipSuccess;
-  ok = ok && hipMalloc(reinterpret_cast<void**>(&b->d_done), sizeof(int) * count) == hipSuccess;
-  ok = ok && hipMalloc(reinterpret_cast<void**>(&b->d_sync), sizeof(BatchSync)) == hipSuccess;
-  ok = ok && hipHostMalloc(reinterpret_cast<void**>(&b->h_probs), sizeof(BatchProblem) * count, hipHostMallocDefault) == hipSuccess;
-  ok = ok && hipHostMalloc(reinterpret_cast<void**>(&b->h_run), sizeof(BatchRun), hipHostMallocDefault) == hipSuccess;
+  bool ok = !zeroed || hipMemset(b->arena, 0, zeroed) == hipSuccess;
+  ok = ok && hipMalloc(reinterpret_cast<void**>(&b->d_ptrs), 2 * sizeof(void*) * count) == hipSuccess;
+  ok = ok && hipMalloc(reinterpret_cast<void**>(&b->d_st), sizeof(DevState) * count) == hipSuccess;
+  ok = ok && hipMalloc(reinterpret_cast<void**>(&b->d_hist), sizeof(double*) * count) == hipSuccess;
+  ok = ok && hipHostMalloc(reinterpret_cast<void**>(&b->h_ptrs), 2 * sizeof(void*) * count, hipHostMallocDefault) == hipSuccess;
   ok = ok && hipHostMalloc(reinterpret_cast<void**>(&b->h_state), sizeof(BatchState) * count, hipHostMallocDefault) == hipSuccess;
-  ok = ok && hipHostMalloc(reinterpret_cast<void**>(&b->h_done), sizeof(int) * count, hipHostMallocDefault) == hipSuccess;
-  ok = ok && hipHostMalloc(reinterpret_cast<void**>(&b->h_sync), sizeof(BatchSync), hipHostMallocDefault) == hipSuccess;
   if (!ok) {
     (void)hipGetLastError();
     free_batch(b);
@@ -312,53 +553,26 @@ homg_status homg_batch_create(homg_batch* out, int count, const int64_t* sides, 
   }
   char* base = static_cast<char*>(b->arena);
   for (int i = 0; i < count; ++i) {
-    BatchProblem& q = b->h_probs[i];
-    std::memset(&q, 0, sizeof(q));
-    const Plan& p = plans[i];
-    const int n = b->sides[i], L = b->levels[i];
-    q.e[0] = base + p.e[0] + size_t(p.el.off) * eb;
-    q.e[1] = base + p.e[1] + size_t(p.el.off) * eb;
-    q.ep = p.el.pitch;
-    for (int m = 0; m < L; ++m) {
-      q.r[m] = base + p.r[m] + size_t(p.rl[m].off) * eb;
-      for (int c = 0; c < 2 && m >= 1; ++c) q.x[m][c] = base + p.x[m][c] + size_t(p.rl[m].off) * eb;
-      if (m >= 1 && (n - 1) / (1 << m) + 1 >= BATCH_LTB_MIN_SIDE) q.x3[m] = base + p.x3[m] + size_t(p.rl[m].off) * eb;
-      q.rp[m] = p.rl[m].pitch;
-      q.len[m] = default_walk_len(2, (n - 1) / (1 << m) + 1);
+    b->hist.push_back(reinterpret_cast<double*>(base + hist[i]));
+    Problem& p = b->probs[i];
+    if (at[i].empty()) continue;
+    p.partials = reinterpret_cast<double*>(base + part[i]);
+    size_t k = 0;
+    for (int m = 0; m <= p.ms; ++m) {
+      p.r[m] = base + at[i][k++];
+      for (int c = 0; m && c < (m < p.ms ? 3 : 2); ++c) p.x[m][c] = base + at[i][k++];
     }
-    if (p.r64 || p.x64[0]) {
-      q.r64 = reinterpret_cast<double*>(base + p.r64) + p.l64.off;
-      q.x64[0] = reinterpret_cast<double*>(base + p.x64[0]) + p.l64.off;
-      q.x64[1] = reinterpret_cast<double*>(base + p.x64[1]) + p.l64.off;
-      q.p64 = p.l64.pitch;
-    }
-    q.partials = reinterpret_cast<double*>(base + p.part);
-    q.history = reinterpret_cast<double*>(base + p.hist);
-    q.n = n;
-    q.levels = L;
-    q.top = L - 1;
-    q.id = i;
   }
-  build_schedule(b);
-  if (hipMalloc(reinterpret_cast<void**>(&b->d_sweep_levels), sizeof(int) * b->sched_cap) != hipSuccess ||
-      hipMemcpy(b->d_sweep_levels, b->sweep_levels.data(), sizeof(int) * b->sweep_levels.size(),
-                hipMemcpyHostToDevice) != hipSuccess) {
+  if (hipMemcpy(b->d_hist, b->hist.data(), sizeof(double*) * count, hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipGetLastError();
     free_batch(b);
-    return bfail(nullptr, HOMG_ERR_OOM, "schedule table allocation failed");
+    return bfail(nullptr, HOMG_ERR_HIP, "batch initialisation failed");
   }
-  int per_cu = 0, cus = 0;
-  size_t lds = 0;
-  if (batch_occupancy(b->prec, count, &per_cu, &lds) != hipSuccess || per_cu < 1 ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device) != hipSuccess) {
-    (void)hipGetLastError();
+  if (homg_status e = build_plan(b)) {
+    const std::string msg = b->err;
     free_batch(b);
-    return bfail(nullptr, HOMG_ERR_HIP, "cannot size the step launches");
+    return bfail(nullptr, e, msg);
   }
-  // one resident wave of workgroups per step launch; they take the step's
-  // tiles round-robin
-  b->grid = per_cu * cus;
-  (void)st;
   if (hipDeviceSynchronize() != hipSuccess) {
     free_batch(b);
     return bfail(nullptr, HOMG_ERR_HIP, "batch initialisation failed");
@@ -379,6 +593,7 @@ homg_status homg_batch_set_tile_rows(homg_batch b, int64_t side, int rows) {
   if (rows < 0 || rows > 4096) return bfail(b, HOMG_ERR_INVALID_ARG, "rows must be in [0, 4096]");
   if (rows == 0) b->tile_rows.erase(int(side));
   else b->tile_rows[int(side)] = rows;
+  b->dirty = true;
   return HOMG_OK;
 }
 
@@ -387,6 +602,7 @@ homg_status homg_batch_set_pass_iters(homg_batch b, int64_t side, int iters) {
   if (iters < 0 || iters > TB_MAX_IT) return bfail(b, HOMG_ERR_INVALID_ARG, "iters must be in [0, 4]");
   if (iters == 0) b->pass_iters.erase(int(side));
   else b->pass_iters[int(side)] = iters;
+  b->dirty = true;
   return HOMG_OK;
 }
 
@@ -396,13 +612,12 @@ homg_status homg_batch_solve(homg_batch b, const double* const* f, double* const
   if (!f || !u) return bfail(b, HOMG_ERR_INVALID_ARG, "null f or u array");
   if (!(tol > 0.0)) return bfail(b, HOMG_ERR_INVALID_ARG, "tol must be > 0");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  apply_tiles(b);
   if (homg_status e = run_once(b, f, u, tol, s)) return e;
   homg_status worst = HOMG_OK;
   for (int i = 0; i < b->count; ++i) {
-    const int dn = b->h_done[i];
+    const int dn = b->h_state[i].done;
     homg_status si = dn == 1 ? HOMG_OK : (dn == 2 ? HOMG_ERR_NUMERICAL : HOMG_ERR_NOT_CONVERGED);
-    if (relres_out) relres_out[i] = b->h_state[i].final_rel;
+    if (relres_out) relres_out[i] = b->h_state[i].rel;
     if (cycles_out) cycles_out[i] = b->h_state[i].cycles;
     if (status_out) status_out[i] = si;
     if (si == HOMG_ERR_NUMERICAL) worst = si;
@@ -439,6 +654,7 @@ homg_status homg_batch_tune(homg_batch b, const double* const* f, double* const*
             its <= TB_MAX_IT) {
           b->tile_rows[side] = rows;
           b->pass_iters[side] = its;
+          b->dirty = true;
           ++hits;
         }
       std::fclose(fp);
@@ -473,7 +689,11 @@ homg_status homg_batch_tune(homg_batch b, const double* const* f, double* const*
   // did work (a run whose problems all meet tol at cycle 0 times nothing)
   auto once = [&](float* ms) {
     copy_u(false);
-    apply_tiles(b);
+    if (b->dirty)
+      if (homg_status e = build_plan(b)) {
+        st = e;
+        return false;
+      }
     if (!hip_ok(hipEventRecord(e0, s), "hipEventRecord")) return false;
     if (homg_status e = run_once(b, f, u, tol, s)) {
       st = e;
@@ -513,6 +733,7 @@ homg_status homg_batch_tune(homg_batch b, const double* const* f, double* const*
     for (int rows : {4, 8, 16, 32, 64, 128}) {
       if (rows == keep || rows > side - 2) continue;
       b->tile_rows[side] = rows;
+      b->dirty = true;
       float ms = 0.f;
       if (!(ok = timed(&ms))) break;
       if (ms < best) {
@@ -521,11 +742,13 @@ homg_status homg_batch_tune(homg_batch b, const double* const* f, double* const*
       }
     }
     b->tile_rows[side] = best_rows;
+    b->dirty = true;
     const int keep_it = depth_for(b, side);
     int best_it = keep_it;
     for (int its = 1; ok && its <= TB_MAX_IT; ++its) {
       if (its == keep_it) continue;
       b->pass_iters[side] = its;
+      b->dirty = true;
       float ms = 0.f;
       if (!(ok = timed(&ms))) break;
       if (ms < best) {
@@ -534,6 +757,7 @@ homg_status homg_batch_tune(homg_batch b, const double* const* f, double* const*
       }
     }
     b->pass_iters[side] = best_it;
+    b->dirty = true;
   }
   copy_u(false);
   hip_ok(hipStreamSynchronize(s), "hipStreamSynchronize");

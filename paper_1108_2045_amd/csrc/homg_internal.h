@@ -299,93 +299,77 @@ hipError_t launch_p2_sweep(int N, int m, double omega, const double* eo, double*
                            const double* const* fam, const Lay& fl, double* u, const Lay& ul, int mode,
                            const int* done, hipStream_t s);
 
-// ---- batched solver (2D, constant coefficient): graph-replayed step launches
 constexpr int BATCH_MAX_LEVELS = 16;
-// Iteration stages of a batched cycle, one int each in the schedule table:
-// kind (bits 0-3), level (4-8), iterations (9-12), index (13-20), zero
-// (21: the stage starts from e = 0, or a hand-over of a level whose
-// x_{it-1} = 0 was never stored), accum (22: the pass adds into u).
-//   BST_SWEEP: iteration `index` (1-based) of coarse level m on its compact
-//              lattice (ping-pong x[m][0] -> x[m][1] -> ...);
-//   BST_XFER:  hand-over of level m after `iterations` iterations to the
-//              compact x_0 of level m - 1 (to the whole grid e[0] if m = 1);
-//              index 1: the iterations ran as one BST_LTB pass (x_it in
-//              x[m][1], x_{it-1} in x3[m]);
-//   BST_L0:    level-0 pass `index` of `iterations` iterations (e[index & 1]
-//              -> e[1 - index & 1]);
-//   BST_LTB:   all `iterations` (<= TB_MAX_IT) iterations of coarse level m
-//              below the top in one multi-iteration pass on its compact
-//              lattice: x[m][0] -> x_it in x[m][1], x_{it-1} in x3[m].
-enum { BST_SWEEP = 1, BST_XFER = 2, BST_L0 = 3, BST_LTB = 4 };
-// Coarse levels whose lattice side is at least this run as one BST_LTB
-// pass; smaller lattices keep one step per iteration.
-constexpr int BATCH_LTB_MIN_SIDE = 17;
-constexpr int BATCH_LTB_LEN = 16;  // band rows of a BST_LTB tile (wave)
-__host__ __device__ inline int bst_code(int kind, int level, int count, int index, bool zero, bool accum) {
-  return kind | (level << 4) | (count << 9) | (index << 13) | (zero ? 1 << 21 : 0) | (accum ? 1 << 22 : 0);
-}
-__host__ __device__ inline int bst_kind(int c) { return c & 15; }
-__host__ __device__ inline int bst_level(int c) { return (c >> 4) & 31; }
-__host__ __device__ inline int bst_count(int c) { return (c >> 9) & 15; }
-__host__ __device__ inline int bst_index(int c) { return (c >> 13) & 255; }
-__host__ __device__ inline bool bst_zero(int c) { return (c >> 21) & 1; }
-__host__ __device__ inline bool bst_accum(int c) { return (c >> 22) & 1; }
 
-struct BatchProblem {         // one problem, read by the step kernels
-  const double* f;            // caller arrays, dense side n
-  double* u;
-  // FP32/BF16 batches: the coarsest level (level top) in FP64 -- its
-  // right-hand side and iterate pair, compact, pitch p64; the iterations
-  // also store their rounding into x[top] for the hand-over
-  double* r64;
-  double* x64[2];
-  int64_t p64;
-  void* e[2];                 // internal e ping-pong, pointer at node (0,0)
-  void* r[BATCH_MAX_LEVELS];  // residual pyramid, pointer at node (0,0) of each level
-  void* x[BATCH_MAX_LEVELS][2];  // compact iterate pair of each coarse level (layout of r)
-  void* x3[BATCH_MAX_LEVELS];    // third compact array: x_{it-1} of a BST_LTB pass
-  int64_t ep;                 // pitch of e
-  int64_t rp[BATCH_MAX_LEVELS];
-  int len[BATCH_MAX_LEVELS];  // rows walked per tile on level-m grids (tile shape)
-  double* partials;           // per-tile norm sums
-  double* history;            // relres after cycles 0..max_cycles
-  int n, levels, top, sweeps; // side, levels, coarsest level visited, iteration stages per cycle
-  int sched_off, id;           // offset of the stage codes in the table; problem index
-  int tile_off, pad1;          // offset of the tiles-per-stage row (one cycle) in the table
+// ---- batched solver (2D, constant coefficient): one launch per stage for
+// all problems.  Every launch takes a list of {descriptor, block} pairs, one
+// per workgroup; st, f, u, hist are indexed by the problem.
+struct BatchResidual {  // residual + first restriction (n >= 5)
+  void* r;
+  void* rc;
+  int64_t rp, cp;
+  double* partials;  // `count` sums of r^2 and of f^2
+  double* fpart;
+  double inv_h2;
+  int prob, n, len, count;
 };
-struct BatchState {
-  int cycles;
-  int retired;                // step in which the problem finished (INT32_MAX while active)
-  double fnorm;
-  double final_rel;
+struct BatchRestrict {  // one restriction to side nc
+  const void* rf;
+  void* rc;
+  int64_t fp, cp;
+  int prob, nc, len, pad;
 };
-struct BatchRun {
-  double tol, omega;
-  int count, max_cycles, max_steps, pad;
+struct BatchPass {  // iterations of one lattice (or level 0) of one problem
+  const void* xo;   // input iterate, or the coarser level's state in l1_*
+  void* xn;
+  void* xp;
+  const void* r;
+  const void* l1_prev;
+  const void* l1_cur;
+  int64_t cp, rp, l1_pitch;
+  double hl2;
+  int prob, n, len, accum;  // len: blocks per axis (tiled), rows per band (walking)
 };
-// Step counter of a batched solve: step kernel j of a replay runs step
-// base + j; the replay's last node advances base.  idle: a step found no
-// active problem (every later step returns at once).
-struct BatchSync {
-  int base, steps, idle, pad;
+struct BatchState {  // what the host reads of a problem
+  int done, cycles;
+  double rel, prev;  // relative residual after the last two cycles
 };
-// Workgroups of one step launch; graph nodes (steps) per replay.
-constexpr int BATCH_STEPS_PER_REPLAY = 64;
-hipError_t batch_occupancy(int prec, int P, int* blocks_per_cu, size_t* lds);
 int default_walk_len(int d, int n);
-int batch_tiles(int side, int len);
-// Reset of the per-solve state (problem states, done flags, step counter).
-hipError_t launch_batch_init(int P, BatchState* bs, int* done, BatchSync* sync, hipStream_t s);
-// Fill every problem's tiles-per-stage row of the table (stages 4 .. of one
-// cycle, at table[tile_off ..]) from its stage codes and tile shapes; run
-// after the table and the problems are uploaded, before the steps.
-hipError_t launch_batch_tile_table(int P, const BatchProblem* probs, int* table, hipStream_t s);
-// Graph of BATCH_STEPS_PER_REPLAY step kernels (steps base .. base + S - 1 of
-// every problem's sequence, each tile of a step one workgroup) and the
-// advance of base.
-hipError_t build_batch_graph(int prec, int P, int grid, const BatchProblem* probs, BatchState* bs,
-                             int* done, const int* levels_of_sweep, const BatchRun* run,
-                             BatchSync* sync, hipGraph_t* out);
+int batch_residual_waves(int n, int len);
+int batch_tiled_side(int n);
+int batch_restrict_tiles(int nc, int len);
+size_t batch_multi_bytes();
+// Fills a multi-level restriction descriptor (see launch_restrict_multi);
+// returns its number of blocks.
+int batch_multi_fill(int prec, void* dst, int prob, int P, int B, void* const* r, const Lay* l);
+hipError_t launch_batch_residual(int prec, const BatchResidual* res, const int2* tiles, int count, bool norm,
+                                 const double* const* f, double* const* u, const DevState* st, hipStream_t s);
+hipError_t launch_batch_restrict(int prec, const BatchRestrict* rs, const int2* tiles, int count, const DevState* st,
+                                 hipStream_t s);
+hipError_t launch_batch_restrict_multi(int prec, const void* ms, const int2* tiles, int count, size_t lds,
+                                       const DevState* st, hipStream_t s);
+// it iterations: lat, from the coarser level's state; kind: BATCH_TILED
+// (into u by BatchPass), or a walking pass that stores x_it, adds it into u,
+// or stores x_it and x_{it-1}.
+enum { BATCH_TILED = -1, BATCH_WALK = 0, BATCH_WALK_ACCUM = 1, BATCH_WALK_PREV = 2 };
+hipError_t launch_batch_pass(int prec, const BatchPass* ps, const int2* tiles, int count, int it, bool lat, int kind,
+                             double omega, const DevState* st, double* const* u, hipStream_t s);
+hipError_t launch_batch_finalize(const BatchResidual* res, int count, DevState* st, double* const* hist, int cycle,
+                                 bool first, double tol, hipStream_t s);
+hipError_t launch_batch_publish(int P, const DevState* st, const double* const* hist, BatchState* out, hipStream_t s);
+// One-workgroup problems and coarse tails (homg_tail.hip): descriptors
+// filled on the host, one workgroup each.  Tails reduce the norm of the
+// residual of `cycle` first (cycle >= 0); whole solves run cycles c0 .. c1.
+// All descriptors of a launch share top64; lds: the largest of theirs.
+size_t batch_tail_bytes(int prec);
+void batch_tail_fill(int prec, void* dst, int n_level, int nlev, const int* its, double omega, const void* r,
+                     int64_t rp, void* sprev, void* scur, int64_t sp, bool top64, DevState* st, double* hist,
+                     const double* partials, int count);
+void batch_small_fill(int prec, void* dst, int n, int nlev, const int* its, double omega, bool top64, bool rr, int prob,
+                      DevState* st, double* hist);
+hipError_t launch_batch_tails(int prec, bool top64, const void* args, int count, size_t lds, int cycle, hipStream_t s);
+hipError_t launch_batch_small(int prec, bool top64, const void* args, int count, size_t lds, const double* const* f,
+                              double* const* u, double tol, int c0, int c1, hipStream_t s);
 
 // ---- learned lattice smoother (2D)
 constexpr int HID = 16;                 // hidden channels

@@ -20,6 +20,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cstring>
+
 #include "homg_device.h"
 #include "homg_internal.h"
 
@@ -133,23 +135,6 @@ Lay padded_layout(int d, int side, int elem_bytes) {
   const int64_t rows = d == 3 ? int64_t(side) * side : side;
   L.alloc = L.off + rows * L.pitch + a;  // tail slack: whole final line
   return L;
-}
-
-// ------------------------------------------------------------ norm of f
-
-__device__ __forceinline__ void tile_norm2_2d(const double* __restrict__ f, int64_t fp, int n,
-                                                  int len, double* __restrict__ partials, int bx, int by, int pidx) {
-  const int x = t2_x(bx);
-  const int y0 = t2_y0(by, len);
-  const int y1 = min(n - 1, y0 + len);
-  double s = 0.0;
-  if (x <= n - 2)
-    for (int y = y0; y < y1; ++y) {
-      double v = f[int64_t(y) * fp + x];
-      s = fmac(v, v, s);
-    }
-  s = block_sum<256>(s);
-  if (threadIdx.x == 0) partials[pidx] = s;
 }
 
 // ------------------------------------------------------------ residual
@@ -315,14 +300,12 @@ __global__ __launch_bounds__(256) void k_residual_3d(
 // west and north face and takes the others from the next lane and the row
 // before.
 template <typename T, bool NORM, bool VAR>
-__global__ __launch_bounds__(256) void k_residual_restrict_2d(
+__device__ __forceinline__ void residual_restrict_wave(
     const double* __restrict__ a, int64_t ap, const double* __restrict__ u, int64_t up, const double* __restrict__ f, int64_t fp,
     T* __restrict__ r, int64_t rp, T* __restrict__ rc, int64_t cp, int n, int len, double inv_h2,
-    double* __restrict__ partials, const int* __restrict__ done, double* __restrict__ fpart) {
+    double* __restrict__ partials, double* __restrict__ fpart, int lb) {
   using C = typename Tr<T>::C;
-  if (*done) return;
-  const int wv = __builtin_amdgcn_readfirstlane(int(xcd_order(blockIdx.x, gridDim.x)) * 4 +
-                                                int(threadIdx.x >> 6));
+  const int wv = __builtin_amdgcn_readfirstlane(lb * 4 + int(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   const int gx = (n - 2 + RR_W - 1) / RR_W;
   // (the four waves of a workgroup side by side on the same band measured
@@ -388,6 +371,16 @@ __global__ __launch_bounds__(256) void k_residual_restrict_2d(
     sf = wave_sum(sf);
     if (lane == 0) fpart[pidx] = sf;
   }
+}
+
+template <typename T, bool NORM, bool VAR>
+__global__ __launch_bounds__(256) void k_residual_restrict_2d(
+    const double* __restrict__ a, int64_t ap, const double* __restrict__ u, int64_t up, const double* __restrict__ f, int64_t fp,
+    T* __restrict__ r, int64_t rp, T* __restrict__ rc, int64_t cp, int n, int len, double inv_h2,
+    double* __restrict__ partials, const int* __restrict__ done, double* __restrict__ fpart) {
+  if (*done) return;
+  residual_restrict_wave<T, NORM, VAR>(a, ap, u, up, f, fp, r, rp, rc, cp, n, len, inv_h2, partials, fpart,
+                                       int(xcd_order(blockIdx.x, gridDim.x)));
 }
 
 // ------------------------------------------------------------ finalize
@@ -1907,17 +1900,15 @@ constexpr int LT2_B = 24;
 constexpr int LT2_NT = 1024;
 
 template <typename T, bool ZERO, bool LAT, int IT, bool VAR>
-__global__ __launch_bounds__(LT2_NT) void k_lattice_2d_tiled(
+__device__ __forceinline__ void lattice_2d_tile(
     const T* __restrict__ xo, T* __restrict__ xn, T* __restrict__ xp, int64_t cp, const T* __restrict__ r,
-    int64_t rp, int n, int nb, typename Tr<T>::C w, typename Tr<T>::C hl2, const int* __restrict__ done,
-    L1Src<T> l1, double* __restrict__ uacc, int64_t up, const double* __restrict__ a, int64_t ap) {
+    int64_t rp, int n, int nb, typename Tr<T>::C w, typename Tr<T>::C hl2, const L1Src<T>& l1,
+    double* __restrict__ uacc, int64_t up, const double* __restrict__ a, int64_t ap, int lb) {
   using C = typename Tr<T>::C;
-  if (*done) return;
   constexpr int S = LT2_B + 2 * IT, S2 = S * S, SC = S / 2 + 2, SC2 = SC * SC;
   __shared__ C X0[S2], X1[S2], Pc[LAT ? SC2 : 1], Cc[LAT ? SC2 : 1];
   __shared__ double A[VAR ? S2 : 1];
   __shared__ C FW[VAR ? S2 : 1], FS[VAR ? S2 : 1];
-  const int lb = int(xcd_order(blockIdx.x, gridDim.x));
   const int bx = lb % nb, by = lb / nb;
   // tile node (i, j) is lattice node (gx0 + i, gy0 + j)
   const int gx0 = LT2_B * bx + 1 - IT, gy0 = LT2_B * by + 1 - IT;
@@ -2014,6 +2005,16 @@ __global__ __launch_bounds__(LT2_NT) void k_lattice_2d_tiled(
   }
 }
 
+template <typename T, bool ZERO, bool LAT, int IT, bool VAR>
+__global__ __launch_bounds__(LT2_NT) void k_lattice_2d_tiled(
+    const T* __restrict__ xo, T* __restrict__ xn, T* __restrict__ xp, int64_t cp, const T* __restrict__ r,
+    int64_t rp, int n, int nb, typename Tr<T>::C w, typename Tr<T>::C hl2, const int* __restrict__ done,
+    L1Src<T> l1, double* __restrict__ uacc, int64_t up, const double* __restrict__ a, int64_t ap) {
+  if (*done) return;
+  lattice_2d_tile<T, ZERO, LAT, IT, VAR>(xo, xn, xp, cp, r, rp, n, nb, w, hl2, l1, uacc, up, a, ap,
+                                         int(xcd_order(blockIdx.x, gridDim.x)));
+}
+
 // ------------------------------------------------------------ multi-level restriction
 // P consecutive full-weighting restrictions of the cycle's chain, r_a ->
 // r_{a+1} -> ... -> r_{a+P}, in one launch: the chain's coarse end, where
@@ -2045,14 +2046,11 @@ constexpr int MR_NT = 1024;
 constexpr int MR_LB = 8;  // tile loads a lane issues before writing LDS
 
 template <typename T, int D>
-__global__ __launch_bounds__(MR_NT) void k_restrict_multi(MultiRestrictPlan mp, const int* __restrict__ done) {
+__device__ __forceinline__ void restrict_multi_block(const MultiRestrictPlan& mp, int lb) {
   using C = typename Tr<T>::C;
-  if (*done) return;
   extern __shared__ __align__(16) unsigned char smem[];
   C* lds = reinterpret_cast<C*>(smem);
   const int P = mp.P, B = mp.B, nb = mp.nb;
-  // neighbouring blocks (shared halo loads) on one XCD
-  const int lb = int(xcd_order(blockIdx.x, gridDim.x));
   const int bx = lb % nb, by = (lb / nb) % nb, bz = D == 3 ? lb / (nb * nb) : 0;
   auto tside = [&](int j) { return j == 0 ? B : ((B + 1) << j) - 1; };
   {
@@ -2109,6 +2107,13 @@ __global__ __launch_bounds__(MR_NT) void k_restrict_multi(MultiRestrictPlan mp, 
     }
     if (j > 0) __syncthreads();
   }
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(MR_NT) void k_restrict_multi(MultiRestrictPlan mp, const int* __restrict__ done) {
+  if (*done) return;
+  // neighbouring blocks (shared halo loads) on one XCD
+  restrict_multi_block<T, D>(mp, int(xcd_order(blockIdx.x, gridDim.x)));
 }
 
 // ------------------------------------------------------------ pack / unpack
@@ -2342,8 +2347,7 @@ size_t restrict_multi_lds(int prec, int d, int P, int B) {
 }
 
 template <typename T>
-static hipError_t restrict_multi_t(int d, int P, int B, void* const* r, const Lay* l, const int* done,
-                                   hipStream_t s) {
+static MultiRestrictPlan multi_plan(int d, int P, int B, void* const* r, const Lay* l) {
   MultiRestrictPlan mp{};
   mp.P = P;
   mp.B = B;
@@ -2357,6 +2361,13 @@ static hipError_t restrict_multi_t(int d, int P, int B, void* const* r, const La
       off += d == 2 ? S * S : S * S * S;
     }
   }
+  return mp;
+}
+
+template <typename T>
+static hipError_t restrict_multi_t(int d, int P, int B, void* const* r, const Lay* l, const int* done,
+                                   hipStream_t s) {
+  const MultiRestrictPlan mp = multi_plan<T>(d, P, B, r, l);
   const size_t lds = restrict_multi_lds(sizeof(T) == 8 ? PREC_F64 : PREC_F32, d, P, B);
   const unsigned blocks = d == 2 ? unsigned(mp.nb * mp.nb) : unsigned(mp.nb * mp.nb * mp.nb);
   if (d == 2) {
@@ -3050,433 +3061,227 @@ hipError_t launch_level_write(int prec, int d, int n, int m, const void* xprev, 
 }
 
 // ------------------------------------------------------------ batched solver
-// Many independent 2D problems of uneven size advanced together.  All
-// problems move in lockstep global steps; at step k every unfinished
-// problem runs the next stage of its own sequence
-//     norm(f), ||f||, residual, norm      (cycle 0)
-//     restriction 0..M-1, per coarse level its iterations on the compact
-//     lattice and the hand-over to the next finer level (to the whole grid
-//     before level 0), level 0 in multi-iteration passes, residual, norm
-//                                                     (cycles 1, 2, ...)
-// One launch of k_batched_step runs one step for all problems: the step's
-// tiles (the same tiles, and the same tile code, as the one-problem
-// kernels) are spread round-robin over the launch's workgroups, and the
-// launch boundary separates steps.  The launches are recorded once in a
-// HIP graph (build_batch_graph) that the host replays.  The norm stage of
-// a cycle retires its problem once the relative residual reaches the
-// tolerance.
+// Many independent 2D problems of uneven size, each launch one stage of the
+// cycle for all of them: the stage's workgroups are listed once per handle
+// (problem and its own block), so a launch needs no map of who is active --
+// a workgroup whose problem is done returns -- and every stage is a kernel of
+// its own, with its own registers and LDS.  (One kernel that ran any stage of
+// any problem, in lockstep steps, took 59 steps a cycle and held every stage
+// at the occupancy of the largest: 47 ms for 512 problems of side 65..1025,
+// 2.5 TB/s in its large steps.)  The stages are the single-problem solver's,
+// block for block.
 
-// Tiles (workgroups) of a 2D stage: TW2 columns by four bands of len rows.
-__device__ __forceinline__ int tiles_of(int side, int len) { return t2_gx(side) * t2_gy(side, len); }
+template <typename T, bool NORM>
+__global__ __launch_bounds__(256) void k_batch_residual(const BatchResidual* __restrict__ res,
+                                                        const int2* __restrict__ tiles,
+                                                        const double* const* __restrict__ f,
+                                                        double* const* __restrict__ u,
+                                                        const DevState* __restrict__ st) {
+  const int2 t = tiles[xcd_order(blockIdx.x, gridDim.x)];
+  const BatchResidual& p = res[t.x];
+  if (!NORM && st[p.prob].done) return;
+  residual_restrict_wave<T, NORM, false>(nullptr, 0, u[p.prob], p.n, f[p.prob], p.n, static_cast<T*>(p.r), p.rp,
+                                         static_cast<T*>(p.rc), p.cp, p.n, p.len, p.inv_h2, p.partials, p.fpart, t.y);
+}
 
-struct StageInfo {
-  int kind;   // BK_* below
-  int level;  // restriction: fine level; iteration stages: level
-  int code;   // iteration stages: the stage's entry of the schedule table
-  int cycle;
-  int step;   // step of the sequence
+template <typename T>
+__global__ __launch_bounds__(256) void k_batch_restrict(const BatchRestrict* __restrict__ rs,
+                                                        const int2* __restrict__ tiles,
+                                                        const DevState* __restrict__ st) {
+  const int2 t = tiles[xcd_order(blockIdx.x, gridDim.x)];
+  const BatchRestrict& p = rs[t.x];
+  if (st[p.prob].done) return;
+  const int gx = t2_gx(p.nc);
+  tile_restrict_2d<T, T>(static_cast<const T*>(p.rf), p.fp, static_cast<T*>(p.rc), p.cp, p.nc, p.len, t.y % gx,
+                         t.y / gx);
+}
+
+struct BatchMulti {
+  MultiRestrictPlan mp;
+  int prob, blocks;
 };
-enum { BK_NONE = 0, BK_NORM = 1, BK_FNORM = 2, BK_RES = 3, BK_FIN = 4, BK_RESTRICT = 5, BK_STAGE = 6 };
-
-__device__ __forceinline__ StageInfo stage_of(const BatchProblem& p, const int* __restrict__ table, int k) {
-  StageInfo si{BK_NONE, 0, 0, 0, 0};
-  if (k == 0) { si.kind = BK_NORM; return si; }
-  if (k == 1) { si.kind = BK_FNORM; return si; }
-  if (k == 2) { si.kind = BK_RES; return si; }
-  if (k == 3) { si.kind = BK_FIN; si.cycle = 0; return si; }
-  const int L = p.top + p.sweeps + 2;
-  const int j = (k - 4) % L;
-  si.cycle = (k - 4) / L + 1;
-  if (j < p.top) { si.kind = BK_RESTRICT; si.level = j; return si; }
-  if (j < p.top + p.sweeps) {
-    si.kind = BK_STAGE;
-    si.code = table[p.sched_off + j - p.top];
-    si.level = bst_level(si.code);
-    return si;
-  }
-  si.kind = (j == p.top + p.sweeps) ? BK_RES : BK_FIN;
-  return si;
-}
-
-// Band length of a problem's multi-iteration level-0 stage: its tuned walk
-// length, at least 16 rows (shorter bands re-read too many halo rows).
-__host__ __device__ __forceinline__ int batch_tb_len(const BatchProblem& p) { return p.len[0] < 16 ? 16 : p.len[0]; }
-constexpr int BATCH_XF_ROWS = 8;  // rows of a hand-over tile
-
-__device__ __forceinline__ int level_side(const BatchProblem& p, int m) { return (p.n - 1) / (1 << m) + 1; }
-
-// Level m of a batched problem is its FP64 coarsest level: reduced-precision
-// storage and m the top (>= 1) level.
 template <typename T>
-__device__ __forceinline__ bool batch_top64(const BatchProblem& p, int m) {
-  return sizeof(T) != 8 && p.top >= 1 && m == p.top;
-}
-
-__device__ __forceinline__ int stage_tiles(const BatchProblem& p, const StageInfo& si) {
-  switch (si.kind) {
-    case BK_STAGE: {
-      const int c = si.code;
-      if (bst_kind(c) == BST_L0) return tb_blocks(p.n, bst_count(c), batch_tb_len(p));
-      if (bst_kind(c) == BST_LTB) return tb_blocks(level_side(p, si.level), bst_count(c), BATCH_LTB_LEN);
-      if (bst_kind(c) == BST_SWEEP) return tiles_of(level_side(p, si.level), p.len[si.level]);
-      const int nt = level_side(p, si.level - 1);  // hand-over target
-      return nt >= 3 ? ((nt - 2 + BX2 - 1) / BX2) * ((nt - 2 + BATCH_XF_ROWS - 1) / BATCH_XF_ROWS) : 0;
-    }
-    case BK_NORM:
-    case BK_RES: return tiles_of(p.n, p.len[0]);
-    case BK_RESTRICT: {
-      const int nc = (p.n - 1) / (2 << si.level) + 1;
-      return nc >= 3 ? tiles_of(nc, p.len[si.level + 1]) : 0;
-    }
-    case BK_FNORM:
-    case BK_FIN: return 1;
-    default: return 0;
-  }
+__global__ __launch_bounds__(MR_NT) void k_batch_restrict_multi(const BatchMulti* __restrict__ ms,
+                                                                const int2* __restrict__ tiles,
+                                                                const DevState* __restrict__ st) {
+  const int2 t = tiles[xcd_order(blockIdx.x, gridDim.x)];
+  if (st[ms[t.x].prob].done) return;
+  restrict_multi_block<T, 2>(ms[t.x].mp, t.y);
 }
 
 template <typename T>
-__device__ __forceinline__ void batch_tile(const BatchProblem& p, BatchState* __restrict__ bs,
-                                           int* __restrict__ done, const StageInfo& si, int t,
-                                           const BatchRun& run) {
+__device__ __forceinline__ L1Src<T> batch_l1(const BatchPass& p) {
+  return L1Src<T>{static_cast<const T*>(p.l1_prev), static_cast<const T*>(p.l1_cur), p.l1_pitch, 0, 0};
+}
+
+// Tiled iterations (a lattice level, or level 0 of small problems).
+template <typename T, bool LAT, int IT>
+__global__ __launch_bounds__(LT2_NT) void k_batch_tiled(const BatchPass* __restrict__ ps,
+                                                        const int2* __restrict__ tiles,
+                                                        const DevState* __restrict__ st, double* const* __restrict__ u,
+                                                        double w) {
   using C = typename Tr<T>::C;
-  const int n = p.n;
-  const int gx = t2_gx(n);
-  const int bx = t % gx, by = t / gx;
-  T* e0 = static_cast<T*>(p.e[0]);
-  T* e1 = static_cast<T*>(p.e[1]);
-  switch (si.kind) {
-    case BK_NORM:
-      tile_norm2_2d(p.f, n, n, p.len[0], p.partials, bx, by, t);
-      break;
-    case BK_RES: {
-      const double h = 1.0 / double(n - 1);
-      tile_residual_2d<T, false>(p.u, n, p.f, n, nullptr, 0, static_cast<T*>(p.r[0]), p.rp[0], n,
-                                 p.len[0], 1.0 / (h * h), p.partials, bx, by, t);
-      break;
-    }
-    case BK_FNORM:
-    case BK_FIN: {
-      const int count = tiles_of(n, p.len[0]);
-      double s = 0.0;
-      for (int i = threadIdx.x; i < count; i += 256) s += p.partials[i];
-      s = block_sum<256>(s);
-      if (threadIdx.x == 0) {
-        BatchState& b = bs[p.id];
-        if (si.kind == BK_FNORM) {
-          const double fn = sqrt(s);
-          b.fnorm = fn > 0.0 ? fn : 1.0;
-        } else {
-          const double rel = sqrt(s) / b.fnorm;
-          p.history[si.cycle] = rel;
-          b.cycles = si.cycle;
-          b.final_rel = rel;
-          int dn = 0;
-          if (!(rel <= 1.7976931348623157e308)) dn = 2;
-          else if (rel <= run.tol) dn = 1;
-          else if (si.cycle >= run.max_cycles) dn = 3;
-          if (dn) {
-            // other workgroups may still be mapping this step's tiles: the
-            // problem stays in this step's map and leaves it from the next
-            __hip_atomic_store(&b.retired, si.step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            done[p.id] = dn;
-          }
-        }
-      }
-      break;
-    }
-    case BK_RESTRICT: {
-      const int nc = (n - 1) / (2 << si.level) + 1;
-      const int gxc = t2_gx(nc);
-      if (batch_top64<T>(p, si.level + 1))
-        tile_restrict_2d<T, double>(static_cast<const T*>(p.r[si.level]), p.rp[si.level], p.r64, p.p64, nc,
-                                    p.len[si.level + 1], t % gxc, t / gxc);
-      else
-        tile_restrict_2d<T>(static_cast<const T*>(p.r[si.level]), p.rp[si.level],
-                            static_cast<T*>(p.r[si.level + 1]), p.rp[si.level + 1], nc,
-                            p.len[si.level + 1], t % gxc, t / gxc);
-      break;
-    }
-    case BK_STAGE: {
-      const int c = si.code, m = si.level, kind = bst_kind(c);
-      const bool zero = bst_zero(c);
-      if (kind == BST_SWEEP && batch_top64<T>(p, m)) {
-        // the coarsest level in FP64 (the formula of the small-lattice
-        // kernel), each iterate also stored rounded for the hand-over
-        const int nm = level_side(p, m), it = bst_index(c);
-        const double* xo = p.x64[(it - 1) & 1];
-        double* xn = p.x64[it & 1];
-        T* xr = static_cast<T*>(p.x[m][it & 1]);
-        const double hl = 1.0 / double(nm - 1), hl2 = hl * hl, w = run.omega / 4.0;
-        const int gxm = t2_gx(nm);
-        const int I = t2_x(t % gxm);
-        const int J0 = t2_y0(t / gxm, p.len[m]), J1 = min(nm - 1, J0 + p.len[m]);
-        if (I <= nm - 2)
-          for (int J = J0; J < J1; ++J) {
-            const int64_t o = int64_t(J) * p.p64 + I;
-            double v;
-            if (zero) {
-              v = relax_const<double>(0.0, (0.0 + 0.0) + (0.0 + 0.0), p.r64[o], w, hl2, 4.0);
-            } else {
-              v = relax_const<double>(xo[o], (xo[o - 1] + xo[o + 1]) + (xo[o - p.p64] + xo[o + p.p64]), p.r64[o],
-                                      w, hl2, 4.0);
-            }
-            xn[o] = v;
-            st(xr + int64_t(J) * p.rp[m] + I, typename Tr<T>::C(v));
-          }
-      } else if (kind == BST_SWEEP) {  // iteration bst_index of level m >= 1 on its compact lattice
-        const int nm = level_side(p, m), it = bst_index(c);
-        const T* xo = static_cast<const T*>(p.x[m][(it - 1) & 1]);
-        T* xn = static_cast<T*>(p.x[m][it & 1]);
-        const double hl = 1.0 / double(nm - 1);
-        const C hl2 = C(hl * hl), w = C(run.omega / 4.0);
-        const int gxm = t2_gx(nm);
-        const T* rm = static_cast<const T*>(p.r[m]);
-        if (zero)
-          tile_sweep_2d_l0<T, SW_ZERO_OLD, false>(xo, xn, p.rp[m], rm, p.rp[m], nullptr, 0, nullptr, 0, nm,
-                                                  p.len[m], w, hl2, t % gxm, t / gxm);
-        else
-          tile_sweep_2d_l0<T, 0, false>(xo, xn, p.rp[m], rm, p.rp[m], nullptr, 0, nullptr, 0, nm, p.len[m],
-                                        w, hl2, t % gxm, t / gxm);
-      } else if (kind == BST_LTB) {  // all iterations of level m in one pass on its compact lattice
-        const int nm = level_side(p, m), cnt = bst_count(c);
-        const T* xo = static_cast<const T*>(p.x[m][0]);
-        T* xn = static_cast<T*>(p.x[m][1]);
-        T* xq = static_cast<T*>(p.x3[m]);
-        const double hl = 1.0 / double(nm - 1);
-        const C hl2 = C(hl * hl), w = C(run.omega / 4.0);
-        const T* rm = static_cast<const T*>(p.r[m]);
-        const int wv = t * 4 + int(threadIdx.x >> 6);
-        switch (cnt) {
-          case 1: tb_body<T, false, false, true, 1>(xo, xn, xq, p.rp[m], rm, p.rp[m], nullptr, 0, nm, BATCH_LTB_LEN, w, hl2, wv); break;
-          case 2: tb_body<T, false, false, true, 2>(xo, xn, xq, p.rp[m], rm, p.rp[m], nullptr, 0, nm, BATCH_LTB_LEN, w, hl2, wv); break;
-          case 3: tb_body<T, false, false, true, 3>(xo, xn, xq, p.rp[m], rm, p.rp[m], nullptr, 0, nm, BATCH_LTB_LEN, w, hl2, wv); break;
-          default: tb_body<T, false, false, true, 4>(xo, xn, xq, p.rp[m], rm, p.rp[m], nullptr, 0, nm, BATCH_LTB_LEN, w, hl2, wv); break;
-        }
-      } else if (kind == BST_XFER) {  // level m's final state to the lattice of level m - 1
-        const int it = bst_count(c), mt = m - 1, nt = level_side(p, mt);
-        const bool ltb = bst_index(c) == 1;  // from one BST_LTB pass
-        const T* xc = static_cast<const T*>(ltb ? p.x[m][1] : p.x[m][it & 1]);
-        const T* xp = static_cast<const T*>(ltb ? p.x3[m] : p.x[m][(it - 1) & 1]);
-        T* dst = mt > 0 ? static_cast<T*>(p.x[mt][0]) : e0;
-        const int64_t dp = mt > 0 ? p.rp[mt] : p.ep;
-        const int gxt = (nt - 2 + BX2 - 1) / BX2;
-        const int I = 1 + (t % gxt) * BX2 + threadIdx.x;
-        const int J0 = 1 + (t / gxt) * BATCH_XF_ROWS, J1 = min(nt - 1, J0 + BATCH_XF_ROWS);
-        if (I <= nt - 2)
-          for (int J = J0; J < J1; ++J) {
-            if (zero)
-              transfer_node_2d<T, true>(xp, xc, p.rp[m], m, dst, dp, mt, I, J);
-            else
-              transfer_node_2d<T, false>(xp, xc, p.rp[m], m, dst, dp, mt, I, J);
-          }
-      } else {  // level-0 pass bst_index of bst_count iterations
-        const int q = bst_index(c), cnt = bst_count(c);
-        const T* eo = (q & 1) ? e1 : e0;
-        T* en = (q & 1) ? e0 : e1;
-        const double h = 1.0 / double(n - 1);
-        const C hl2 = C(h * h), w = C(run.omega / 4.0);
-        const T* rm = static_cast<const T*>(p.r[0]);
-        const int len = batch_tb_len(p), wv = t * 4 + int(threadIdx.x >> 6);
-        const bool accum = bst_accum(c);
-#define BATCH_TB(Z, A, IT) \
-  tb_body<T, Z, A, false, IT>(eo, en, nullptr, p.ep, rm, p.rp[0], p.u, n, n, len, w, hl2, wv)
-#define BATCH_TB_IT(Z, A)             \
-  switch (cnt) {                      \
-    case 1: BATCH_TB(Z, A, 1); break; \
-    case 2: BATCH_TB(Z, A, 2); break; \
-    case 3: BATCH_TB(Z, A, 3); break; \
-    default: BATCH_TB(Z, A, 4); break; \
-  }
-        if (zero) {
-          if (accum) { BATCH_TB_IT(true, true); } else { BATCH_TB_IT(true, false); }
-        } else {
-          if (accum) { BATCH_TB_IT(false, true); } else { BATCH_TB_IT(false, false); }
-        }
-#undef BATCH_TB_IT
-#undef BATCH_TB
-      }
-      break;
-    }
-    default:
-      break;
-  }
+  const int2 t = tiles[xcd_order(blockIdx.x, gridDim.x)];
+  const BatchPass& p = ps[t.x];
+  if (st[p.prob].done) return;
+  lattice_2d_tile<T, false, LAT, IT, false>(static_cast<const T*>(p.xo), static_cast<T*>(p.xn), static_cast<T*>(p.xp),
+                                            p.cp, static_cast<const T*>(p.r), p.rp, p.n, p.len, C(w), C(p.hl2),
+                                            batch_l1<T>(p), p.accum ? u[p.prob] : nullptr, p.n, nullptr, 0, t.y);
 }
 
-// One step of every active problem's sequence: k = base + j.  Every
-// workgroup builds the same tile map (prefix sums of the active problems'
-// tile counts for their stage at step k, looked up in each problem's row
-// of tiles per stage) and takes the tiles g = blockIdx.x,
-// blockIdx.x + gridDim.x, ...  A problem is active in step k unless it
-// retired in an earlier step; the step that retires it is written by its
-// finalize tile while other workgroups may be building this step's map,
-// and either value they read keeps it in this step, so all maps agree.
-template <typename T>
-__global__ __launch_bounds__(256) void k_batched_step(const BatchProblem* __restrict__ probs,
-                                                      BatchState* __restrict__ bs,
-                                                      int* __restrict__ done,
-                                                      const int* __restrict__ levels_of_sweep,
-                                                      const BatchRun* __restrict__ runp,
-                                                      BatchSync* __restrict__ sync, int j) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  if (sync->idle) return;
-  const BatchRun run = *runp;
-  const int k = sync->base + j;
-  if (k >= run.max_steps) return;
-  const int P = run.count;
-  int* pref = reinterpret_cast<int*>(smem);  // P + 1 prefix sums of tile counts
-  for (int i = threadIdx.x; i < P; i += 256) {
-    const BatchProblem& p = probs[i];
-    const int ret = __hip_atomic_load(&bs[i].retired, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    int tiles = 0;
-    if (ret >= k)  // the row of tiles per stage of a cycle (k_batch_tile_table)
-      tiles = k < 4 ? stage_tiles(p, stage_of(p, levels_of_sweep, k))
-                    : levels_of_sweep[p.tile_off + (k - 4) % (p.top + p.sweeps + 2)];
-    pref[i + 1] = tiles;
-  }
-  if (threadIdx.x == 0) pref[0] = 0;
-  __syncthreads();
-  // scan by chunks: each thread scans its own chunk, the chunk totals are
-  // scanned across the workgroup (within each wave by shuffles, then the
-  // four wave totals), and each thread adds its chunk's offset
-  const int chunk = (P + 255) / 256;
-  const int lo = threadIdx.x * chunk + 1, hi = min(P, lo + chunk - 1);
-  int acc = 0;
-  for (int i = lo; i <= hi; ++i) { acc += pref[i]; pref[i] = acc; }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int incl = acc;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int v = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += v;
-  }
-  __shared__ int wave_total[4];
-  if (lane == 63) wave_total[wave] = incl;
-  __syncthreads();
-  int off = incl - acc;
-  for (int q = 0; q < wave; ++q) off += wave_total[q];
-  for (int i = lo; i <= hi; ++i) pref[i] += off;
-  __syncthreads();
-  const int total = pref[P];
-  if (total == 0) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) sync->idle = 1;
-    return;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) sync->steps = k + 1;
-  for (int g = blockIdx.x; g < total; g += gridDim.x) {
-    // problem owning global tile g: last i with pref[i] <= g
-    int a = 0, b = P;
-    while (b - a > 1) {
-      const int mid = (a + b) >> 1;
-      if (pref[mid] <= g) a = mid; else b = mid;
-    }
-    const BatchProblem& p = probs[a];
-    StageInfo si = stage_of(p, levels_of_sweep, k);
-    si.step = k;
-    batch_tile<T>(p, bs, done, si, g - pref[a], run);
+// Walking iterations: KIND 0 a pass that stores x_it, 1 level 0's last (into
+// u), 2 a lattice's (x_{it-1} too).
+template <typename T, bool LAT, int KIND, int IT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_batch_walk(
+    const BatchPass* __restrict__ ps, const int2* __restrict__ tiles, const DevState* __restrict__ st,
+    double* const* __restrict__ u, double w) {
+  using C = typename Tr<T>::C;
+  const int2 t = tiles[xcd_order(blockIdx.x, gridDim.x)];
+  const BatchPass& p = ps[t.x];
+  if (st[p.prob].done) return;
+  const int wv = t.y * 4 + int(threadIdx.x >> 6);
+  tb_body<T, false, KIND == 1, KIND == 2, IT, LAT>(static_cast<const T*>(p.xo), static_cast<T*>(p.xn),
+                                                   static_cast<T*>(p.xp), p.cp, static_cast<const T*>(p.r), p.rp,
+                                                   KIND == 1 ? u[p.prob] : nullptr, p.n, p.n, p.len, C(w), C(p.hl2),
+                                                   wv, batch_l1<T>(p));
+}
+
+// Norm of the latest residual of every listed problem (one workgroup each),
+// as k_finalize; first: the state starts.
+__global__ __launch_bounds__(FIN_NT) void k_batch_finalize(const BatchResidual* __restrict__ res,
+                                                           DevState* __restrict__ sts, double* const* __restrict__ hist,
+                                                           int cycle, int first, double tol) {
+  const BatchResidual& p = res[blockIdx.x];
+  DevState v;
+  if (first) {
+    const double fn = sqrt(fin_sum(p.fpart, p.count));
+    v.done = 0;
+    v.cycles = -1;
+    v.stop_on_tol = 1;
+    v.pad = 0;
+    v.fnorm = fn > 0.0 ? fn : 1.0;
+    v.tol = tol;
     __syncthreads();
+  } else {
+    v = sts[p.prob];
+    if (v.done) return;
+  }
+  const double s = fin_sum(p.partials, p.count);
+  if (threadIdx.x == 0) {
+    hist[p.prob][cycle] = fin_update(v, s, cycle);
+    sts[p.prob] = v;
   }
 }
 
-__global__ __launch_bounds__(256) void k_batch_tile_table(const BatchProblem* __restrict__ probs, int* table) {
-  const BatchProblem& p = probs[blockIdx.x];
-  const int L = p.top + p.sweeps + 2;
-  for (int j = threadIdx.x; j < L; j += 256) table[p.tile_off + j] = stage_tiles(p, stage_of(p, table, 4 + j));
-}
-
-__global__ __launch_bounds__(64) void k_batch_advance(BatchSync* sync, int steps) {
-  if (threadIdx.x == 0) sync->base += steps;
-}
-
-__global__ __launch_bounds__(256) void k_batch_init(BatchState* bs, int* done, int P, BatchSync* sync) {
+// What the host reads after a batch of cycles (out: pinned host memory).
+__global__ __launch_bounds__(256) void k_batch_publish(int P, const DevState* __restrict__ sts,
+                                                       const double* const* __restrict__ hist, BatchState* out) {
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < P) {
-    bs[i].cycles = -1;
-    bs[i].retired = 0x7fffffff;
-    bs[i].fnorm = 1.0;
-    bs[i].final_rel = 0.0;
-    done[i] = 0;
-  }
-  if (i == 0) {
-    sync->base = 0;
-    sync->steps = 0;
-    sync->idle = 0;
-  }
+  if (i >= P) return;
+  const DevState v = sts[i];
+  const int c = max(v.cycles, 0);
+  out[i] = BatchState{v.done, v.cycles, hist[i][c], c > 0 ? hist[i][c - 1] : 0.0};
 }
 
 int default_walk_len(int d, int n) { return walk_len(d, n); }
+int batch_residual_waves(int n, int len) { return rr_waves(n, len); }
+int batch_tiled_side(int n) { return (n - 2 + LT2_B - 1) / LT2_B; }
+int batch_restrict_tiles(int nc, int len) { return t2_gx(nc) * t2_gy(nc, len); }
+size_t batch_multi_bytes() { return sizeof(BatchMulti); }
 
-int batch_tiles(int side, int len) { return t2_gx(side) * t2_gy(side, len); }
-
-hipError_t batch_occupancy(int prec, int P, int* blocks_per_cu, size_t* lds) {
-  *lds = size_t(P + 1) * sizeof(int);
+int batch_multi_fill(int prec, void* dst, int prob, int P, int B, void* const* r, const Lay* l) {
+  BatchMulti m{};
   switch (prec) {
-    case PREC_F64: return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_batched_step<double>, 256, *lds);
-    case PREC_F32: return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_batched_step<float>, 256, *lds);
-    default: return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k_batched_step<bf16>, 256, *lds);
+    case PREC_F64: m.mp = multi_plan<double>(2, P, B, r, l); break;
+    case PREC_F32: m.mp = multi_plan<float>(2, P, B, r, l); break;
+    default: m.mp = multi_plan<bf16>(2, P, B, r, l); break;
   }
+  m.prob = prob;
+  m.blocks = m.mp.nb * m.mp.nb;
+  std::memcpy(dst, &m, sizeof m);
+  return m.blocks;
 }
 
-hipError_t launch_batch_tile_table(int P, const BatchProblem* probs, int* table, hipStream_t s) {
-  hipLaunchKernelGGL(k_batch_tile_table, dim3(P), dim3(256), 0, s, probs, table);
-  return hipGetLastError();
-}
-
-// Reset of a batched solve's per-problem state and step counter (an
-// ordinary launch on the caller's stream before the first replay).
-hipError_t launch_batch_init(int P, BatchState* bs, int* done, BatchSync* sync, hipStream_t s) {
-  hipLaunchKernelGGL(k_batch_init, dim3((P + 255) / 256), dim3(256), 0, s, bs, done, P, sync);
-  return hipGetLastError();
-}
-
-// The graph one replay runs: BATCH_STEPS_PER_REPLAY step launches in a
-// chain (each `grid` workgroups of 256 lanes; step j of the replay runs
-// global step base + j), then the one-lane node that advances base.
-hipError_t build_batch_graph(int prec, int P, int grid, const BatchProblem* probs, BatchState* bs,
-                             int* done, const int* levels_of_sweep, const BatchRun* run,
-                             BatchSync* sync, hipGraph_t* out) {
-  *out = nullptr;
-  hipGraph_t g = nullptr;
-  hipError_t e = hipGraphCreate(&g, 0);
-  if (e != hipSuccess) return e;
-  void* fn = nullptr;
+hipError_t launch_batch_residual(int prec, const BatchResidual* res, const int2* tiles, int count, bool norm,
+                                 const double* const* f, double* const* u, const DevState* st, hipStream_t s) {
+#define BR_CASE(T)                                                                                            \
+  if (norm) HOMG_LAUNCH((k_batch_residual<T, true>), dim3(count), dim3(256), s, res, tiles, f, u, st);        \
+  HOMG_LAUNCH((k_batch_residual<T, false>), dim3(count), dim3(256), s, res, tiles, f, u, st)
   switch (prec) {
-    case PREC_F64: fn = reinterpret_cast<void*>(k_batched_step<double>); break;
-    case PREC_F32: fn = reinterpret_cast<void*>(k_batched_step<float>); break;
-    default: fn = reinterpret_cast<void*>(k_batched_step<bf16>); break;
+    case PREC_F64: BR_CASE(double);
+    case PREC_F32: BR_CASE(float);
+    default: BR_CASE(bf16);
   }
-  int js[BATCH_STEPS_PER_REPLAY];
-  hipGraphNode_t prev = nullptr;
-  for (int j = 0; j < BATCH_STEPS_PER_REPLAY && e == hipSuccess; ++j) {
-    js[j] = j;
-    void* args[] = {&probs, &bs, &done, &levels_of_sweep, &run, &sync, &js[j]};
-    hipKernelNodeParams kp{};
-    kp.func = fn;
-    kp.gridDim = dim3(grid);
-    kp.blockDim = dim3(256);
-    kp.sharedMemBytes = unsigned(size_t(P + 1) * sizeof(int));
-    kp.kernelParams = args;
-    hipGraphNode_t node = nullptr;
-    e = hipGraphAddKernelNode(&node, g, prev ? &prev : nullptr, prev ? 1 : 0, &kp);
-    prev = node;
+#undef BR_CASE
+}
+
+hipError_t launch_batch_restrict(int prec, const BatchRestrict* rs, const int2* tiles, int count, const DevState* st,
+                                 hipStream_t s) {
+  switch (prec) {
+    case PREC_F64: HOMG_LAUNCH((k_batch_restrict<double>), dim3(count), dim3(256), s, rs, tiles, st);
+    case PREC_F32: HOMG_LAUNCH((k_batch_restrict<float>), dim3(count), dim3(256), s, rs, tiles, st);
+    default: HOMG_LAUNCH((k_batch_restrict<bf16>), dim3(count), dim3(256), s, rs, tiles, st);
   }
-  if (e == hipSuccess) {
-    int steps = BATCH_STEPS_PER_REPLAY;
-    void* args[] = {&sync, &steps};
-    hipKernelNodeParams kp{};
-    kp.func = reinterpret_cast<void*>(k_batch_advance);
-    kp.gridDim = dim3(1);
-    kp.blockDim = dim3(64);
-    kp.sharedMemBytes = 0;
-    kp.kernelParams = args;
-    hipGraphNode_t node = nullptr;
-    e = hipGraphAddKernelNode(&node, g, &prev, 1, &kp);
+}
+
+hipError_t launch_batch_restrict_multi(int prec, const void* ms, const int2* tiles, int count, size_t lds,
+                                       const DevState* st, hipStream_t s) {
+  const BatchMulti* m = static_cast<const BatchMulti*>(ms);
+#define BM_CASE(T)                                                                                           \
+  do {                                                                                                       \
+    hipError_t e_ = allow_lds(k_batch_restrict_multi<T>, lds);                                               \
+    if (e_ != hipSuccess) return e_;                                                                         \
+    HOMG_LAUNCH_SMEM((k_batch_restrict_multi<T>), dim3(count), dim3(MR_NT), lds, s, m, tiles, st);           \
+  } while (0)
+  switch (prec) {
+    case PREC_F64: BM_CASE(double); break;
+    case PREC_F32: BM_CASE(float); break;
+    default: BM_CASE(bf16); break;
   }
-  if (e != hipSuccess) {
-    (void)hipGraphDestroy(g);
-    return e;
+#undef BM_CASE
+}
+
+template <typename T, bool LAT>
+static hipError_t batch_pass_t(const BatchPass* ps, const int2* tiles, int count, int it, int kind, double w,
+                               const DevState* st, double* const* u, hipStream_t s) {
+#define BP_IT(IT)                                                                                           \
+  do {                                                                                                      \
+    if (kind < 0) HOMG_LAUNCH((k_batch_tiled<T, LAT, IT>), dim3(count), dim3(LT2_NT), s, ps, tiles, st, u, w); \
+    if (kind == 1) HOMG_LAUNCH((k_batch_walk<T, LAT, 1, IT>), dim3(count), dim3(256), s, ps, tiles, st, u, w); \
+    if (kind == 2) HOMG_LAUNCH((k_batch_walk<T, LAT, 2, IT>), dim3(count), dim3(256), s, ps, tiles, st, u, w); \
+    HOMG_LAUNCH((k_batch_walk<T, LAT, 0, IT>), dim3(count), dim3(256), s, ps, tiles, st, u, w);             \
+  } while (0)
+  switch (it) {
+    case 1: BP_IT(1); break;
+    case 2: BP_IT(2); break;
+    case 3: BP_IT(3); break;
+    default: BP_IT(4); break;
   }
-  *out = g;
-  return hipSuccess;
+#undef BP_IT
+}
+
+hipError_t launch_batch_pass(int prec, const BatchPass* ps, const int2* tiles, int count, int it, bool lat, int kind,
+                             double omega, const DevState* st, double* const* u, hipStream_t s) {
+  if (it < 1 || it > TB_MAX_IT || it > LT_MAX_IT) return hipErrorInvalidValue;
+  const double w = omega / 4.0;
+#define BP_CASE(T)                                                            \
+  return lat ? batch_pass_t<T, true>(ps, tiles, count, it, kind, w, st, u, s) \
+             : batch_pass_t<T, false>(ps, tiles, count, it, kind, w, st, u, s)
+  switch (prec) {
+    case PREC_F64: BP_CASE(double);
+    case PREC_F32: BP_CASE(float);
+    default: BP_CASE(bf16);
+  }
+#undef BP_CASE
+}
+
+hipError_t launch_batch_finalize(const BatchResidual* res, int count, DevState* st, double* const* hist, int cycle,
+                                 bool first, double tol, hipStream_t s) {
+  HOMG_LAUNCH(k_batch_finalize, dim3(count), dim3(FIN_NT), s, res, st, hist, cycle, first ? 1 : 0, tol);
+}
+
+hipError_t launch_batch_publish(int P, const DevState* st, const double* const* hist, BatchState* out, hipStream_t s) {
+  HOMG_LAUNCH(k_batch_publish, dim3((P + 255) / 256), dim3(256), s, P, st, hist, out);
 }
 
 }  // namespace homg

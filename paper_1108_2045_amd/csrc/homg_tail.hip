@@ -57,15 +57,23 @@ struct TailArgs {
   T* sprev;               // its final x_{it-1} and x_it
   T* scur;
   int64_t rp, rpl, sp, spl;
-  const double* partials; // the residual sums of cycle `cycle`, if not reduced yet (cycle >= 0)
-  int count, cycle;
+  const double* partials; // the previous residual's sums
+  int count;
   // whole solves
-  const double* f;        // dense, side nms
-  double* u;
-  double inv_h2, tol;
-  int c0, c1, stop, rr;   // cycles c0 .. c1; rr: order of the norms' sums (see below)
-  DevState* hst;          // pinned mirrors
+  int rr;                 // order of the norms' sums (see below)
+  int prob, pad;
+  double inv_h2;
+  DevState* hst;          // pinned mirrors, or null
   double* hhist;
+};
+
+// What changes from launch to launch.
+struct TailRun {
+  int cycle;        // coarse tail: the cycle whose norm is not reduced yet, or -1
+  const double* f;  // whole solves: dense, side nms
+  double* u;
+  double tol;
+  int c0, c1, stop; // cycles c0 .. c1
 };
 
 template <int D>
@@ -205,7 +213,7 @@ __device__ __forceinline__ C tail_relax(const C* src, int i, int nk, int pl, C c
 // side restricted in FP64 from the stored values of the level below, its
 // iterates FP64 -- and only its final pair rounded to the storage type.
 template <typename T, int D, bool VAR, bool TOP64, bool SOLVE>
-__global__ __launch_bounds__(TAIL_NT) void k_coarse_tail(TailArgs<T> q) {
+__device__ __forceinline__ void tail_block(const TailArgs<T>& q, const TailRun& run) {
   using C = typename Tr<T>::C;
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_done;
@@ -224,7 +232,7 @@ __global__ __launch_bounds__(TAIL_NT) void k_coarse_tail(TailArgs<T> q) {
 
   DevState st = *q.st;
   if (!SOLVE && st.done) return;
-  if (SOLVE && q.c0 > 0 && st.done) return;
+  if (SOLVE && run.c0 > 0 && st.done) return;
 
   // loads first: the level's right-hand side, or f and u with the boundary
   // values next to the lane's nodes
@@ -240,12 +248,12 @@ __global__ __launch_bounds__(TAIL_NT) void k_coarse_tail(TailArgs<T> q) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int64_t row = pl + int64_t(min(tn.y0 + k, n - 1)) * n;
-      uv[k] = q.u[row + xc];
-      fv[k] = q.f[row + xc];
-      ue[k] = q.u[row];  // x = 0, used by the first lane of a row
-      uzlo[k] = D == 3 ? q.u[int64_t(min(tn.y0 + k, n - 1)) * n + xc] : 0.0;  // z = 0
+      uv[k] = run.u[row + xc];
+      fv[k] = run.f[row + xc];
+      ue[k] = run.u[row];  // x = 0, used by the first lane of a row
+      uzlo[k] = D == 3 ? run.u[int64_t(min(tn.y0 + k, n - 1)) * n + xc] : 0.0;  // z = 0
     }
-    ulo = q.u[pl + xc];  // y = 0
+    ulo = run.u[pl + xc];  // y = 0
   }
   if (VAR)
     for (int i = threadIdx.x; i < n * n; i += TAIL_NT) A0[i] = q.a[int64_t(i / n) * q.ap + i % n];
@@ -256,10 +264,10 @@ __global__ __launch_bounds__(TAIL_NT) void k_coarse_tail(TailArgs<T> q) {
   }
   if (TOP64)
     for (int i = threadIdx.x; i < 3 * tail_count<D>(side(ktop)); i += TAIL_NT) top64[i] = 0.0;
-  if (!SOLVE && q.cycle >= 0) {
+  if (!SOLVE && run.cycle >= 0) {
     const double s = fin_sum(q.partials, q.count);
     if (threadIdx.x == 0) {
-      q.hist[q.cycle] = fin_update(st, s, q.cycle);
+      q.hist[run.cycle] = fin_update(st, s, run.cycle);
       *q.st = st;
       s_done = st.done;
     }
@@ -287,7 +295,7 @@ __global__ __launch_bounds__(TAIL_NT) void k_coarse_tail(TailArgs<T> q) {
     for (int k = 0; k < 4; ++k) ws[k] = w / ((C(fx[k]) + C(x_next<D>(1.0, fx[k]))) + (C(fy[k]) + C(fy[k + 1])));
   }
 
-  for (int cyc = SOLVE ? q.c0 : 0;; ++cyc) {
+  for (int cyc = SOLVE ? run.c0 : 0;; ++cyc) {
     if constexpr (SOLVE) {
       // ---- residual and its norm
       const TailExchange<D, double> ex{reinterpret_cast<double*>(smem + q.x_off)};
@@ -379,20 +387,20 @@ __global__ __launch_bounds__(TAIL_NT) void k_coarse_tail(TailArgs<T> q) {
           const double fn = sqrt(total(sums + 64));
           st.done = 0;
           st.cycles = -1;
-          st.stop_on_tol = q.stop;
+          st.stop_on_tol = run.stop;
           st.pad = 0;
           st.fnorm = fn > 0.0 ? fn : 1.0;
-          st.tol = q.tol;
+          st.tol = run.tol;
         }
         if (tn.lane == 0) {
           const double rel = fin_update(st, s, cyc);
           q.hist[cyc] = rel;
-          q.hhist[cyc] = rel;
+          if (q.hhist) q.hhist[cyc] = rel;
           s_done = st.done;
         }
       }
       __syncthreads();
-      if (s_done || cyc >= q.c1) break;
+      if (s_done || cyc >= run.c1) break;
     } else {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -618,12 +626,30 @@ __global__ __launch_bounds__(TAIL_NT) void k_coarse_tail(TailArgs<T> q) {
     const int64_t pl = int64_t(tn.z) * n * n * (D == 3);
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (tn.in(k)) q.u[pl + int64_t(tn.y0 + k) * n + tn.x] = uv[k];
+      if (tn.in(k)) run.u[pl + int64_t(tn.y0 + k) * n + tn.x] = uv[k];
     if (threadIdx.x == 0) {
       *q.st = st;
-      *q.hst = st;
+      if (q.hst) *q.hst = st;
     }
   }
+}
+
+template <typename T, int D, bool VAR, bool TOP64, bool SOLVE>
+__global__ __launch_bounds__(TAIL_NT) void k_coarse_tail(TailArgs<T> q, TailRun run) {
+  tail_block<T, D, VAR, TOP64, SOLVE>(q, run);
+}
+
+// One workgroup per problem of a batch.
+template <typename T, bool TOP64>
+__global__ __launch_bounds__(TAIL_NT) void k_batch_tail(const TailArgs<T>* __restrict__ args, int cycle) {
+  tail_block<T, 2, false, TOP64, false>(args[blockIdx.x], TailRun{cycle, nullptr, nullptr, 0.0, 0, 0, 0});
+}
+template <typename T, bool TOP64>
+__global__ __launch_bounds__(TAIL_NT) void k_batch_small(const TailArgs<T>* __restrict__ args,
+                                                         const double* const* __restrict__ f,
+                                                         double* const* __restrict__ u, double tol, int c0, int c1) {
+  const TailArgs<T>& q = args[blockIdx.x];
+  tail_block<T, 2, false, TOP64, true>(q, TailRun{-1, f[q.prob], u[q.prob], tol, c0, c1, 1});
 }
 
 // LDS layout: byte offsets of the areas behind the C arrays.
@@ -661,20 +687,21 @@ TailLds tail_lds(int prec, int d, int nms, int nlev, bool top64, bool var, bool 
 }
 
 template <typename T, int D, bool VAR, bool TOP64, bool SOLVE>
-hipError_t launch_t(const TailArgs<T>& a, size_t lds, hipStream_t s) {
+hipError_t launch_t(const TailArgs<T>& a, const TailRun& run, size_t lds, hipStream_t s) {
   hipError_t e = allow_lds(k_coarse_tail<T, D, VAR, TOP64, SOLVE>, lds);
   if (e != hipSuccess) return e;
-  HOMG_LAUNCH_SMEM((k_coarse_tail<T, D, VAR, TOP64, SOLVE>), dim3(1), dim3(TAIL_NT), lds, s, a);
+  HOMG_LAUNCH_SMEM((k_coarse_tail<T, D, VAR, TOP64, SOLVE>), dim3(1), dim3(TAIL_NT), lds, s, a, run);
 }
 
 template <typename T, bool SOLVE>
-hipError_t launch_d(int d, bool top64, bool var, const TailArgs<T>& a, size_t lds, hipStream_t s) {
+hipError_t launch_d(int d, bool top64, bool var, const TailArgs<T>& a, const TailRun& run, size_t lds, hipStream_t s) {
   constexpr bool RED = sizeof(T) != 8;  // reduced precision: the FP64 coarsest level exists
+  const bool t64 = RED && top64;
   if (d == 3)
-    return RED && top64 ? launch_t<T, 3, false, RED, SOLVE>(a, lds, s) : launch_t<T, 3, false, false, SOLVE>(a, lds, s);
+    return t64 ? launch_t<T, 3, false, RED, SOLVE>(a, run, lds, s) : launch_t<T, 3, false, false, SOLVE>(a, run, lds, s);
   if (var)
-    return RED && top64 ? launch_t<T, 2, true, RED, SOLVE>(a, lds, s) : launch_t<T, 2, true, false, SOLVE>(a, lds, s);
-  return RED && top64 ? launch_t<T, 2, false, RED, SOLVE>(a, lds, s) : launch_t<T, 2, false, false, SOLVE>(a, lds, s);
+    return t64 ? launch_t<T, 2, true, RED, SOLVE>(a, run, lds, s) : launch_t<T, 2, true, false, SOLVE>(a, run, lds, s);
+  return t64 ? launch_t<T, 2, false, RED, SOLVE>(a, run, lds, s) : launch_t<T, 2, false, false, SOLVE>(a, run, lds, s);
 }
 
 template <typename T>
@@ -727,8 +754,8 @@ static hipError_t tail_t(int prec, int d, int nms, int nlev, const int* its, dou
   q.spl = sl.plane;
   q.partials = partials;
   q.count = count;
-  q.cycle = partials ? cycle : -1;
-  return launch_d<T, false>(d, top64, a != nullptr, q, L.bytes, s);
+  const TailRun run{partials ? cycle : -1, nullptr, nullptr, 0.0, 0, 0, 0};
+  return launch_d<T, false>(d, top64, a != nullptr, q, run, L.bytes, s);
 }
 
 hipError_t launch_coarse_tail(int prec, int d, int nms, int nlev, const int* its, double omega, const double* a,
@@ -757,17 +784,11 @@ static hipError_t small_solve_t(int prec, int d, int n, int nlev, const int* its
   const TailLds L = tail_lds(prec, d, n, nlev, top64, a != nullptr, true);
   TailArgs<T> q = make_args<T>(L, d, n, nlev, its, omega, a, al, st, hist);
   const double h = 1.0 / double(n - 1);
-  q.f = f;
-  q.u = u;
   q.inv_h2 = 1.0 / (h * h);
-  q.tol = tol;
-  q.c0 = c0;
-  q.c1 = c1;
-  q.stop = stop;
   q.rr = rr;
   q.hst = hst;
   q.hhist = hhist;
-  return launch_d<T, true>(d, top64, a != nullptr, q, L.bytes, s);
+  return launch_d<T, true>(d, top64, a != nullptr, q, TailRun{-1, f, u, tol, c0, c1, stop}, L.bytes, s);
 }
 
 hipError_t launch_small_solve(int prec, int d, int n, int nlev, const int* its, double omega, const double* a,
@@ -785,6 +806,102 @@ hipError_t launch_small_solve(int prec, int d, int n, int nlev, const int* its, 
     default: SMALL_CASE(bf16);
   }
 #undef SMALL_CASE
+}
+
+size_t batch_tail_bytes(int prec) {
+  return prec == PREC_F64 ? sizeof(TailArgs<double>) : (prec == PREC_F32 ? sizeof(TailArgs<float>) : sizeof(TailArgs<bf16>));
+}
+
+template <typename T>
+static void batch_tail_t(int prec, void* dst, int n, int nlev, const int* its, double omega, const void* r, int64_t rp,
+                         void* sprev, void* scur, int64_t sp, bool top64, DevState* st, double* hist,
+                         const double* partials, int count) {
+  TailArgs<T> q = make_args<T>(tail_lds(prec, 2, n, nlev, top64, false, false), 2, n, nlev, its, omega, nullptr, Lay(),
+                               st, hist);
+  q.r = static_cast<const T*>(r);
+  q.rp = rp;
+  q.sprev = static_cast<T*>(sprev);
+  q.scur = static_cast<T*>(scur);
+  q.sp = sp;
+  q.partials = partials;
+  q.count = count;
+  *static_cast<TailArgs<T>*>(dst) = q;
+}
+
+void batch_tail_fill(int prec, void* dst, int n, int nlev, const int* its, double omega, const void* r, int64_t rp,
+                     void* sprev, void* scur, int64_t sp, bool top64, DevState* st, double* hist,
+                     const double* partials, int count) {
+#define TAIL_FILL(T) \
+  batch_tail_t<T>(prec, dst, n, nlev, its, omega, r, rp, sprev, scur, sp, top64, st, hist, partials, count)
+  switch (prec) {
+    case PREC_F64: TAIL_FILL(double); break;
+    case PREC_F32: TAIL_FILL(float); break;
+    default: TAIL_FILL(bf16); break;
+  }
+#undef TAIL_FILL
+}
+
+template <typename T>
+static void batch_small_t(int prec, void* dst, int n, int nlev, const int* its, double omega, bool top64, bool rr,
+                          int prob, DevState* st, double* hist) {
+  TailArgs<T> q = make_args<T>(tail_lds(prec, 2, n, nlev, top64, false, true), 2, n, nlev, its, omega, nullptr, Lay(),
+                               st, hist);
+  const double h = 1.0 / double(n - 1);
+  q.inv_h2 = 1.0 / (h * h);
+  q.rr = rr;
+  q.prob = prob;
+  *static_cast<TailArgs<T>*>(dst) = q;
+}
+
+void batch_small_fill(int prec, void* dst, int n, int nlev, const int* its, double omega, bool top64, bool rr, int prob,
+                      DevState* st, double* hist) {
+  switch (prec) {
+    case PREC_F64: batch_small_t<double>(prec, dst, n, nlev, its, omega, top64, rr, prob, st, hist); break;
+    case PREC_F32: batch_small_t<float>(prec, dst, n, nlev, its, omega, top64, rr, prob, st, hist); break;
+    default: batch_small_t<bf16>(prec, dst, n, nlev, its, omega, top64, rr, prob, st, hist); break;
+  }
+}
+
+template <typename T, bool TOP64>
+static hipError_t batch_tails_t(const void* args, int count, size_t lds, int cycle, hipStream_t s) {
+  hipError_t e = allow_lds(k_batch_tail<T, TOP64>, lds);
+  if (e != hipSuccess) return e;
+  HOMG_LAUNCH_SMEM((k_batch_tail<T, TOP64>), dim3(count), dim3(TAIL_NT), lds, s, static_cast<const TailArgs<T>*>(args),
+                   cycle);
+}
+
+hipError_t launch_batch_tails(int prec, bool top64, const void* args, int count, size_t lds, int cycle, hipStream_t s) {
+  switch (prec) {
+    case PREC_F64: return batch_tails_t<double, false>(args, count, lds, cycle, s);
+    case PREC_F32:
+      return top64 ? batch_tails_t<float, true>(args, count, lds, cycle, s)
+                   : batch_tails_t<float, false>(args, count, lds, cycle, s);
+    default:
+      return top64 ? batch_tails_t<bf16, true>(args, count, lds, cycle, s)
+                   : batch_tails_t<bf16, false>(args, count, lds, cycle, s);
+  }
+}
+
+template <typename T, bool TOP64>
+static hipError_t batch_small_launch(const void* args, int count, size_t lds, const double* const* f, double* const* u,
+                                     double tol, int c0, int c1, hipStream_t s) {
+  hipError_t e = allow_lds(k_batch_small<T, TOP64>, lds);
+  if (e != hipSuccess) return e;
+  HOMG_LAUNCH_SMEM((k_batch_small<T, TOP64>), dim3(count), dim3(TAIL_NT), lds, s, static_cast<const TailArgs<T>*>(args),
+                   f, u, tol, c0, c1);
+}
+
+hipError_t launch_batch_small(int prec, bool top64, const void* args, int count, size_t lds, const double* const* f,
+                              double* const* u, double tol, int c0, int c1, hipStream_t s) {
+  switch (prec) {
+    case PREC_F64: return batch_small_launch<double, false>(args, count, lds, f, u, tol, c0, c1, s);
+    case PREC_F32:
+      return top64 ? batch_small_launch<float, true>(args, count, lds, f, u, tol, c0, c1, s)
+                   : batch_small_launch<float, false>(args, count, lds, f, u, tol, c0, c1, s);
+    default:
+      return top64 ? batch_small_launch<bf16, true>(args, count, lds, f, u, tol, c0, c1, s)
+                   : batch_small_launch<bf16, false>(args, count, lds, f, u, tol, c0, c1, s);
+  }
 }
 
 }  // namespace homg
