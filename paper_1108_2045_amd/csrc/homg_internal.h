@@ -404,9 +404,10 @@ int train_bwd_rows(int nm);
 hipError_t launch_train_bwd(int nm, float hl2, const float* x, const float* r, const float* a,
                             const float* z, const double* e0, const float* w, float* part,
                             int64_t pstride, hipStream_t s);
-// out[j] = sum of part[j][0..rows) (FP64, fixed order), j = 0..NW.
+// out[j] = sum of part[j][0..rows) (FP64, fixed order), j = 0..NW; given
+// energy, the last of them there too.
 hipError_t launch_train_reduce(const float* part, int64_t pstride, int rows, double* out,
-                               hipStream_t s);
+                               hipStream_t s, double* energy = nullptr);
 hipError_t launch_train_adam(const double* sums, int batch, const double* e0s, const int* idx,
                              float* theta, float* m1, float* m2, uint16_t* wbf, float* w32,
                              int step, double lr, double beta1, double beta2, double eps,

@@ -82,8 +82,10 @@ template <typename C>
 __device__ __forceinline__ C hmean(C a, C b) { return C(2) * a * b / (a + b); }
 
 // Shared memory of one tile of the training kernels: features as float4
-// per node (channel 3 unused), hidden layer with padded rows.
+// per node (channel 3 unused), hidden layer with padded rows, Z as the
+// inference's.
 constexpr int FPL = R2 * R2;     // one feature plane
+constexpr int TZS = 12;          // Z row stride in floats (taps 0..8, 16-byte rows)
 template <typename C>
 struct TileLds {
   C x[R3 * R3];
@@ -91,13 +93,42 @@ struct TileLds {
   float4 f[FPL];
   float h[NT * HP];
 };
+struct FwdLds {
+  float x[R3 * R3];
+  float a[R3 * R3];
+  float4 f[FPL];
+  float z[NT * TZS];
+};
+
+// The three features of the node at c3 of the staged halo-3 region.
+template <bool VAR, typename C>
+__device__ __forceinline__ float4 node_features(const C* x, const C* a, int c3, C rv, C hl2) {
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  const C xc = x[c3];
+  const C xw = x[c3 - 1], xe = x[c3 + 1], xs = x[c3 - R3], xn = x[c3 + R3];
+  if constexpr (!VAR) {
+    const C flux = (((xc - xw) + (xc - xe)) + (xc - xs)) + (xc - xn);
+    v.x = float((hl2 * rv - flux) / C(4));
+  } else {
+    const C ac = a[c3];
+    const C aw = hmean(ac, a[c3 - 1]), ae = hmean(ac, a[c3 + 1]);
+    const C as = hmean(ac, a[c3 - R3]), an = hmean(ac, a[c3 + R3]);
+    const C sa = ((aw + ae) + as) + an;
+    const C flux = ((aw * (xc - xw) + ae * (xc - xe)) + as * (xc - xs)) + an * (xc - xn);
+    const C rho = (hl2 * rv - flux) / sa;
+    v.x = float(rho);
+    v.y = float(rho * (ae - aw) / (ae + aw));
+    v.z = float(rho * (an - as) / (an + as));
+  }
+  return v;
+}
 
 // Stage x and a on the halo-3 region of the tile whose owned block starts
 // at (J0, I0), then the features on the halo-2 region.  Nodes outside the
 // lattice read x = 0, a = 1; features are 0 off the interior.  XT/RT/AT:
 // storage of x, r_m, a (AT = void: constant coefficient).
-template <typename C, typename XT, typename RT, typename AT>
-__device__ __forceinline__ void stage_features(TileLds<C>& L, const XT* __restrict__ x, int64_t xp,
+template <typename C, typename XT, typename RT, typename AT, typename LDS>
+__device__ __forceinline__ void stage_features(LDS& L, const XT* __restrict__ x, int64_t xp,
                                                const RT* __restrict__ r, int64_t rp,
                                                const AT* __restrict__ a, int64_t ap, int nm,
                                                int J0, int I0, C hl2) {
@@ -110,89 +141,53 @@ __device__ __forceinline__ void stage_features(TileLds<C>& L, const XT* __restri
   }
   __syncthreads();
   for (int q = t; q < R2 * R2; q += NT) {
-    const int jj = q / R2, ii = q % R2;
-    const int J = J0 - 2 + jj, I = I0 - 2 + ii;
+    const int J = J0 - 2 + q / R2, I = I0 - 2 + q % R2;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (J >= 1 && J <= nm - 2 && I >= 1 && I <= nm - 2) {
-      const int c3 = (jj + 1) * R3 + (ii + 1);
-      const C xc = L.x[c3];
-      const C xw = L.x[c3 - 1], xe = L.x[c3 + 1], xs = L.x[c3 - R3], xn = L.x[c3 + R3];
-      const C rv = C(ldv(r + int64_t(J) * rp + I));
-      if constexpr (std::is_void<AT>::value) {
-        const C flux = (((xc - xw) + (xc - xe)) + (xc - xs)) + (xc - xn);
-        v.x = float((hl2 * rv - flux) / C(4));
-      } else {
-        const C ac = L.a[c3];
-        const C aw = hmean(ac, L.a[c3 - 1]), ae = hmean(ac, L.a[c3 + 1]);
-        const C as = hmean(ac, L.a[c3 - R3]), an = hmean(ac, L.a[c3 + R3]);
-        const C sa = ((aw + ae) + as) + an;
-        const C flux = ((aw * (xc - xw) + ae * (xc - xe)) + as * (xc - xs)) + an * (xc - xn);
-        const C rho = (hl2 * rv - flux) / sa;
-        v.x = float(rho);
-        v.y = float(rho * (ae - aw) / (ae + aw));
-        v.z = float(rho * (an - as) / (an + as));
-      }
-    }
+    if (J >= 1 && J <= nm - 2 && I >= 1 && I <= nm - 2)
+      v = node_features<!std::is_void<AT>::value>(L.x, L.a, (q / R2 + 1) * R3 + (q % R2 + 1),
+                                                  C(ldv(r + int64_t(J) * rp + I)), hl2);
     L.f[q] = v;
   }
   __syncthreads();
 }
 
-// Hidden layer at the lane's node of the halo-1 region (one node per lane):
-// pre-activations P[16] in registers, H = max(P, 0) stored in LDS (0 off the
-// interior).  Returns whether the node is interior.
-template <typename C>
-__device__ __forceinline__ bool stage_hidden(TileLds<C>& L, const float* __restrict__ w, int nm,
-                                             int J0, int I0, float P[HID]) {
-  const int t = threadIdx.x;
-  const int jj = t / R1, ii = t % R1;
-  const int J = J0 - 1 + jj, I = I0 - 1 + ii;
-  const bool in = J >= 1 && J <= nm - 2 && I >= 1 && I <= nm - 2;
+// The network's contractions in FP32 on the matrix cores (weights are FP32
+// values of any kind here): v_mfma_f32_16x16x4_f32, D = A B + D with A 16 x 4
+// (lane: row lane % 16, column lane / 16), B 4 x 16 (row lane / 16, column
+// lane % 16) and D[4 (lane / 16) + r][lane % 16].  One instruction takes 16
+// nodes of a row.  First layer: K slot s = 9 ci + k of the 27 features of a
+// node's window, seven instructions.  Its result leaves the lane the channels
+// 4 g + r of its node, the second layer's operand as it is when K slot g of
+// instruction r stands for channel 4 g + r.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+struct NetConst {
+  float w1[7], w2[4];
+  int off[7];  // of the lane's features from those of the node's window corner
+};
+__device__ __forceinline__ NetConst net_const(const float* __restrict__ w) {
+  const int col = threadIdx.x & 15, g = (threadIdx.x & 63) >> 4;
+  NetConst n;
 #pragma unroll
-  for (int c = 0; c < HID; ++c) P[c] = 0.f;
-  if (in) {
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      const int dy = k / 3 - 1, dx = k % 3 - 1;
-      const float4 fv = L.f[(jj + 1 + dy) * R2 + (ii + 1 + dx)];
-#pragma unroll
-      for (int c = 0; c < HID; ++c) {
-        float p = P[c];
-        p = __builtin_fmaf(w[c * 27 + 0 * 9 + k], fv.x, p);
-        p = __builtin_fmaf(w[c * 27 + 1 * 9 + k], fv.y, p);
-        p = __builtin_fmaf(w[c * 27 + 2 * 9 + k], fv.z, p);
-        P[c] = p;
-      }
-    }
+  for (int st = 0; st < 7; ++st) {
+    const int s = 4 * st + g, k = s % 9;
+    n.w1[st] = s < 27 ? w[col * 27 + s] : 0.f;
+    n.off[st] = s < 27 ? 4 * ((k / 3) * R2 + k % 3) + s / 9 : 0;
   }
-  float* hrow = L.h + t * HP;
 #pragma unroll
-  for (int c = 0; c < HID; c += 4)
-    *reinterpret_cast<float4*>(hrow + c) =
-        make_float4(fmaxf(P[c], 0.f), fmaxf(P[c + 1], 0.f), fmaxf(P[c + 2], 0.f), fmaxf(P[c + 3], 0.f));
-  __syncthreads();
-  return in;
+  for (int r = 0; r < 4; ++r) n.w2[r] = col < 9 ? w[NW1 + (4 * g + r) * 9 + col] : 0.f;
+  return n;
 }
-
-// Output at owned node o (0 <= o < 196): y = sum_c sum_k W2[c][k] H_c(p + o_k).
-template <typename C>
-__device__ __forceinline__ float tile_output(const TileLds<C>& L, const float* __restrict__ w, int o) {
-  const int oj = o / TO, oi = o % TO;
-  float y = 0.f;
+// Pre-activations of the 16 nodes of row jj of the halo-1 region.
+__device__ __forceinline__ f32x4 hidden_row(const float4* f, const NetConst& n, int jj) {
+  const float* base = reinterpret_cast<const float*>(f) + 4 * (jj * R2 + int(threadIdx.x & 15));
+  const bool last = ((threadIdx.x & 63) >> 4) < 3;  // slot 27 carries nothing
+  f32x4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int k = 0; k < 9; ++k) {
-    const int dy = k / 3 - 1, dx = k % 3 - 1;
-    const float* hv = L.h + ((oj + 1 + dy) * R1 + (oi + 1 + dx)) * HP;
-#pragma unroll
-    for (int c = 0; c < HID; c += 4) {
-      const float4 h4 = *reinterpret_cast<const float4*>(hv + c);
-      y = __builtin_fmaf(w[NW1 + (c + 0) * 9 + k], h4.x, y);
-      y = __builtin_fmaf(w[NW1 + (c + 1) * 9 + k], h4.y, y);
-      y = __builtin_fmaf(w[NW1 + (c + 2) * 9 + k], h4.z, y);
-      y = __builtin_fmaf(w[NW1 + (c + 3) * 9 + k], h4.w, y);
-    }
+  for (int st = 0; st < 7; ++st) {
+    const float v = base[n.off[st]];
+    d = __builtin_amdgcn_mfma_f32_16x16x4f32(n.w1[st], st < 6 || last ? v : 0.f, d, 0, 0, 0);
   }
-  return y;
+  return d;
 }
 
 // ---------------------------------------------------------------- inference
@@ -224,7 +219,6 @@ __device__ __forceinline__ float tile_output(const TileLds<C>& L, const float* _
 //     and zeros: two MFMAs), written to LDS;
 // and after a barrier the output at a node is y = sum_k Z[k][node + o_k].
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 struct Parts {  // an FP32 value as three BF16 parts, in the upper halves of FP32 words
   uint32_t hi, mid, lo;
@@ -252,7 +246,7 @@ __device__ __forceinline__ uint32_t pair16(uint32_t lo_word, uint32_t hi_word) {
   return (lo_word >> 16) | (hi_word & 0xffff0000u);
 }
 
-constexpr int ZS = 12;            // Z row stride in floats (taps 0..8, 16-byte rows)
+constexpr int ZS = TZS;
 
 template <typename C>
 struct InferLds {
@@ -570,7 +564,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 // ---------------------------------------------------------------- training
 // Dense FP32 compact arrays of side nm (node (J, I) at J nm + I).
 
-// z = delta - y at interior nodes (y alone when delta is null).
+// z = delta - y at interior nodes (y alone when delta is null).  With the
+// channel sums on the vector units, one node per lane, it took 22 us at 513^2.
 template <bool VAR>
 __global__ __launch_bounds__(NT) void k_train_fwd(const float* __restrict__ x,
                                                   const float* __restrict__ r,
@@ -578,29 +573,54 @@ __global__ __launch_bounds__(NT) void k_train_fwd(const float* __restrict__ x,
                                                   const float* __restrict__ delta,
                                                   float* __restrict__ z, int nm, float hl2,
                                                   const float* __restrict__ w) {
-  __shared__ TileLds<float> L;
-  const int J0 = 1 + blockIdx.y * TO, I0 = 1 + blockIdx.x * TO;
+  __shared__ FwdLds L;
+  const int J0 = 1 + blockIdx.y * TO, I0 = 1 + blockIdx.x * TO, t = threadIdx.x;
+  const int J = J0 + t / TO, I = I0 + t % TO;
+  const bool own = t < NOWN && J <= nm - 2 && I <= nm - 2;
+  const float dv = own && delta ? delta[int64_t(J) * nm + I] : 0.f;
+  const NetConst nc = net_const(w);
   if constexpr (VAR)
     stage_features<float, float, float, float>(L, x, nm, r, nm, a, nm, nm, J0, I0, hl2);
   else
     stage_features<float, float, float, void>(L, x, nm, r, nm, nullptr, 0, nm, J0, I0, hl2);
-  float P[HID];
-  (void)stage_hidden<float>(L, w, nm, J0, I0, P);
-  const int o = threadIdx.x;
-  if (o < NOWN) {
-    const int J = J0 + o / TO, I = I0 + o % TO;
-    if (J <= nm - 2 && I <= nm - 2) {
-      const float y = tile_output<float>(L, w, o);
-      const int64_t p = int64_t(J) * nm + I;
-      z[p] = delta ? delta[p] - y : y;
-    }
+  const int col = t & 15, g = (t & 63) >> 4, wave = t >> 6;
+  const bool col_in = I0 - 1 + col >= 1 && I0 - 1 + col <= nm - 2;
+#pragma unroll
+  for (int rr = 0; rr < 4; ++rr) {
+    const int jj = wave * 4 + rr;
+    const bool in = col_in && J0 - 1 + jj >= 1 && J0 - 1 + jj <= nm - 2;
+    const f32x4 d = hidden_row(L.f, nc, jj);
+    f32x4 y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      y = __builtin_amdgcn_mfma_f32_16x16x4f32(nc.w2[q], in ? fmaxf(d[q], 0.f) : 0.f, y, 0, 0, 0);
+    if (g < 3) *reinterpret_cast<f32x4*>(L.z + (jj * R1 + col) * TZS + 4 * g) = y;  // taps 4g .. 4g+3
+  }
+  __syncthreads();
+  if (own) {
+    const int oj = t / TO, oi = t % TO;
+    float y = 0.f;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) y += L.z[((oj + k / 3) * R1 + (oi + k % 3)) * TZS + k];
+    z[int64_t(J) * nm + I] = delta ? dv - y : y;
   }
 }
 
 // Gradient partial sums of one sample.  Workgroup b visits tiles b, b + G,
-// ...; lane t accumulates elements t, t + 256, t + 512 of the 577-vector
-// (576 weight gradients of L = E(z)/E(delta), then E(z)); the row of
-// workgroup b goes to part[j * pstride + b].
+// ...; the row of workgroup b (576 weight gradients of L = E(z)/E(delta),
+// then E(z)) goes to part[j * pstride + b].
+//
+// The weight gradients are contractions over the tile's nodes,
+//   dW1[c][s] = sum_o dP_c(o) X_s(o)   (16 x 27, owned nodes; X_s the feature
+//     ci at the node o + o_k, s = 9 ci + k),
+//   dW2[c][k] = sum_q H_c(q) g(q - o_k)  (16 x 9, the halo-1 region; g = 0 off
+//     the owned nodes),
+// and run on the matrix cores in FP32 (v_mfma_f32_16x16x4_f32: A[i][k] with
+// i = lane % 16, k = lane / 16, B[k][j] with j = lane % 16, D[4 (lane / 16) +
+// r][j]), four nodes of a row per instruction, each wave taking every fourth
+// row.  One lane per gradient element with two LDS reads per product took
+// 135 us per call at 513^2, nine tenths of it in these sums; this takes 28 us,
+// the chain of a tile's phases (1369 tiles, 768 workgroups resident).
 template <bool VAR>
 __global__ __launch_bounds__(NT) void k_train_bwd(const float* __restrict__ x,
                                                   const float* __restrict__ r,
@@ -609,32 +629,53 @@ __global__ __launch_bounds__(NT) void k_train_bwd(const float* __restrict__ x,
                                                   const double* __restrict__ e0,
                                                   const float* __restrict__ w,
                                                   float* __restrict__ part, int64_t pstride) {
+  constexpr int GP = R1 + 2;            // pitch of go: the halo-1 region and a ring of zeros
+  constexpr int DP = 16;                // owned row of dp padded to whole instructions
   __shared__ TileLds<float> L;
   __shared__ float gs[NT];              // g on the halo-1 region
+  __shared__ float go[GP * GP];         // g on the owned nodes, 0 around them
   __shared__ float zs[R2 * R2];         // z on the halo-2 region
-  __shared__ float dp[NOWN * HP];       // dP on owned nodes
-  __shared__ float ez[NOWN];            // z (A z) on owned nodes
-  const int t = threadIdx.x;
+  __shared__ float dp[TO * DP * HP];    // dP on owned nodes
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int col = lane & 15, grp = lane >> 4;
   const int tiles_x = (nm - 2 + TO - 1) / TO;
   const int tiles = tiles_x * tiles_x;
   const float gscale = float(-2.0 / *e0);
-  float acc[3] = {0.f, 0.f, 0.f};
+  const NetConst nc = net_const(w);
+  for (int q = t; q < GP * GP; q += NT) go[q] = 0.f;
+  // the lane's feature s (two column tiles) and tap k: offsets from node (0, 0)
+  auto feature = [&](int s) { return 4 * ((1 + (s % 9) / 3) * R2 + 1 + s % 3) + s / 9; };
+  const bool has1 = 16 + col < 27, has2 = col < 9;
+  const int off0 = feature(col), off1 = has1 ? feature(16 + col) : 0;
+  const int off2 = has2 ? (2 - col / 3) * GP + 2 - col % 3 : 0;
+  f32x4 d1a = {0.f, 0.f, 0.f, 0.f}, d1b = d1a, d2 = d1a;
+  float eacc = 0.f;
   for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const int J0 = 1 + (tile / tiles_x) * TO, I0 = 1 + (tile % tiles_x) * TO;
-    if constexpr (VAR)
-      stage_features<float, float, float, float>(L, x, nm, r, nm, a, nm, nm, J0, I0, hl2);
-    else
-      stage_features<float, float, float, void>(L, x, nm, r, nm, nullptr, 0, nm, J0, I0, hl2);
-    float P[HID];
-    (void)stage_hidden<float>(L, w, nm, J0, I0, P);
     for (int q = t; q < R2 * R2; q += NT) {
       const int J = J0 - 2 + q / R2, I = I0 - 2 + q % R2;
       zs[q] = (J >= 1 && J <= nm - 2 && I >= 1 && I <= nm - 2) ? z[int64_t(J) * nm + I] : 0.f;
     }
-    __syncthreads();
+    if constexpr (VAR)
+      stage_features<float, float, float, float>(L, x, nm, r, nm, a, nm, nm, J0, I0, hl2);
+    else
+      stage_features<float, float, float, void>(L, x, nm, r, nm, nullptr, 0, nm, J0, I0, hl2);
+    {  // the hidden layer, four rows per wave
+      const bool col_in = I0 - 1 + col >= 1 && I0 - 1 + col <= nm - 2;
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+        const int jj = wave * 4 + rr;
+        const bool in = col_in && J0 - 1 + jj >= 1 && J0 - 1 + jj <= nm - 2;
+        f32x4 d = hidden_row(L.f, nc, jj);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) d[q] = in ? fmaxf(d[q], 0.f) : 0.f;
+        *reinterpret_cast<f32x4*>(L.h + (jj * R1 + col) * HP + 4 * grp) = d;
+      }
+    }
     {  // g = -2 (A z) / E(delta) on the halo-1 region, z (A z) on owned nodes
       const int jj = t / R1, ii = t % R1;
       const int J = J0 - 1 + jj, I = I0 - 1 + ii;
+      const bool own = jj >= 1 && jj <= TO && ii >= 1 && ii <= TO;
       float g = 0.f;
       if (J >= 1 && J <= nm - 2 && I >= 1 && I <= nm - 2) {
         const int c2 = (jj + 1) * R2 + (ii + 1);
@@ -651,78 +692,83 @@ __global__ __launch_bounds__(NT) void k_train_bwd(const float* __restrict__ x,
           az = (((zc - zs[c2 - 1]) + (zc - zs[c2 + 1])) + (zc - zs[c2 - R2])) + (zc - zs[c2 + R2]);
         }
         g = gscale * az;
-        if (jj >= 1 && jj <= TO && ii >= 1 && ii <= TO) ez[(jj - 1) * TO + (ii - 1)] = zc * az;
-      } else if (jj >= 1 && jj <= TO && ii >= 1 && ii <= TO) {
-        ez[(jj - 1) * TO + (ii - 1)] = 0.f;
+        if (own) eacc += zc * az;
       }
       gs[t] = g;
+      if (own) go[(jj + 1) * GP + ii + 1] = g;
     }
     __syncthreads();
-    if (t < NOWN) {  // dP_c(q) = [P_c(q) > 0] sum_k W2[c][k] g(q - o_k) at owned q
-      const int oj = t / TO, oi = t % TO;
-      const int J = J0 + oj, I = I0 + oi;
-      const bool in = J <= nm - 2 && I <= nm - 2;
+    if (t < TO * DP) {  // dP_c(q) = [P_c(q) > 0] sum_k W2[c][k] g(q - o_k) at owned q
+      const int oj = t / DP, oi = t % DP;
+      const bool in = oi < TO && J0 + oj <= nm - 2 && I0 + oi <= nm - 2;
       float gk[9];
 #pragma unroll
       for (int k = 0; k < 9; ++k) {
         const int dy = k / 3 - 1, dx = k % 3 - 1;
         gk[k] = in ? gs[(oj + 1 - dy) * R1 + (oi + 1 - dx)] : 0.f;
       }
-      const float* hq = L.h + ((oj + 1) * R1 + (oi + 1)) * HP;
+      const float* hq = L.h + ((oj + 1) * R1 + (in ? oi + 1 : 0)) * HP;
 #pragma unroll
       for (int c = 0; c < HID; ++c) {
         float dh = 0.f;
 #pragma unroll
         for (int k = 0; k < 9; ++k) dh = __builtin_fmaf(w[NW1 + c * 9 + k], gk[k], dh);
-        dp[t * HP + c] = hq[c] > 0.f ? dh : 0.f;
+        dp[t * HP + c] = in && hq[c] > 0.f ? dh : 0.f;
       }
     }
     __syncthreads();
-    // weight gradients over the owned nodes (outside ones carry dP = g = 0)
+    const float* fl = reinterpret_cast<const float*>(L.f);
+    for (int oj = wave; oj < TO; oj += 4)
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
-      const int j = t + s * NT;
-      if (j < NW1) {
-        const int c = j / 27, ci = (j % 27) / 9, k = j % 9;
-        const int dy = k / 3 - 1, dx = k % 3 - 1;
-        float sum = 0.f;
-        for (int o = 0; o < NOWN; ++o) {
-          const int oj = o / TO, oi = o % TO;
-          const float4 fv = L.f[(oj + 2 + dy) * R2 + (oi + 2 + dx)];
-          const float xv = ci == 0 ? fv.x : (ci == 1 ? fv.y : fv.z);
-          sum = __builtin_fmaf(dp[o * HP + c], xv, sum);
-        }
-        acc[s] += sum;
-      } else if (j < NW) {
-        const int c = (j - NW1) / 9, k = (j - NW1) % 9;
-        const int dy = k / 3 - 1, dx = k % 3 - 1;
-        float sum = 0.f;
-        for (int o = 0; o < NOWN; ++o) {
-          const int oj = o / TO, oi = o % TO;
-          const float gv = gs[(oj + 1) * R1 + (oi + 1)];
-          sum = __builtin_fmaf(gv, L.h[((oj + 1 + dy) * R1 + (oi + 1 + dx)) * HP + c], sum);
-        }
-        acc[s] += sum;
-      } else if (j == NW) {
-        float sum = 0.f;
-        for (int o = 0; o < NOWN; ++o) sum += ez[o];
-        acc[s] += sum;
+      for (int st = 0; st < 4; ++st) {
+        const int oi = 4 * st + grp;  // (the padded nodes 14 and 15 carry dP = 0)
+        const float pa = dp[(oj * DP + oi) * HP + col];
+        const float* f = fl + 4 * (oj * R2 + oi);
+        const float f1 = f[off1];
+        d1a = __builtin_amdgcn_mfma_f32_16x16x4f32(pa, f[off0], d1a, 0, 0, 0);
+        d1b = __builtin_amdgcn_mfma_f32_16x16x4f32(pa, has1 ? f1 : 0.f, d1b, 0, 0, 0);
       }
-    }
+    for (int jj = wave; jj < R1; jj += 4)
+#pragma unroll
+      for (int st = 0; st < 4; ++st) {
+        const int ii = 4 * st + grp;
+        const float gv = go[jj * GP + ii + off2];
+        d2 = __builtin_amdgcn_mfma_f32_16x16x4f32(L.h[(jj * R1 + ii) * HP + col], has2 ? gv : 0.f, d2, 0, 0, 0);
+      }
     __syncthreads();
   }
+  // the four waves' sums, added in order
+  float* red = dp;
+  float* mine = red + wave * 3 * 256 + lane * 4;
 #pragma unroll
-  for (int s = 0; s < 3; ++s) {
-    const int j = t + s * NT;
-    if (j <= NW) part[int64_t(j) * pstride + blockIdx.x] = acc[s];
+  for (int q = 0; q < 4; ++q) {
+    mine[q] = d1a[q];
+    mine[256 + q] = d1b[q];
+    mine[512 + q] = d2[q];
   }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) eacc += __shfl_xor(eacc, o, 64);
+  if (lane == 0) gs[wave] = eacc;
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < 3; ++m) {
+    float v = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v += red[q * 3 * 256 + m * 256 + t];
+    const int l = t >> 2, c = 4 * (l >> 4) + (t & 3), j = l & 15;
+    const int to = m < 2 ? (16 * m + j < 27 ? c * 27 + 16 * m + j : -1) : (j < 9 ? NW1 + c * 9 + j : -1);
+    if (to >= 0) part[int64_t(to) * pstride + blockIdx.x] = v;
+  }
+  if (t == 0) part[int64_t(NW) * pstride + blockIdx.x] = ((gs[0] + gs[1]) + gs[2]) + gs[3];
 }
 
 // Sum of each partial row in a fixed order: out[j] = sum_b part[j][b],
-// FP64 accumulation (one workgroup per element j).
+// FP64 accumulation (one workgroup per element j).  The last element, E(z),
+// also goes to *energy (nullable).
 __global__ __launch_bounds__(256) void k_train_reduce(const float* __restrict__ part,
                                                       int64_t pstride, int rows,
-                                                      double* __restrict__ out) {
+                                                      double* __restrict__ out,
+                                                      double* __restrict__ energy) {
   __shared__ double red[256];
   const int j = blockIdx.x;
   double s = 0.0;
@@ -733,7 +779,10 @@ __global__ __launch_bounds__(256) void k_train_reduce(const float* __restrict__ 
     if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[j] = red[0];
+  if (threadIdx.x == 0) {
+    out[j] = red[0];
+    if (energy && j == NW) *energy = red[0];
+  }
 }
 
 // Mean gradient over the batch (the `batch` rows of sums, stride NW + 1,
@@ -809,12 +858,20 @@ __global__ __launch_bounds__(256) void k_energy_part(const float* __restrict__ v
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ void k_sum_small(const double* __restrict__ part, int count, double* __restrict__ out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < count; ++i) s += part[i];
-    *out = s;
+// Sum of `count` values in a fixed order by one workgroup (a single lane's
+// loop took 52 us for 1024).
+__global__ __launch_bounds__(256) void k_sum_small(const double* __restrict__ part, int count,
+                                                   double* __restrict__ out) {
+  __shared__ double red[256];
+  double s = 0.0;
+  for (int i = threadIdx.x; i < count; i += 256) s += part[i];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    __syncthreads();
   }
+  if (threadIdx.x == 0) *out = red[0];
 }
 
 // FP32 values -> BF16 (RNE) and their FP32 expansion.
@@ -994,8 +1051,8 @@ hipError_t launch_train_bwd(int nm, float hl2, const float* x, const float* r, c
 }
 
 hipError_t launch_train_reduce(const float* part, int64_t pstride, int rows, double* out,
-                               hipStream_t s) {
-  LL_LAUNCH(k_train_reduce, dim3(NW + 1), dim3(256), s, part, pstride, rows, out);
+                               hipStream_t s, double* energy) {
+  LL_LAUNCH(k_train_reduce, dim3(NW + 1), dim3(256), s, part, pstride, rows, out, energy);
 }
 
 hipError_t launch_train_adam(const double* sums, int batch, const double* e0s, const int* idx,
@@ -1023,7 +1080,7 @@ hipError_t launch_energy(const float* v, const float* a, int nm, double* part, d
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_sum_small, dim3(1), dim3(64), 0, s, part, blocks, out);
+  hipLaunchKernelGGL(k_sum_small, dim3(1), dim3(256), 0, s, part, blocks, out);
   return hipGetLastError();
 }
 

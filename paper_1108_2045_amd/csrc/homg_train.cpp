@@ -382,23 +382,27 @@ homg_status homg_learn_grad(int nm, double hl, const float* x, const float* r, c
   if (nm < 3 || nm > 65537 || !(hl > 0.0)) return tfail(nullptr, HOMG_ERR_INVALID_ARG, "invalid size or spacing");
   if (!x || !r || !delta || !w || !grad) return tfail(nullptr, HOMG_ERR_INVALID_ARG, "null array");
   hipStream_t s = static_cast<hipStream_t>(stream);
+  // one allocation (each hipMalloc / hipFree pair costs some 30 us): E(z) and
+  // E(delta) side by side for one copy, the energy's sums, the gradient's, z
   DevBufs tmp;
-  float *z, *part;
-  double *epart, *e0;
-  TCHK(nullptr, tmp.alloc(&z, size_t(nm) * nm));
-  TCHK(nullptr, tmp.alloc(&part, size_t(NW + 1) * TRAIN_MAX_ROWS));
-  TCHK(nullptr, tmp.alloc(&epart, ENERGY_MAX_PARTS));
-  TCHK(nullptr, tmp.alloc(&e0, 1));
+  char* base;
+  const size_t b_ep = 256, b_part = b_ep + sizeof(double) * ENERGY_MAX_PARTS,
+               b_z = b_part + sizeof(float) * size_t(NW + 1) * TRAIN_MAX_ROWS;
+  TCHK(nullptr, tmp.alloc(&base, b_z + sizeof(float) * size_t(nm) * nm));
+  double* pair = reinterpret_cast<double*>(base);
+  double* e0 = pair + 1;
+  double* epart = reinterpret_cast<double*>(base + b_ep);
+  float* part = reinterpret_cast<float*>(base + b_part);
+  float* z = reinterpret_cast<float*>(base + b_z);
   const float hl2 = float(hl * hl);
   TCHK(nullptr, launch_energy(delta, a, nm, epart, e0, s));
   TCHK(nullptr, launch_train_fwd(nm, hl2, x, r, a, delta, z, w, s));
   TCHK(nullptr, launch_train_bwd(nm, hl2, x, r, a, z, e0, w, part, TRAIN_MAX_ROWS, s));
-  TCHK(nullptr, launch_train_reduce(part, TRAIN_MAX_ROWS, train_bwd_rows(nm), grad, s));
-  double ez = 0.0, e0h = 0.0;
-  TCHK(nullptr, hipMemcpyAsync(&ez, grad + NW, sizeof(double), hipMemcpyDeviceToHost, s));
-  TCHK(nullptr, hipMemcpyAsync(&e0h, e0, sizeof(double), hipMemcpyDeviceToHost, s));
+  TCHK(nullptr, launch_train_reduce(part, TRAIN_MAX_ROWS, train_bwd_rows(nm), grad, s, pair));
+  double h[2] = {0.0, 0.0};
+  TCHK(nullptr, hipMemcpyAsync(h, pair, sizeof h, hipMemcpyDeviceToHost, s));
   TCHK(nullptr, hipStreamSynchronize(s));
-  if (loss) *loss = e0h > 0.0 ? ez / e0h : 0.0;
+  if (loss) *loss = h[1] > 0.0 ? h[0] / h[1] : 0.0;
   return HOMG_OK;
 }
 
