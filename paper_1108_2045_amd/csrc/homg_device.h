@@ -140,10 +140,27 @@ __device__ __forceinline__ float lane_next_or(float edge, float v) {
 
 // ------------------------------------------------------------ reductions
 
+// v + the value `n` lanes on in its row of 16 (DPP rotation).
+template <int N>
+__device__ __forceinline__ double add_rot16(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = unsigned(__builtin_amdgcn_update_dpp(0, int(b), 0x120 + N, 0xf, 0xf, true));
+  const unsigned hi = unsigned(__builtin_amdgcn_update_dpp(0, int(b >> 32), 0x120 + N, 0xf, 0xf, true));
+  return v + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Sum over the wave, in every lane: pairs 32 lanes apart, then 16, 8, 4, 2, 1.
+// Once lanes 8 apart hold the same sum, the lane 4 on in a row of 16 holds
+// what the lane with bit 2 flipped does, and so on down: the last four steps
+// are row rotations (VALU moves; six steps of lane shuffles, two LDS crossbar
+// operations each, were bound by the crossbar where 16 waves summed at once).
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v += __shfl_xor(v, 32, 64);
+  v += __shfl_xor(v, 16, 64);
+  v = add_rot16<8>(v);
+  v = add_rot16<4>(v);
+  v = add_rot16<2>(v);
+  return add_rot16<1>(v);
 }
 
 // Deterministic block sum (fixed order for a fixed block size); result valid

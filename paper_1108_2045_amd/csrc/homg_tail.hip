@@ -14,14 +14,24 @@
 //    iteration at 65^2).  3D: a wave is one plane of 16 columns by 4 groups of
 //    4 rows, x neighbours by DPP row shifts, y neighbours from the lane's own
 //    rows and the lanes 16 away, and the planes above and below through LDS;
-//  * the coarser levels have at most 31^2 or 7^3 interior nodes: one per lane,
-//    its value, right-hand side and position kept in registers, neighbours
-//    through LDS;
-//  * levels of at most 64 interior nodes (sides 9, 5, 3; in 3D 5, 3), their
-//    restrictions and hand-overs are run by the first wave alone without
-//    barriers: a third of all phases.
+//  * 2D: the coarser levels keep one node per lane in registers, rows of 32,
+//    16 or 8 lanes (sides 33, 17 and up to 9; the last lane of a row is the
+//    boundary, so DPP shifts give the x neighbours).  Sides 33 and 17 exchange
+//    rows through LDS with a barrier per iteration; sides up to 9 are one
+//    wave's, rows by lane shuffles, no barrier and no LDS.  The code is
+//    written out per side (33, 17, 9, 5, 3), with sides, offsets and spacings
+//    known at compile time: as a loop over levels each began with scalar
+//    loads and taken branches, 600 of its 1700 clocks.  The first restriction
+//    is formed from the finest level's registers.
+//    (Four nodes per lane on the coarser levels too were slower: one wave's
+//    instruction issue.)
+//  * 3D: the coarser levels have at most 7^3 interior nodes, one per lane, its
+//    value, right-hand side and position in registers, neighbours through
+//    LDS; sides 5 and 3 run in the first wave alone.  Written out per side too.
 // Node formulas, summation orders and rounding points are those of the
 // multi-workgroup kernels, so every form gives the same bits.
+#include <type_traits>
+
 #include "homg_device.h"
 #include "homg_internal.h"
 
@@ -31,21 +41,11 @@ namespace {
 
 constexpr int TAIL_NT = 1024;
 
-// Per-level constants, worked out on the host (the reciprocals and h^2 are
-// the correctly rounded values the device division would give), so that no
-// level starts with a division.
-struct TailLevel {
-  int it;        // iterations of level ms + k
-  int off;       // element offset of the level's R, P, Q arrays in LDS (k >= 1)
-  float inv_ni;  // 1 / (nk - 2): splits the level's interior nodes
-  int pad;
-  double hl2;    // h^2 = (1 / (nk - 1))^2
-};
-
 template <typename T>
 struct TailArgs {
-  TailLevel lv[BATCH_MAX_LEVELS];
+  int it[BATCH_MAX_LEVELS];  // iterations of level ms + k
   int nms, nlev;          // side of the finest level, number of levels
+  double hl2;             // h^2 of the finest level
   double w;               // omega / 2d, or omega with a variable coefficient
   int x_off, a_off, t_off, s_off;  // byte offsets in LDS: exchange, coefficient, FP64 coarsest level, sums
   const double* a;        // nodal coefficient of the finest level (node 0), or null
@@ -168,33 +168,248 @@ struct TailExchange {
   }
 };
 
-// Relaxation factors of a variable-coefficient node: relax_var's face
-// coefficients and w / sum, kept over a level's iterations (the same
-// operations, so the same bits).
+// Relaxation of a variable-coefficient node from its face coefficients and
+// w / their sum, kept over a level's iterations (relax_var's operations, so
+// the same bits).
 template <typename C>
 struct VarNode {
   C xm, xp, ym, yp, ws;
-  __device__ __forceinline__ void set(double c, double axm, double axp, double aym, double ayp, C w) {
-    xm = C(harm(c, axm));
-    xp = C(harm(c, axp));
-    ym = C(harm(c, aym));
-    yp = C(harm(c, ayp));
-    ws = w / ((xm + xp) + (ym + yp));
-  }
   __device__ __forceinline__ C relax(C c, C vxm, C vxp, C vym, C vyp, C r, C hl2) const {
     const C flux = fmac(xm, c - vxm, xp * (c - vxp)) + fmac(ym, c - vym, yp * (c - vyp));
     return fmac(ws, fmac(hl2, r, -flux), c);
   }
 };
 
-// One interior node of a coarser level, its neighbours in LDS (pitch nk,
-// plane nk^2).
-template <int D, bool VAR, typename C>
-__device__ __forceinline__ C tail_relax(const C* src, int i, int nk, int pl, C c, C r, C w, C hl2, const VarNode<C>& vn) {
-  if (VAR) return vn.relax(c, src[i - 1], src[i + 1], src[i - nk], src[i + nk], r, hl2);
-  const C q = (src[i - 1] + src[i + 1]) + (src[i - nk] + src[i + nk]);
-  if (D == 2) return relax_const<C>(c, q, r, w, hl2, C(4));
-  return relax_const<C>(c, q + (src[i - pl] + src[i + pl]), r, w, hl2, C(6));
+// The coarser levels' arrays in LDS (offsets in elements): R, P and Q of every
+// side below the largest, largest first; in 3D after R of the finest level.
+// Sides and offsets are compile-time, one instance of the code per side.
+template <int D, int S>
+constexpr int LEV_OFF = LEV_OFF<D, 2 * S - 1> + 3 * (D == 2 ? 1 : 2 * S - 1) * (2 * S - 1) * (2 * S - 1);
+template <>
+constexpr int LEV_OFF<2, 33> = 1024;  // after an exchange row per wave
+template <>
+constexpr int LEV_OFF<3, 9> = 17 * 17 * 17;
+template <int D>
+constexpr int LEV_END = LEV_OFF<D, 3> + 3 * (D == 2 ? 9 : 27);
+
+// The starting values of rows y0 .. y0 + 3 (y0 odd) of column x of a 2D level
+// from the coarser level's pair (pitch = side nh): its lattice nodes take cur,
+// the others the interpolant of prv.  Positions off the grid are clamped
+// (their values are dropped by the caller).
+template <typename T, typename C = typename Tr<T>::C>
+__device__ __forceinline__ void hand_over_2d(const C* prv, const C* cur, int nh, int x, int y0, C (&v)[4]) {
+  const int xi = min(x >> 1, nh - 2), j0 = y0 >> 1;
+  const C tx = C(x & 1) * C(0.5);
+  C xr[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const C* p = prv + min(j0 + d, nh - 1) * nh + xi;
+    xr[d] = lerp(p[0], p[1], tx);
+  }
+  const C l1 = cur[min(j0 + 1, nh - 1) * nh + xi], l3 = cur[min(j0 + 2, nh - 1) * nh + xi];
+  const bool even = !(x & 1);
+  v[0] = rnd<T>(lerp(xr[0], xr[1], C(0.5)));
+  v[1] = even ? l1 : rnd<T>(lerp(xr[1], xr[2], C(0)));
+  v[2] = rnd<T>(lerp(xr[1], xr[2], C(0.5)));
+  v[3] = even ? l3 : rnd<T>(lerp(xr[2], xr[3], C(0)));
+}
+
+// 2D coarser levels: lanes per row of a level of side S.
+template <int S>
+constexpr int ROW_W = S > 17 ? 32 : S > 9 ? 16 : 8;
+
+// A 2D level of side S, one node per lane, rows of W lanes (lane W - 1 of a
+// row holds x = W, the boundary or beyond: 0).  W = 8: the first wave alone.
+// W = 16, 32: the first four or all waves hold rows, every wave of the
+// workgroup calls it (barriers); X: two exchange buffers of W + 1 rows.  V:
+// the arithmetic (FP64 for the coarsest level of reduced-precision cycles,
+// whose iterates are not rounded).  hi: the next coarser level's arrays (side
+// (S + 1) / 2, ith iterations), unread if zero.  Leaves the final pair, rounded
+// to T, where its parity puts it (x_it in Q if it is odd), interior nodes only.
+template <typename T, typename V, bool VAR, int S>
+__device__ __forceinline__ void row_level(const V* R, typename Tr<T>::C* me, int it, V w, bool zero,
+                                          const typename Tr<T>::C* hi, int ith, const double* A, int ap, int as, V* X) {
+  using C = typename Tr<T>::C;
+  constexpr bool EXACT = sizeof(V) != sizeof(C);  // FP64 iterates in a reduced-precision cycle
+  constexpr int W = ROW_W<S>, BUF = (W + 1) * W, H = (S + 1) / 2;
+  constexpr double h = 1.0 / double(S - 1);
+  const V hl2 = V(h * h);
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const bool on = wv < W * W / 64;
+  const int x = 1 + (lane & (W - 1)), y = 1 + (W == 8 ? 0 : wv * (64 / W)) + lane / W;
+  const bool in = on && x <= S - 2 && y <= S - 2;
+  const int i = min(y, S - 2) * S + min(x, S - 2);
+  V v = V(0), pv = V(0), cw = V(0), ce = V(0), cs = V(0), cn = V(0), ws = V(0), r = V(0);
+  V* const mine = X + y * W + (x - 1);
+  if (on) {  // (whole waves)
+    r = R[i];
+    if constexpr (VAR) {
+      const double* p = A + (min(y, S - 2) * ap + min(x, S - 2)) * as;
+      const double c = p[0];
+      cw = V(harm(c, p[-as]));
+      ce = V(harm(c, p[as]));
+      cs = V(harm(c, p[-as * ap]));
+      cn = V(harm(c, p[as * ap]));
+      ws = w / ((cw + ce) + (cs + cn));
+    }
+    if constexpr (!EXACT && S > 3) {
+      if (!zero) {
+        const C* prv = hi + ((ith & 1) ? H * H : 2 * H * H);
+        const C* cur = hi + ((ith & 1) ? 2 * H * H : H * H);
+        const int c0 = min(y >> 1, H - 2) * H + min(x >> 1, H - 2);
+        const C p00 = prv[c0], p01 = prv[c0 + 1], p10 = prv[c0 + H], p11 = prv[c0 + H + 1], lat = cur[c0];
+        const C tx = C(x & 1) * C(0.5), ty = C(y & 1) * C(0.5);
+        const C t = rnd<T>(lerp(lerp(p00, p01, tx), lerp(p10, p11, tx), ty));
+        v = in ? (((x | y) & 1) ? t : lat) : V(0);
+      }
+    }
+    if (W > 8 && y == 1) mine[-W] = mine[BUF - W] = V(0);  // row 0 of both buffers
+  }
+  auto step = [&](int buf) {
+    V ym, yp;
+    if constexpr (W == 8) {
+      const V dn = __shfl_up(v, 8, 64), up = __shfl_down(v, 8, 64);
+      ym = lane < 8 ? V(0) : dn;
+      yp = lane < 56 ? up : V(0);
+    } else {
+      if (on) mine[buf * BUF] = v;
+      __syncthreads();
+      if (!on) return;
+      ym = mine[buf * BUF - W];
+      yp = mine[buf * BUF + (y < W ? W : 0)];  // (row W is the boundary's)
+    }
+    const V xm = lane_prev(v), xp = lane_next(v);
+    V nv;
+    if constexpr (VAR) {
+      const V flux = fmac(cw, v - xm, ce * (v - xp)) + fmac(cs, v - ym, cn * (v - yp));
+      nv = fmac(ws, fmac(hl2, r, -flux), v);
+    } else {
+      nv = relax_const<V>(v, (xm + xp) + (ym + yp), r, w, hl2, V(4));
+    }
+    pv = v;
+    if constexpr (EXACT)
+      v = in ? nv : V(0);
+    else
+      v = in ? rnd<T>(nv) : V(0);
+  };
+  int t = 0;
+  for (; t + 2 <= it; t += 2) {  // a taken branch costs as much as four FP64 operations
+    step(1);
+    step(0);
+  }
+  if (t < it) step(1);
+  if (in) {
+    C* oc = me + ((it & 1) ? 2 * S * S : S * S);
+    C* op = me + ((it & 1) ? S * S : 2 * S * S);
+    oc[i] = EXACT ? rnd<T>(C(v)) : C(v);
+    op[i] = EXACT ? rnd<T>(C(pv)) : C(pv);
+  }
+}
+
+// Full weighting of side 2 S - 1 (F) onto the 2D level of side S in the same
+// rows of lanes (as k_restrict_2d: rows, then their sum).
+template <typename T, typename V, int S>
+__device__ __forceinline__ void row_restrict(const typename Tr<T>::C* F, V* R) {
+  constexpr int W = ROW_W<S>, NF = 2 * S - 1;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  if (wv >= W * W / 64) return;
+  const int x = 1 + (lane & (W - 1)), y = 1 + (W == 8 ? 0 : wv * (64 / W)) + lane / W;
+  if (x > S - 2 || y > S - 2) return;
+  const typename Tr<T>::C* p = F + 2 * y * NF + 2 * x;
+  auto rs = [&](int o) { return fmac(V(2), V(p[o]), V(p[o - 1]) + V(p[o + 1])); };
+  const V top = rs(-NF), mid = rs(0), bot = rs(NF);
+  const V v = fmac(V(2), mid, top + bot) * V(0.0625);
+  R[y * S + x] = sizeof(V) != sizeof(typename Tr<T>::C) ? v : V(rnd<T>(typename Tr<T>::C(v)));
+}
+
+// The interior node of a 3D level of side S that the lane holds (x, y, z from 1).
+template <int S>
+__device__ __forceinline__ bool box_node(int& I, int& J, int& K) {
+  constexpr int NI = S - 2;
+  const bool on = int(threadIdx.x) < NI * NI * NI;
+  const int i = on ? int(threadIdx.x) : 0;
+  K = 1 + i / (NI * NI);
+  J = 1 + i / NI % NI;
+  I = 1 + i % NI;
+  return on;
+}
+
+// Full weighting of side 2 S - 1 (F) onto the 3D level of side S, one node per
+// lane (as k_restrict_3d: rows, planes, then their sum).
+template <typename T, typename V, int S>
+__device__ __forceinline__ void box_restrict(const typename Tr<T>::C* F, V* R) {
+  constexpr int NF = 2 * S - 1, FPL = NF * NF;
+  int I, J, K;
+  if (!box_node<S>(I, J, K)) return;
+  const typename Tr<T>::C* p = F + 2 * K * FPL + 2 * J * NF + 2 * I;
+  auto rs = [&](int o) { return fmac(V(2), V(p[o]), V(p[o - 1]) + V(p[o + 1])); };
+  auto ps = [&](int o) { return fmac(V(2), rs(o), rs(o - NF) + rs(o + NF)); };
+  const V top = ps(-FPL), mid = ps(0), bot = ps(FPL);
+  const V v = fmac(V(2), mid, top + bot) * V(0.015625);
+  R[(K * S + J) * S + I] = sizeof(V) != sizeof(typename Tr<T>::C) ? v : V(rnd<T>(typename Tr<T>::C(v)));
+}
+
+// A 3D level of side S, one node per lane, its neighbours through LDS: the
+// hand-over from the next coarser level's arrays (hi: side (S + 1) / 2, ith
+// iterations; 0 if zero) and its iterations.  X holds R, then the two iterates
+// V of the FP64 coarsest level (EXACT) or the level's own P, Q; me is the
+// level's arrays.  The final pair ends in P and Q where its parity puts it.
+template <typename T, typename V, int S, typename Sync>
+__device__ __forceinline__ void box_level(V* X, typename Tr<T>::C* me, int it, V w, bool zero,
+                                          const typename Tr<T>::C* hi, int ith, Sync&& sync) {
+  using C = typename Tr<T>::C;
+  constexpr bool EXACT = sizeof(V) != sizeof(C);
+  constexpr int PL = S * S, N = S * S * S, H = (S + 1) / 2, HN = H * H * H;
+  constexpr double h = 1.0 / double(S - 1);
+  const V hl2 = V(h * h);
+  int I, J, K;
+  const bool on = box_node<S>(I, J, K);
+  const int i = (K * S + J) * S + I;
+  V* const xa = X + N;
+  V* const xb = X + 2 * N;
+  const V rv = X[i];
+  V c = V(0), prev = V(0);
+  if constexpr (!EXACT && S > 3) {
+    if (!zero) {
+      // lattice nodes of the coarser level take its x_it, the others the
+      // interpolant of its x_{it-1}
+      const C* cur = hi + ((ith & 1) ? 2 : 1) * HN;
+      const C* p = hi + ((ith & 1) ? 1 : 2) * HN;
+      const int c0 = ((K >> 1) * H + (J >> 1)) * H + (I >> 1);
+      const C tx = C(I & 1) * C(0.5), ty = C(J & 1) * C(0.5), tz = C(K & 1) * C(0.5);
+      const C lat = cur[c0];
+      p += c0;
+      const C* p2 = p + H * H;
+      const C top = lerp(lerp(p[0], p[1], tx), lerp(p[H], p[H + 1], tx), ty);
+      const C bot = lerp(lerp(p2[0], p2[1], tx), lerp(p2[H], p2[H + 1], tx), ty);
+      c = ((I | J | K) & 1) ? rnd<T>(lerp(top, bot, tz)) : lat;
+    }
+  }
+  if (on) xa[i] = c;
+  sync();
+  auto step = [&](const V* src, V* dst) {
+    prev = c;
+    if (on) {
+      const V q = ((src[i - 1] + src[i + 1]) + (src[i - S] + src[i + S])) + (src[i - PL] + src[i + PL]);
+      c = relax_const<V>(c, q, rv, w, hl2, V(6));
+      if constexpr (!EXACT) c = rnd<T>(c);
+      dst[i] = c;
+    }
+    sync();
+  };
+  int t = 0;
+  for (; t + 2 <= it; t += 2) {
+    step(xa, xb);
+    step(xb, xa);
+  }
+  if (t < it) step(xa, xb);
+  if constexpr (EXACT) {
+    if (on) {
+      me[((it & 1) ? 1 : 2) * N + i] = rnd<T>(C(prev));
+      me[((it & 1) ? 2 : 1) * N + i] = rnd<T>(C(c));
+    }
+    sync();
+  }
 }
 
 // ---- one workgroup -----------------------------------------------------
@@ -217,17 +432,15 @@ __device__ __forceinline__ void tail_block(const TailArgs<T>& q, const TailRun& 
   using C = typename Tr<T>::C;
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_done;
-  const int n = q.nms, nlev = q.nlev, ktop = nlev - 1;
+  const int n = q.nms, nlev = q.nlev;
+  const int S1 = (n + 1) / 2, Stop = ((n - 1) >> (nlev - 1)) + 1;  // sides of the next level and the coarsest
   const TailNodes<D> tn(n);
   C* base = reinterpret_cast<C*>(smem);
-  C* R0 = base;  // level ms's right-hand side; then R, P, Q of every coarser level
+  C* R0 = base;  // 3D: level ms's right-hand side, then R, P, Q of every coarser level
+  C* E0 = base;  // 2D: an exchange row per wave, then the coarser levels' arrays
   double* A0 = reinterpret_cast<double*>(smem + q.a_off);
   double* top64 = reinterpret_cast<double*>(smem + q.t_off);
   double* sums = reinterpret_cast<double*>(smem + q.s_off);
-  auto side = [&](int k) { return ((n - 1) >> k) + 1; };
-  auto lvl = [&](int k, int which) {
-    return k == 0 ? R0 : base + q.lv[k].off + which * tail_count<D>(side(k));
-  };
   const C w = C(q.w);
 
   DevState st = *q.st;
@@ -258,12 +471,10 @@ __device__ __forceinline__ void tail_block(const TailArgs<T>& q, const TailRun& 
   if (VAR)
     for (int i = threadIdx.x; i < n * n; i += TAIL_NT) A0[i] = q.a[int64_t(i / n) * q.ap + i % n];
   // the coarser levels' arrays start at 0 (their boundary nodes stay so)
-  if (nlev > 1) {
-    const int end = q.lv[ktop].off + 3 * tail_count<D>(side(ktop));
-    for (int i = q.lv[1].off + int(threadIdx.x); i < end; i += TAIL_NT) base[i] = C(0);
-  }
+  for (int i = LEV_OFF<D, (D == 2 ? 33 : 9)> + int(threadIdx.x); i < LEV_END<D>; i += TAIL_NT) base[i] = C(0);
+  if (SOLVE && threadIdx.x < 128) sums[threadIdx.x] = 0.0;
   if (TOP64)
-    for (int i = threadIdx.x; i < 3 * tail_count<D>(side(ktop)); i += TAIL_NT) top64[i] = 0.0;
+    for (int i = threadIdx.x; i < 3 * tail_count<D>(Stop); i += TAIL_NT) top64[i] = 0.0;
   if (!SOLVE && run.cycle >= 0) {
     const double s = fin_sum(q.partials, q.count);
     if (threadIdx.x == 0) {
@@ -295,12 +506,53 @@ __device__ __forceinline__ void tail_block(const TailArgs<T>& q, const TailRun& 
     for (int k = 0; k < 4; ++k) ws[k] = w / ((C(fx[k]) + C(x_next<D>(1.0, fx[k]))) + (C(fy[k]) + C(fy[k + 1])));
   }
 
+  // waves whose nodes all lie off the grid only take part in the barriers
+  const bool wave_on = D == 2 ? 4 * tn.wv + 1 <= n - 2 : tn.wv + 1 <= n - 2;
+  const bool wave_put = (D == 2 ? 4 * tn.wv : tn.wv) <= n - 2;  // (the boundary's values too)
+  // iterations of the level of a side, read once
+  constexpr int NSIDE = D == 2 ? 5 : 3;  // sides 3, 5, 9 (17, 33)
+  int its[NSIDE];
+#pragma unroll
+  for (int j = 0, S = 3; j < NSIDE; ++j, S = 2 * S - 1) {
+    int k = 1;
+    while (((n - 1) >> k) + 1 > S) ++k;
+    its[j] = S < n && S >= Stop ? q.it[k] : 0;
+  }
+  const int it0 = q.it[0];
+  const C hl20 = C(q.hl2);
+  // 2D: the restriction of level ms's right-hand side, from registers (as
+  // k_restrict_2d: row sums, then their sum): a lane's rows y0 + 1 and y0 + 3
+  // are coarse rows; the row above the second comes from the next wave
+  auto row_sum = [&](auto two, C c) {
+    using V = decltype(two);
+    return fmac(two, V(c), V(lane_prev(c)) + V(lane_next(c)));
+  };
+  auto put_first = [&](const C (&rr)[4]) {
+    if (wave_on) E0[tn.wv * 64 + tn.lane] = rr[0];
+  };
+  auto get_first = [&](const C (&rr)[4], auto two, auto* R) {
+    if (!wave_on) return;
+    using V = decltype(two);
+    const int S = S1;
+    const C up = 4 * tn.wv + 5 <= n - 2 ? E0[(tn.wv + 1) * 64 + tn.lane] : C(0);
+    const V s0 = row_sum(two, rr[0]), s1 = row_sum(two, rr[1]), s2 = row_sum(two, rr[2]), s3 = row_sum(two, rr[3]),
+            s4 = row_sum(two, up);
+    const V a = fmac(two, s1, s0 + s2) * V(0.0625), b = fmac(two, s3, s2 + s4) * V(0.0625);
+    auto put = [&](int J, V v) {
+      if (!(tn.x & 1) && tn.x <= n - 3 && J <= S - 2)
+        R[J * S + (tn.x >> 1)] = sizeof(V) != sizeof(C) ? v : V(rnd<T>(C(v)));
+    };
+    put(2 * tn.wv + 1, a);
+    put(2 * tn.wv + 2, b);
+  };
+
   for (int cyc = SOLVE ? run.c0 : 0;; ++cyc) {
     if constexpr (SOLVE) {
       // ---- residual and its norm
       const TailExchange<D, double> ex{reinterpret_cast<double*>(smem + q.x_off)};
-      ex.put(tn, uv);
+      if (wave_put) ex.put(tn, uv);
       __syncthreads();
+      if (wave_on) {
       double ym0, yp3, zm[4], zp[4];
       ex.get_y(tn, uv, ulo, ym0, yp3);
       if (D == 3) ex.get_z(tn, uzlo, zm, zp);
@@ -362,12 +614,17 @@ __device__ __forceinline__ void tail_block(const TailArgs<T>& q, const TailRun& 
       };
       partial(sr, sums);
       if (first) partial(sf, sums + 64);
+      if (D == 3) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (tn.in(k)) R0[o0 + (tn.y0 + k) * n] = r[k];
+        for (int k = 0; k < 4; ++k)
+          if (tn.in(k)) R0[o0 + (tn.y0 + k) * n] = r[k];
+      }
+      }  // wave_on
+      if (D == 2) put_first(r);
       __syncthreads();
       if (tn.wv == 0) {
         int cnt;
+        const bool first = cyc == 0;
         auto total = [&](double* p) {
           double v;
           if (D == 2 && !q.rr) {  // four waves (16 rows) per partial sum
@@ -405,185 +662,200 @@ __device__ __forceinline__ void tail_block(const TailArgs<T>& q, const TailRun& 
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         r[k] = tn.in(k) ? r[k] : C(0);
-        if (tn.in(k)) R0[o0 + (tn.y0 + k) * n] = r[k];
+        if (D == 3 && tn.in(k)) R0[o0 + (tn.y0 + k) * n] = r[k];
       }
+      if (D == 2) put_first(r);
       __syncthreads();
     }
 
-    // ---- restriction pyramid (full weighting, as k_restrict_*), one node per lane
-    auto restrict_to = [&](int k) {
-      const int nf = side(k - 1), nc = side(k), ni = nc - 2, cnt = tail_count<D>(ni);
-      const int i = threadIdx.x;
-      if (i >= cnt) return;
-      const C* F = lvl(k - 1, 0);
-      int I, J, K;
-      tail_split<D>(i, ni, q.lv[k].inv_ni, I, J, K);
-      ++I, ++J, K += D == 3;
-      const int o = (D == 3 ? K * nc * nc : 0) + J * nc + I;
-      const int fp = nf, fpl = nf * nf;
-      const int c = (D == 3 ? 2 * K * fpl : 0) + 2 * J * fp + 2 * I;
-      auto weigh = [&](auto two, auto scale) {  // as k_restrict_*: rows, then planes
-        using V = decltype(two);
-        auto rs = [&](int p) { return fmac(two, V(F[p]), V(F[p - 1]) + V(F[p + 1])); };
-        if (D == 2) {
-          const V top = rs(c - fp), mid = rs(c), bot = rs(c + fp);
-          return fmac(two, mid, top + bot) * scale;
+    // ---- the coarser levels: sides below n, not below the schedule's coarsest
+    double* const X64 = reinterpret_cast<double*>(smem + q.x_off);
+    C* const X = reinterpret_cast<C*>(smem + q.x_off);
+    auto has = [&](int S) { return S <= S1 && S >= Stop; };
+    auto down = [&](auto sz) {  // the restriction onto side S
+      constexpr int S = decltype(sz)::value;
+      const bool t64 = TOP64 && S == Stop;
+      if constexpr (D == 2) {
+        const C* F = base + LEV_OFF<2, (S < 33 ? 2 * S - 1 : 33)>;
+        if (S == S1) {
+          if (t64)
+            get_first(r, 2.0, top64);
+          else
+            get_first(r, C(2), base + LEV_OFF<2, S>);
+        } else if constexpr (S < 33) {
+          if (t64)
+            row_restrict<T, double, S>(F, top64);
+          else
+            row_restrict<T, C, S>(F, base + LEV_OFF<2, S>);
         }
-        auto ps = [&](int p) { return fmac(two, rs(p), rs(p - fp) + rs(p + fp)); };
-        const V top = ps(c - fpl), mid = ps(c), bot = ps(c + fpl);
-        return fmac(two, mid, top + bot) * scale;
-      };
-      if (TOP64 && k == ktop)
-        top64[o] = weigh(2.0, D == 2 ? 0.0625 : 0.015625);
-      else
-        lvl(k, 0)[o] = rnd<T>(weigh(C(2), D == 2 ? C(0.0625) : C(0.015625)));
+      } else {
+        const C* F = S == S1 ? base : base + LEV_OFF<3, (S < 9 ? 2 * S - 1 : 9)>;
+        if (t64)
+          box_restrict<T, double, S>(F, top64);
+        else
+          box_restrict<T, C, S>(F, base + LEV_OFF<3, S>);
+      }
     };
-
-    // ---- a coarser level: hand-over from the level above (or 0) and its
-    // iterations, one node per lane; sync() between phases
-    auto run_coarse = [&](int k, auto&& sync) {
-      const int nk = side(k), pl = nk * nk, ni = nk - 2, cnt = tail_count<D>(ni);
-      const bool on = int(threadIdx.x) < cnt;
-      int I, J, K;
-      tail_split<D>(on ? int(threadIdx.x) : 0, ni, q.lv[k].inv_ni, I, J, K);
-      ++I, ++J, K += D == 3;
-      const int i = (D == 3 ? K * pl : 0) + J * nk + I;
-      C* xa = lvl(k, 1);
-      C* xb = lvl(k, 2);
-      const int it = q.lv[k].it;
-      const int as = 1 << k;
-      const double* ap = A0 + J * as * n + I * as;
-      if (TOP64 && k == ktop) {
-        double* ya = top64 + tail_count<D>(nk);
-        double* yb = ya + tail_count<D>(nk);
-        const double rv = top64[i], hl2d = q.lv[k].hl2;
-        VarNode<double> vn;
-        if (VAR) vn.set(ap[0], ap[-as], ap[as], ap[-as * n], ap[as * n], q.w);
-        double c = 0.0, prev = 0.0;
-        if (on) ya[i] = 0.0;
-        sync();
-        for (int t = 1; t <= it; ++t) {
-          const double* src = (t & 1) ? ya : yb;
-          double* dst = (t & 1) ? yb : ya;
-          prev = c;
-          if (on) {
-            c = tail_relax<D, VAR>(src, i, nk, pl, c, rv, q.w, hl2d, vn);
-            dst[i] = c;
+    auto up = [&](auto sz, int it, int ith, auto&& sync) {  // side S's hand-over and iterations
+      constexpr int S = decltype(sz)::value;
+      const bool t64 = TOP64 && S == Stop;
+      C* const me = base + LEV_OFF<D, S>;
+      const C* hi = base + LEV_OFF<D, (S > 3 ? (S + 1) / 2 : 3)>;
+      if constexpr (D == 2) {
+        const int as = (n - 1) / (S - 1);
+        if (t64)
+          row_level<T, double, VAR, S>(top64, me, it, q.w, true, hi, 0, A0, n, as, X64);
+        else
+          row_level<T, C, VAR, S>(me, me, it, w, S == Stop, hi, ith, A0, n, as, X);
+      } else {
+        if (t64)
+          box_level<T, double, S>(top64, me, it, q.w, true, hi, 0, sync);
+        else
+          box_level<T, C, S>(me, me, it, w, S == Stop, hi, ith, sync);
+      }
+    };
+    using S33 = std::integral_constant<int, 33>;
+    using S17 = std::integral_constant<int, 17>;
+    using S9 = std::integral_constant<int, 9>;
+    using S5 = std::integral_constant<int, 5>;
+    using S3 = std::integral_constant<int, 3>;
+    auto one_wave = [] { wave_sync(); };
+    auto all_waves = [] { __syncthreads(); };
+    if (nlev > 1) {
+      if constexpr (D == 2) {
+        if (has(33)) {
+          down(S33());
+          __syncthreads();
+        }
+        if (has(17)) {
+          down(S17());
+          __syncthreads();
+        }
+        // the first restriction takes every wave's registers; the rest of the
+        // levels of one wave is that wave's
+        if (S1 <= 9) {
+          if (S1 == 9)
+            down(S9());
+          else if (S1 == 5)
+            down(S5());
+          else
+            down(S3());
+          __syncthreads();
+        }
+        if (Stop <= 9) {
+          if (tn.wv == 0) {
+            if (has(9)) {
+              if (S1 > 9) down(S9());
+              wave_sync();
+            }
+            if (has(5)) {
+              if (S1 > 5) down(S5());
+              wave_sync();
+            }
+            if (has(3)) {
+              if (S1 > 3) down(S3());
+              wave_sync();
+              up(S3(), its[0], 0, one_wave);
+              wave_sync();
+            }
+            if (has(5)) {
+              up(S5(), its[1], its[0], one_wave);
+              wave_sync();
+            }
+            if (has(9)) up(S9(), its[2], its[1], one_wave);
           }
-          sync();
+          __syncthreads();
         }
-        if (on) {  // the final pair where run_coarse leaves every level's: by the parity of it
-          ((it & 1) ? xa : xb)[i] = rnd<T>(C(prev));
-          ((it & 1) ? xb : xa)[i] = rnd<T>(C(c));
+        if (has(17)) {
+          up(S17(), its[NSIDE > 3 ? 3 : 0], its[2], all_waves);
+          __syncthreads();
         }
-        sync();
-        return;
+        if (has(33)) {
+          up(S33(), its[NSIDE > 3 ? 4 : 0], its[NSIDE > 3 ? 3 : 0], all_waves);
+          __syncthreads();
+        }
+      } else {
+        if (has(9)) {
+          down(S9());
+          __syncthreads();
+        }
+        if (Stop <= 5) {  // sides 5 and 3: the first wave's
+          if (tn.wv == 0) {
+            if (has(5)) {
+              down(S5());
+              wave_sync();
+            }
+            if (has(3)) {
+              down(S3());
+              wave_sync();
+              up(S3(), its[0], 0, one_wave);
+            }
+            if (has(5)) up(S5(), its[1], its[0], one_wave);
+          }
+          __syncthreads();
+        }
+        if (has(9)) up(S9(), its[2], its[1], all_waves);
       }
-      const C hl2 = C(q.lv[k].hl2);
-      VarNode<C> vn;
-      if (VAR) vn.set(ap[0], ap[-as], ap[as], ap[-as * n], ap[as * n], w);
-      const C rv = lvl(k, 0)[i];
-      C c = C(0);
-      if (k < ktop) {
-        // lattice nodes of level k + 1 take its x_it, the others the
-        // interpolant of its x_{it-1}
-        const int nh = side(k + 1), ph = nh * nh, ith = q.lv[k + 1].it;
-        const C* cur = lvl(k + 1, (ith & 1) ? 2 : 1);
-        const C* prv = lvl(k + 1, (ith & 1) ? 1 : 2);
-        const int c0 = (D == 3 ? (K >> 1) * ph : 0) + (J >> 1) * nh + (I >> 1);
-        const C tx = C(I & 1) * C(0.5), ty = C(J & 1) * C(0.5), tz = C(K & 1) * C(0.5);
-        const C lat = cur[c0];
-        C v;
-        if (D == 2) {
-          const C top = lerp(prv[c0], prv[c0 + 1], tx), bot = lerp(prv[c0 + nh], prv[c0 + nh + 1], tx);
-          v = lerp(top, bot, ty);
-        } else {
-          const C* p = prv + c0;
-          const C* p2 = p + ph;
-          const C top = lerp(lerp(p[0], p[1], tx), lerp(p[nh], p[nh + 1], tx), ty);
-          const C bot = lerp(lerp(p2[0], p2[1], tx), lerp(p2[nh], p2[nh + 1], tx), ty);
-          v = lerp(top, bot, tz);
-        }
-        c = (!(I & 1) && !(J & 1) && !(K & 1)) ? lat : rnd<T>(v);
-      }
-      if (on) xa[i] = c;
-      sync();
-      for (int t = 1; t <= it; ++t) {
-        const C* src = (t & 1) ? xa : xb;
-        C* dst = (t & 1) ? xb : xa;
-        if (on) {
-          c = rnd<T>(tail_relax<D, VAR>(src, i, nk, pl, c, rv, w, hl2, vn));
-          dst[i] = c;
-        }
-        sync();
-      }
-    };
-
-    // levels ks .. ktop have at most 64 interior nodes: the first wave's
-    int ks = 1;
-    while (ks < nlev && tail_count<D>(side(ks) - 2) > 64) ++ks;
-    for (int k = 1; k < ks; ++k) {
-      restrict_to(k);
-      __syncthreads();
     }
-    if (ks < nlev) {
-      if (tn.wv == 0) {
-        for (int k = ks; k < nlev; ++k) {
-          restrict_to(k);
-          wave_sync();
-        }
-        for (int k = ktop; k >= ks; --k) run_coarse(k, [] { wave_sync(); });
-      }
-      __syncthreads();
-    }
-    for (int k = ks - 1; k >= 1; --k) run_coarse(k, [] { __syncthreads(); });
 
     // ---- the finest level, in registers
     C v[4] = {C(0), C(0), C(0), C(0)}, pv[4];
-    if (nlev > 1) {
-      const int nh = side(1), ph = nh * nh, ith = q.lv[1].it;
-      const C* cur = lvl(1, (ith & 1) ? 2 : 1);
-      const C* prv = lvl(1, (ith & 1) ? 1 : 2);
-      // rows y0 .. y0 + 3 (y0 odd) lie in coarser rows j0, j0 + 1, j0 + 1,
-      // j0 + 2; indices of lanes off the grid are clamped, their values dropped
-      const int xi = min(tn.x >> 1, nh - 2), j0 = tn.y0 >> 1, zk = D == 3 ? min(tn.z >> 1, nh - 2) : 0;
-      const C tx = C(tn.x & 1) * C(0.5), tz = C(tn.z & 1) * C(0.5);
-      C yi[2][4];
+    if (nlev > 1 && wave_on) {
+      const int nh = S1, ph = nh * nh;
+      const int ith = q.it[1];
+      const C* base1;
+      if (D == 2)
+        base1 = base + (nh == 33 ? LEV_OFF<2, 33> : nh == 17 ? LEV_OFF<2, 17> : nh == 9 ? LEV_OFF<2, 9>
+                        : nh == 5 ? LEV_OFF<2, 5> : LEV_OFF<2, 3>);
+      else
+        base1 = base + (nh == 9 ? LEV_OFF<3, 9> : nh == 5 ? LEV_OFF<3, 5> : LEV_OFF<3, 3>);
+      const C* cur = base1 + ((ith & 1) ? 2 : 1) * tail_count<D>(nh);
+      const C* prv = base1 + ((ith & 1) ? 1 : 2) * tail_count<D>(nh);
+      if constexpr (D == 2) {
+        hand_over_2d<T>(prv, cur, nh, tn.x, tn.y0, v);
 #pragma unroll
-      for (int e = 0; e < (D == 3 ? 2 : 1); ++e) {
-        C xr[4];
+        for (int k = 0; k < 4; ++k) v[k] = tn.in(k) ? v[k] : C(0);
+      } else {
+        // rows y0 .. y0 + 3 (y0 odd) lie in coarser rows j0, j0 + 1, j0 + 1,
+        // j0 + 2; indices of lanes off the grid are clamped, their values dropped
+        const int xi = min(tn.x >> 1, nh - 2), j0 = tn.y0 >> 1, zk = min(tn.z >> 1, nh - 2);
+        const C tx = C(tn.x & 1) * C(0.5), tz = C(tn.z & 1) * C(0.5);
+        C yi[2][4];
 #pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          const C* p = prv + (D == 3 ? (zk + e) * ph : 0) + min(j0 + d, nh - 1) * nh + xi;
-          xr[d] = lerp(p[0], p[1], tx);
+        for (int e = 0; e < 2; ++e) {
+          C xr[4];
+#pragma unroll
+          for (int d = 0; d < 4; ++d) {
+            const C* p = prv + (zk + e) * ph + min(j0 + d, nh - 1) * nh + xi;
+            xr[d] = lerp(p[0], p[1], tx);
+          }
+          yi[e][0] = lerp(xr[0], xr[1], C(0.5));
+          yi[e][1] = lerp(xr[1], xr[2], C(0));
+          yi[e][2] = lerp(xr[1], xr[2], C(0.5));
+          yi[e][3] = lerp(xr[2], xr[3], C(0));
         }
-        yi[e][0] = lerp(xr[0], xr[1], C(0.5));
-        yi[e][1] = lerp(xr[1], xr[2], C(0));
-        yi[e][2] = lerp(xr[1], xr[2], C(0.5));
-        yi[e][3] = lerp(xr[2], xr[3], C(0));
-      }
-      const bool even = !(tn.x & 1) && (D == 2 || !(tn.z & 1));
+        const bool even = !(tn.x & 1) && !(tn.z & 1);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        C t = D == 3 ? lerp(yi[0][k], yi[1][k], tz) : yi[0][k];
-        if (k & 1) {  // an even row: a lattice node of level 1 where x (and z) are even
-          const C lat = cur[(D == 3 ? zk * ph : 0) + min(j0 + 1 + (k >> 1), nh - 1) * nh + xi];
-          t = even ? lat : rnd<T>(t);
-        } else {
-          t = rnd<T>(t);
+        for (int k = 0; k < 4; ++k) {
+          C t = rnd<T>(lerp(yi[0][k], yi[1][k], tz));
+          if (k & 1) {  // an even row: a lattice node of level 1 where x and z are even
+            const C lat = cur[zk * ph + min(j0 + 1 + (k >> 1), nh - 1) * nh + xi];
+            t = even ? lat : t;
+          }
+          v[k] = tn.in(k) ? t : C(0);
         }
-        v[k] = tn.in(k) ? t : C(0);
       }
     }
-    const C hl2 = C(q.lv[0].hl2);
-    const int it = q.lv[0].it;
+    const C hl2 = hl20;
+    const int it = it0;
     constexpr int XN = D == 2 ? 2 * 16 * 64 : 4 * TAIL_NT;
     C last[4];
     for (int t = 1; t <= it; ++t) {
       // two exchange buffers in turn: one barrier per iteration
       const TailExchange<D, C> ex{reinterpret_cast<C*>(smem + q.x_off) + (t & 1) * XN};
-      ex.put(tn, v);
+      if (wave_put) ex.put(tn, v);
       __syncthreads();
+      if (!wave_on) continue;
       C ym0, yp3, zm[4], zp[4];
       const C zero4[4] = {C(0), C(0), C(0), C(0)};
       ex.get_y(tn, v, C(0), ym0, yp3);
@@ -654,7 +926,6 @@ __global__ __launch_bounds__(TAIL_NT) void k_batch_small(const TailArgs<T>* __re
 
 // LDS layout: byte offsets of the areas behind the C arrays.
 struct TailLds {
-  int off[BATCH_MAX_LEVELS];
   int x_off, a_off, t_off, s_off;
   size_t bytes;
 };
@@ -665,11 +936,7 @@ TailLds tail_lds(int prec, int d, int nms, int nlev, bool top64, bool var, bool 
     const size_t nk = size_t((nms - 1) >> k) + 1;
     return d == 2 ? nk * nk : nk * nk * nk;
   };
-  size_t cnt = nodes(0);
-  for (int k = 1; k < nlev; ++k) {
-    L.off[k] = int(cnt);
-    cnt += 3 * nodes(k);
-  }
+  const size_t cnt = d == 2 ? LEV_END<2> : LEV_END<3>;
   auto take = [&](size_t& at, size_t bytes) {
     at = (at + 15) & ~size_t(15);
     const size_t o = at;
@@ -678,9 +945,11 @@ TailLds tail_lds(int prec, int d, int nms, int nlev, bool top64, bool var, bool 
   };
   size_t at = cnt * cs;
   const size_t xn = d == 2 ? 2 * 16 * 64 : 4 * size_t(TAIL_NT);  // one exchange buffer
-  L.x_off = take(at, std::max(2 * xn * cs, solve ? xn * 8 : size_t(0)));
+  const bool t64 = top64 && prec != PREC_F64;
+  const size_t rows64 = d == 2 && t64 ? 2 * 33 * 32 * 8 : 0;  // an FP64 level's exchange
+  L.x_off = take(at, std::max({2 * xn * cs, solve ? xn * 8 : size_t(0), rows64}));
   L.a_off = take(at, var ? nodes(0) * 8 : 0);
-  L.t_off = take(at, top64 && prec != PREC_F64 ? 3 * nodes(nlev - 1) * 8 : 0);
+  L.t_off = take(at, t64 ? 3 * nodes(nlev - 1) * 8 : 0);
   L.s_off = take(at, solve ? 128 * 8 : 0);
   L.bytes = at;
   return L;
@@ -708,13 +977,10 @@ template <typename T>
 TailArgs<T> make_args(const TailLds& L, int d, int nms, int nlev, const int* its, double omega, const double* a,
                       const Lay& al, DevState* st, double* hist) {
   TailArgs<T> q{};
-  for (int k = 0; k < nlev; ++k) {
-    const int nk = ((nms - 1) >> k) + 1;
-    const double h = 1.0 / double(nk - 1);
-    q.lv[k] = TailLevel{its[k], L.off[k], 1.0f / float(nk - 2), 0, h * h};
-  }
+  for (int k = 0; k < nlev; ++k) q.it[k] = its[k];
   q.nms = nms;
   q.nlev = nlev;
+  q.hl2 = (1.0 / double(nms - 1)) * (1.0 / double(nms - 1));
   q.w = a ? omega : omega / double(2 * d);
   q.x_off = L.x_off;
   q.a_off = L.a_off;

@@ -74,3 +74,12 @@ def test_options(B, torch_cuda, d, n, opts, prec):
 def test_more_cycles_than_one_launch(B, torch_cuda):
     """A slow schedule (level 0 alone) past the 64 cycles of one launch."""
     compare(B, torch_cuda, 2, 17, "fp64", False, cycles=130, levels=1)
+
+
+@pytest.mark.parametrize("var", [False, True])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("n,levels", [(65, 2), (65, 4), (65, 5), (129, 3), (129, 4), (129, 5), (129, 6)])
+def test_coarsest_side(B, torch_cuda, n, levels, prec, var):
+    """The coarsest level at each side the tail writes out (33, 17, 9, 5),
+    in FP64 in the reduced-precision cycles."""
+    compare(B, torch_cuda, 2, n, prec, var, cycles=3, levels=levels, max_i=5)
