@@ -397,18 +397,18 @@ def learned_section(P, W, torch, dev, n=1025, train_seeds=range(100, 164), held_
 
 
 LEARNED_MACS_PER_NODE = 576       # 3 features x 16 channels x 9 taps + 16 channels x 9 taps
-LEARNED_MFMA_FLOPS_PER_NODE = 8 * 16 * 32 * 2  # eight 16x16x32 MFMAs per 16 nodes of the halo-1 region
+LEARNED_MFMA_FLOPS = 8 * 16 * 16 * 32 * 2  # eight 16x16x32 MFMAs per 16 nodes of a row of the hidden layer
 BF16_MFMA_PEAK_TFLOPS = 2500.0
 
 
 def learned_kernel_rate(s, f, n, torch):
-    """The learned relaxation's level-0 iteration in one profiled learned
-    solve: time per launch, useful FLOP rate (the network's 576 MACs per
+    """The learned relaxation's level-0 iterations in one profiled learned
+    solve: time per iteration, useful FLOP rate (the network's 576 MACs per
     interior node) and the FLOP rate the matrix cores execute (six
-    first-layer and two second-layer MFMAs per 16-node row: the three-part
-    BF16 split of the activations, the zero-padded K slots and the halo
-    recompute of 16 x 16 regions for 14 x 14 owned nodes), both against the
-    dense BF16 MFMA peak."""
+    first-layer and two second-layer MFMAs per 16 nodes of a row: the
+    three-part BF16 split of the activations, the zero-padded K slots and the
+    halo recompute of the 32 x 32 blocks, which shrink by 3 nodes a side per
+    iteration of a launch), both against the dense BF16 MFMA peak."""
     u = torch.zeros_like(f)
     s.set_profiling(True)
     s.solve(f, u, tol=1e-10, raise_on_status=False)
@@ -417,12 +417,18 @@ def learned_kernel_rate(s, f, n, torch):
     launches = sum(e["launches"] for e in ent)
     if not launches:
         return None
-    t = sum(e["ms"] for e in ent) / 1e3 / launches
-    nodes = float(n - 2) ** 2
-    tiles = ((n - 2 + 13) // 14) ** 2
-    useful = 2.0 * LEARNED_MACS_PER_NODE * nodes / t / 1e12
-    executed = LEARNED_MFMA_FLOPS_PER_NODE * 256.0 * tiles / t / 1e12
-    return {"level0_launches": launches, "level0_avg_us": 1e6 * t,
+    iters, flops = 0, 0.0
+    for e in ent:
+        it = ((e["mode"] >> 4) & 3) + 1
+        widths = [32 - 6 * k for k in range(it)]
+        groups = sum(w * (2 if w > 16 else 1) for w in widths)
+        blocks = ((n - 2 + widths[-1] - 3) // (widths[-1] - 2)) ** 2
+        iters += e["launches"] * it
+        flops += e["launches"] * float(LEARNED_MFMA_FLOPS) * groups * blocks
+    t = sum(e["ms"] for e in ent) / 1e3
+    useful = 2.0 * LEARNED_MACS_PER_NODE * float(n - 2) ** 2 * iters / t / 1e12
+    executed = flops / t / 1e12
+    return {"level0_launches": launches, "level0_iterations": iters, "level0_avg_us": 1e6 * t / iters,
             "useful_TFLOPs": useful, "executed_mfma_TFLOPs": executed,
             "peak_TFLOPs": BF16_MFMA_PEAK_TFLOPS, "useful_frac": useful / BF16_MFMA_PEAK_TFLOPS,
             "executed_frac": executed / BF16_MFMA_PEAK_TFLOPS}

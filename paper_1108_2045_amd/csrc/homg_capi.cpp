@@ -290,12 +290,25 @@ bool top64(const homg_ctx* h) {
   return h->prec != PREC_F64 && h->active_smoother == 0 && h->top_level >= 1 && h->r64;
 }
 
+// Whether the learned iterations of level m run several to a launch on blocks
+// (level 0, or a compact lattice with a third array).
+bool learned_tiled(const homg_ctx* h, int m) {
+  return h->temporal == 2 && (m == 0 || (m < int(h->xp3.size()) && h->xp3[m])) && learned_tiles_lds(h->prec) <= h->lds_limit;
+}
+
+// Iterations of a learned level of side nm per launch: four recompute up to 4
+// nodes per owned one, which is free while the blocks fit the chip at once
+// (129^2: 13.7 us against 2 x 8.5 for two launches of two); from 257^2 on two
+// (257^2: the same 21 us either way, 513^2 31 against 45).
+int learned_per_launch(int nm) { return nm <= LEARNED_DEEP_SIDE ? LEARNED_TILE_IT : 2; }
+
 // Whether level mt's iterations (chained execution, damped Jacobi) run as
 // multi-iteration passes whose first pass takes its input iterate from level
 // mt + 1's compact state: level 0, or a compact lattice too large for one
 // workgroup.
 bool lat_target(const homg_ctx* h, int mt) {
-  if (h->temporal != 2 || h->active_smoother != 0 || mt < 0 || h->pow2) return false;
+  if (h->temporal != 2 || mt < 0 || h->pow2) return false;
+  if (h->active_smoother == 1) return mt + 1 < h->levels && learned_tiled(h, mt);
   if (top64(h) && mt == h->top_level) return false;  // starts from an FP64 x_0
   const int nm = (h->n - 1) / (1 << mt) + 1;
   if (nm < 5 || mt + 1 >= h->levels) return false;
@@ -617,6 +630,26 @@ homg_status run_level_learned(homg_ctx* h, int m, int it, bool first, bool last,
   const Lay& alm = am ? h->al[m] : none;
   const int l = 1 << m, nm = (h->n - 1) / l + 1;
   const double hl = double(l) / double(h->n - 1);
+  const L1State* l1 = h->lat_level == m ? &h->lat : nullptr;
+  h->lat_level = -1;
+  const bool tiled = learned_tiled(h, m);
+  if (l1 && !tiled)
+    return fail(h, HOMG_ERR_UNSUPPORTED, "the coarser level left no state for this level's iterations");
+  if (m == 0 && tiled) {
+    const int gmax = learned_per_launch(nm);
+    for (int t0 = 0; t0 < it; t0 += gmax) {
+      const int g = std::min(gmax, it - t0);
+      const bool zero = first && t0 == 0, accum = last && t0 + g == it;
+      const L1State* src = t0 == 0 ? l1 : nullptr;
+      LAUNCH_K(h, s, K_LEARNED, 0,
+               SW_TBLOCK | (zero ? SW_ZERO_OLD : 0) | (accum ? SW_ACCUM : 0) | ((g - 1) << 4) | (src ? 128 : 0),
+               launch_learned_tiles(h->prec, nm, g, hl, zero || src ? nullptr : h->e[*cur],
+                                    accum ? nullptr : h->e[1 - *cur], nullptr, h->el, h->r[0], h->rl[0], am, alm,
+                                    accum ? acc : nullptr, h->dl, src, h->w32, done, s));
+      *cur = 1 - *cur;
+    }
+    return HOMG_OK;
+  }
   if (m == 0) {
     for (int t = 0; t < it; ++t) {
       int mode = 0;
@@ -640,9 +673,23 @@ homg_status run_level_learned(homg_ctx* h, int m, int it, bool first, bool last,
                                   h->rl[m], am, alm, X[0], X[1], cl, h->w32, done, s));
     return finish_level(h, m, last, next_m, last ? SW_ACCUM : 0, X[0], X[1], cur, acc, done, s);
   }
-  if (!first && !chained_in)
+  if (!first && !chained_in && !l1)
     LAUNCH_K(h, s, K_GATHER, m, 0, launch_gather(h->prec, h->d, h->e[*cur], h->el, l, X[0], cl, done, s));
   int src = 0;
+  if (tiled) {  // (x_{it-1} of the last launch into the third array)
+    const int gmax = learned_per_launch(nm);
+    for (int t0 = 0; t0 < it; t0 += gmax) {
+      const int g = std::min(gmax, it - t0);
+      const bool zero = first && t0 == 0;
+      const L1State* ls = t0 == 0 ? l1 : nullptr;
+      LAUNCH_K(h, s, K_LEARNED, m, SW_TBLOCK | (zero ? SW_ZERO_OLD : 0) | ((g - 1) << 4) | (ls ? 128 : 0),
+               launch_learned_tiles(h->prec, nm, g, hl, zero || ls ? nullptr : X[src], X[1 - src],
+                                    t0 + g == it ? h->xp3[m] : nullptr, cl, h->r[m], h->rl[m], am, alm, nullptr, none,
+                                    ls, h->w32, done, s));
+      src = 1 - src;
+    }
+    return finish_level(h, m, last, next_m, last ? SW_ACCUM : 0, h->xp3[m], X[src], cur, acc, done, s);
+  }
   for (int t = 1; t <= it; ++t) {
     const int mode = (first && t == 1) ? SW_ZERO_OLD : 0;
     LAUNCH_K(h, s, K_LEARNED, m, mode,
@@ -658,18 +705,20 @@ homg_status run_level_learned(homg_ctx* h, int m, int it, bool first, bool last,
 // Number of leading schedule entries the coarse tail runs (0: none) and
 // the finest of their levels.  They must start at the coarsest level,
 // descend one level at a time, fit one workgroup, not be visited again, and
-// be followed by level ms - 1 (chained execution, damped Jacobi).
+// be followed by level ms - 1 (chained execution).
 int tail_levels(const homg_ctx* h, int* ms) {
   const int np = int(h->sched.size() / 2);
-  if (h->temporal != 2 || h->active_smoother != 0 || np < 3 || h->pow2) return 0;
+  if (h->temporal != 2 || np < 3 || h->pow2) return 0;
+  const bool learned = h->active_smoother == 1;
   if (h->sched[0] != h->top_level) return 0;
   int cnt = 0;
   for (int p = 0; p + 1 < np && p < BATCH_MAX_LEVELS; ++p) {
     const int m = h->sched[2 * p];
     if (m != h->top_level - p || m < 1) break;
     const int nm = (h->n - 1) / (1 << m) + 1;
-    if (nm > tail_max_side(h->d) ||
-        coarse_tail_lds(h->prec, h->d, nm, p + 1, top64(h), h->has_coef, false) > h->lds_limit)
+    if (learned ? nm > LEARNED_TAIL_SIDE || learned_tiles_lds(h->prec) > h->lds_limit
+                : nm > tail_max_side(h->d) ||
+                      coarse_tail_lds(h->prec, h->d, nm, p + 1, top64(h), h->has_coef, false) > h->lds_limit)
       break;
     cnt = p + 1;
   }
@@ -682,7 +731,7 @@ int tail_levels(const homg_ctx* h, int* ms) {
   // a last coarse level in reduced precision runs whole-grid iterations
   // (its iterate goes into u unrounded) and reads the whole grid, which the
   // tail does not write; level 0 takes the tail's state
-  if (cnt + 1 == np && h->prec != PREC_F64 && !(*ms == 1 && lat_target(h, 0))) return 0;
+  if (!learned && cnt + 1 == np && h->prec != PREC_F64 && !(*ms == 1 && lat_target(h, 0))) return 0;
   return cnt;
 }
 
@@ -865,12 +914,20 @@ homg_status enqueue_cycle(homg_ctx* h, const double* f, double* acc, int cycle, 
     for (int k = 0; k < ntail; ++k) its[k] = h->sched[2 * (ntail - 1 - k) + 1];
     const int nms = (h->n - 1) / (1 << ms) + 1;
     const bool next_last = size_t(ntail) + 1 == np;
-    const bool lat = lat_target(h, ms - 1) && !(next_last && h->prec != PREC_F64 && ms > 1);
+    const bool learned = h->active_smoother == 1;
+    const bool lat = lat_target(h, ms - 1) && !(!learned && next_last && h->prec != PREC_F64 && ms > 1);
     // the tail leaves level ms's state; level ms - 1's first pass
     // interpolates it, or else the multi-workgroup hand-over kernel does
     const Lay none;
-    LAUNCH_K(h, s, K_TAIL, ms, 1,
-             launch_coarse_tail(h->prec, h->d, nms, ntail, its, h->omega, h->has_coef ? h->a[ms] : nullptr,
+    if (learned)
+      LAUNCH_K(h, s, K_TAIL, ms, 8,
+               launch_learned_tail(h->prec, nms, ntail, its, h->has_coef ? h->a[ms] : nullptr,
+                                   h->has_coef ? h->al[ms] : none, h->r[ms], h->rl[ms], h->xc[2 * ms],
+                                   h->xc[2 * ms + 1], h->rl[ms], h->w32, f ? h->st : h->zero_st, h->hist,
+                                   f && h->fin_pending >= 0 ? h->partials : nullptr, h->fin_count, h->fin_pending, s));
+    else
+      LAUNCH_K(h, s, K_TAIL, ms, 1,
+               launch_coarse_tail(h->prec, h->d, nms, ntail, its, h->omega, h->has_coef ? h->a[ms] : nullptr,
                                 h->has_coef ? h->al[ms] : none, h->r[ms], h->rl[ms],
                                 h->xc[2 * ms], h->xc[2 * ms + 1], h->rl[ms], top64(h), f ? h->st : h->zero_st,
                                 h->hist, f && h->fin_pending >= 0 ? h->partials : nullptr, h->fin_count,

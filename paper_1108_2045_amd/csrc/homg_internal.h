@@ -395,6 +395,24 @@ hipError_t launch_learned_iter(int prec, int nm, double hl, const void* xi, cons
                                void* xo, const void* r, const Lay& rl, const double* a,
                                const Lay& al, double* u, const Lay& ul, const float* w, int mode,
                                const int* done, hipStream_t s);
+// Chained execution (homg_learned_tiles.hip).  Up to LEARNED_TILE_IT
+// relaxations of a lattice of side n in one launch: x_0 is 0, the array xo, or
+// the next coarser level's state l1; x_it into xn and x_{it-1} into xp
+// (nullable; layout cl, none may alias xo), or u += x_it.
+constexpr int LEARNED_TILE_IT = 4;
+constexpr int LEARNED_DEEP_SIDE = 129;  // largest side that takes so many (two above)
+hipError_t launch_learned_tiles(int prec, int n, int it, double hl, const void* xo, void* xn, void* xp, const Lay& cl,
+                                const void* r, const Lay& rl, const double* a, const Lay& al, double* u, const Lay& ul,
+                                const L1State* l1, const float* w, const int* done, hipStream_t s);
+// The leading coarse levels of the schedule, the finest of side n <=
+// LEARNED_TAIL_SIDE, in one workgroup (as launch_coarse_tail: restrictions
+// from r, its[k] iterations of the level 2^k times coarser, the finest level's
+// final pair into sprev and scur, the previous cycle's norm first).
+constexpr int LEARNED_TAIL_SIDE = 33;
+hipError_t launch_learned_tail(int prec, int n, int nlev, const int* its, const double* a, const Lay& al, const void* r,
+                               const Lay& rl, void* sprev, void* scur, const Lay& sl, const float* w, DevState* st,
+                               double* hist, const double* partials, int count, int cycle, hipStream_t s);
+size_t learned_tiles_lds(int prec);
 // Training on dense FP32 compact arrays of side nm.  fwd: z = delta - y (y if
 // delta is null).  bwd: per-workgroup partial sums of dL/dw (576) and E(z)
 // into part[j * pstride + row], rows = train_bwd_rows(nm); e0 = &E(delta).

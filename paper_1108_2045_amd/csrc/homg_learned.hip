@@ -21,8 +21,10 @@
 // The work is a dense 576-MAC contraction per node over LDS-resident tiles:
 // a workgroup owns a 14 x 14 block of lattice nodes and stages x and a on
 // its 20 x 20 halo region, the features on 18 x 18 and the hidden layer on
-// 16 x 16; both channel contractions run on the matrix cores (see the
-// inference section below).
+// 16 x 16; both channel contractions run on the matrix cores
+// (homg_learned_device.h).  k_learned_iter here runs one iteration per launch
+// (unchained execution, and lattices below 65^2 outside the one-workgroup
+// tail); chained execution runs several (homg_learned_tiles.hip).
 //
 // Training kernels (FP32, dense compact arrays): forward writes z = delta -
 // y; backward recomputes the tile's features and hidden layer, forms
@@ -41,6 +43,7 @@
 #include <type_traits>
 
 #include "homg_internal.h"
+#include "homg_learned_device.h"
 
 namespace homg {
 
@@ -159,7 +162,6 @@ __device__ __forceinline__ void stage_features(LDS& L, const XT* __restrict__ x,
 // node's window, seven instructions.  Its result leaves the lane the channels
 // 4 g + r of its node, the second layer's operand as it is when K slot g of
 // instruction r stands for channel 4 g + r.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 struct NetConst {
   float w1[7], w2[4];
   int off[7];  // of the lane's features from those of the node's window corner
@@ -195,100 +197,14 @@ __device__ __forceinline__ f32x4 hidden_row(const float4* f, const NetConst& n, 
 // xo = xi + y (or u += xi + y with ACCUM, the last iteration of a cycle).
 // ZERO: xi = 0 (the first iteration of a cycle; nothing is read from xi).
 //
-// The two channel contractions run on the matrix cores
-// (v_mfma_f32_16x16x32_bf16: D = A B + D with A 16 x 32, B 32 x 16, BF16
-// operands, FP32 accumulation).  Operand layout (one wave, lane l,
-// g = l / 16): A[i][k] with i = l % 16, k = 8 g + e; B[k][j] with
-// j = l % 16, same k; D[i][j] with j = l % 16, i = 4 g + r.  The weights
-// are BF16 values already; each FP32 activation is split exactly into three
-// BF16 parts (hi = its top 8 significant bits, mid = the next 8 of the
-// remainder, lo = the rest, which fits BF16 exactly since 24 = 3 x 8), so
-// every product is exact and only the FP32 accumulation rounds: FP32
-// arithmetic on the matrix cores.
-//
-// Per 16-node row of the tile's halo-1 region (four rows per wave):
-//   first layer  D1[c][node] = sum_s W1[c][s] F[s][node] over K slots
-//     s = 12 dy + 4 dx + ci of the 3 x 3 window (27 of 64 slots carry
-//     weights), with the features F read from LDS already split, four BF16
-//     per node (two MFMAs per part, six in all);
-//   H = max(D1, 0) on interior nodes, 0 elsewhere -- the lane holds
-//     channels 4g .. 4g+3 of its node, which is exactly the B operand the
-//     second layer needs, so H never leaves registers;
-//   second layer Z[tap][node] = sum_c W2[c][tap] H[c][node] (K slots
-//     8 g + e: hi / mid of channel 4 g + e % 4, then lo of channel 4 g + e
-//     and zeros: two MFMAs), written to LDS;
-// and after a barrier the output at a node is y = sum_k Z[k][node + o_k].
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
-struct Parts {  // an FP32 value as three BF16 parts, in the upper halves of FP32 words
-  uint32_t hi, mid, lo;
-};
-
-__device__ __forceinline__ Parts split3(float v) {
-  Parts p;
-  p.hi = __float_as_uint(v) & 0xffff0000u;
-  const float r1 = v - __uint_as_float(p.hi);
-  p.mid = __float_as_uint(r1) & 0xffff0000u;
-  p.lo = __float_as_uint(r1 - __uint_as_float(p.mid));
-  return p;
-}
-
-// Eight BF16-valued FP32 numbers as a BF16 vector (exact).
-__device__ __forceinline__ bf16x8 pack8(const float (&v)[8]) {
-  uint32_t p[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-    p[k] = (__float_as_uint(v[2 * k]) >> 16) | (__float_as_uint(v[2 * k + 1]) & 0xffff0000u);
-  return __builtin_bit_cast(bf16x8, p);
-}
-
-__device__ __forceinline__ uint32_t pair16(uint32_t lo_word, uint32_t hi_word) {
-  return (lo_word >> 16) | (hi_word & 0xffff0000u);
-}
-
-constexpr int ZS = TZS;
-
+constexpr int ZPL = NT + 4;  // one Z plane
 template <typename C>
 struct InferLds {
-  float z[NT * ZS];               // Z[node][tap] on the halo-1 region
+  float z[9 * ZPL];               // Z[tap][node] on the halo-1 region
   C x[2][R3 * R3];                // x on the halo-3 region, two tiles in flight
   float a[R3 * R3];               // coefficient on the halo-3 region
   uint64_t fb[3 * FPL];           // features: part, node; four BF16 each (channels 0-2, then 0)
 };
-
-// The lane's operands that do not change from tile to tile.  First-layer K
-// slot s (two MFMAs, s in [0, 64)) holds channel s % 4 of feature node
-// (dy, dx) = (s / 12, (s % 12) / 4) of the 3 x 3 window (channel 3 and
-// s >= 36 are zero weights): with the features stored as four BF16 per
-// node, a lane's eight slots of the first MFMA are two whole nodes and
-// those of the second one node (lanes 0-15) or nothing.
-struct LaneConst {
-  bf16x8 w1a, w1b, w2a, w2b;  // A operands: first layer (two MFMAs); second layer (two)
-};
-
-__device__ __forceinline__ LaneConst lane_const(const float* __restrict__ w) {
-  const int lane = threadIdx.x & 63;
-  const int ii = lane & 15, g = lane >> 4;
-  float va1[8], vb1[8], va[8], vb[8];
-  LaneConst k;
-  auto w1 = [&](int s) {  // W1[c = ii][ci][tap] at K slot s
-    const int dy = s / 12, dx = (s % 12) / 4, ci = s % 4;
-    return s < 36 && ci < 3 ? w[ii * 27 + ci * 9 + 3 * dy + dx] : 0.f;
-  };
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    va1[e] = w1(8 * g + e);
-    vb1[e] = w1(32 + 8 * g + e);
-    const float w2 = ii < 9 ? w[NW1 + (4 * g + (e & 3)) * 9 + ii] : 0.f;  // W2[c][tap = ii]
-    va[e] = w2;
-    vb[e] = e < 4 ? w2 : 0.f;
-  }
-  k.w1a = pack8(va1);
-  k.w1b = pack8(vb1);
-  k.w2a = pack8(va);
-  k.w2b = pack8(vb);
-  return k;
-}
 
 // Global inputs of one tile held in registers: x and a on the halo-3
 // region, r on the halo-2 region, at most two values each per lane.  They
@@ -336,79 +252,6 @@ struct TileInputs {
   }
 };
 
-__device__ __forceinline__ float frcp(float v) { return __builtin_amdgcn_rcpf(v); }
-
-// Features at feature node q of the tile (halo-2 region), split and stored.
-// The residual part is formed in the cycle precision C; the coefficient
-// factors (face harmonic means, their sum and the two ratios) in FP32 with
-// the hardware reciprocal -- all of it is rounded to FP32 for the network.
-template <typename C, bool VAR>
-__device__ __forceinline__ void put_features(InferLds<C>& L, const C* X, int q, bool interior, C rv,
-                                             C hl2) {
-  float f0 = 0.f, f1 = 0.f, f2 = 0.f;
-  if (interior) {
-    const int jj = q / R2, ii = q % R2;
-    const int c3 = (jj + 1) * R3 + (ii + 1);
-    const C xc = X[c3];
-    const C dw = xc - X[c3 - 1], de = xc - X[c3 + 1], ds = xc - X[c3 - R3], dn = xc - X[c3 + R3];
-    if constexpr (!VAR) {
-      f0 = float((hl2 * rv - (((dw + de) + ds) + dn)) * C(0.25));
-    } else {
-      const float ac = L.a[c3];
-      const float aw0 = L.a[c3 - 1], ae0 = L.a[c3 + 1], as0 = L.a[c3 - R3], an0 = L.a[c3 + R3];
-      const float aw = 2.f * ac * aw0 * frcp(ac + aw0), ae = 2.f * ac * ae0 * frcp(ac + ae0);
-      const float as = 2.f * ac * as0 * frcp(ac + as0), an = 2.f * ac * an0 * frcp(ac + an0);
-      const float sa = ((aw + ae) + as) + an;
-      const C flux = ((C(aw) * dw + C(ae) * de) + C(as) * ds) + C(an) * dn;
-      f0 = float((hl2 * rv - flux) * C(frcp(sa)));
-      f1 = f0 * ((ae - aw) * frcp(ae + aw));
-      f2 = f0 * ((an - as) * frcp(an + as));
-    }
-  }
-  const Parts p0 = split3(f0), p1 = split3(f1), p2 = split3(f2);
-  // one 8-byte store per part: channels 0, 1, 2 and a zero
-  auto node = [](uint32_t c0, uint32_t c1, uint32_t c2) {
-    return uint64_t(pair16(c0, c1)) | (uint64_t(c2 >> 16) << 32);
-  };
-  L.fb[q] = node(p0.hi, p1.hi, p2.hi);
-  L.fb[FPL + q] = node(p0.mid, p1.mid, p2.mid);
-  L.fb[2 * FPL + q] = node(p0.lo, p1.lo, p2.lo);
-}
-
-// Both layers for row jj of the halo-1 region (row J of the lattice); Z to LDS.
-template <typename C>
-__device__ __forceinline__ void row_contract(InferLds<C>& L, const LaneConst& k, int jj, bool row_in,
-                                             bool col_in) {
-  const int lane = threadIdx.x & 63;
-  const int ii = lane & 15, g = lane >> 4;
-  // the lane's window nodes (see lane_const): first MFMA two nodes, second
-  // MFMA node (2, 2) for lanes 0-15 (read by all lanes, kept by those)
-  const int na = g == 0 ? 0 : g == 1 ? 2 : g == 2 ? R2 + 1 : 2 * R2;
-  const int nb = g == 0 ? 1 : g == 1 ? R2 : g == 2 ? R2 + 2 : 2 * R2 + 1;
-  const uint64_t* fb = L.fb + jj * R2 + ii;
-  f32x4 d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int part = 0; part < 3; ++part) {
-    const uint64_t* fp = fb + part * FPL;
-    const uint64_t b1[2] = {fp[na], fp[nb]};
-    const uint64_t c = fp[2 * R2 + 2];
-    const uint64_t b2[2] = {g == 0 ? c : uint64_t(0), uint64_t(0)};
-    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k.w1a, __builtin_bit_cast(bf16x8, b1), d, 0, 0, 0);
-    d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k.w1b, __builtin_bit_cast(bf16x8, b2), d, 0, 0, 0);
-  }
-  const bool in = row_in && col_in;
-  Parts h[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) h[r] = split3((in & (d[r] > 0.f)) ? d[r] : 0.f);  // no short circuit: a select
-  const uint32_t ba[4] = {pair16(h[0].hi, h[1].hi), pair16(h[2].hi, h[3].hi), pair16(h[0].mid, h[1].mid),
-                          pair16(h[2].mid, h[3].mid)};
-  const uint32_t bb[4] = {pair16(h[0].lo, h[1].lo), pair16(h[2].lo, h[3].lo), 0u, 0u};
-  f32x4 z = {0.f, 0.f, 0.f, 0.f};
-  z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k.w2a, __builtin_bit_cast(bf16x8, ba), z, 0, 0, 0);
-  z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k.w2b, __builtin_bit_cast(bf16x8, bb), z, 0, 0, 0);
-  if (g < 3) *reinterpret_cast<f32x4*>(L.z + (jj * R1 + ii) * ZS + 4 * g) = z;  // taps 4g .. 4g+3
-}
-
 // The three stages of one tile (owned block at (J0, I0)): features from
 // x and a in LDS (r of the lane's two halo-2 slots in registers), both
 // contractions into Z, and the output sum at owned node (oj, oi).
@@ -416,11 +259,19 @@ template <typename C, bool VAR>
 __device__ __forceinline__ void tile_features(InferLds<C>& L, const C* X, int nm, int J0, int I0,
                                               const C (&rv)[2], C hl2) {
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int q = threadIdx.x + k * NT;
+  for (int j = 0; j < 2; ++j) {
+    const int q = threadIdx.x + j * NT;
     if (q < R2 * R2) {
       const int J = J0 - 2 + q / R2, I = I0 - 2 + q % R2;
-      put_features<C, VAR>(L, X, q, J >= 1 && J <= nm - 2 && I >= 1 && I <= nm - 2, rv[k], hl2);
+      float f0 = 0.f, f1 = 0.f, f2 = 0.f;
+      if (J >= 1 && J <= nm - 2 && I >= 1 && I <= nm - 2) {
+        const int c = (q / R2 + 1) * R3 + (q % R2 + 1);
+        const C xc = X[c];
+        FaceFactors k;
+        if constexpr (VAR) k.set(L.a[c], L.a[c - 1], L.a[c + 1], L.a[c - R3], L.a[c + R3]);
+        node_feature<VAR, C>(k, xc - X[c - 1], xc - X[c + 1], xc - X[c - R3], xc - X[c + R3], rv[j], hl2, f0, f1, f2);
+      }
+      store_features<FPL>(L.fb + q, f0, f1, f2);
     }
   }
 }
@@ -432,16 +283,8 @@ __device__ __forceinline__ void tile_contract(InferLds<C>& L, const LaneConst& k
 #pragma unroll
   for (int rr = 0; rr < 4; ++rr) {
     const int jj = wave * 4 + rr, J = J0 - 1 + jj;
-    row_contract<C>(L, kc, jj, J >= 1 && J <= nm - 2, col_in);
+    contract16<R2, FPL, ZPL>(L.z + jj * R1, L.fb + jj * R2, kc, col_in && J >= 1 && J <= nm - 2);
   }
-}
-
-template <typename C>
-__device__ __forceinline__ float tile_y(const InferLds<C>& L, int oj, int oi) {
-  float y = 0.f;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) y += L.z[((oj + k / 3) * R1 + (oi + k % 3)) * ZS + k];
-  return y;
 }
 
 template <typename T, bool ZERO, bool ACCUM, bool VAR>
@@ -487,7 +330,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
       const int oj = t / TO, oi = t % TO;
       const int J = J0 + oj, I = I0 + oi;
       if (J <= nm - 2 && I <= nm - 2) {
-        const C v = X[(oj + 3) * R3 + (oi + 3)] + C(tile_y(L, oj, oi));
+        const C v = X[(oj + 3) * R3 + (oi + 3)] + C(sum_taps<R1, ZPL>(L.z + oj * R1 + oi));
         if constexpr (ACCUM) {
           u[J * int(up) + I] += double(v);
         } else {
@@ -545,7 +388,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
       const int oj = t / TO, oi = t % TO;
       if (oj + 1 <= nm - 2 && oi + 1 <= nm - 2) {
         const int q = (oj + 3) * R3 + (oi + 3);
-        const C v = src[q] + C(tile_y(L, oj, oi));
+        const C v = src[q] + C(sum_taps<R1, ZPL>(L.z + oj * R1 + oi));
         dst[q] = stored<T>(v);  // each iterate rounded to the storage type, as stored by the multi-launch path
       }
     }
