@@ -386,20 +386,21 @@ homg_status run_level(homg_ctx* h, int m, int it, bool first, bool last, int nex
       // compact form: the level's marks alone; the whole grid is written
       // before level 0 and by the last level
       double* X[2] = {h->p2x[2 * m], h->p2x[2 * m + 1]};
-      int src = 0;
+      int src = 0, t0 = 0;
       if (h->p2_level == m) {
         // a level that follows itself goes on from its last state, whose
         // ghosts the last iteration left too
         src = h->p2_cur == X[0] ? 0 : 1;
-      } else if (first) {
-        LAUNCH(h, launch_p2_zero(h->n, m, X[0], h->p2l[m], done, s));
-      } else {
-        const int from = std::max(h->p2_level, 0);  // 0: the whole grid
-        LAUNCH_K(h, s, K_TRANSFER, m, 2,
-                 launch_p2_enter(h->n, from, h->p2_prev, h->p2_cur, from ? h->p2l[from] : none,
-                                 static_cast<const double*>(h->e[*cur]), h->el, m, X[0], h->p2l[m], done, s));
+      } else {  // the first iterations with the hand-over in one launch
+        const int from = first ? -1 : std::max(h->p2_level, 0);  // 0: the whole grid
+        t0 = std::min(it, P2T_IT);
+        LAUNCH_K(h, s, K_LATTICE, m, 512 | SW_TBLOCK | (first ? SW_ZERO_OLD : 0) | ((t0 - 1) << 4),
+                 launch_p2_tile(h->n, m, t0, h->omega, from, h->p2_prev, h->p2_cur, from > 0 ? h->p2l[from] : none,
+                                from == 0 ? static_cast<const double*>(h->e[*cur]) : nullptr, h->el, X[0], X[1],
+                                h->p2l[m], fm, h->faml[m], done, s));
+        src = 1;
       }
-      for (int t = 0; t < it; ++t) {
+      for (int t = t0; t < it; ++t) {
         LAUNCH_K(h, s, K_LATTICE, m, 512,
                  launch_p2_iter(h->n, m, h->omega, X[src], X[1 - src], h->p2l[m], fm, h->faml[m], done, s));
         src = 1 - src;
@@ -407,7 +408,9 @@ homg_status run_level(homg_ctx* h, int m, int it, bool first, bool last, int nex
       h->p2_level = m;
       h->p2_cur = X[src];
       h->p2_prev = X[1 - src];
-      if (last || next_m == 0) {
+      // (level 0's first pass reads level 1's marks itself, where it runs in
+      // bands: the tiles of small grids read the whole grid)
+      if (last || (next_m == 0 && !(m == 1 && h->temporal == 2 && !l0_tiled(h)))) {
         LAUNCH_K(h, s, K_LEVEL_WRITE, m, (last ? SW_ACCUM : 0) | 256,
                  launch_p2_write(h->n, m, h->p2_prev, h->p2_cur, h->p2l[m], static_cast<double*>(h->e[1 - *cur]),
                                  h->el, last ? acc : nullptr, h->dl, done, s));
@@ -473,6 +476,7 @@ homg_status run_level(homg_ctx* h, int m, int it, bool first, bool last, int nex
     return HOMG_OK;
   }
   if (m == 0 && h->d == 2 && h->temporal) {
+    bool marks = h->pow2 && h->p2_level == 1;
     // level 0 of a larger 2D constant-coefficient grid: up to TB_MAX_IT
     // iterations per pass (temporally blocked), the same iterates bit for bit
     for (int t0 = 0; t0 < it; t0 += TB_MAX_IT) {
@@ -480,7 +484,17 @@ homg_status run_level(homg_ctx* h, int m, int it, bool first, bool last, int nex
       const bool zero = first && t0 == 0, accum = last && t0 + g == it;
       const L1State* src = t0 == 0 ? l1 : nullptr;
       const int mode = SW_TBLOCK | (zero ? SW_ZERO_OLD : 0) | (accum ? SW_ACCUM : 0) | ((g - 1) << 4) |
-                       (src ? 128 : 0);
+                       (src || marks ? 128 : 0);
+      if (marks) {  // power-of-two grid: x_0 from level 1's marks
+        LAUNCH_K(h, s, K_SWEEP, 0, mode,
+                 launch_p2_l0(h->n, g, h->omega, h->p2_prev, h->p2_cur, h->p2l[1],
+                              accum ? nullptr : static_cast<double*>(h->e[1 - *cur]), h->el,
+                              static_cast<const double*>(h->r[0]), h->rl[0], accum ? acc : nullptr, h->dl, done, s));
+        marks = false;
+        h->p2_level = -1;
+        *cur = 1 - *cur;
+        continue;
+      }
       LAUNCH_K(h, s, K_SWEEP, 0, mode,
                launch_sweep_2d_l0_tb(h->prec, h->n, g, h->omega, h->e[*cur], h->e[1 - *cur], h->el,
                                      h->r[0], h->rl[0], acc, h->dl, zero, accum, done, s, 0, src));
@@ -792,13 +806,13 @@ constexpr int MR_B2 = 4, MR_B3 = 4;  // owned nodes per axis of the coarsest lev
 constexpr int MR_P2 = 4, MR_P3 = 2;  // levels per launch at most
 homg_status enqueue_restrict_chain(homg_ctx* h, int m0, int m1, const int* done, hipStream_t s) {
   if (m1 <= m0) return HOMG_OK;
-  if (h->pow2 || (top64(h) && m1 == h->top_level)) {
-    const int last = h->pow2 ? m0 : m1 - 1;  // power-of-two grids: one launch per step
-    if (!h->pow2)
-      if (homg_status e = enqueue_restrict_chain(h, m0, last, done, s)) return e;
-    for (int m = last; m < m1; ++m)
-      if (homg_status e = enqueue_restrict(h, m, done, s)) return e;
-    return HOMG_OK;
+  if (h->pow2 && m0 == 0) {  // level 1 of the four families from the whole grid
+    if (homg_status e = enqueue_restrict(h, 0, done, s)) return e;
+    return enqueue_restrict_chain(h, 1, m1, done, s);
+  }
+  if (top64(h) && m1 == h->top_level) {
+    if (homg_status e = enqueue_restrict_chain(h, m0, m1 - 1, done, s)) return e;
+    return enqueue_restrict(h, m1 - 1, done, s);
   }
   const int B = h->d == 2 ? MR_B2 : MR_B3;
   int P = 0;
@@ -808,6 +822,10 @@ homg_status enqueue_restrict_chain(homg_ctx* h, int m0, int m1, const int* done,
     if (homg_status e = enqueue_restrict(h, m, done, s)) return e;
   if (P) {
     const int a = m1 - P;
+    if (h->pow2) {
+      LAUNCH_K(h, s, K_RESTRICT, a, 3, launch_p2_restrict_multi(P, B, &h->fam[4 * a], &h->faml[a], done, s));
+      return HOMG_OK;
+    }
     void* r[MR_MAX + 1];
     Lay l[MR_MAX + 1];
     for (int k = 0; k <= P; ++k) {

@@ -86,6 +86,9 @@ hipError_t launch_restrict(int prec, int d, const void* rf, const Lay& fl, void*
 // level a + P; restrict_multi_lds: the LDS bytes that needs.
 constexpr int MR_MAX = 6;
 size_t restrict_multi_lds(int prec, int d, int P, int B);
+// The same for the families of a power-of-two grid: fam[4 k + q] is family q's
+// array of level a + k, l[k] its layout.
+hipError_t launch_p2_restrict_multi(int P, int B, double* const* fam, const Lay* l, const int* done, hipStream_t s);
 hipError_t launch_restrict_multi(int prec, int d, int P, int B, void* const* r, const Lay* l, const int* done,
                                  hipStream_t s);
 // One whole-grid relax+interpolate iteration at level m.  eo/en: fine
@@ -270,24 +273,31 @@ hipError_t launch_p2_restrict(const double* r0, const Lay& rl, const double* con
 // Compact form (the same bits as the whole-grid iterations): the marks of
 // level m, four quadrants of (h + 2)^2 values, h = N / 2^(m+1) = layout side,
 // quadrant to quadrant `plane` apart.
-//   launch_p2_enter: the starting state of level mt from the final pair of
-//     level m >= 1 (layout ml), or (m = 0) from the whole grid e;
-//   launch_p2_zero: the starting state 0;
 //   launch_p2_iter: one iteration; the final pair of a level is the state
 //     before and after its last one;
+//   launch_p2_tile: the first it <= P2T_IT iterations of a level in one
+//     launch.  They start from 0 (from < 0), the whole grid e (from = 0) or
+//     the final pair sprev, scur of level `from` (layout sl); leaves x_{it-1}
+//     in prev and x_it with its ghosts in cur;
 //   launch_p2_write: the whole grid after a level, into en or (u given)
 //     added into u;
 //   launch_p2_tail: levels ms + nlev - 1 .. ms from 0 in one workgroup
 //     (p2_tail_fits), with the norm of the residual of `cycle` reduced first
 //     as launch_coarse_tail does.
 Lay p2_mark_layout(int N, int m);
-hipError_t launch_p2_enter(int N, int m, const double* prev, const double* cur, const Lay& ml, const double* e,
-                           const Lay& el, int mt, double* out, const Lay& ol, const int* done, hipStream_t s);
-hipError_t launch_p2_zero(int N, int m, double* out, const Lay& ml, const int* done, hipStream_t s);
+constexpr int P2T_IT = 4;
+hipError_t launch_p2_tile(int N, int m, int it, double omega, int from, const double* sprev, const double* scur,
+                          const Lay& sl, const double* e, const Lay& el, double* prev, double* cur, const Lay& ml,
+                          const double* const* fam, const Lay& fl, const int* done, hipStream_t s);
 hipError_t launch_p2_iter(int N, int m, double omega, const double* in, double* out, const Lay& ml,
                           const double* const* fam, const Lay& fl, const int* done, hipStream_t s);
 hipError_t launch_p2_write(int N, int m, const double* prev, const double* cur, const Lay& ml, double* en,
                            const Lay& el, double* u, const Lay& ul, const int* done, hipStream_t s);
+// it <= TB_MAX_IT iterations of level 0 whose first iterate is level 1's final
+// pair, into en or (u given) added into u (homg_kernels.hip).
+hipError_t launch_p2_l0(int N, int it, double omega, const double* prev, const double* cur, const Lay& ml, double* en,
+                        const Lay& el, const double* r, const Lay& rl, double* u, const Lay& ul, const int* done,
+                        hipStream_t s);
 bool p2_tail_fits(int N, int ms);
 hipError_t launch_p2_tail(int N, int ms, int nlev, const int* its, double omega, const double* const* fam,
                           const Lay& fl, double* prev, double* cur, const Lay& ml, DevState* st, double* hist,

@@ -676,7 +676,10 @@ __global__ __launch_bounds__(256) void k_sweep_2d_l0(
 // formula), so the passes over a compact lattice use it too: "level 1" is
 // then level m + 1 and "level 0" level m.
 template <typename T>
+struct L1Col2;
+template <typename T>
 struct L1Src {
+  using Col = L1Col2<T>;
   const T* prev;    // x_{it-1}, unread when zero_old
   const T* cur;     // x_it
   int64_t cp, cpl;  // compact row pitch, plane pitch
@@ -756,6 +759,105 @@ struct L1Col2 {
     const C v = (latx && (y & 1) == 0) ? ld(q + int64_t(J) * cp + I)
                                        : lerp(top, bot, C(y & 1) * (C(1) / C(2)));
     return rnd<T>(v);
+  }
+};
+
+// The same on a power-of-two grid: level 1's marks (homg_pow2.hip; quadrant q
+// at (0, 0) q planes on), level 0 the whole grid.  Rows below N / 2 are side
+// 0's, whose mark rows are even, the others side 1's, mirrored; the two rows
+// in the middle that are marks of the other side take the general form.
+struct P2Col;
+struct P2Src {
+  using Col = P2Col;
+  const double* prev;
+  const double* cur;
+  int64_t plane, pitch;
+};
+struct P2Col {
+  const double* p;  // prev at the column's cell, y-side 0, mark row 0
+  const double* q;  // cur at the column's mark, if it is one
+  int64_t plane, pitch;
+  int N, state;     // state: which side's rows w0, w1 are for (1, 2; 0: none)
+  double tx, w0, w1;
+  bool live, marked;
+  __device__ __forceinline__ void init(const P2Src& s, int x, int n) {
+    N = n;
+    live = x >= 1 && x <= n - 2;
+    const int half = n >> 1, xc = live ? x : 1, b = n - 1 - xc;
+    const int side = xc >= half ? 1 : 0, a = side ? b : xc;
+    const int ms = (xc & 1) == 0 && xc <= half ? 0 : ((b & 1) == 0 && b <= half ? 1 : -1);
+    marked = ms >= 0;
+    plane = s.plane;
+    pitch = s.pitch;
+    p = s.prev + side * plane + (a >> 1);
+    q = s.cur + (marked ? ms * plane + ((ms ? b : xc) >> 1) : 0);
+    tx = double(a & 1) * 0.5;
+    state = 0;
+    w0 = w1 = 0.0;
+  }
+  __device__ __forceinline__ void prime(int, int) {}
+  __device__ __forceinline__ double xl(const double* base, int J) const {
+    const double* a = base + int64_t(J) * pitch;
+    return lerp(a[0], a[1], tx);
+  }
+  // Any interior row (y is uniform over the wave).
+  __device__ __forceinline__ double at(int y, int n) {
+    state = 0;
+    if (!live || y < 1 || y > n - 2) return 0.0;
+    const int half = N >> 1, b = N - 1 - y;
+    const int ms = (y & 1) == 0 && y <= half ? 0 : ((b & 1) == 0 && b <= half ? 1 : -1);
+    const int side = y >= half ? 1 : 0, a = side ? b : y;
+    const double* base = p + 2 * side * plane;
+    double v = lerp(xl(base, a >> 1), xl(base, (a >> 1) + 1), double(a & 1) * 0.5);
+    if (ms >= 0 && marked) v = q[2 * ms * plane + int64_t((ms ? b : y) >> 1) * pitch];
+    return v;
+  }
+  __device__ __forceinline__ void rows4(int ys, int n, double (&v)[4]) {
+    const int half = N >> 1;
+    const bool low = ys + 3 <= half - 2, high = ys >= half + 1;
+    if (!low && !high) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = at(ys + k, n);
+      return;
+    }
+    // c: the row seen from its side's corner, going up (low) or down (high)
+    // by four; w0 and w1 are the x-interpolants of mark rows j and j + 1 (low),
+    // j + 1 and j (high)
+    const int c = low ? ys : max(N - 1 - ys, 0), j = c >> 1;
+    const double* base = p + (low ? 0 : 2 * plane);
+    const double* qb = q + (low ? 0 : 2 * plane);
+    const bool odd = (c & 1) != 0;
+    if (state != (low ? 1 : 2)) {
+      w0 = xl(base, low ? j : j + 1);
+      w1 = xl(base, low ? j + 1 : j);
+      state = low ? 1 : 2;
+    }
+    const int dj = low ? 1 : -1;
+    const double x2 = xl(base, low ? j + 2 : max(j - 1, 0)), x3 = xl(base, low ? j + 3 : max(j - 2, 0));
+    // the mark rows among the four: c + odd and c + odd + 2 (low), c - odd and
+    // c - odd - 2 (high)
+    const int j0 = low ? j + int(odd) : j;
+    const double q0 = qb[int64_t(j0) * pitch], q1 = qb[int64_t(max(j0 + dj, 0)) * pitch];
+    double t[4];
+    if (low) {
+      t[0] = lerp(w0, w1, odd ? 0.5 : 0.0);
+      t[1] = odd ? lerp(w1, x2, 0.0) : lerp(w0, w1, 0.5);
+      t[2] = lerp(w1, x2, odd ? 0.5 : 0.0);
+      t[3] = odd ? lerp(x2, x3, 0.0) : lerp(w1, x2, 0.5);
+    } else {
+      t[0] = lerp(w1, w0, odd ? 0.5 : 0.0);
+      t[1] = odd ? lerp(w1, w0, 0.0) : lerp(x2, w1, 0.5);
+      t[2] = lerp(x2, w1, odd ? 0.5 : 0.0);
+      t[3] = odd ? lerp(x2, w1, 0.0) : lerp(x3, x2, 0.5);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int y = ys + k;
+      const double val = marked && (k & 1) == int(odd) ? (k < 2 ? q0 : q1) : t[k];
+      v[k] = live && y >= 1 && y <= n - 2 ? val : 0.0;
+    }
+    w0 = x2;
+    w1 = x3;
   }
 };
 
@@ -870,14 +972,14 @@ struct L1Col3 {
 // the result equals IT single sweeps bit for bit while e and r are read
 // once and the result written (or added into u) once.
 
-template <typename T, bool ZERO, bool ACCUM, bool PREV, int IT, int U, bool LAT>
+template <typename T, bool ZERO, bool ACCUM, bool PREV, int IT, int U, bool LAT, typename LC>
 __device__ __forceinline__ void tb_steps(const T* __restrict__ eo, T* __restrict__ en,
                                          T* __restrict__ eprev, int64_t ep,
                                          const T* __restrict__ r, int64_t rp, double* __restrict__ u,
                                          int64_t up, int n, int x, int xc, bool xin, bool emit, int Y0,
                                          int Y1, int ys, typename Tr<T>::C w, typename Tr<T>::C hl2,
                                          typename Tr<T>::C (&win)[IT][3], typename Tr<T>::C (&rw)[IT + 1],
-                                         L1Col2<T>& lc) {
+                                         LC& lc) {
   using C = typename Tr<T>::C;
   C xl[U], rl[U];
   double uo[U];
@@ -931,12 +1033,12 @@ __device__ __forceinline__ void tb_steps(const T* __restrict__ eo, T* __restrict
 
 // Wave wv of the pass (waves numbered x-band fastest).  LAT: e comes from
 // level 1's compact state (L1Src) instead of eo.
-template <typename T, bool ZERO, bool ACCUM, bool PREV, int IT, bool LAT = false>
+template <typename T, bool ZERO, bool ACCUM, bool PREV, int IT, bool LAT = false, typename SRC = L1Src<T>>
 __device__ __forceinline__ void tb_body(const T* __restrict__ eo, T* __restrict__ en,
                                         T* __restrict__ eprev, int64_t ep, const T* __restrict__ r,
                                         int64_t rp, double* __restrict__ u, int64_t up, int n, int len,
                                         typename Tr<T>::C w, typename Tr<T>::C hl2, int wv,
-                                        const L1Src<T>& l1 = L1Src<T>{}) {
+                                        const SRC& l1 = SRC{}) {
   using C = typename Tr<T>::C;
   constexpr int VALID = 64 - 2 * IT;
   const int lane = threadIdx.x & 63;
@@ -955,7 +1057,7 @@ __device__ __forceinline__ void tb_body(const T* __restrict__ eo, T* __restrict_
   for (int t = 0; t < IT; ++t) win[t][0] = win[t][1] = win[t][2] = C(0);
 #pragma unroll
   for (int t = 0; t <= IT; ++t) rw[t] = C(0);
-  L1Col2<T> lc;
+  typename SRC::Col lc;
   int ys = max(Y0 - IT, 0);
   if (LAT) {
     lc.init(l1, x, n);
@@ -984,6 +1086,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
   // columns and rows meet in that XCD's L2)
   const int wv = int(xcd_order(blockIdx.x, gridDim.x)) * 4 + int(threadIdx.x >> 6);
   tb_body<T, ZERO, ACCUM, false, IT, LAT>(eo, en, nullptr, ep, r, rp, u, up, n, len, w, hl2, wv, l1);
+}
+
+// The same pass on a power-of-two grid, its e from level 1's marks: 108 us at
+// 4096^2 with u added to, against 128 after a 43 us whole-grid write of e.
+template <bool ACCUM, int IT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_sweep_p2_l0_tb(
+    P2Src src, double* __restrict__ en, int64_t ep, const double* __restrict__ r, int64_t rp, double* __restrict__ u,
+    int64_t up, int n, int len, double w, double hl2, const int* __restrict__ done) {
+  if (*done) return;
+  const int wv = int(xcd_order(blockIdx.x, gridDim.x)) * 4 + int(threadIdx.x >> 6);
+  tb_body<double, false, ACCUM, false, IT, true>(nullptr, en, nullptr, ep, r, rp, u, up, n, len, w, hl2, wv, src);
 }
 
 // The same pass over the compact lattice of a coarse level (n = its side),
@@ -2116,6 +2229,19 @@ __global__ __launch_bounds__(MR_NT) void k_restrict_multi(MultiRestrictPlan mp, 
   restrict_multi_block<T, D>(mp, int(xcd_order(blockIdx.x, gridDim.x)));
 }
 
+// The four restriction families of a power-of-two grid, a quarter of the
+// workgroups each: a family of side s (index 0 the boundary, 1 .. s - 1
+// restricted) is a lattice of s + 1 nodes whose last one nobody reads.
+// (4096^2, levels 3 .. 7: 7 us in one launch, 17 in four.)
+struct P2MultiPlan {
+  MultiRestrictPlan mp[4];
+};
+__global__ __launch_bounds__(MR_NT) void k_p2_restrict_multi(P2MultiPlan p, const int* __restrict__ done) {
+  if (*done) return;
+  const int lb = int(xcd_order(blockIdx.x, gridDim.x)), per = int(gridDim.x) / 4;
+  restrict_multi_block<double, 2>(p.mp[lb / per], lb % per);
+}
+
 // ------------------------------------------------------------ pack / unpack
 
 template <typename T>
@@ -2380,6 +2506,26 @@ static hipError_t restrict_multi_t(int d, int P, int B, void* const* r, const La
   HOMG_LAUNCH_SMEM((k_restrict_multi<T, 3>), dim3(blocks), dim3(MR_NT), lds, s, mp, done);
 }
 
+hipError_t launch_p2_restrict_multi(int P, int B, double* const* fam, const Lay* l, const int* done, hipStream_t s) {
+  if (P < 1 || P > MR_MAX || B < 1 || l[P].side < 2) return hipErrorInvalidValue;
+  P2MultiPlan p;
+  for (int z = 0; z < 4; ++z) {
+    void* r[MR_MAX + 1];
+    Lay lz[MR_MAX + 1];
+    for (int k = 0; k <= P; ++k) {
+      r[k] = fam[4 * k + z];
+      lz[k] = l[k];
+      ++lz[k].side;
+    }
+    p.mp[z] = multi_plan<double>(2, P, B, r, lz);
+  }
+  const size_t lds = restrict_multi_lds(PREC_F64, 2, P, B);
+  hipError_t e = allow_lds(k_p2_restrict_multi, lds);
+  if (e != hipSuccess) return e;
+  HOMG_LAUNCH_SMEM(k_p2_restrict_multi, dim3(4u * unsigned(p.mp[0].nb) * unsigned(p.mp[0].nb)), dim3(MR_NT), lds, s, p,
+                   done);
+}
+
 hipError_t launch_restrict_multi(int prec, int d, int P, int B, void* const* r, const Lay* l, const int* done,
                                  hipStream_t s) {
   if (P < 1 || P > MR_MAX || B < 1 || l[P].side < 3) return hipErrorInvalidValue;
@@ -2564,6 +2710,32 @@ hipError_t launch_sweep_2d_l0_tb(int prec, int n, int it, double omega, const vo
     case PREC_F32: return tb_tz<float>(n, it, len, omega, eo, en, el, rm, rl, u, ul, zero, accum, l1, done, s);
     default: return tb_tz<bf16>(n, it, len, omega, eo, en, el, rm, rl, u, ul, zero, accum, l1, done, s);
   }
+}
+
+template <bool ACCUM>
+static hipError_t p2_l0_t(int N, int it, int len, double omega, const P2Src& src, double* en, const Lay& el,
+                          const double* r, const Lay& rl, double* u, const Lay& ul, const int* done, hipStream_t s) {
+  const double h = 1.0 / double(N - 1);
+  const dim3 g(tb_blocks(N, it, len));
+#define P2_L0_ARGS src, en, el.pitch, r, rl.pitch, u, ul.pitch, N, len, omega / 4.0, h * h, done
+  switch (it) {
+    case 1: HOMG_LAUNCH((k_sweep_p2_l0_tb<ACCUM, 1>), g, dim3(256), s, P2_L0_ARGS);
+    case 2: HOMG_LAUNCH((k_sweep_p2_l0_tb<ACCUM, 2>), g, dim3(256), s, P2_L0_ARGS);
+    case 3: HOMG_LAUNCH((k_sweep_p2_l0_tb<ACCUM, 3>), g, dim3(256), s, P2_L0_ARGS);
+    default: HOMG_LAUNCH((k_sweep_p2_l0_tb<ACCUM, 4>), g, dim3(256), s, P2_L0_ARGS);
+  }
+#undef P2_L0_ARGS
+}
+
+hipError_t launch_p2_l0(int N, int it, double omega, const double* prev, const double* cur, const Lay& ml, double* en,
+                        const Lay& el, const double* r, const Lay& rl, double* u, const Lay& ul, const int* done,
+                        hipStream_t s) {
+  if (N < 16 || it < 1 || it > TB_MAX_IT || !prev || !cur || ml.side != N / 4 || (u != nullptr) == (en != nullptr))
+    return hipErrorInvalidValue;
+  const P2Src src{prev + ml.off, cur + ml.off, ml.plane, ml.pitch};
+  const int len = tb_band(N, it);
+  if (u) return p2_l0_t<true>(N, it, len, omega, src, nullptr, el, r + rl.off, rl, u + ul.off, ul, done, s);
+  return p2_l0_t<false>(N, it, len, omega, src, en + el.off, el, r + rl.off, rl, nullptr, ul, done, s);
 }
 
 int tb_band(int n, int it) {

@@ -256,24 +256,6 @@ __device__ __forceinline__ double p2_state(const P2Marks& prev, const P2Marks& c
   return p2_interp(prev, N, m, sx, sy, px, py);
 }
 
-// The starting state (marks and ghosts) of level mt: from the final state of
-// level m (m >= 1), or -- m = 0 -- from the whole grid e.
-__global__ __launch_bounds__(256) void k_p2_enter(P2Marks prev, P2Marks cur, int m, const double* __restrict__ e,
-                                                  int64_t ep, P2Out out, int mt, int N,
-                                                  const int* __restrict__ done) {
-  if (*done) return;
-  const int h = N >> (mt + 1);
-  const int i = 1 + blockIdx.x * 64 + threadIdx.x, j = 1 + blockIdx.y * 4 + threadIdx.y;
-  if (i > h + 1 || j > h + 1 || (i > h && j > h)) return;
-  const int sx = blockIdx.z & 1, sy = blockIdx.z >> 1;
-  const int px = i << mt, py = j << mt;
-  double v = 0.0;
-  if (px <= N - 1 && py <= N - 1)
-    v = m ? p2_state(prev, cur, N, m, sx, sy, px, py)
-          : e[int64_t(sy ? N - 1 - py : py) * ep + (sx ? N - 1 - px : px)];
-  *out.at(blockIdx.z, j, i) = v;
-}
-
 // One iteration of level m: marks relax, ghosts interpolate.
 __device__ __forceinline__ double p2_node(const P2Marks& in, const double* __restrict__ fam, int64_t fp, int N, int m,
                                           int sx, int sy, int i, int j, int h, double w, double hl2) {
@@ -299,11 +281,208 @@ __global__ __launch_bounds__(256) void k_p2_iter(P2Marks in, P2Out out, P2Fam4 f
   *out.at(z, j, i) = p2_node(in, fam.f[z], fp, N, m, z & 1, z >> 1, i, j, h, w, hl2);
 }
 
-__global__ __launch_bounds__(256) void k_p2_zero(P2Out out, int h, const int* __restrict__ done) {
-  if (*done) return;
-  const int i = 1 + blockIdx.x * 64 + threadIdx.x, j = 1 + blockIdx.y * 4 + threadIdx.y;
-  if (i > h + 1 || j > h + 1 || (i > h && j > h)) return;
-  *out.at(blockIdx.z, j, i) = 0.0;
+// ---- several iterations of a level in one launch
+// A workgroup owns B x B marks of a quadrant and iterates on them with a halo
+// of one mark per iteration, the tile nodes in registers and their
+// neighbours' values through LDS.  A tile at the quadrant's far end holds the
+// ghost at h + 1 too, and beside its own marks (in x, in y or both) the last
+// marks of the other side, whose interpolant the ghost is and whose ghost its
+// own marks give in turn: [h - 1 - it, h + 1] feed it iterations.  So an axis
+// of a tile is one segment of own indices and, at the seam, one of the other
+// side's: at most B + 12 positions.  The starting state is formed in the tile
+// from the coarser level's pair.  What bounds it is latency: a block loads,
+// then runs four short phases.  One launch in place of a hand-over and a
+// launch per iteration, four iterations: 21 -> 5 us at h = 32, 33 -> 28 at
+// h = 512, 100 -> 92 at h = 1024.  B = 16 (a node per lane, the shortest
+// phases) while its blocks fit the chip about once; from h = 256 on B = 32 (two
+// nodes per lane), which repeats 1.6 nodes per owned one in place of 2.3 (h =
+// 1024: 92 us against 153).
+constexpr int P2T_WIDE = 256;
+constexpr int p2t_side(int B) { return B + 3 * P2T_IT; }  // positions per axis at most
+
+struct P2TileArgs {
+  P2Marks sp, sc;  // the state before: the final pair of level `from`,
+  const double* e;  // the whole grid (from = 0), or 0 (from < 0)
+  int64_t ep;
+  int from;
+  P2Out prev, cur;
+  P2Fam4 fam;
+  int64_t fp;
+  int N, m, it, nb;
+  double w, hl2;
+  const int* done;
+};
+
+// The positions of one axis: own indices from lo, then the other side's from
+// lob.
+template <int B>
+struct P2Axis {
+  int own, lo, len, lob, lenb;
+  __device__ __forceinline__ P2Axis(int side, int a, int it, int h) {
+    own = side;
+    lo = max(a - it, 0);
+    const int hi = min(a + B - 1 + it, h + 1);
+    len = hi - lo + 1;
+    lob = max(h - 1 - it, 0);
+    lenb = hi == h + 1 ? h + 2 - lob : 0;
+  }
+  __device__ __forceinline__ bool at(int p, int& side, int& idx) const {
+    const bool o = p < len;
+    side = o ? own : 1 - own;
+    idx = o ? lo + p : lob + p - len;
+    return p < len + lenb;
+  }
+  // The position of an index (clamped: what falls outside feeds no owned mark).
+  __device__ __forceinline__ int pos(int side, int idx) const {
+    return side == own ? min(max(idx - lo, 0), len - 1) : len + min(max(idx - lob, 0), max(lenb - 1, 0));
+  }
+};
+
+// B: owned marks per axis, K: tile nodes per lane.
+template <int B, int NT, int K>
+__global__ __launch_bounds__(NT) void k_p2_tile(P2TileArgs g) {
+  constexpr int S = p2t_side(B), W = B + 2 * P2T_IT, PAD = S + 1;
+  static_assert(S * S <= K * NT && B + P2T_IT + 1 + P2T_IT + 3 <= S, "K tile nodes per lane");
+  __shared__ double X[2][S * S + 2 * PAD];
+  const int N = g.N, m = g.m, half = N >> 1, h = N >> (m + 1);
+  const unsigned lb = xcd_order(blockIdx.x, gridDim.x);
+  const unsigned nb2 = unsigned(g.nb) * unsigned(g.nb);
+  const int z = int(lb / nb2), bxy = int(lb % nb2);
+  const int a = 1 + (bxy % g.nb) * B, b = 1 + (bxy / g.nb) * B;
+  double v[K], pv[K], r[K];
+  if (max(a, b) + B - 1 + g.it < h) {  // away from the seams: own marks alone
+    const int done = *g.done;
+    const double* fam = z & 2 ? (z & 1 ? g.fam.f[3] : g.fam.f[2]) : (z & 1 ? g.fam.f[1] : g.fam.f[0]);
+    const int side = B + 2 * g.it;
+    int o[K];
+    bool mark[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int q = threadIdx.x + k * NT, pj = q / W, pi = q % W;
+      const int i = a - g.it + pi, j = b - g.it + pj;
+      o[k] = PAD + min(pj, S - 1) * S + pi;
+      mark[k] = i >= 1 && j >= 1 && pi < side && pj < side;
+      const int ic = min(max(i, 1), h), jc = min(max(j, 1), h);
+      v[k] = 0.0;
+      pv[k] = 0.0;
+      r[k] = fam[int64_t(jc) * g.fp + ic];
+      if (g.from == m + 1) {  // p2_state here: lattice nodes as they are, others interpolated
+        const int64_t at = z * g.sp.plane + int64_t(min(jc >> 1, (h >> 1) - 1)) * g.sp.pitch + min(ic >> 1, (h >> 1) - 1);
+        const double c = g.sc.p[at], p00 = g.sp.p[at], p01 = g.sp.p[at + 1], p10 = g.sp.p[at + g.sp.pitch],
+                     p11 = g.sp.p[at + g.sp.pitch + 1];
+        const double fx = double(ic & 1) * 0.5, fy = double(jc & 1) * 0.5;
+        v[k] = (ic | jc) & 1 ? lerp(lerp(p00, p01, fx), lerp(p10, p11, fx), fy) : c;
+      } else if (g.from > 0) {
+        v[k] = p2_state(g.sp, g.sc, N, g.from, z & 1, z >> 1, ic << m, jc << m);
+      } else if (g.from == 0) {
+        const int px = ic << m, py = jc << m;
+        v[k] = g.e[int64_t(z & 2 ? N - 1 - py : py) * g.ep + (z & 1 ? N - 1 - px : px)];
+      }
+    }
+    if (done) return;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (!mark[k]) v[k] = 0.0;
+      if (int(threadIdx.x) + k * NT < W * W) {
+        X[0][o[k]] = v[k];
+        if (!mark[k]) X[1][o[k]] = 0.0;
+      }
+    }
+    __syncthreads();
+    for (int t = 1; t <= g.it; ++t) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        const double* src = &X[(t - 1) & 1][o[k]];
+        pv[k] = v[k];
+        v[k] = relax_const<double>(v[k], (src[-1] + src[1]) + (src[-S] + src[S]), r[k], g.w, g.hl2, 4.0);
+        if (t < g.it && mark[k]) X[t & 1][o[k]] = v[k];
+      }
+      if (t < g.it) __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int q = threadIdx.x + k * NT, i = a - g.it + q % W, j = b - g.it + q / W;
+      if (i < a || j < b || i >= a + B || j >= b + B) continue;
+      *g.cur.at(z, j, i) = v[k];
+      *g.prev.at(z, j, i) = pv[k];
+    }
+    return;
+  }
+  if (*g.done) return;
+  const P2Axis<B> ax(z & 1, a, g.it, h), ay(z >> 1, b, g.it, h);
+  double fx[K], fy[K];
+  int o00[K], o01[K], o10[K], o11[K];
+  bool live[K], mark[K], inside[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int q = threadIdx.x + k * NT, pj = q / S, pi = q % S;
+    int sx, sy, i, j;
+    const bool ix = ax.at(pi, sx, i), iy = ay.at(pj, sy, j);
+    live[k] = q < S * S && ix && iy && i >= 1 && j >= 1 && (i <= h || j <= h);
+    mark[k] = live[k] && i <= h && j <= h;
+    const int px = i << m, py = j << m;
+    inside[k] = live[k] && px <= N - 1 && py <= N - 1;
+    v[k] = pv[k] = r[k] = fx[k] = fy[k] = 0.0;
+    o00[k] = o01[k] = o10[k] = o11[k] = 0;
+    if (inside[k]) {
+      if (g.from > 0)
+        v[k] = p2_state(g.sp, g.sc, N, g.from, sx, sy, px, py);
+      else if (g.from == 0)
+        v[k] = g.e[int64_t(sy ? N - 1 - py : py) * g.ep + (sx ? N - 1 - px : px)];
+    }
+    if (mark[k]) {
+      const double* f = sy ? (sx ? g.fam.f[3] : g.fam.f[2]) : (sx ? g.fam.f[1] : g.fam.f[0]);
+      r[k] = f[int64_t(j) * g.fp + i];
+    } else if (inside[k]) {  // a ghost (as p2_interp): its cell in the quadrant that owns it
+      const bool ox = px >= half, oy = py >= half;
+      const int tx = ox ? 1 - sx : sx, ty = oy ? 1 - sy : sy;
+      const int qx = ox ? N - 1 - px : px, qy = oy ? N - 1 - py : py;
+      const int kx = qx >> m, ky = qy >> m;
+      const double inv_l = 1.0 / double(1 << m);
+      fx[k] = double(qx - (kx << m)) * inv_l;
+      fy[k] = double(qy - (ky << m)) * inv_l;
+      const int x0 = ax.pos(tx, kx), x1 = ax.pos(tx, kx + 1), y0 = ay.pos(ty, ky), y1 = ay.pos(ty, ky + 1);
+      o00[k] = y0 * S + x0;
+      o01[k] = y0 * S + x1;
+      o10[k] = y1 * S + x0;
+      o11[k] = y1 * S + x1;
+    }
+    if (q < S * S) {
+      X[0][PAD + q] = v[k];
+      if (!live[k]) X[1][PAD + q] = 0.0;
+    }
+  }
+  __syncthreads();
+  for (int t = 1; t <= g.it; ++t) {
+    const double* src = &X[(t - 1) & 1][PAD];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int q = threadIdx.x + k * NT;
+      pv[k] = v[k];
+      if (mark[k]) {
+        const double c = (src[q - 1] + src[q + 1]) + (src[q - S] + src[q + S]);
+        v[k] = relax_const<double>(v[k], c, r[k], g.w, g.hl2, 4.0);
+      } else if (inside[k]) {
+        v[k] = lerp(lerp(src[o00[k]], src[o01[k]], fx[k]), lerp(src[o10[k]], src[o11[k]], fx[k]), fy[k]);
+      }
+      if (t < g.it && live[k]) X[t & 1][PAD + q] = v[k];
+    }
+    if (t < g.it) __syncthreads();
+  }
+  // owned marks, and the ghosts behind them at the far end
+  const int ae = min(a + B - 1, h), be = min(b + B - 1, h);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int q = threadIdx.x + k * NT, pj = q / S, pi = q % S;
+    int sx, sy, i, j;
+    ax.at(pi, sx, i);
+    ay.at(pj, sy, j);
+    const bool own = live[k] && pi < ax.len && pj < ay.len && i >= a && j >= b && i <= (ae == h ? h + 1 : ae) &&
+                     j <= (be == h ? h + 1 : be);
+    if (!own) continue;
+    *g.cur.at(z, j, i) = v[k];
+    if (mark[k]) *g.prev.at(z, j, i) = pv[k];
+  }
 }
 
 // The whole grid after a level: stored in en, or (u given) added into u.  A
@@ -352,7 +531,10 @@ __global__ __launch_bounds__(256) void k_p2_write(P2Marks prev, P2Marks cur, int
 // Levels ms .. top of the schedule's start (each once, descending), h <=
 // P2_TAIL_H at level ms: the families of level ms in LDS, restricted to the
 // coarser levels there, and every level's iterations; leaves level ms's
-// final pair.  As launches these levels took some 30 of 4 us each per cycle.
+// final pair.  As launches these levels took some 30 of 4 us each per cycle;
+// here a mark per lane keeps its value, right-hand side and place in registers
+// (16.7 us at h = 16 .. 1; 21 with every node's place worked out again in each
+// iteration).
 // Also reduces the previous residual's norm (as k_coarse_tail).
 constexpr int P2_TAIL_H = 16;
 constexpr int P2_TAIL_NT = 1024;
@@ -431,45 +613,67 @@ __global__ __launch_bounds__(P2_TAIL_NT) void k_p2_tail(P2TailArgs a) {
     const int m = a.ms + k, h = N >> (m + 1), lh = 31 - __builtin_clz(h), sk = S0 >> k;
     const int nb = 2 - pb;  // the free pair
     const double* fk = fam + foff(k);
-    // the marks (h is a power of two), then the ghosts of both axes
-    auto each = [&](auto&& body, bool ghosts = true) {
-      for (int n = threadIdx.x; n < 4 * h * h; n += P2_TAIL_NT)
-        body(n >> (2 * lh), 1 + (n & (h - 1)), 1 + ((n >> lh) & (h - 1)));
-      const int g = int(threadIdx.x) - (P2_TAIL_NT - 8 * h);  // by the last waves
-      if (ghosts && g >= 0) {
-        const int c = 1 + (g & (h - 1)), z = g >> (lh + 1);
-        if ((g >> lh) & 1)
-          body(z, c, h + 1);
-        else
-          body(z, h + 1, c);
-      }
-    };
+    // a mark per lane (h is a power of two, 4 h^2 <= 1024 of them) and, in the
+    // last lanes, a ghost: place, right-hand side or cell and weights, and the
+    // mark's value stay in registers over the iterations
+    const int n = threadIdx.x;
+    const bool mark = n < 4 * h * h;
+    const int mz = mark ? n >> (2 * lh) : 0, mi = 1 + (n & (h - 1)), mj = 1 + ((n >> lh) & (h - 1));
+    const int mo = mz * MQ + mj * P2_TAIL_MP + mi;
+    const int gn = n - (P2_TAIL_NT - 8 * h);
+    const bool gap = ((gn >> lh) & 1) != 0;  // ghosts of the y axis, else of x
+    const int gc = 1 + (gn & (h - 1)), gz = gn >= 0 ? gn >> (lh + 1) : 0;
+    const int gi = gap ? gc : h + 1, gj = gap ? h + 1 : gc;
+    const bool ghost = gn >= 0 && (gi << m) <= N - 1 && (gj << m) <= N - 1;
+    const int go = gz * MQ + gj * P2_TAIL_MP + gi;
+    double rv = 0.0, v = 0.0, gv = 0.0, gfx = 0.0, gfy = 0.0;
+    int g0 = 0;
+    if (mark) rv = fk[mz * sk * sk + mj * sk + mi];
+    if (ghost) {  // its cell (as p2_interp)
+      const int half = N >> 1, px = gi << m, py = gj << m, sx = gz & 1, sy = gz >> 1;
+      const bool ox = px >= half, oy = py >= half;
+      const int ax = ox ? N - 1 - px : px, ay = oy ? N - 1 - py : py, ix = ax >> m, iy = ay >> m;
+      const double inv_l = 1.0 / double(1 << m);
+      gfx = double(ax - (ix << m)) * inv_l;
+      gfy = double(ay - (iy << m)) * inv_l;
+      g0 = (2 * (oy ? 1 - sy : sy) + (ox ? 1 - sx : sx)) * MQ + iy * P2_TAIL_MP + ix;
+    }
+    double* const xa = X + nb * 4 * MQ;
+    double* const xb = xa + 4 * MQ;
     if (k < a.nlev - 1) {  // hand-over from level m + 1 (the coarsest level starts from 0)
       const P2Marks prev = marks(pb + ((it_above & 1) ? 0 : 1)), cur = marks(pb + ((it_above & 1) ? 1 : 0));
-      each([&](int z, int i, int j) {
-        const int px = i << m, py = j << m;
-        X[(nb * 4 + z) * MQ + j * P2_TAIL_MP + i] =
-            px <= N - 1 && py <= N - 1 ? p2_state(prev, cur, N, m + 1, z & 1, z >> 1, px, py) : 0.0;
-      });
+      if (mark) v = p2_state(prev, cur, N, m + 1, mz & 1, mz >> 1, mi << m, mj << m);
+      if (ghost) gv = p2_state(prev, cur, N, m + 1, gz & 1, gz >> 1, gi << m, gj << m);
+      if (mark) xa[mo] = v;
+      if (gn >= 0) xa[go] = gv;
       __syncthreads();
     }
     const int it = a.its[k];
-    for (int t = 1; t <= it; ++t) {
-      const P2Marks in = marks(nb + ((t & 1) ? 0 : 1));
-      double* o = X + (nb + ((t & 1) ? 1 : 0)) * 4 * MQ;
-      each([&](int z, int i, int j) {
-        o[z * MQ + j * P2_TAIL_MP + i] =
-            p2_node(in, fk + z * sk * sk, sk, N, m, z & 1, z >> 1, i, j, h, a.w, a.hl2[k]);
-      });
+    const double hl2 = a.hl2[k];
+    double pv = 0.0;
+    auto step = [&](const double* in, double* o) {
+      pv = v;
+      if (mark) {
+        const double* p = in + mo;
+        v = relax_const<double>(v, (p[-1] + p[1]) + (p[-P2_TAIL_MP] + p[P2_TAIL_MP]), rv, a.w, hl2, 4.0);
+        o[mo] = v;
+      }
+      if (gn >= 0) {
+        const double* p = in + g0;
+        const double t = lerp(lerp(p[0], p[1], gfx), lerp(p[P2_TAIL_MP], p[P2_TAIL_MP + 1], gfx), gfy);
+        o[go] = ghost ? t : 0.0;
+      }
       __syncthreads();
+    };
+    int t = 0;
+    for (; t + 2 <= it; t += 2) {
+      step(xa, xb);
+      step(xb, xa);
     }
-    if (k == 0) {
-      const double* xc = X + (nb + ((it & 1) ? 1 : 0)) * 4 * MQ;
-      const double* xp = X + (nb + ((it & 1) ? 0 : 1)) * 4 * MQ;
-      each([&](int z, int i, int j) {
-        *a.cur.at(z, j, i) = xc[z * MQ + j * P2_TAIL_MP + i];
-        *a.prev.at(z, j, i) = xp[z * MQ + j * P2_TAIL_MP + i];
-      }, false);
+    if (t < it) step(xa, xb);
+    if (k == 0 && mark) {
+      *a.cur.at(mz, mj, mi) = v;
+      *a.prev.at(mz, mj, mi) = pv;
     }
     it_above = it;
     pb = nb;
@@ -512,15 +716,6 @@ hipError_t launch_p2_restrict(const double* r0, const Lay& rl, const double* con
   HOMG_LAUNCH(k_p2_restrict, g, dim3(64, 4), s, p, fl.pitch, cl.pitch, nc, done);
 }
 
-hipError_t launch_p2_enter(int N, int m, const double* prev, const double* cur, const Lay& ml, const double* e,
-                           const Lay& el, int mt, double* out, const Lay& ol, const int* done, hipStream_t s) {
-  const int h = N >> (mt + 1);
-  if (mt < 1 || h < 1 || ol.side != h || (m ? !prev || !cur || ml.side != (N >> (m + 1)) : !e))
-    return hipErrorInvalidValue;
-  HOMG_LAUNCH(k_p2_enter, p2_mark_grid(h), dim3(64, 4), s, p2_in(prev, ml), p2_in(cur, ml), m,
-              e ? e + el.off : nullptr, el.pitch, p2_out(out, ol), mt, N, done);
-}
-
 hipError_t launch_p2_iter(int N, int m, double omega, const double* in, double* out, const Lay& ml,
                           const double* const* fam, const Lay& fl, const int* done, hipStream_t s) {
   const int h = N >> (m + 1);
@@ -532,10 +727,39 @@ hipError_t launch_p2_iter(int N, int m, double omega, const double* in, double* 
               omega / 4.0, hl * hl, done);
 }
 
-hipError_t launch_p2_zero(int N, int m, double* out, const Lay& ml, const int* done, hipStream_t s) {
+hipError_t launch_p2_tile(int N, int m, int it, double omega, int from, const double* sprev, const double* scur,
+                          const Lay& sl, const double* e, const Lay& el, double* prev, double* cur, const Lay& ml,
+                          const double* const* fam, const Lay& fl, const int* done, hipStream_t s) {
   const int h = N >> (m + 1);
-  if (m < 1 || h < 1 || ml.side != h) return hipErrorInvalidValue;
-  HOMG_LAUNCH(k_p2_zero, p2_mark_grid(h), dim3(64, 4), s, p2_out(out, ml), h, done);
+  if (m < 1 || h < 1 || it < 1 || it > P2T_IT || ml.side != h || fl.side != (N >> m) || (from == 0 && !e) ||
+      (from > 0 && (!sprev || !scur || sl.side != (N >> (from + 1)))))
+    return hipErrorInvalidValue;
+  P2TileArgs g{};
+  if (from > 0) {
+    g.sp = p2_in(sprev, sl);
+    g.sc = p2_in(scur, sl);
+  } else if (from == 0) {
+    g.e = e + el.off;
+    g.ep = el.pitch;
+  }
+  g.from = from;
+  g.prev = p2_out(prev, ml);
+  g.cur = p2_out(cur, ml);
+  for (int z = 0; z < 4; ++z) g.fam.f[z] = fam[z] + fl.off;
+  g.fp = fl.pitch;
+  g.N = N;
+  g.m = m;
+  g.it = it;
+  g.w = omega / 4.0;
+  const double hl = double(1 << m) / double(N - 1);
+  g.hl2 = hl * hl;
+  g.done = done;
+  if (h >= P2T_WIDE) {
+    g.nb = (h + 31) / 32;
+    HOMG_LAUNCH((k_p2_tile<32, 1024, 2>), dim3(4u * unsigned(g.nb) * unsigned(g.nb)), dim3(1024), s, g);
+  }
+  g.nb = (h + 15) / 16;
+  HOMG_LAUNCH((k_p2_tile<16, 832, 1>), dim3(4u * unsigned(g.nb) * unsigned(g.nb)), dim3(832), s, g);
 }
 
 hipError_t launch_p2_write(int N, int m, const double* prev, const double* cur, const Lay& ml, double* en,

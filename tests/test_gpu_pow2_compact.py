@@ -48,3 +48,16 @@ def test_compact_form_is_bitwise_identical(B, torch_cuda, N, opts):
         s.close()
     for o in outs[1:]:
         assert np.array_equal(o[0], outs[0][0]) and o[1] == outs[0][1] and np.array_equal(o[2], outs[0][2])
+
+
+@pytest.mark.parametrize("N,opts", [
+    (32, {"levels": 2, "max_i": 2}), (64, {"levels": 3, "max_i": 4}), (128, {"levels": 2, "max_i": 5}),
+    (256, {"levels": 2, "max_i": 1}), (512, {"levels": 4, "max_i": 3}), (512, {"max_i": 2}), (1024, {"max_i": 6}),
+    (1024, {"schedule": [(4, 2), (1, 3), (0, 4)]}), (512, {"schedule": [(2, 2), (0, 2), (1, 1), (0, 7)]}),
+    (512, {"schedule": [(3, 2), (1, 4), (1, 2), (0, 1), (0, 2)]}),
+])
+def test_blocks_of_marks(B, torch_cuda, N, opts):
+    """Several iterations per launch on blocks of marks, across the seams of
+    the quadrants, and level 0 from level 1's marks, without the one-workgroup
+    tail or with few levels in it."""
+    test_compact_form_is_bitwise_identical(B, torch_cuda, N, opts)
