@@ -132,6 +132,10 @@ struct homg_ctx {
   std::vector<double*> p2x;
   std::vector<Lay> p2l;
   int p2_level = -1;
+  // factors of the variable coefficient's levels from face_level (the first of
+  // side tail_max_side(2) or less) on, one after the other (launch_faces)
+  double* faces = nullptr;
+  int face_level = 0;
   double* p2_prev = nullptr;
   double* p2_cur = nullptr;
   // L1 error (Sec. 4): partial sums and per-iteration results (allocated on first use)
@@ -245,6 +249,7 @@ void free_ctx(homg_ctx* h) {
   for (void* p : h->xp3) (void)hipFree(p);
   for (double* p : h->fam) (void)hipFree(p);
   (void)hipFree(h->p2_base);
+  (void)hipFree(h->faces);
   (void)hipFree(h->partials);
   (void)hipFree(h->st);
   (void)hipFree(h->hist);
@@ -716,6 +721,15 @@ homg_status run_level_learned(homg_ctx* h, int m, int it, bool first, bool last,
   return finish_level(h, m, last, next_m, wmode, X[1 - src], X[src], cur, acc, done, s);
 }
 
+// The factors of level m (one the one-workgroup kernels may run), or null:
+// constant coefficient.
+const double* level_faces(const homg_ctx* h, int m) {
+  if (!h->has_coef) return nullptr;
+  const double* p = h->faces;
+  for (int k = h->face_level; k < m; ++k) p += 3 * size_t(h->al[k].side) * size_t(h->al[k].side);
+  return p;
+}
+
 // Number of leading schedule entries the coarse tail runs (0: none) and
 // the finest of their levels.  They must start at the coarsest level,
 // descend one level at a time, fit one workgroup, not be visited again, and
@@ -724,6 +738,7 @@ int tail_levels(const homg_ctx* h, int* ms) {
   const int np = int(h->sched.size() / 2);
   if (h->temporal != 2 || np < 3 || h->pow2) return 0;
   const bool learned = h->active_smoother == 1;
+  if (!learned && h->has_coef && !h->faces) return 0;
   if (h->sched[0] != h->top_level) return 0;
   int cnt = 0;
   for (int p = 0; p + 1 < np && p < BATCH_MAX_LEVELS; ++p) {
@@ -945,8 +960,7 @@ homg_status enqueue_cycle(homg_ctx* h, const double* f, double* acc, int cycle, 
                                    f && h->fin_pending >= 0 ? h->partials : nullptr, h->fin_count, h->fin_pending, s));
     else
       LAUNCH_K(h, s, K_TAIL, ms, 1,
-               launch_coarse_tail(h->prec, h->d, nms, ntail, its, h->omega, h->has_coef ? h->a[ms] : nullptr,
-                                h->has_coef ? h->al[ms] : none, h->r[ms], h->rl[ms],
+               launch_coarse_tail(h->prec, h->d, nms, ntail, its, h->omega, level_faces(h, ms), h->r[ms], h->rl[ms],
                                 h->xc[2 * ms], h->xc[2 * ms + 1], h->rl[ms], top64(h), f ? h->st : h->zero_st,
                                 h->hist, f && h->fin_pending >= 0 ? h->partials : nullptr, h->fin_count,
                                 h->fin_pending, s));
@@ -1035,6 +1049,7 @@ homg_status solve_result(homg_ctx* h, bool stop_on_tol, long long launches0, int
 bool small_solve(const homg_ctx* h) {
   const int np = int(h->sched.size() / 2);
   if (h->temporal != 2 || h->active_smoother != 0 || h->pow2 || h->n > tail_max_side(h->d)) return false;
+  if (h->has_coef && !h->faces) return false;
   if (np != h->top_level + 1 || np > BATCH_MAX_LEVELS) return false;
   for (int p = 0; p < np; ++p)
     if (h->sched[2 * p] != h->top_level - p) return false;
@@ -1049,13 +1064,11 @@ homg_status run_small_solve(homg_ctx* h, const double* f, double* u, double tol,
   int its[BATCH_MAX_LEVELS];
   for (int k = 0; k < np; ++k) its[k] = h->sched[2 * (np - 1 - k) + 1];
   const int limit = stop_on_tol ? h->max_cycles : fixed_cycles;
-  const Lay none;
   int syncs = 0;
   for (int c0 = 0;; c0 += SMALL_SOLVE_CYCLES) {
     const int c1 = std::min(limit, c0 + SMALL_SOLVE_CYCLES);
     LAUNCH_K(h, s, K_TAIL, 0, 2,
-             launch_small_solve(h->prec, h->d, h->n, np, its, h->omega, h->has_coef ? h->a[0] : nullptr,
-                                h->has_coef ? h->al[0] : none, f, u, top64(h), residual_restricts(h), c0, c1,
+             launch_small_solve(h->prec, h->d, h->n, np, its, h->omega, level_faces(h, 0), f, u, top64(h), residual_restricts(h), c0, c1,
                                 stop_on_tol ? tol : 0.0, stop_on_tol ? 1 : 0, h->st, h->hist, h->h_st, h->h_hist, s));
     HIPCHK(h, hipStreamSynchronize(s));
     ++syncs;
@@ -1423,10 +1436,18 @@ homg_status homg_set_coefficient(homg_handle h, const double* a, void* stream) {
         return e;
     for (int m = 0; m < h->levels; ++m)
       HIPCHK(h, hipMemsetAsync(h->a[m], 0, sizeof(double) * h->al[m].alloc, s));
+    while (h->face_level < h->levels && h->al[h->face_level].side > tail_max_side(2)) ++h->face_level;
+    size_t cnt = 0;
+    for (int m = h->face_level; m <= h->top_level; ++m) cnt += 3 * size_t(h->al[m].side) * size_t(h->al[m].side);
+    if (cnt)
+      if (homg_status e = dev_alloc(h, reinterpret_cast<void**>(&h->faces), sizeof(double) * cnt)) return e;
   }
   // level-m lattice coefficients: the nodal values sampled every 2^m nodes
   for (int m = 0; m < h->levels; ++m)
     LAUNCH(h, launch_sample(h->d, a, h->dl, 1 << m, h->a[m], h->al[m], s));
+  if (h->faces)
+    LAUNCH(h, launch_faces(h->prec, h->top_level - h->face_level + 1, &h->a[h->face_level], &h->al[h->face_level],
+                           h->r64 != nullptr, h->omega, h->faces, s));
   h->has_coef = true;
   return HOMG_OK;
 }

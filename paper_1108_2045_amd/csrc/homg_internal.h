@@ -216,8 +216,8 @@ hipError_t launch_lattice_small(int prec, int d, int nm, int l, int it, double o
 // of at most tail_max_side(d) (its nodes in registers, four per lane).
 // coarse_tail_lds: the LDS bytes.  top64 (FP32/BF16 cycles): the coarsest
 // level in FP64 (its restriction, iterates and arithmetic), rounded to the
-// storage type only for the hand-over.  a (2D, or null): level ms's nodal
-// coefficient, layout al.
+// storage type only for the hand-over.  faces (2D, or null): the factors of
+// level ms and the coarser levels behind it, as launch_faces leaves them.
 //
 // launch_coarse_tail: restricts r_ms (side nms, layout rl) and leaves level
 // ms's final x_it and x_{it-1} in scur and sprev (layout sl, interior nodes)
@@ -231,13 +231,20 @@ hipError_t launch_lattice_small(int prec, int d, int nm, int l, int it, double o
 // the state.  rr: the norms summed as launch_residual_restrict_2d's, else as
 // launch_residual's.
 constexpr int tail_max_side(int d) { return d == 2 ? 65 : 17; }
+// launch_faces: per level k < levels (sides at most tail_max_side(2), one half
+// of the one before) of a variable coefficient three arrays of side^2 values,
+// one level after the other: the face coefficients west and south of each node
+// and omega / the sum of its four, in the cycle's arithmetic (wide_last: the
+// last level's in FP64).
+hipError_t launch_faces(int prec, int levels, const double* const* a, const Lay* al, bool wide_last, double omega,
+                        double* out, hipStream_t s);
 size_t coarse_tail_lds(int prec, int d, int nms, int nlev, bool top64, bool var, bool solve);
-hipError_t launch_coarse_tail(int prec, int d, int nms, int nlev, const int* its, double omega, const double* a,
-                              const Lay& al, const void* rms, const Lay& rl, void* sprev, void* scur, const Lay& sl,
+hipError_t launch_coarse_tail(int prec, int d, int nms, int nlev, const int* its, double omega,
+                              const double* faces, const void* rms, const Lay& rl, void* sprev, void* scur, const Lay& sl,
                               bool top64, DevState* st, double* hist, const double* partials, int count, int cycle,
                               hipStream_t s);
-hipError_t launch_small_solve(int prec, int d, int n, int nlev, const int* its, double omega, const double* a,
-                              const Lay& al, const double* f, double* u, bool top64, bool rr, int c0, int c1,
+hipError_t launch_small_solve(int prec, int d, int n, int nlev, const int* its, double omega,
+                              const double* faces, const double* f, double* u, bool top64, bool rr, int c0, int c1,
                               double tol, int stop, DevState* st, double* hist, DevState* hst, double* hhist,
                               hipStream_t s);
 // FP64 coarsest level of a reduced-precision cycle: the restriction to it

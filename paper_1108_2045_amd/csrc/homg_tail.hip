@@ -47,9 +47,8 @@ struct TailArgs {
   int nms, nlev;          // side of the finest level, number of levels
   double hl2;             // h^2 of the finest level
   double w;               // omega / 2d, or omega with a variable coefficient
-  int x_off, a_off, t_off, s_off;  // byte offsets in LDS: exchange, coefficient, FP64 coarsest level, sums
-  const double* a;        // nodal coefficient of the finest level (node 0), or null
-  int64_t ap;
+  int x_off, a_off, t_off, s_off;  // byte offsets in LDS: exchange, coarser levels' factors, FP64 coarsest level, sums
+  const double* faces;    // variable coefficient: the levels' factors (launch_faces), or null
   DevState* st;
   double* hist;
   // coarse tail
@@ -228,7 +227,7 @@ constexpr int ROW_W = S > 17 ? 32 : S > 9 ? 16 : 8;
 // to T, where its parity puts it (x_it in Q if it is odd), interior nodes only.
 template <typename T, typename V, bool VAR, int S>
 __device__ __forceinline__ void row_level(const V* R, typename Tr<T>::C* me, int it, V w, bool zero,
-                                          const typename Tr<T>::C* hi, int ith, const double* A, int ap, int as, V* X) {
+                                          const typename Tr<T>::C* hi, int ith, const double* fac, V* X) {
   using C = typename Tr<T>::C;
   constexpr bool EXACT = sizeof(V) != sizeof(C);  // FP64 iterates in a reduced-precision cycle
   constexpr int W = ROW_W<S>, BUF = (W + 1) * W, H = (S + 1) / 2;
@@ -244,13 +243,11 @@ __device__ __forceinline__ void row_level(const V* R, typename Tr<T>::C* me, int
   if (on) {  // (whole waves)
     r = R[i];
     if constexpr (VAR) {
-      const double* p = A + (min(y, S - 2) * ap + min(x, S - 2)) * as;
-      const double c = p[0];
-      cw = V(harm(c, p[-as]));
-      ce = V(harm(c, p[as]));
-      cs = V(harm(c, p[-as * ap]));
-      cn = V(harm(c, p[as * ap]));
-      ws = w / ((cw + ce) + (cs + cn));
+      cw = V(fac[i]);
+      ce = V(fac[i + 1]);
+      cs = V(fac[S * S + i]);
+      cn = V(fac[S * S + i + S]);
+      ws = V(fac[2 * S * S + i]);
     }
     if constexpr (!EXACT && S > 3) {
       if (!zero) {
@@ -438,7 +435,7 @@ __device__ __forceinline__ void tail_block(const TailArgs<T>& q, const TailRun& 
   C* base = reinterpret_cast<C*>(smem);
   C* R0 = base;  // 3D: level ms's right-hand side, then R, P, Q of every coarser level
   C* E0 = base;  // 2D: an exchange row per wave, then the coarser levels' arrays
-  double* A0 = reinterpret_cast<double*>(smem + q.a_off);
+  double* A0 = reinterpret_cast<double*>(smem + q.a_off);  // VAR: the coarser levels' factors
   double* top64 = reinterpret_cast<double*>(smem + q.t_off);
   double* sums = reinterpret_cast<double*>(smem + q.s_off);
   const C w = C(q.w);
@@ -468,8 +465,28 @@ __device__ __forceinline__ void tail_block(const TailArgs<T>& q, const TailRun& 
     }
     ulo = run.u[pl + xc];  // y = 0
   }
-  if (VAR)
-    for (int i = threadIdx.x; i < n * n; i += TAIL_NT) A0[i] = q.a[int64_t(i / n) * q.ap + i % n];
+  // VAR: the factors (launch_faces) of the lane's nodes -- west of each (the
+  // east ones are the next lane's), south of each and north of the last, w /
+  // sum -- to registers, the coarser levels' to LDS.  Formed here, with some twenty
+  // divisions a lane in every launch, whole solves took 371 us at 65^2 (336
+  // now) and 220 at 33^2 (207), the tail 18.6 (17.9).
+  double fx[4], fy[5];
+  C ws[4];
+  if (VAR) {
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      const double* p = q.faces + min(tn.y0 + k, n - 1) * n + xc;
+      fy[k] = p[n * n];
+      if (k < 4) {
+        fx[k] = p[0];
+        ws[k] = C(p[2 * n * n]);
+      }
+    }
+    const double* next = q.faces + 3 * n * n;
+    int cnt = 0;
+    for (int k = 1; k < nlev; ++k) cnt += 3 * (((n - 1) >> k) + 1) * (((n - 1) >> k) + 1);
+    for (int i = threadIdx.x; i < cnt; i += TAIL_NT) A0[i] = next[i];
+  }
   // the coarser levels' arrays start at 0 (their boundary nodes stay so)
   for (int i = LEV_OFF<D, (D == 2 ? 33 : 9)> + int(threadIdx.x); i < LEV_END<D>; i += TAIL_NT) base[i] = C(0);
   if (SOLVE && threadIdx.x < 128) sums[threadIdx.x] = 0.0;
@@ -486,26 +503,6 @@ __device__ __forceinline__ void tail_block(const TailArgs<T>& q, const TailRun& 
     if (s_done) return;
   }
   const int o0 = (D == 3 ? zc * n * n : 0) + xc;  // the lane's column in R0
-  // VAR: the lane's face coefficients -- west of each node (the east ones
-  // are the next lane's: harm is symmetric to the bit) and south of each,
-  // then north of the last -- and w / their sum
-  double fx[4], fy[5];
-  C ws[4];
-  if (VAR) {
-    __syncthreads();
-    const double* col = A0 + xc;
-    double a = col[(min(tn.y0, n - 1) - 1) * n];
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-      const double b = col[min(tn.y0 + k, n - 1) * n];
-      fy[k] = harm(b, a);
-      if (k < 4) fx[k] = harm(b, col[min(tn.y0 + k, n - 1) * n - 1]);
-      a = b;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) ws[k] = w / ((C(fx[k]) + C(x_next<D>(1.0, fx[k]))) + (C(fy[k]) + C(fy[k + 1])));
-  }
-
   // waves whose nodes all lie off the grid only take part in the barriers
   const bool wave_on = D == 2 ? 4 * tn.wv + 1 <= n - 2 : tn.wv + 1 <= n - 2;
   const bool wave_put = (D == 2 ? 4 * tn.wv : tn.wv) <= n - 2;  // (the boundary's values too)
@@ -702,11 +699,13 @@ __device__ __forceinline__ void tail_block(const TailArgs<T>& q, const TailRun& 
       C* const me = base + LEV_OFF<D, S>;
       const C* hi = base + LEV_OFF<D, (S > 3 ? (S + 1) / 2 : 3)>;
       if constexpr (D == 2) {
-        const int as = (n - 1) / (S - 1);
+        const int o1 = S1 == 33 ? LEV_OFF<2, 33> : S1 == 17 ? LEV_OFF<2, 17> : S1 == 9 ? LEV_OFF<2, 9>
+                       : S1 == 5 ? LEV_OFF<2, 5> : LEV_OFF<2, 3>;
+        const double* fac = A0 + (LEV_OFF<2, S> - o1);  // (three arrays per level too)
         if (t64)
-          row_level<T, double, VAR, S>(top64, me, it, q.w, true, hi, 0, A0, n, as, X64);
+          row_level<T, double, VAR, S>(top64, me, it, q.w, true, hi, 0, fac, X64);
         else
-          row_level<T, C, VAR, S>(me, me, it, w, S == Stop, hi, ith, A0, n, as, X);
+          row_level<T, C, VAR, S>(me, me, it, w, S == Stop, hi, ith, fac, X);
       } else {
         if (t64)
           box_level<T, double, S>(top64, me, it, q.w, true, hi, 0, sync);
@@ -948,7 +947,9 @@ TailLds tail_lds(int prec, int d, int nms, int nlev, bool top64, bool var, bool 
   const bool t64 = top64 && prec != PREC_F64;
   const size_t rows64 = d == 2 && t64 ? 2 * 33 * 32 * 8 : 0;  // an FP64 level's exchange
   L.x_off = take(at, std::max({2 * xn * cs, solve ? xn * 8 : size_t(0), rows64}));
-  L.a_off = take(at, var ? nodes(0) * 8 : 0);
+  size_t facs = 0;
+  for (int k = 1; k < nlev; ++k) facs += 3 * nodes(k);
+  L.a_off = take(at, var ? facs * 8 : 0);
   L.t_off = take(at, t64 ? 3 * nodes(nlev - 1) * 8 : 0);
   L.s_off = take(at, solve ? 128 * 8 : 0);
   L.bytes = at;
@@ -974,20 +975,19 @@ hipError_t launch_d(int d, bool top64, bool var, const TailArgs<T>& a, const Tai
 }
 
 template <typename T>
-TailArgs<T> make_args(const TailLds& L, int d, int nms, int nlev, const int* its, double omega, const double* a,
-                      const Lay& al, DevState* st, double* hist) {
+TailArgs<T> make_args(const TailLds& L, int d, int nms, int nlev, const int* its, double omega, const double* faces,
+                      DevState* st, double* hist) {
   TailArgs<T> q{};
   for (int k = 0; k < nlev; ++k) q.it[k] = its[k];
   q.nms = nms;
   q.nlev = nlev;
   q.hl2 = (1.0 / double(nms - 1)) * (1.0 / double(nms - 1));
-  q.w = a ? omega : omega / double(2 * d);
+  q.w = faces ? omega : omega / double(2 * d);
   q.x_off = L.x_off;
   q.a_off = L.a_off;
   q.t_off = L.t_off;
   q.s_off = L.s_off;
-  q.a = a ? a + al.off : nullptr;
-  q.ap = al.pitch;
+  q.faces = faces;
   q.st = st;
   q.hist = hist;
   return q;
@@ -1005,12 +1005,12 @@ size_t coarse_tail_lds(int prec, int d, int nms, int nlev, bool top64, bool var,
 }
 
 template <typename T>
-static hipError_t tail_t(int prec, int d, int nms, int nlev, const int* its, double omega, const double* a,
-                         const Lay& al, const void* rms, const Lay& rl, void* sprev, void* scur, const Lay& sl,
+static hipError_t tail_t(int prec, int d, int nms, int nlev, const int* its, double omega, const double* faces,
+                         const void* rms, const Lay& rl, void* sprev, void* scur, const Lay& sl,
                          bool top64, DevState* st, double* hist, const double* partials, int count, int cycle,
                          hipStream_t s) {
-  const TailLds L = tail_lds(prec, d, nms, nlev, top64, a != nullptr, false);
-  TailArgs<T> q = make_args<T>(L, d, nms, nlev, its, omega, a, al, st, hist);
+  const TailLds L = tail_lds(prec, d, nms, nlev, top64, faces != nullptr, false);
+  TailArgs<T> q = make_args<T>(L, d, nms, nlev, its, omega, faces, st, hist);
   q.r = static_cast<const T*>(rms) + rl.off;
   q.rp = rl.pitch;
   q.rpl = rl.plane;
@@ -1021,18 +1021,18 @@ static hipError_t tail_t(int prec, int d, int nms, int nlev, const int* its, dou
   q.partials = partials;
   q.count = count;
   const TailRun run{partials ? cycle : -1, nullptr, nullptr, 0.0, 0, 0, 0};
-  return launch_d<T, false>(d, top64, a != nullptr, q, run, L.bytes, s);
+  return launch_d<T, false>(d, top64, faces != nullptr, q, run, L.bytes, s);
 }
 
-hipError_t launch_coarse_tail(int prec, int d, int nms, int nlev, const int* its, double omega, const double* a,
-                              const Lay& al, const void* rms, const Lay& rl, void* sprev, void* scur, const Lay& sl,
+hipError_t launch_coarse_tail(int prec, int d, int nms, int nlev, const int* its, double omega, const double* faces,
+                              const void* rms, const Lay& rl, void* sprev, void* scur, const Lay& sl,
                               bool top64, DevState* st, double* hist, const double* partials, int count, int cycle,
                               hipStream_t s) {
-  if (!tail_ok(d, nms, nlev) || nlev < 2 || (a && d != 2) || !rms || !sprev || !scur || sl.side != nms ||
-      rl.side != nms || (a && al.side != nms))
+  if (!tail_ok(d, nms, nlev) || nlev < 2 || (faces && d != 2) || !rms || !sprev || !scur || sl.side != nms ||
+      rl.side != nms)
     return hipErrorInvalidValue;
 #define TAIL_CASE(T)                                                                                           \
-  return tail_t<T>(prec, d, nms, nlev, its, omega, a, al, rms, rl, sprev, scur, sl, top64, st, hist, partials, \
+  return tail_t<T>(prec, d, nms, nlev, its, omega, faces, rms, rl, sprev, scur, sl, top64, st, hist, partials, \
                    count, cycle, s)
   switch (prec) {
     case PREC_F64: TAIL_CASE(double);
@@ -1043,28 +1043,28 @@ hipError_t launch_coarse_tail(int prec, int d, int nms, int nlev, const int* its
 }
 
 template <typename T>
-static hipError_t small_solve_t(int prec, int d, int n, int nlev, const int* its, double omega, const double* a,
-                                const Lay& al, const double* f, double* u, bool top64, bool rr, int c0, int c1,
+static hipError_t small_solve_t(int prec, int d, int n, int nlev, const int* its, double omega, const double* faces,
+                                const double* f, double* u, bool top64, bool rr, int c0, int c1,
                                 double tol, int stop, DevState* st, double* hist, DevState* hst, double* hhist,
                                 hipStream_t s) {
-  const TailLds L = tail_lds(prec, d, n, nlev, top64, a != nullptr, true);
-  TailArgs<T> q = make_args<T>(L, d, n, nlev, its, omega, a, al, st, hist);
+  const TailLds L = tail_lds(prec, d, n, nlev, top64, faces != nullptr, true);
+  TailArgs<T> q = make_args<T>(L, d, n, nlev, its, omega, faces, st, hist);
   const double h = 1.0 / double(n - 1);
   q.inv_h2 = 1.0 / (h * h);
   q.rr = rr;
   q.hst = hst;
   q.hhist = hhist;
-  return launch_d<T, true>(d, top64, a != nullptr, q, TailRun{-1, f, u, tol, c0, c1, stop}, L.bytes, s);
+  return launch_d<T, true>(d, top64, faces != nullptr, q, TailRun{-1, f, u, tol, c0, c1, stop}, L.bytes, s);
 }
 
-hipError_t launch_small_solve(int prec, int d, int n, int nlev, const int* its, double omega, const double* a,
-                              const Lay& al, const double* f, double* u, bool top64, bool rr, int c0, int c1,
+hipError_t launch_small_solve(int prec, int d, int n, int nlev, const int* its, double omega, const double* faces,
+                              const double* f, double* u, bool top64, bool rr, int c0, int c1,
                               double tol, int stop, DevState* st, double* hist, DevState* hst, double* hhist,
                               hipStream_t s) {
-  if (!tail_ok(d, n, nlev) || (a && (d != 2 || al.side != n)) || !f || !u || c1 < c0 || (top64 && nlev < 2))
+  if (!tail_ok(d, n, nlev) || (faces && d != 2) || !f || !u || c1 < c0 || (top64 && nlev < 2))
     return hipErrorInvalidValue;
 #define SMALL_CASE(T)                                                                                            \
-  return small_solve_t<T>(prec, d, n, nlev, its, omega, a, al, f, u, top64, rr, c0, c1, tol, stop, st, hist, hst, \
+  return small_solve_t<T>(prec, d, n, nlev, its, omega, faces, f, u, top64, rr, c0, c1, tol, stop, st, hist, hst, \
                           hhist, s)
   switch (prec) {
     case PREC_F64: SMALL_CASE(double);
@@ -1072,6 +1072,56 @@ hipError_t launch_small_solve(int prec, int d, int n, int nlev, const int* its, 
     default: SMALL_CASE(bf16);
   }
 #undef SMALL_CASE
+}
+
+// ---- variable coefficient: the factors of the levels one workgroup may run
+
+struct FaceLevel {
+  const double* a;  // nodal coefficient at (0, 0)
+  int64_t ap;
+  int side, off, wide;  // wide: w / sum in FP64 whatever the storage type
+};
+struct FaceArgs {
+  FaceLevel lv[8];
+  double* out;
+  double w;
+  int f32;  // w / sum in FP32
+};
+__global__ __launch_bounds__(256) void k_faces(FaceArgs q) {
+  const FaceLevel& L = q.lv[blockIdx.y];
+  const int S = L.side, i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= S * S) return;
+  const int y = i / S, x = i % S;
+  const double* p = L.a + y * L.ap + x;
+  const double c = p[0];
+  // (face coefficients are symmetric to the bit: each is formed once)
+  const double w = x > 0 ? harm(c, p[-1]) : 0.0, s = y > 0 ? harm(c, p[-L.ap]) : 0.0;
+  double d = 0.0;
+  if (x > 0 && y > 0 && x < S - 1 && y < S - 1) {
+    const double e = harm(c, p[1]), n = harm(c, p[L.ap]);
+    d = q.f32 && !L.wide ? double(float(q.w) / ((float(w) + float(e)) + (float(s) + float(n))))
+                         : q.w / ((w + e) + (s + n));
+  }
+  double* o = q.out + L.off + i;
+  o[0] = w;
+  o[S * S] = s;
+  o[2 * S * S] = d;
+}
+
+hipError_t launch_faces(int prec, int levels, const double* const* a, const Lay* al, bool wide_last, double omega,
+                        double* out, hipStream_t s) {
+  if (levels < 1 || levels > 8) return hipErrorInvalidValue;
+  FaceArgs q{};
+  int off = 0;
+  for (int k = 0; k < levels; ++k) {
+    if (al[k].side > tail_max_side(2)) return hipErrorInvalidValue;
+    q.lv[k] = FaceLevel{a[k] + al[k].off, al[k].pitch, al[k].side, off, wide_last && k == levels - 1};
+    off += 3 * al[k].side * al[k].side;
+  }
+  q.out = out;
+  q.w = omega;
+  q.f32 = prec != PREC_F64;
+  HOMG_LAUNCH(k_faces, dim3(unsigned(al[0].side * al[0].side + 255) / 256, unsigned(levels)), dim3(256), s, q);
 }
 
 size_t batch_tail_bytes(int prec) {
@@ -1082,7 +1132,7 @@ template <typename T>
 static void batch_tail_t(int prec, void* dst, int n, int nlev, const int* its, double omega, const void* r, int64_t rp,
                          void* sprev, void* scur, int64_t sp, bool top64, DevState* st, double* hist,
                          const double* partials, int count) {
-  TailArgs<T> q = make_args<T>(tail_lds(prec, 2, n, nlev, top64, false, false), 2, n, nlev, its, omega, nullptr, Lay(),
+  TailArgs<T> q = make_args<T>(tail_lds(prec, 2, n, nlev, top64, false, false), 2, n, nlev, its, omega, nullptr,
                                st, hist);
   q.r = static_cast<const T*>(r);
   q.rp = rp;
@@ -1110,7 +1160,7 @@ void batch_tail_fill(int prec, void* dst, int n, int nlev, const int* its, doubl
 template <typename T>
 static void batch_small_t(int prec, void* dst, int n, int nlev, const int* its, double omega, bool top64, bool rr,
                           int prob, DevState* st, double* hist) {
-  TailArgs<T> q = make_args<T>(tail_lds(prec, 2, n, nlev, top64, false, true), 2, n, nlev, its, omega, nullptr, Lay(),
+  TailArgs<T> q = make_args<T>(tail_lds(prec, 2, n, nlev, top64, false, true), 2, n, nlev, its, omega, nullptr,
                                st, hist);
   const double h = 1.0 / double(n - 1);
   q.inv_h2 = 1.0 / (h * h);
