@@ -133,7 +133,8 @@ struct homg_ctx {
   std::vector<Lay> p2l;
   int p2_level = -1;
   // factors of the variable coefficient's levels from face_level (the first of
-  // side tail_max_side(2) or less) on, one after the other (launch_faces)
+  // side tail_max_side(2) or less) on, one after the other (launch_faces),
+  // behind the last level's coefficient in its allocation
   double* faces = nullptr;
   int face_level = 0;
   double* p2_prev = nullptr;
@@ -249,7 +250,6 @@ void free_ctx(homg_ctx* h) {
   for (void* p : h->xp3) (void)hipFree(p);
   for (double* p : h->fam) (void)hipFree(p);
   (void)hipFree(h->p2_base);
-  (void)hipFree(h->faces);
   (void)hipFree(h->partials);
   (void)hipFree(h->st);
   (void)hipFree(h->hist);
@@ -1430,17 +1430,18 @@ homg_status homg_set_coefficient(homg_handle h, const double* a, void* stream) {
   DeviceGuard guard(h->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (h->a.empty()) {
-    h->a.assign(h->levels, nullptr);
-    for (int m = 0; m < h->levels; ++m)
-      if (homg_status e = dev_alloc(h, reinterpret_cast<void**>(&h->a[m]), sizeof(double) * h->al[m].alloc))
-        return e;
-    for (int m = 0; m < h->levels; ++m)
-      HIPCHK(h, hipMemsetAsync(h->a[m], 0, sizeof(double) * h->al[m].alloc, s));
+    h->face_level = 0;
     while (h->face_level < h->levels && h->al[h->face_level].side > tail_max_side(2)) ++h->face_level;
     size_t cnt = 0;
     for (int m = h->face_level; m <= h->top_level; ++m) cnt += 3 * size_t(h->al[m].side) * size_t(h->al[m].side);
-    if (cnt)
-      if (homg_status e = dev_alloc(h, reinterpret_cast<void**>(&h->faces), sizeof(double) * cnt)) return e;
+    h->a.assign(h->levels, nullptr);
+    for (int m = 0; m < h->levels; ++m)
+      if (homg_status e = dev_alloc(h, reinterpret_cast<void**>(&h->a[m]),
+                                    sizeof(double) * (h->al[m].alloc + (m + 1 == h->levels ? cnt : 0))))
+        return e;
+    for (int m = 0; m < h->levels; ++m)
+      HIPCHK(h, hipMemsetAsync(h->a[m], 0, sizeof(double) * h->al[m].alloc, s));
+    if (cnt) h->faces = h->a[h->levels - 1] + h->al[h->levels - 1].alloc;
   }
   // level-m lattice coefficients: the nodal values sampled every 2^m nodes
   for (int m = 0; m < h->levels; ++m)
