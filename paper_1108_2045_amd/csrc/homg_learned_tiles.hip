@@ -2,8 +2,10 @@
 // levels per launch (2D, chained execution).
 //
 // What bounds it: on lattices up to 129^2 the launch and the chain of phases
-// of one block, above that the vector instructions (about 90 per node and
-// iteration around 576 multiply-adds on the matrix cores).  One launch per
+// of one block; above that the phases between barriers with 16 waves on a CU:
+// at 1025^2 vector issue (1300 instructions a wave for two iterations) fills 36
+// of a pass's 50 us, LDS 20 and the matrix cores 10, and dropping the masks of
+// blocks away from the boundary (60 instructions) left it at 50.  One launch per
 // iteration with a hand-over launch per level took 406 us a cycle at 1025^2
 // (FP64, 10 levels); these two kernels take 229.  A workgroup keeps a 32 x 32
 // block of the hidden layer and
