@@ -292,11 +292,11 @@ __global__ __launch_bounds__(256) void k_p2_iter(P2Marks in, P2Out out, P2Fam4 f
 // side's: at most B + 12 positions.  The starting state is formed in the tile
 // from the coarser level's pair.  What bounds it is latency: a block loads,
 // then runs four short phases.  One launch in place of a hand-over and a
-// launch per iteration, four iterations: 21 -> 5 us at h = 32, 33 -> 28 at
-// h = 512, 100 -> 92 at h = 1024.  B = 16 (a node per lane, the shortest
+// launch per iteration, four iterations: 21 -> 5 us at h = 32, 33 -> 27 at
+// h = 512, 100 -> 88 at h = 1024.  B = 16 (a node per lane, the shortest
 // phases) while its blocks fit the chip about once; from h = 256 on B = 32 (two
 // nodes per lane), which repeats 1.6 nodes per owned one in place of 2.3 (h =
-// 1024: 92 us against 153).
+// 1024: 92 us against 153, before the offsets were 32-bit).
 constexpr int P2T_WIDE = 256;
 constexpr int p2t_side(int B) { return B + 3 * P2T_IT; }  // positions per axis at most
 
@@ -354,22 +354,28 @@ __global__ __launch_bounds__(NT) void k_p2_tile(P2TileArgs g) {
     const int done = *g.done;
     const double* fam = z & 2 ? (z & 1 ? g.fam.f[3] : g.fam.f[2]) : (z & 1 ? g.fam.f[1] : g.fam.f[0]);
     const int side = B + 2 * g.it;
-    int o[K];
+    // 32-bit offsets from the quadrant's arrays (launch_p2_tile checks them; with
+    // 64-bit products and a division per node and use 92 us at h = 1024, now 88)
+    const double* const sp = g.sp.p + z * g.sp.plane;
+    const double* const sc = g.sc.p + z * g.sc.plane;
+    const int fp = int(g.fp), pp = int(g.sp.pitch), op = int(g.cur.pitch);
+    int pj[K], pi[K], o[K];
     bool mark[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int q = threadIdx.x + k * NT, pj = q / W, pi = q % W;
-      const int i = a - g.it + pi, j = b - g.it + pj;
-      o[k] = PAD + min(pj, S - 1) * S + pi;
-      mark[k] = i >= 1 && j >= 1 && pi < side && pj < side;
+      pj[k] = k ? pj[k - 1] + NT / W : int(threadIdx.x) / W;
+      pi[k] = k ? pi[k - 1] + NT % W : int(threadIdx.x) % W;
+      if (k && pi[k] >= W) pi[k] -= W, ++pj[k];
+      const int i = a - g.it + pi[k], j = b - g.it + pj[k];
+      o[k] = PAD + min(pj[k], S - 1) * S + pi[k];
+      mark[k] = i >= 1 && j >= 1 && pi[k] < side && pj[k] < side;
       const int ic = min(max(i, 1), h), jc = min(max(j, 1), h);
       v[k] = 0.0;
       pv[k] = 0.0;
-      r[k] = fam[int64_t(jc) * g.fp + ic];
+      r[k] = fam[jc * fp + ic];
       if (g.from == m + 1) {  // p2_state here: lattice nodes as they are, others interpolated
-        const int64_t at = z * g.sp.plane + int64_t(min(jc >> 1, (h >> 1) - 1)) * g.sp.pitch + min(ic >> 1, (h >> 1) - 1);
-        const double c = g.sc.p[at], p00 = g.sp.p[at], p01 = g.sp.p[at + 1], p10 = g.sp.p[at + g.sp.pitch],
-                     p11 = g.sp.p[at + g.sp.pitch + 1];
+        const int at = min(jc >> 1, (h >> 1) - 1) * pp + min(ic >> 1, (h >> 1) - 1);
+        const double c = sc[at], p00 = sp[at], p01 = sp[at + 1], p10 = sp[at + pp], p11 = sp[at + pp + 1];
         const double fx = double(ic & 1) * 0.5, fy = double(jc & 1) * 0.5;
         v[k] = (ic | jc) & 1 ? lerp(lerp(p00, p01, fx), lerp(p10, p11, fx), fy) : c;
       } else if (g.from > 0) {
@@ -383,28 +389,34 @@ __global__ __launch_bounds__(NT) void k_p2_tile(P2TileArgs g) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       if (!mark[k]) v[k] = 0.0;
-      if (int(threadIdx.x) + k * NT < W * W) {
+      if (pj[k] < W) {
         X[0][o[k]] = v[k];
         if (!mark[k]) X[1][o[k]] = 0.0;
       }
     }
     __syncthreads();
-    for (int t = 1; t <= g.it; ++t) {
+    auto step = [&](int t, const double* in, double* out) {
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        const double* src = &X[(t - 1) & 1][o[k]];
+        const double* src = in + o[k];
         pv[k] = v[k];
         v[k] = relax_const<double>(v[k], (src[-1] + src[1]) + (src[-S] + src[S]), r[k], g.w, g.hl2, 4.0);
-        if (t < g.it && mark[k]) X[t & 1][o[k]] = v[k];
+        if (t < g.it && mark[k]) out[o[k]] = v[k];
       }
       if (t < g.it) __syncthreads();
+    };
+    for (int t = 1; t <= g.it; t += 2) {
+      step(t, X[0], X[1]);
+      if (t < g.it) step(t + 1, X[1], X[0]);
     }
+    double* const oc = g.cur.p + z * g.cur.plane;
+    double* const op_ = g.prev.p + z * g.prev.plane;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int q = threadIdx.x + k * NT, i = a - g.it + q % W, j = b - g.it + q / W;
+      const int i = a - g.it + pi[k], j = b - g.it + pj[k];
       if (i < a || j < b || i >= a + B || j >= b + B) continue;
-      *g.cur.at(z, j, i) = v[k];
-      *g.prev.at(z, j, i) = pv[k];
+      oc[j * op + i] = v[k];
+      op_[j * op + i] = pv[k];
     }
     return;
   }
@@ -734,6 +746,8 @@ hipError_t launch_p2_tile(int N, int m, int it, double omega, int from, const do
   if (m < 1 || h < 1 || it < 1 || it > P2T_IT || ml.side != h || fl.side != (N >> m) || (from == 0 && !e) ||
       (from > 0 && (!sprev || !scur || sl.side != (N >> (from + 1)))))
     return hipErrorInvalidValue;
+  const int64_t lim = int64_t(1) << 31;  // 32-bit offsets inside a quadrant
+  if (fl.pitch * fl.side >= lim || ml.plane >= lim || (from > 0 && sl.plane >= lim)) return hipErrorInvalidValue;
   P2TileArgs g{};
   if (from > 0) {
     g.sp = p2_in(sprev, sl);
