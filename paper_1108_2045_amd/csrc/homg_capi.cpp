@@ -1612,14 +1612,17 @@ homg_status homg_set_smoother(homg_handle h, int smoother, const float* w, doubl
     }
     LAUNCH(h, launch_round_weights(w, h->wbf, h->w32, s));
   }
-  if (smoother == HOMG_SMOOTHER_LEARNED && h->xc.empty()) {
-    // compact lattice pairs of every coarse level (boundary nodes stay 0)
+  if (smoother == HOMG_SMOOTHER_LEARNED) {
+    // the compact lattice pairs of the coarse levels that the handle does not
+    // hold yet (temporal_block 0; boundary nodes stay 0)
     const int eb = prec_bytes(h->prec);
-    h->xc.assign(2 * h->levels, nullptr);
+    if (h->xc.empty()) h->xc.assign(2 * h->levels, nullptr);
     for (int m = 1; m < h->levels; ++m)
       for (int b = 0; b < 2; ++b) {
-        if (homg_status e = dev_alloc(h, &h->xc[2 * m + b], size_t(h->rl[m].alloc) * eb)) return e;
-        HIPCHK(h, hipMemsetAsync(h->xc[2 * m + b], 0, size_t(h->rl[m].alloc) * eb, s));
+        void*& x = h->xc[2 * m + b];
+        if (x) continue;
+        if (homg_status e = dev_alloc(h, &x, size_t(h->rl[m].alloc) * eb)) return e;
+        HIPCHK(h, hipMemsetAsync(x, 0, size_t(h->rl[m].alloc) * eb, s));
       }
   }
   h->smoother = smoother;
