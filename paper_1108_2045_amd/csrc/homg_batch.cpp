@@ -57,6 +57,7 @@ struct Problem {
 struct homg_batch_ctx {
   int count = 0, prec = 0, max_i = 4, max_cycles = 200;
   double omega = 0.8;
+  int def_rows = 16;              // default rows per tile (default_rows)
   std::vector<int> sides;
   std::map<int, int> tile_rows;   // side -> rows per tile (absent: default)
   std::map<int, int> pass_iters;  // side -> iterations per level-0 pass (absent: TB_MAX_IT)
@@ -141,7 +142,7 @@ int default_rows(const homg_batch_ctx* b) {
 int rows_for(const homg_batch_ctx* b, int side) {
   auto it = b->tile_rows.find(side);
   if (it != b->tile_rows.end() && it->second > 0) return std::min(it->second, side - 2);
-  return std::min(default_rows(b), side - 2);
+  return std::min(b->def_rows, side - 2);
 }
 
 int depth_for(const homg_batch_ctx* b, int side) {
@@ -528,6 +529,7 @@ homg_status homg_batch_create(homg_batch* out, int count, const int64_t* sides, 
     }
   }
   zeroed = total;
+  b->def_rows = default_rows(b);
   // the largest problems first in every list: a launch does not end on them
   std::stable_sort(b->big.begin(), b->big.end(), [&](int x, int y) { return b->sides[x] > b->sides[y]; });
   std::vector<size_t> part(count), hist(count);
