@@ -36,6 +36,7 @@ namespace {
 struct PassGroup {
   int it, kind;
   bool lat;
+  int desc;          // its first descriptor (the tiles count from it)
   int first, count;  // its workgroups in the tile list
 };
 struct TileRange {
@@ -314,7 +315,7 @@ homg_status build_plan(homg_batch_ctx* b) {
         q.n = nm;
         q.len = walk ? (m ? LATTICE_ROWS : std::max(16, rows_for(b, p.n))) : batch_tiled_side(nm);
         q.accum = accum ? 1 : 0;
-        mine.push_back({PassGroup{g, kind, lat, 0, 0}, q});
+        mine.push_back({PassGroup{g, kind, lat, 0, 0, 0}, q});
         src = 1 - src;
       }
       if (m) {
@@ -328,20 +329,48 @@ homg_status build_plan(homg_batch_ctx* b) {
       seq[pos].push_back(mine[k]);
     }
   }
+  // (Levels of many iterations repeat the same launch, the two iterates
+  // alternating: a launch takes its tiles from the one before it and its
+  // descriptors from the one before that where they are the same.  With lists of
+  // their own 32768 iterations of level 0 at 32769^2 were 2.5e9 tiles.)
   std::vector<BatchPass> passes;
   b->passes.clear();
+  using Key = std::tuple<int, int, bool>;
+  struct Made {
+    std::vector<BatchPass> q;
+    int desc, first, count;
+  };
+  std::map<Key, Made> made[2];  // of the last position and the one before
   for (size_t pos = seq.size(); pos-- > 0;) {
-    std::map<std::tuple<int, int, bool>, std::vector<BatchPass>> by;  // the largest problems stay first
-    for (auto& e : seq[pos]) by[std::make_tuple(e.first.it, e.first.kind, e.first.lat)].push_back(e.second);
-    for (auto& kv : by) {
-      PassGroup g{std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first), int(tiles.size()), 0};
-      for (const BatchPass& q : kv.second) {
-        passes.push_back(q);
-        add_tiles(int(passes.size()) - 1, g.kind == BATCH_TILED ? q.len * q.len : tb_blocks(q.n, g.it, q.len));
+    std::map<Key, Made> now;  // the largest problems stay first
+    for (auto& e : seq[pos]) now[Key(e.first.it, e.first.kind, e.first.lat)].q.push_back(e.second);
+    for (auto& kv : now) {
+      const int it = std::get<0>(kv.first), kind = std::get<1>(kv.first);
+      Made& m = kv.second;
+      auto same = [&](const std::map<Key, Made>& from, auto&& eq) -> const Made* {
+        const auto f = from.find(kv.first);
+        if (f == from.end() || f->second.q.size() != m.q.size()) return nullptr;
+        return std::equal(m.q.begin(), m.q.end(), f->second.q.begin(), eq) ? &f->second : nullptr;
+      };
+      if (const Made* o = same(made[1], [](const BatchPass& a, const BatchPass& c) { return !std::memcmp(&a, &c, sizeof a); })) {
+        m.desc = o->desc;
+      } else {
+        m.desc = int(passes.size());
+        passes.insert(passes.end(), m.q.begin(), m.q.end());
       }
-      g.count = int(tiles.size()) - g.first;
-      b->passes.push_back(g);
+      if (const Made* o = same(made[0], [](const BatchPass& a, const BatchPass& c) { return a.n == c.n && a.len == c.len; })) {
+        m.first = o->first;
+        m.count = o->count;
+      } else {
+        m.first = int(tiles.size());
+        for (size_t k = 0; k < m.q.size(); ++k)
+          add_tiles(int(k), kind == BATCH_TILED ? m.q[k].len * m.q[k].len : tb_blocks(m.q[k].n, it, m.q[k].len));
+        m.count = int(tiles.size()) - m.first;
+      }
+      b->passes.push_back(PassGroup{it, kind, std::get<2>(kv.first), m.desc, m.first, m.count});
     }
+    made[1] = std::move(made[0]);
+    made[0] = std::move(now);
   }
   // one allocation for all lists
   std::vector<char> host;
@@ -389,7 +418,7 @@ homg_status enqueue_cycle(homg_batch_ctx* b, int pending, hipStream_t s) {
                                         b->multi_lds, b->d_st, s));
   BHIP(b, launch_batch_tails(b->prec, red, b->plan + b->o_tail, int(b->big.size()), b->tail_lds, pending, s));
   for (const PassGroup& g : b->passes)
-    BHIP(b, launch_batch_pass(b->prec, ps, tiles + g.first, g.count, g.it, g.lat, g.kind, b->omega, b->d_st, u, s));
+    BHIP(b, launch_batch_pass(b->prec, ps + g.desc, tiles + g.first, g.count, g.it, g.lat, g.kind, b->omega, b->d_st, u, s));
   BHIP(b, launch_batch_residual(b->prec, reinterpret_cast<const BatchResidual*>(b->plan + b->o_res),
                                 tiles + b->residual.first, b->residual.count, false, f, u, b->d_st, s));
   return HOMG_OK;

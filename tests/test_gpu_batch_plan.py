@@ -1,7 +1,10 @@
 """What the batched solver prepares on the host: its cost and its memory."""
 import time
 
+import numpy as np
 import pytest
+
+import workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -36,3 +39,45 @@ def test_making_a_batch_is_linear_in_its_problems(B, torch_cuda):
     seconds(10)
     few = seconds(2000)
     assert seconds(16000) <= 20 * few + 0.05
+
+
+def held(torch, make):
+    """(device memory the handle made by make() holds, the handle)"""
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    h = make()
+    torch.cuda.synchronize()
+    return before - torch.cuda.mem_get_info()[0], h
+
+
+def test_lists_do_not_grow_with_the_iterations(B, torch_cuda):
+    """A level of many iterations repeats one launch: its lists are kept once
+    (a list per launch was 190 MB here, 20 GB at the largest side)."""
+    small, h = held(torch_cuda, lambda: B.BatchSolver([8193], precision="bf16", max_i=8))
+    h.close()
+    many, h = held(torch_cuda, lambda: B.BatchSolver([8193], precision="bf16", max_i=8192))
+    h.close()
+    print("8193^2: %d MB with 8 iterations a level, %d MB with 8192" % (small >> 20, many >> 20), flush=True)
+    assert many <= small + (64 << 20)
+
+
+@pytest.mark.parametrize("sides,prec,max_i,its", [([257, 129, 513, 129], "fp64", 40, {129: 3}),
+                                                  ([1025, 129], "bf16", 21, {1025: 2}),
+                                                  ([2049, 513, 129], "fp32", 13, {2049: 1, 513: 4})])
+def test_many_iterations_equal_single_solves(B, torch_cuda, sides, prec, max_i, its):
+    """Levels of many passes, of different numbers in each problem: bit for bit
+    as single solves."""
+    torch = torch_cuda
+    print("batch lists %s %s max_i=%d %s" % (sides, prec, max_i, its), flush=True)
+    fs = [torch.from_numpy(W.uniform(2, n, seed=i)).cuda() for i, n in enumerate(sides)]
+    us = [torch.zeros_like(f) for f in fs]
+    b = B.BatchSolver(sides, precision=prec, max_i=max_i, max_cycles=3)
+    for n, k in its.items():
+        b.set_pass_iters(n, k)
+    res = b.solve(fs, us, tol=1e-300, raise_on_status=False)
+    for i, n in enumerate(sides):
+        s = B.Solver(2, n, precision=prec, max_i=max_i)
+        v = torch.zeros_like(fs[i])
+        s.solve_cycles(fs[i], v, 3)
+        assert res["cycles"][i] == 3 and np.array_equal(us[i].cpu().numpy(), v.cpu().numpy()), (n, i)
+        s.close()
