@@ -21,6 +21,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <new>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -49,7 +50,7 @@ struct Problem {
   Lay el, rl[BATCH_MAX_LEVELS];
   char* r[BATCH_MAX_LEVELS] = {};  // right-hand sides of levels 0 .. ms (arrays as allocated)
   char* x[BATCH_MAX_LEVELS][3] = {};  // levels 1 .. ms: iterate pair; below ms also x_{it-1}
-  char* e[2] = {nullptr, nullptr};    // level 0's iterates, if it takes several passes
+  char* e[2] = {nullptr, nullptr};    // level 0's iterates, if it may take several passes
   double* partials = nullptr;
 };
 
@@ -64,15 +65,17 @@ struct homg_batch_ctx {
   std::map<int, int> pass_iters;  // side -> iterations per level-0 pass (absent: TB_MAX_IT)
   std::vector<Problem> probs;
   std::vector<int> big, small[2];  // problems solved in stages; by one workgroup (small[1]: FP64 coarsest level)
-  // stage lists; dirty: to be made (again) before the next solve
+  // stage lists; dirty: to be made (again) before the next solve, on whose
+  // stream they go up from lists (kept while the copy may be in flight)
   bool dirty = true;
+  std::vector<char> lists;
   std::vector<PassGroup> passes;   // in launch order
   std::vector<TileRange> restricts;  // restriction a -> a + 1 at [a]
   TileRange residual, multi;
   size_t multi_lds = 0, tail_lds = 0, small_lds[2] = {0, 0};
   size_t o_res = 0, o_rs = 0, o_multi = 0, o_pass = 0, o_tail = 0, o_small[2] = {0, 0}, o_tiles = 0;  // in plan
   char* plan = nullptr;
-  size_t plan_bytes = 0;
+  size_t plan_bytes = 0;  // enough for any tile rows and pass iterations (plan_bound)
   // per-call inputs and results
   void** h_ptrs = nullptr;  // f, then u (pinned), and their device copy
   void** d_ptrs = nullptr;
@@ -81,7 +84,6 @@ struct homg_batch_ctx {
   double** d_hist = nullptr;      // per problem
   std::vector<double*> hist;
   void* arena = nullptr;
-  void* e_arena = nullptr;
   int device = 0;
   std::string err;
 };
@@ -111,7 +113,6 @@ int side_k(int64_t n) {
 void free_batch(homg_batch_ctx* b) {
   if (!b) return;
   (void)hipFree(b->arena);
-  (void)hipFree(b->e_arena);
   (void)hipFree(b->plan);
   (void)hipFree(b->d_ptrs);
   (void)hipFree(b->d_st);
@@ -160,35 +161,67 @@ constexpr int64_t BATCH_TILED_NODES = 1 << 21;
 
 constexpr int LATTICE_ROWS = 16;  // rows per band of a walking lattice pass
 
-// The stage lists of the current tile shapes and pass depths.
-homg_status build_plan(homg_batch_ctx* b) {
+constexpr int MULTI_B = 4, MULTI_P = 4;  // the multi-level restriction: owned nodes per axis, levels at most
+
+bool latency_bound(const homg_batch_ctx* b) {
+  int64_t nodes = 0;
+  for (int i : b->big) nodes += int64_t(b->sides[i]) * b->sides[i];
+  return nodes <= BATCH_TILED_NODES;
+}
+// Restriction steps of a problem that run as one multi-level launch.
+int multi_steps(const Problem& p, bool small_batch) {
+  return small_batch && p.ms - 1 >= 2 ? std::min(p.ms - 1, MULTI_P) : 0;
+}
+bool walks(bool small_batch, int side) { return !(small_batch && side <= LT2_MAX_SIDE); }
+
+// Bytes that build_plan's lists take at most, whatever the tile rows and pass
+// iterations.  Of the pass lists there is one set for each run of launches
+// that differ in their iterates alone (two sets of descriptors, the iterates
+// alternate).  A run ends where the problems of some side go over to their next
+// kind of launch: a level's first, a further or its last one.
+size_t plan_bound(const homg_batch_ctx* b) {
+  const bool small_batch = latency_bound(b);
+  int64_t runs = 1;
+  int last = 0;  // (big is sorted by side)
+  for (int i : b->big) {
+    if (b->sides[i] != last) runs += 3 * b->probs[i].ms + 1;
+    last = b->sides[i];
+  }
+  int64_t tiles = 0, rs = 0, multi = 0, descs = 0;
+  for (int i : b->big) {
+    const Problem& p = b->probs[i];
+    tiles += (batch_residual_waves(p.n, 2) + 3) / 4;
+    const int P = multi_steps(p, small_batch);
+    for (int a = 1; a < p.ms - P; ++a, ++rs) {
+      const int nc = (p.n - 1) / (2 << a) + 1;
+      tiles += batch_restrict_tiles(nc, default_walk_len(2, nc));
+    }
+    if (P) {
+      const int nb = (p.rl[p.ms].side - 1 + MULTI_B - 1) / MULTI_B;
+      tiles += int64_t(nb) * nb;
+      ++multi;
+    }
+    for (int m = 0; m < p.ms; ++m) {
+      const int nm = (p.n - 1) / (1 << m) + 1, it = level_iters(b, p.levels, m);
+      const int64_t launches = m ? (it + LT_MAX_IT - 1) / LT_MAX_IT : it;
+      const int64_t ts = batch_tiled_side(nm);
+      tiles += std::min(launches, runs) * (walks(small_batch, nm) ? tb_blocks(nm, TB_MAX_IT, LATTICE_ROWS) : ts * ts);
+      descs += std::min(launches, 2 * runs);
+    }
+  }
+  const size_t ta = batch_tail_bytes(b->prec);
+  return sizeof(BatchResidual) * b->big.size() + sizeof(BatchRestrict) * rs + batch_multi_bytes() * multi +
+         ta * (b->big.size() + b->small[0].size() + b->small[1].size()) + sizeof(BatchPass) * descs +
+         sizeof(int2) * tiles + 8 * 256;  // each of the eight lists starts at a multiple of 256 bytes
+}
+
+// The stage lists of the current tile shapes and pass depths, on the host
+// alone: what a solve needs on the device is there since the handle was made.
+homg_status build_plan(homg_batch_ctx* b) try {
   const int eb = prec_bytes(b->prec);
   const bool red = b->prec != PREC_F64;
   auto node = [&](char* p, const Lay& l) -> char* { return p ? p + size_t(l.off) * eb : nullptr; };
-  // level 0 in several passes keeps its iterates
-  size_t need_e = 0;
-  int64_t nodes = 0;
-  for (int i : b->big) {
-    Problem& p = b->probs[i];
-    nodes += int64_t(p.n) * p.n;
-    if (level_iters(b, p.levels, 0) > depth_for(b, p.n)) need_e += 2 * ((size_t(p.el.alloc) * eb + 255) & ~size_t(255));
-  }
-  if (need_e) {
-    (void)hipFree(b->e_arena);
-    b->e_arena = nullptr;
-    if (hipMalloc(&b->e_arena, need_e) != hipSuccess) {
-      (void)hipGetLastError();
-      return bfail(b, HOMG_ERR_OOM, "batch allocation of " + std::to_string(need_e) + " bytes failed");
-    }
-    BHIP(b, hipMemset(b->e_arena, 0, need_e));  // boundaries stay 0
-    char* at = static_cast<char*>(b->e_arena);
-    for (int i : b->big) {
-      Problem& p = b->probs[i];
-      if (level_iters(b, p.levels, 0) <= depth_for(b, p.n)) continue;
-      for (int c = 0; c < 2; ++c, at += (size_t(p.el.alloc) * eb + 255) & ~size_t(255)) p.e[c] = at;
-    }
-  }
-  const bool small_batch = nodes <= BATCH_TILED_NODES;
+  const bool small_batch = latency_bound(b);
 
   std::vector<int2> tiles;
   auto add_tiles = [&](int desc, int n) {
@@ -210,19 +243,15 @@ homg_status build_plan(homg_batch_ctx* b) {
   // the chain 1 -> ms: single steps, then the last P as one launch
   std::vector<BatchRestrict> rs;
   std::vector<char> multi;
-  constexpr int MULTI_B = 4, MULTI_P = 4;
   b->multi_lds = 0;
   int deepest = 0;
   for (int i : b->big) deepest = std::max(deepest, b->probs[i].ms);
   b->restricts.assign(deepest + 1, TileRange{});
-  auto multi_steps = [&](const Problem& p) {
-    return small_batch && p.ms - 1 >= 2 ? std::min(p.ms - 1, MULTI_P) : 0;
-  };
   for (int a = 1; a <= deepest; ++a) {
     const int first = int(tiles.size());
     for (int i : b->big) {
       const Problem& p = b->probs[i];
-      if (a >= p.ms - multi_steps(p)) continue;
+      if (a >= p.ms - multi_steps(p, small_batch)) continue;
       const int nc = (p.n - 1) / (2 << a) + 1, len = default_walk_len(2, nc);
       rs.push_back(BatchRestrict{node(p.r[a], p.rl[a]), node(p.r[a + 1], p.rl[a + 1]), p.rl[a].pitch,
                                  p.rl[a + 1].pitch, i, nc, len, 0});
@@ -235,7 +264,7 @@ homg_status build_plan(homg_batch_ctx* b) {
     int k = 0;
     for (int i : b->big) {
       Problem& p = b->probs[i];
-      const int P = multi_steps(p);
+      const int P = multi_steps(p, small_batch);
       if (!P) continue;
       void* r[MR_MAX + 1];
       Lay l[MR_MAX + 1];
@@ -290,7 +319,7 @@ homg_status build_plan(homg_batch_ctx* b) {
       const int step = m ? LT_MAX_IT : depth_for(b, p.n);
       const Lay& cl = m ? p.rl[m] : p.el;
       const double h = 1.0 / double(nm - 1);
-      const bool walk = !(small_batch && nm <= LT2_MAX_SIDE);
+      const bool walk = walks(small_batch, nm);
       int src = 1;
       for (int t0 = 0; t0 < it; t0 += step) {
         const int g = std::min(step, it - t0);
@@ -313,7 +342,7 @@ homg_status build_plan(homg_batch_ctx* b) {
         q.hl2 = h * h;
         q.prob = i;
         q.n = nm;
-        q.len = walk ? (m ? LATTICE_ROWS : std::max(16, rows_for(b, p.n))) : batch_tiled_side(nm);
+        q.len = walk ? (m ? LATTICE_ROWS : std::max(LATTICE_ROWS, rows_for(b, p.n))) : batch_tiled_side(nm);
         q.accum = accum ? 1 : 0;
         mine.push_back({PassGroup{g, kind, lat, 0, 0, 0}, q});
         src = 1 - src;
@@ -387,17 +416,19 @@ homg_status build_plan(homg_batch_ctx* b) {
   for (int t = 0; t < 2; ++t) b->o_small[t] = put(smalls[t].data(), smalls[t].size());
   b->o_pass = put(passes.data(), sizeof(BatchPass) * passes.size());
   b->o_tiles = put(tiles.data(), sizeof(int2) * tiles.size());
-  if (host.size() > b->plan_bytes) {
-    (void)hipFree(b->plan);
-    b->plan = nullptr;
-    b->plan_bytes = 0;
-    if (hipMalloc(reinterpret_cast<void**>(&b->plan), host.size()) != hipSuccess) {
-      (void)hipGetLastError();
-      return bfail(b, HOMG_ERR_OOM, "stage list allocation of " + std::to_string(host.size()) + " bytes failed");
-    }
-    b->plan_bytes = host.size();
-  }
-  BHIP(b, hipMemcpy(b->plan, host.data(), host.size(), hipMemcpyHostToDevice));
+  if (host.size() > b->plan_bytes)
+    return bfail(b, HOMG_ERR_WORKSPACE, "the stage lists exceed their allocation");
+  b->lists = std::move(host);
+  return HOMG_OK;
+} catch (const std::bad_alloc&) {
+  return bfail(b, HOMG_ERR_OOM, "host allocation of the stage lists failed");
+}
+
+// The lists on the device, on stream s.
+homg_status ready_plan(homg_batch_ctx* b, hipStream_t s) {
+  if (!b->dirty) return HOMG_OK;
+  if (homg_status e = build_plan(b)) return e;
+  BHIP(b, hipMemcpyAsync(b->plan, b->lists.data(), b->lists.size(), hipMemcpyHostToDevice, s));
   b->dirty = false;
   return HOMG_OK;
 }
@@ -433,8 +464,7 @@ homg_status run_once(homg_batch_ctx* b, const double* const* f, double* const* u
     b->h_ptrs[i] = const_cast<double*>(f[i]);
     b->h_ptrs[b->count + i] = u[i];
   }
-  if (b->dirty)
-    if (homg_status e = build_plan(b)) return e;
+  if (homg_status e = ready_plan(b, s)) return e;
   BHIP(b, hipMemcpyAsync(b->d_ptrs, b->h_ptrs, 2 * sizeof(void*) * b->count, hipMemcpyHostToDevice, s));
   const double* const* df = reinterpret_cast<const double* const*>(b->d_ptrs);
   double* const* du = reinterpret_cast<double* const*>(b->d_ptrs + b->count);
@@ -556,6 +586,8 @@ homg_status homg_batch_create(homg_batch* out, int count, const int64_t* sides, 
       at[i].push_back(take(bytes));
       for (int c = 0; m && c < (m < p.ms ? 3 : 2); ++c) at[i].push_back(take(bytes));
     }
+    if (level_iters(b, L, 0) > 1)  // level 0's iterates (passes may be of one iteration)
+      for (int c = 0; c < 2; ++c) at[i].push_back(take(size_t(p.el.alloc) * eb));
   }
   zeroed = total;
   b->def_rows = default_rows(b);
@@ -593,13 +625,21 @@ homg_status homg_batch_create(homg_batch* out, int count, const int64_t* sides, 
       p.r[m] = base + at[i][k++];
       for (int c = 0; m && c < (m < p.ms ? 3 : 2); ++c) p.x[m][c] = base + at[i][k++];
     }
+    for (int c = 0; c < 2 && k < at[i].size(); ++c) p.e[c] = base + at[i][k++];
   }
   if (hipMemcpy(b->d_hist, b->hist.data(), sizeof(double*) * count, hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipGetLastError();
     free_batch(b);
     return bfail(nullptr, HOMG_ERR_HIP, "batch initialisation failed");
   }
-  if (homg_status e = build_plan(b)) {
+  b->plan_bytes = plan_bound(b);
+  if (hipMalloc(reinterpret_cast<void**>(&b->plan), b->plan_bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    const size_t bytes = b->plan_bytes;
+    free_batch(b);
+    return bfail(nullptr, HOMG_ERR_OOM, "stage list allocation of " + std::to_string(bytes) + " bytes failed");
+  }
+  if (homg_status e = ready_plan(b, nullptr)) {
     const std::string msg = b->err;
     free_batch(b);
     return bfail(nullptr, e, msg);
@@ -720,11 +760,10 @@ homg_status homg_batch_tune(homg_batch b, const double* const* f, double* const*
   // did work (a run whose problems all meet tol at cycle 0 times nothing)
   auto once = [&](float* ms) {
     copy_u(false);
-    if (b->dirty)
-      if (homg_status e = build_plan(b)) {
-        st = e;
-        return false;
-      }
+    if (homg_status e = ready_plan(b, s)) {
+      st = e;
+      return false;
+    }
     if (!hip_ok(hipEventRecord(e0, s), "hipEventRecord")) return false;
     if (homg_status e = run_once(b, f, u, tol, s)) {
       st = e;

@@ -81,3 +81,34 @@ def test_many_iterations_equal_single_solves(B, torch_cuda, sides, prec, max_i, 
         s.solve_cycles(fs[i], v, 3)
         assert res["cycles"][i] == 3 and np.array_equal(us[i].cpu().numpy(), v.cpu().numpy()), (n, i)
         s.close()
+
+
+def test_settings_take_no_memory_in_a_solve(B, torch_cuda):
+    """Tile rows and pass iterations changed between solves: nothing is
+    allocated (level 0's iterates were, and the lists), on a stream of the
+    caller's, and the results stay."""
+    torch = torch_cuda
+    sides = [513] * 8 + [129, 33]
+    fs = [torch.from_numpy(W.uniform(2, n, seed=i)).cuda() for i, n in enumerate(sides)]
+    b = B.BatchSolver(sides, precision="fp64")
+    us = [torch.zeros_like(f) for f in fs]
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):  # (a stream's first use takes memory of the runtime's own)
+        first = b.solve(fs, us, tol=1e-8)
+        want = [u.cpu().numpy() for u in us]
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for rows, its in ((1, 1), (64, 2), (5, 3), (0, 0)):
+        for n in set(sides):
+            b.set_tile_rows(n, rows)
+            b.set_pass_iters(n, its)
+        with torch.cuda.stream(s):
+            for u in us:
+                u.zero_()
+            res = b.solve(fs, us, tol=1e-8)
+            got = [u.cpu().numpy() for u in us]
+        print("rows %d, iterations %d: %d bytes less" % (rows, its, free - torch.cuda.mem_get_info()[0]), flush=True)
+        assert torch.cuda.mem_get_info()[0] >= free
+        assert res["cycles"] == first["cycles"]
+        assert all(np.array_equal(u, v) for u, v in zip(got, want))
