@@ -303,23 +303,24 @@ homg_status homg_get_profile(homg_handle h, homg_kernel_time *out, int cap, int 
  *   residual, cycles and homg_status.  Returns HOMG_OK if every problem
  *   converged, HOMG_ERR_NOT_CONVERGED / HOMG_ERR_NUMERICAL if any did not,
  *   HOMG_ERR_HIP on a runtime failure.  Synchronises the stream.
- * homg_batch_set_tile_rows: rows per tile (the tile shape of the
- *   fine-grid stages) for all problems of side `side`; 0 restores the
- *   default.
+ * homg_batch_set_tile_rows: rows per tile for all problems of side `side`;
+ *   0 restores the default.  The residual walks tiles of that many rows, and
+ *   level 0's passes of at least 16 (with few nodes in all they run on square
+ *   tiles of their own instead).
  * homg_batch_set_pass_iters: iterations per level-0 pass (1..4; 0 restores
  *   the default 4) for all problems of side `side`.  Every pass depth gives
- *   the same iterates bit for bit; only the traffic and the number of steps
- *   change.
+ *   the same iterates bit for bit; only the traffic and the number of passes
+ *   change.  Neither setting reaches problems of side up to 65.
  * homg_batch_tune: picks both by timing candidates on the given inputs:
- *   coordinate descent over the sides, largest first, tile rows in {4, ...,
- *   128} and then pass iterations in {1, ..., 4}, each candidate timed as
+ *   coordinate descent over the sides above 65, largest first, tile rows in
+ *   {4, ..., 128} and then pass iterations in {1, ..., 4}, each candidate timed as
  *   the median of three solves.  Every timed solve starts from the caller's
  *   u (a device copy is saved first and restored before each run and at the
  *   end, so u is left as given); HOMG_ERR_INVALID_ARG if a run needs no
  *   cycle at all (every initial guess already meets tol).  The choice is
  *   read from / appended to the text file cache_path (lines "<arch/CUs/
  *   precision/MaxI key> <side> <rows> <iterations>"; NULL: no cache); a
- *   cache that covers every side skips the timing.
+ *   cache that covers every side above 65 skips the timing.
  */
 typedef struct homg_batch_ctx *homg_batch;
 

@@ -712,6 +712,8 @@ homg_status homg_batch_tune(homg_batch b, const double* const* f, double* const*
   const char* pname = b->prec == PREC_F64 ? "fp64" : (b->prec == PREC_F32 ? "fp32" : "bf16");
   int cus = 0;
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device);
+  // the sides solved in stages: the others read neither setting
+  const std::vector<int> staged(std::upper_bound(distinct.begin(), distinct.end(), tail_max_side(2)), distinct.end());
   char key[128];
   std::snprintf(key, sizeof key, "gfx950/cu%d/%s/maxi%d/rows+iters", cus, pname, b->max_i);
   // cache: lines of the form   <key> <side> <rows> <iterations per level-0 pass>
@@ -721,7 +723,7 @@ homg_status homg_batch_tune(homg_batch b, const double* const* f, double* const*
       int side = 0, rows = 0, its = 0, hits = 0;
       while (std::fgets(line, sizeof line, fp))
         if (std::sscanf(line, "%127s %d %d %d", k2, &side, &rows, &its) == 4 && std::strcmp(k2, key) == 0 &&
-            std::find(distinct.begin(), distinct.end(), side) != distinct.end() && rows > 0 && its > 0 &&
+            std::find(staged.begin(), staged.end(), side) != staged.end() && rows > 0 && its > 0 &&
             its <= TB_MAX_IT) {
           b->tile_rows[side] = rows;
           b->pass_iters[side] = its;
@@ -729,7 +731,7 @@ homg_status homg_batch_tune(homg_batch b, const double* const* f, double* const*
           ++hits;
         }
       std::fclose(fp);
-      if (hits >= int(distinct.size())) return HOMG_OK;
+      if (hits >= int(staged.size())) return HOMG_OK;
     }
   }
   // Every candidate starts from the caller's initial guesses: they are saved
@@ -796,7 +798,7 @@ homg_status homg_batch_tune(homg_batch b, const double* const* f, double* const*
   bool ok = st == HOMG_OK && once(&warm) && timed(&best);
   // coordinate descent over the sides, largest first: tile rows, then the
   // iterations per level-0 pass
-  for (auto it = distinct.rbegin(); ok && it != distinct.rend(); ++it) {
+  for (auto it = staged.rbegin(); ok && it != staged.rend(); ++it) {
     const int side = *it;
     const int keep = rows_for(b, side);
     int best_rows = keep;

@@ -112,3 +112,24 @@ def test_settings_take_no_memory_in_a_solve(B, torch_cuda):
         assert torch.cuda.mem_get_info()[0] >= free
         assert res["cycles"] == first["cycles"]
         assert all(np.array_equal(u, v) for u, v in zip(got, want))
+
+
+def tuned(B, torch, sides, path=None):
+    """seconds a tuning run takes"""
+    fs = [torch.from_numpy(W.uniform(2, n, seed=i % 3)).cuda() for i, n in enumerate(sides)]
+    us = [torch.zeros_like(f) for f in fs]
+    b = B.BatchSolver(sides, precision="fp32")
+    b.solve(fs, us, tol=1e-2)
+    for u in us:
+        u.zero_()
+    t = time.perf_counter()
+    b.tune(fs, us, tol=1e-2, cache_path=path)
+    return time.perf_counter() - t
+
+
+def test_tuner_leaves_out_sides_without_stages(B, torch_cuda):
+    """Problems of side up to 65 read neither setting: the tuner times no
+    candidates for them (4 solves against 28 for as many problems of side 129)."""
+    small, staged = tuned(B, torch_cuda, [65] * 200), tuned(B, torch_cuda, [129] * 200)
+    print("tuned in %.4f s (side 65), %.4f s (side 129)" % (small, staged), flush=True)
+    assert small <= 0.5 * staged
