@@ -318,9 +318,10 @@ homg_status homg_get_profile(homg_handle h, homg_kernel_time *out, int cap, int 
  *   u (a device copy is saved first and restored before each run and at the
  *   end, so u is left as given); HOMG_ERR_INVALID_ARG if a run needs no
  *   cycle at all (every initial guess already meets tol).  The choice is
- *   read from / appended to the text file cache_path (lines "<arch/CUs/
- *   precision/MaxI key> <side> <rows> <iterations>"; NULL: no cache); a
- *   cache that covers every side above 65 skips the timing.
+ *   read from / appended to the text file cache_path (lines "<key> <side>
+ *   <rows> <iterations>", the key arch/CUs/precision/MaxI/form of the passes
+ *   and default rows, which the whole batch decides; NULL: no cache); a cache
+ *   that covers every side above 65 skips the timing.
  */
 typedef struct homg_batch_ctx *homg_batch;
 

@@ -714,8 +714,12 @@ homg_status homg_batch_tune(homg_batch b, const double* const* f, double* const*
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device);
   // the sides solved in stages: the others read neither setting
   const std::vector<int> staged(std::upper_bound(distinct.begin(), distinct.end(), tail_max_side(2)), distinct.end());
+  // what the best settings depend on beside the side: the passes' kernels
+  // (latency_bound) and the number of waves in flight (default_rows), both of the
+  // whole batch
   char key[128];
-  std::snprintf(key, sizeof key, "gfx950/cu%d/%s/maxi%d/rows+iters", cus, pname, b->max_i);
+  std::snprintf(key, sizeof key, "gfx950/cu%d/%s/maxi%d/%s%d", cus, pname, b->max_i,
+                latency_bound(b) ? "tiles" : "bands", b->def_rows);
   // cache: lines of the form   <key> <side> <rows> <iterations per level-0 pass>
   if (cache_path) {
     if (FILE* fp = std::fopen(cache_path, "r")) {

@@ -133,3 +133,16 @@ def test_tuner_leaves_out_sides_without_stages(B, torch_cuda):
     small, staged = tuned(B, torch_cuda, [65] * 200), tuned(B, torch_cuda, [129] * 200)
     print("tuned in %.4f s (side 65), %.4f s (side 129)" % (small, staged), flush=True)
     assert small <= 0.5 * staged
+
+
+def test_tuner_cache_is_kept_per_kind_of_batch(B, torch_cuda, tmp_path):
+    """What was chosen for a batch whose passes run on tiles is not taken for
+    one of the same sides whose passes walk, nor the other way round; each is
+    found again for its own."""
+    path = tmp_path / "tiles.txt"
+    lines = []
+    for sides in ([129, 257, 33], [129, 257, 33] * 40, [257, 33, 129], [129, 257, 33] * 41):
+        tuned(B, torch_cuda, sides, str(path))
+        lines.append([ln.split() for ln in path.read_text().split("\n") if ln.strip()])
+    assert [len(v) for v in lines] == [3, 6, 6, 6]
+    assert len({ln[0] for ln in lines[-1]}) == 2
