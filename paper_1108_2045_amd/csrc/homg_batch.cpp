@@ -455,7 +455,7 @@ homg_status enqueue_cycle(homg_batch_ctx* b, int pending, hipStream_t s) {
   return HOMG_OK;
 }
 
-constexpr int SMALL_CYCLES = 64;  // cycles per launch of the one-workgroup problems
+constexpr int SMALL_CYCLES = 64;  // cycles per launch of the one-workgroup problems (at most 126 iterations each)
 
 homg_status run_once(homg_batch_ctx* b, const double* const* f, double* const* u, double tol,
                      hipStream_t s) {

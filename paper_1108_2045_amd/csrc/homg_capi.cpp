@@ -1046,17 +1046,19 @@ homg_status solve_result(homg_ctx* h, bool stop_on_tol, long long launches0, int
 // schedule descends from its coarsest level to level 0, each level once.
 // One launch replaces five per cycle; at these sizes a cycle is latency
 // alone.  With profiling on it is one entry (kind 10, level 0, mode 2).
+// A launch runs so many cycles and iterations at most, so that it ends within
+// a few ms (0.4 us an iteration); a schedule whose cycle has more iterations
+// runs as separate launches.
+constexpr int SMALL_SOLVE_CYCLES = 64, SMALL_SOLVE_ITERATIONS = 8192;
 bool small_solve(const homg_ctx* h) {
   const int np = int(h->sched.size() / 2);
   if (h->temporal != 2 || h->active_smoother != 0 || h->pow2 || h->n > tail_max_side(h->d)) return false;
   if (h->has_coef && !h->faces) return false;
-  if (np != h->top_level + 1 || np > BATCH_MAX_LEVELS) return false;
+  if (np != h->top_level + 1 || np > BATCH_MAX_LEVELS || h->total_sweeps > SMALL_SOLVE_ITERATIONS) return false;
   for (int p = 0; p < np; ++p)
     if (h->sched[2 * p] != h->top_level - p) return false;
   return coarse_tail_lds(h->prec, h->d, h->n, np, top64(h), h->has_coef, true) <= h->lds_limit;
 }
-
-constexpr int SMALL_SOLVE_CYCLES = 64;  // cycles per launch at most
 
 homg_status run_small_solve(homg_ctx* h, const double* f, double* u, double tol, bool stop_on_tol, int fixed_cycles,
                             long long launches0, hipStream_t s, homg_info* info) {
@@ -1064,9 +1066,10 @@ homg_status run_small_solve(homg_ctx* h, const double* f, double* u, double tol,
   int its[BATCH_MAX_LEVELS];
   for (int k = 0; k < np; ++k) its[k] = h->sched[2 * (np - 1 - k) + 1];
   const int limit = stop_on_tol ? h->max_cycles : fixed_cycles;
+  const int step = std::min(SMALL_SOLVE_CYCLES, SMALL_SOLVE_ITERATIONS / h->total_sweeps);
   int syncs = 0;
-  for (int c0 = 0;; c0 += SMALL_SOLVE_CYCLES) {
-    const int c1 = std::min(limit, c0 + SMALL_SOLVE_CYCLES);
+  for (int c0 = 0;; c0 += step) {
+    const int c1 = std::min(limit, c0 + step);
     LAUNCH_K(h, s, K_TAIL, 0, 2,
              launch_small_solve(h->prec, h->d, h->n, np, its, h->omega, level_faces(h, 0), f, u, top64(h), residual_restricts(h), c0, c1,
                                 stop_on_tol ? tol : 0.0, stop_on_tol ? 1 : 0, h->st, h->hist, h->h_st, h->h_hist, s));
