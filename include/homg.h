@@ -251,23 +251,32 @@ homg_status homg_step_cycle(homg_handle h, const double *r0, double *acc, void *
  * times are accumulated per kernel class (kind, level, mode) at the end of
  * every solve and by homg_get_profile.  Enabling or disabling clears the
  * accumulated times.
- *   kind: 0 unused (the first residual also sums f^2), 1 residual, 2 norm finalisation, 3 restriction from
- *   `level` to level+1, 4 whole-grid iteration at `level`, 5 sampling of the
- *   grid on the level lattice, 6 iterations on the compact lattice, 7
- *   whole-grid pass of a blocked level, 8 learned relaxation of the level
- *   lattice (level 0: of the whole grid), 9 hand-over of a finished coarse
- *   level to the lattice of `level` (chained execution), 10 the leading
- *   coarse levels down to `level` in one workgroup (chained execution).
+ *   kind: 0 unused (the first residual also sums f^2), 1 residual, 2 norm
+ *   finalisation, 3 restriction from `level` to level+1, 4 whole-grid
+ *   iteration at `level`, 5 sampling of the grid on the level lattice, 6
+ *   iterations on the compact lattice, 7 whole-grid pass of a blocked level, 8
+ *   learned relaxation of the level lattice (level 0: of the whole grid), 9
+ *   hand-over of a finished coarse level to the lattice of `level` (chained
+ *   execution), 10 the leading coarse levels down to `level` in one workgroup
+ *   (chained execution).
  *   mode (kind 1): 1 = the pass also restricts the residual to level 1;
+ *   mode (kind 3): 1 = onto the FP64 coarsest level, 2 = the four families of
+ *   a power-of-two grid, 3 = several levels in one launch;
+ *   mode (kind 5): 0 = onto the lattice, 1 = widened for the FP64 coarsest
+ *   level, 2 = its final iterates rounded back;
  *   mode (kinds 4, 6, 7, 8): bit 0 = starts from e = 0, bit 1 = adds into u;
  *   bit 2 (kinds 6, 8) = every iteration of the level in one workgroup that
- *   holds the whole lattice; bit 3 (kinds 4, 6) = several iterations in one
- *   temporally blocked pass, bits 4-5 their number minus one, bit 6 (kind
- *   6) = the pass also stores the iterate before its last, bit 7 (kinds 4,
- *   6) = the pass takes its first iterate from the next coarser level's
- *   compact state (chained execution: no hand-over or whole-grid write in
- *   between), bit 8 = on LDS tiles (kind 4 with bit 3, kind 6); mode (kind 10): 1 = the coarse levels down to `level`, 2 = the
- *   cycles of a whole solve of a small grid (level 0).
+ *   holds the whole lattice; bit 3 (kinds 4, 6, 8) = several iterations in one
+ *   launch, bits 4-5 their number minus one; bit 6 (kind 6) = the pass also
+ *   stores the iterate before its last; bit 7 (kinds 4, 6, 8) = the pass takes
+ *   its first iterate from the next coarser level's compact state (chained
+ *   execution: no hand-over or whole-grid write in between); bit 8 = on LDS
+ *   tiles (kinds 4 and 6 with bit 3), the FP64 coarsest level (kind 6 without),
+ *   on a power-of-two grid (kind 4 without, kind 7); bit 9 (kind 6) = the marks
+ *   of a power-of-two grid;
+ *   mode (kind 10): 1 = the coarse levels down to `level`, 2 = the cycles of
+ *   a whole solve of a small grid (level 0), 4 = the coarse levels of a
+ *   power-of-two grid, 8 = the coarse levels with the learned relaxation.
  * homg_get_profile synchronises outstanding events, then writes up to cap
  * entries and their count in *len.
  */

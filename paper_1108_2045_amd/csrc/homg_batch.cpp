@@ -13,7 +13,8 @@
 // the start of every later launch.  The host reads the states after a few
 // cycles and sizes the next batch of cycles from the slowest problem.
 // Aligned at their ends the sequences of problems of different depth share
-// their launches: side 65 .. 1025 takes 8 launches a cycle.
+// their launches: side 65 .. 1025 takes 9 launches a cycle (three
+// restrictions, the tails, three lattice levels, level 0, the residual).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -129,8 +130,11 @@ int level_iters(const homg_batch_ctx* b, int levels, int m) {
 // Default rows per tile: 16, halved while the batch's residual pass has
 // fewer than 8192 waves (the card's wave slots) and tiles more than 4 rows.
 // Longer tiles load fewer halo rows, shorter ones keep a small batch from
-// being a few serial chains; 512 problems of side 65 .. 1025 took 24.7 ms with
-// 8 or 16 rows, 25.3 with 32, 26.7 with 64.
+// being a few serial chains.  Solves with 4, 8, 16, 32 and 64 rows (FP32; the
+// default's in brackets): 512 problems of side 65 .. 1025 24.7, [23.9] with 8
+// or 16, 24.5, 26.1 ms; 64 of side 1025 12.0, 11.8, [11.9], 12.2, 13.0 ms; 8 of
+// side 1025 2.05, 2.08, [2.12], 2.02, 2.34 ms; 8 of side 129 [0.35], 0.37, 0.41,
+// 0.49, 0.71 ms; 2 of side 1025 [1.23], 1.22, 1.27, 1.48, 1.87 ms.
 int default_rows(const homg_batch_ctx* b) {
   int rows = 16;
   for (; rows > 4; rows /= 2) {
@@ -157,9 +161,19 @@ int depth_for(const homg_batch_ctx* b, int side) {
 // walking waves) and the end of the restriction chain in one launch (above,
 // one launch per step).  512 problems of side 65 .. 1025, 143e6 nodes: the
 // lattice passes took 570 us a cycle on tiles, the chain 476 us in one launch.
+// Whole solves, time of the one form over the other's by total nodes: side 129
+// 0.25e6 0.89, 1.0e6 1.06, 2.1e6 1.22; 257 0.5e6 0.87, 1.0e6 0.97, 2.0e6 1.18;
+// 513 0.8e6 0.87, 1.8e6 1.13, 3.9e6 1.47; 1025, whose level 0 walks in either
+// form, 1.1e6 0.74, 3.2e6 0.87, 7.4e6 1.05, 16e6 1.21.  The line lies between
+// the two groups: one problem of side 1025 is to be on tiles, and batches of
+// small sides give away up to a fifth just below it.
 constexpr int64_t BATCH_TILED_NODES = 1 << 21;
 
-constexpr int LATTICE_ROWS = 16;  // rows per band of a walking lattice pass
+// Rows per band of a walking lattice pass, and level 0's least.  Solves with 8,
+// 16 and 32 (FP32): 512 problems of side 65 .. 1025 24.19, 24.05, 24.16 ms, 64 of
+// side 1025 11.94, 11.90, 11.96 ms; few problems, where bands are short of
+// waves, gain from 8 what those lose: 8 of side 1025 2.06, 2.12, 2.28 ms.
+constexpr int LATTICE_ROWS = 16;
 
 constexpr int MULTI_B = 4, MULTI_P = 4;  // the multi-level restriction: owned nodes per axis, levels at most
 

@@ -3,11 +3,11 @@
 //
 // What bounds it: on lattices up to 129^2 the launch and the chain of phases
 // of one block; above that the phases between barriers with 16 waves on a CU:
-// at 1025^2 vector issue (1300 instructions a wave for two iterations) fills 36
-// of a pass's 50 us, LDS 20 and the matrix cores 10, and dropping the masks of
+// at 1025^2 vector issue (1290 instructions a wave for two iterations) fills 31
+// of a pass's 50 us, LDS 20 and the matrix cores 11, and dropping the masks of
 // blocks away from the boundary (60 instructions) left it at 50.  One launch per
-// iteration with a hand-over launch per level took 406 us a cycle at 1025^2
-// (FP64, 10 levels); these two kernels take 229.  A workgroup keeps a 32 x 32
+// iteration with a hand-over launch per level takes 396 us a cycle at 1025^2
+// (FP64, 10 levels); with these two kernels it is 231.  A workgroup keeps a 32 x 32
 // block of the hidden layer and
 //  * k_learned_tiles runs up to four iterations of one level on it, the block
 //    shrinking by three nodes a side each, the coefficient factors of a lane's
@@ -55,8 +55,10 @@ struct LearnedTileArgs {
 };
 
 // Blocks above which 8 waves take one, two to a CU: one workgroup of 16 waves
-// to a CU leaves it idle at its barriers (1025^2, two iterations: 82 us with
-// 16 waves, 61 with 8); fewer blocks than CUs finish sooner with 16 waves.
+// to a CU leaves it idle at its barriers; fewer blocks than CUs finish sooner
+// with 16 waves.  Level 0's last pass with 16 and with 8 waves (FP64): 129^2 (four
+// iterations, 121 blocks) 13.5 and 15.0 us, 257^2 (two, 121) 9.4 and 10.1; 513^2
+// (two, 484) 18.5 and 15.5, 1025^2 67 and 49, 2049^2 241 and 165.
 constexpr int LB_WIDE_BLOCKS = 256;
 
 template <typename C>

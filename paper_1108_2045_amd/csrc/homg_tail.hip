@@ -1,6 +1,6 @@
 // homg_tail.hip -- the parts of a cycle that one workgroup runs alone: the
 // leading coarse levels of the schedule (the coarse tail) and, on grids of
-// side up to TAIL_MAX_2D / TAIL_MAX_3D, whole solves.
+// side up to tail_max_side (2D 65, 3D 17), whole solves.
 //
 // What bounds them is latency, not bandwidth or arithmetic: a few thousand
 // nodes at most, some 35 iterations, restrictions and hand-overs one after

@@ -509,7 +509,7 @@ def residual_noalloc(f, u, r, stream=None):
 
 
 class BatchSolver:
-    """Many independent 2D Poisson problems advanced together (one launch per step for all)."""
+    """Many independent 2D Poisson problems advanced together (one launch per stage of a cycle for all)."""
 
     def __init__(self, sides, precision="fp32", omega=0.0, max_i=4, max_cycles=200):
         L = lib()
