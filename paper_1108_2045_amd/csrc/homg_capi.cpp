@@ -1432,18 +1432,20 @@ homg_status homg_set_coefficient(homg_handle h, const double* a, void* stream) {
     return fail(h, HOMG_ERR_INVALID_ARG, "coefficient only applies to the diffusion stencil");
   DeviceGuard guard(h->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (h->a.empty()) {
+  if (!h->faces) {
+    // the arrays the handle does not hold yet (none, unless an allocation failed)
     h->face_level = 0;
     while (h->face_level < h->levels && h->al[h->face_level].side > tail_max_side(2)) ++h->face_level;
     size_t cnt = 0;
     for (int m = h->face_level; m <= h->top_level; ++m) cnt += 3 * size_t(h->al[m].side) * size_t(h->al[m].side);
-    h->a.assign(h->levels, nullptr);
-    for (int m = 0; m < h->levels; ++m)
+    h->a.resize(h->levels, nullptr);
+    for (int m = 0; m < h->levels; ++m) {
+      if (h->a[m]) continue;
       if (homg_status e = dev_alloc(h, reinterpret_cast<void**>(&h->a[m]),
                                     sizeof(double) * (h->al[m].alloc + (m + 1 == h->levels ? cnt : 0))))
         return e;
-    for (int m = 0; m < h->levels; ++m)
       HIPCHK(h, hipMemsetAsync(h->a[m], 0, sizeof(double) * h->al[m].alloc, s));
+    }
     if (cnt) h->faces = h->a[h->levels - 1] + h->al[h->levels - 1].alloc;
   }
   // level-m lattice coefficients: the nodal values sampled every 2^m nodes
@@ -1609,10 +1611,10 @@ homg_status homg_set_smoother(homg_handle h, int smoother, const float* w, doubl
   DeviceGuard guard(h->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (w) {
-    if (!h->w32) {
-      if (homg_status e = dev_alloc(h, reinterpret_cast<void**>(&h->w32), sizeof(float) * NW)) return e;
+    if (!h->wbf)
       if (homg_status e = dev_alloc(h, reinterpret_cast<void**>(&h->wbf), sizeof(uint16_t) * NW)) return e;
-    }
+    if (!h->w32)
+      if (homg_status e = dev_alloc(h, reinterpret_cast<void**>(&h->w32), sizeof(float) * NW)) return e;
     LAUNCH(h, launch_round_weights(w, h->wbf, h->w32, s));
   }
   if (smoother == HOMG_SMOOTHER_LEARNED) {
